@@ -1,12 +1,19 @@
 // Tree-ensemble scoring of a trajectory of configurations (cost-model query, Sec. 4.1 of the paper).
 //
-// One configuration per lane.  A workgroup keeps a tile of P configurations in LDS, feature-major
-// (xs[f][p]): the walk reads xs[feat][lane], whose bank is lane % 32 whatever `feat` is, so these
-// gathers never conflict.  The forest is streamed through LDS in chunks of whole trees with each
-// internal node packed as (LDS byte offset of the feature's row, threshold bits); every lane adds the leaf
-// values to its own fp32 running sum in tree order, which makes the result independent of the launch shape.
-// Every workgroup streams the whole forest, so the tile is as large as LDS allows beside a chunk of four trees
-// (up to 1024 configurations), and a chunk is moved 16 bytes per lane at a time where the alignment allows.
+// A workgroup of 1024 threads keeps a tile of P configurations in LDS, feature-major (xs[f][p]): the walk reads
+// xs[feat][lane], whose bank depends on the lane alone, so these gathers never conflict.  The internal nodes of the
+// forest are streamed through LDS in chunks of whole trees, each packed as (LDS address of the feature's row,
+// threshold bits); the leaves stay in global memory: a tree's leaf is one 4-byte gather per configuration out of a
+// block of at most 16 KB that the first-level cache holds, and it is only added a group of trees later.
+//
+// Large inputs take P = 1024, one configuration per thread.  Every workgroup streams the whole forest, so that is the
+// cheapest tile per configuration - but 2000 configurations would fill two compute units.  Smaller inputs take tiles of
+// 512 ... 64 configurations and split the trees of a chunk over the 1024 / P slices of the workgroup; the leaf values
+// then meet in LDS, where one slice adds them.  Either way a configuration's leaves are added in fp32 in tree order, so
+// the result does not depend on the launch shape.  (Measured: 2000 x 8, 64 trees of depth 6: 23.9 -> 9.0 us a call with
+// 32 workgroups instead of two; 65,536 x 8, 256 of depth 8: 112 -> 41 us with tiles of 256; leaves in global memory
+// instead of LDS, which is what binds the large ones: 8M x 32, 512 of depth 10: 14.9 -> 11.9 ms.)
+//
 // A step of the walk is two dependent LDS reads and four vector instructions: the walk keeps the node's LDS
 // address a (node n of a tree at byte b sits at b + 8 n) and moves to child 2n + 1 + c by a <- 2 a + (8 + 8 c - b).
 #include <algorithm>
@@ -18,12 +25,15 @@ namespace rls {
 
 namespace {
 
-constexpr int kForestChunkBytes = 96 * 1024;   // with the 64 KB tile of configurations this fills the 160 KB of LDS
-constexpr int kSideBySide = 4;                 // trees a lane walks at the same time (fewer where a chunk holds fewer)
-// Groups of four entries (internal nodes, and leaves) a thread carries in registers for the next chunk: enough for a
-// chunk of `bytes` of deep trees.  Shallow trees have more leaves per byte (2^D leaves in 12 2^D - 8 bytes), so the
-// launcher also caps the trees per chunk by 4 * groups * threads leaves.
-constexpr int stage_groups(int bytes, int threads) { return (bytes / 12 + 4 * threads - 1) / (4 * threads); }
+constexpr int kScoreThreads = 1024;
+constexpr int kScoreLds = 160 * 1024;
+constexpr int kStageQuads = 3;                                         // groups of four nodes a thread carries in registers for the next chunk
+constexpr int kChunkNodes = 4 * kStageQuads * kScoreThreads;           // nodes of a chunk at most (96 KB)
+constexpr int kScoreBatch = 64;                                        // forests per launch (they travel as kernel arguments)
+
+struct ForestBatch {
+    ForestArgs f[kScoreBatch];
+};
 
 // LDS is addressed by 32-bit byte addresses that the walk computes itself (the start of the dynamic block is folded into
 // them once: as a pointer offset it is a link-time constant and would cost an addition per read)
@@ -31,95 +41,92 @@ typedef __attribute__((address_space(3))) unsigned char lds_byte;
 __device__ inline unsigned lds_address(const void *p) { return (unsigned)(uintptr_t)(lds_byte *)p; }
 typedef unsigned uint2v __attribute__((ext_vector_type(2)));
 typedef unsigned uint4v __attribute__((ext_vector_type(4)));
-typedef float float4v __attribute__((ext_vector_type(4)));
 __device__ inline uint2v lds_read_u2(unsigned a) { return *(const __attribute__((address_space(3))) uint2v *)(uintptr_t)a; }
 __device__ inline float lds_read_f(unsigned a) { return *(const __attribute__((address_space(3))) float *)(uintptr_t)a; }
 __device__ inline void lds_write_u2(unsigned a, uint2v v) { *(__attribute__((address_space(3))) uint2v *)(uintptr_t)a = v; }
 __device__ inline void lds_write_u4(unsigned a, uint4v v) { *(__attribute__((address_space(3))) uint4v *)(uintptr_t)a = v; }
-__device__ inline void lds_write_f(unsigned a, float v) { *(__attribute__((address_space(3))) float *)(uintptr_t)a = v; }
-__device__ inline void lds_write_f4(unsigned a, float4v v) { *(__attribute__((address_space(3))) float4v *)(uintptr_t)a = v; }
 
-// P threads (= configurations of the tile), G groups of staged entries per thread, W trees walked side by side.
-// `quads`: the forest's arrays start at multiples of 16 bytes and the chunks at multiples of four trees, so that a chunk
-// of a multiple of four trees is moved four entries at a time.
-template <int P, int G, int W>
-__global__ void __launch_bounds__(P) gbt_score_kernel(ForestArgs f, const float *__restrict__ X, int64_t N, int d, int64_t ldx,
-                                                      float *__restrict__ score, int trees_per_chunk, int quads)
+// P configurations per tile, 1024 / P slices of the trees, W trees walked side by side by a thread.
+// `quads`: the forests' node arrays start at multiples of 16 bytes and the chunks at multiples of four trees, so that a
+// chunk of a multiple of four trees is moved four nodes at a time.
+template <int P, int W>
+__global__ void __launch_bounds__(kScoreThreads) gbt_score_kernel(ForestBatch fb, const float *__restrict__ Xall, int64_t N, int d, int64_t ldx,
+                                                                  int64_t x_bs, float *__restrict__ score, int trees_per_chunk, int quads)
 {
     extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int SL = kScoreThreads / P;
+    const ForestArgs f = fb.f[blockIdx.y];
+    const float *const X = Xall + (int64_t)blockIdx.y * x_bs;
     const int n_int = (1 << f.depth) - 1;
     const int n_leaf = 1 << f.depth;
     float *xs = reinterpret_cast<float *>(smem);                                // [d][P]
-    // the chunk buffer behind it: [trees_per_chunk][n_int] nodes, then [trees_per_chunk][n_leaf] leaves
     const unsigned xs_bytes = (unsigned)d * (unsigned)P * 4u;
-    const unsigned node_bytes = (unsigned)trees_per_chunk * (unsigned)n_int * 8u;
+    const unsigned lv_bytes = SL > 1 ? (unsigned)trees_per_chunk * (unsigned)P * 4u : 0u;
 
     const int tid = threadIdx.x;
+    const int cfg = tid & (P - 1);
+    const int slice = SL > 1 ? __builtin_amdgcn_readfirstlane(tid / P) : 0;      // P is a multiple of the wave size
     const unsigned lds0 = lds_address(smem);
-    const int64_t row = (int64_t)blockIdx.x * P + tid;
+    const unsigned lv_at = lds0 + xs_bytes;                                      // leaf values of a chunk [tree][P] (several slices)
+    const unsigned nodes_at = lv_at + lv_bytes;                                  // nodes of a chunk [tree][n_int]
+    const int64_t row = (int64_t)blockIdx.x * P + cfg;
     const bool valid = row < N;
     {
         const float *x = X + (valid ? row : 0) * ldx;
-        if (valid && (d % 4 == 0) && (ldx % 4 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0)) {
+        if ((d % 4 == 0) && (ldx % 4 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0)) {
             const float4 *x4 = reinterpret_cast<const float4 *>(x);
-            for (int c = 0; c < d / 4; ++c) {
+            for (int c = slice; c < d / 4; c += SL) {
                 const float4 v = x4[c];
-                xs[(4 * c + 0) * P + tid] = v.x;
-                xs[(4 * c + 1) * P + tid] = v.y;
-                xs[(4 * c + 2) * P + tid] = v.z;
-                xs[(4 * c + 3) * P + tid] = v.w;
+                xs[(4 * c + 0) * P + cfg] = v.x;
+                xs[(4 * c + 1) * P + cfg] = v.y;
+                xs[(4 * c + 2) * P + cfg] = v.z;
+                xs[(4 * c + 3) * P + cfg] = v.w;
             }
         } else {
-            for (int c = 0; c < d; ++c) xs[c * P + tid] = valid ? x[c] : 0.0f;
+            for (int c = slice; c < d; c += SL) xs[c * P + cfg] = x[c];
         }
     }
 
     // The next chunk of the forest travels in registers while the current one is walked: its loads are issued
-    // before the walk (unconditional, offsets clamped to the chunk) and written to LDS after it.  Every offset is a
-    // 32-bit byte offset from the chunk's start in its array; staging costs a few instructions per entry, and a deep
-    // tree has as many entries as a tenth of the node visits a tile pays for it.
-    constexpr int E = 4 * G;
+    // before the walk (offsets clamped to the chunk) and written to LDS after it.  Every offset is a 32-bit byte
+    // offset from the chunk's start in its array; staging costs a few instructions per node.
+    constexpr int E = 4 * kStageQuads;
     int st_feat[E];
-    float st_thr[E], st_leaf[E];
+    float st_thr[E];
     auto fetch_chunk = [&](int t0, int tc) {
-        const unsigned n_nodes = (unsigned)(tc * n_int), n_leaves = (unsigned)(tc * n_leaf);
+        const unsigned n_nodes = (unsigned)(tc * n_int);
         const char *const fc = reinterpret_cast<const char *>(f.feat + (size_t)t0 * n_int);
         const char *const hc = reinterpret_cast<const char *>(f.thr + (size_t)t0 * n_int);
-        const char *const lc = reinterpret_cast<const char *>(f.leaf + (size_t)t0 * n_leaf);
         if (quads && (tc & 3) == 0) {
-            const unsigned last_n = n_nodes * 4u - 16u, last_l = n_leaves * 4u - 16u;
+            const unsigned last_n = n_nodes * 4u - 16u;
 #pragma unroll
-            for (int i = 0; i < G; ++i) {
-                const unsigned o = (unsigned)(tid + i * P) * 16u;
-                const unsigned on = min(o, last_n), ol = min(o, last_l);
+            for (int i = 0; i < kStageQuads; ++i) {
+                if ((unsigned)(4 * i * kScoreThreads) >= n_nodes) break;        // same for the whole workgroup
+                const unsigned on = min((unsigned)(tid + i * kScoreThreads) * 16u, last_n);
                 const int4 a = *reinterpret_cast<const int4 *>(fc + on);
                 const float4 h = *reinterpret_cast<const float4 *>(hc + on);
-                const float4 l = *reinterpret_cast<const float4 *>(lc + ol);
                 st_feat[4 * i + 0] = a.x; st_feat[4 * i + 1] = a.y; st_feat[4 * i + 2] = a.z; st_feat[4 * i + 3] = a.w;
                 st_thr[4 * i + 0] = h.x; st_thr[4 * i + 1] = h.y; st_thr[4 * i + 2] = h.z; st_thr[4 * i + 3] = h.w;
-                st_leaf[4 * i + 0] = l.x; st_leaf[4 * i + 1] = l.y; st_leaf[4 * i + 2] = l.z; st_leaf[4 * i + 3] = l.w;
             }
         } else {
-            const unsigned last_n = n_nodes * 4u - 4u, last_l = n_leaves * 4u - 4u;
+            const unsigned last_n = n_nodes * 4u - 4u;
 #pragma unroll
             for (int i = 0; i < E; ++i) {
-                const unsigned o = (unsigned)(tid + i * P) * 4u;
-                const unsigned on = min(o, last_n), ol = min(o, last_l);
+                if ((unsigned)(i * kScoreThreads) >= n_nodes) break;
+                const unsigned on = min((unsigned)(tid + i * kScoreThreads) * 4u, last_n);
                 st_feat[i] = *reinterpret_cast<const int *>(fc + on);
                 st_thr[i] = *reinterpret_cast<const float *>(hc + on);
-                st_leaf[i] = *reinterpret_cast<const float *>(lc + ol);
             }
         }
     };
     // a node in LDS: (LDS address of its feature's row of the tile, threshold bits)
     auto row_of = [&](int ft) { return lds0 + (unsigned)min(max(ft, 0), d - 1) * (unsigned)(P * 4); };
     auto store_chunk = [&](int tc) {
-        const unsigned nodes_end = (unsigned)(tc * n_int) * 8u, leaves_end = (unsigned)(tc * n_leaf) * 4u;
-        const unsigned nodes_at = lds0 + xs_bytes, leaves_at = nodes_at + node_bytes;
+        const unsigned nodes_end = (unsigned)(tc * n_int) * 8u;
         if (quads && (tc & 3) == 0) {
 #pragma unroll
-            for (int i = 0; i < G; ++i) {
-                const unsigned g = (unsigned)(tid + i * P);
+            for (int i = 0; i < kStageQuads; ++i) {
+                const unsigned g = (unsigned)(tid + i * kScoreThreads);
                 if (g * 32u < nodes_end) {
                     uint4v lo, hi;
                     lo.x = row_of(st_feat[4 * i + 0]); lo.y = __float_as_uint(st_thr[4 * i + 0]);
@@ -129,34 +136,37 @@ __global__ void __launch_bounds__(P) gbt_score_kernel(ForestArgs f, const float 
                     lds_write_u4(nodes_at + g * 32u, lo);
                     lds_write_u4(nodes_at + g * 32u + 16u, hi);
                 }
-                if (g * 16u < leaves_end) {
-                    float4v l;
-                    l.x = st_leaf[4 * i + 0]; l.y = st_leaf[4 * i + 1]; l.z = st_leaf[4 * i + 2]; l.w = st_leaf[4 * i + 3];
-                    lds_write_f4(leaves_at + g * 16u, l);
-                }
             }
         } else {
 #pragma unroll
             for (int i = 0; i < E; ++i) {
-                const unsigned e = (unsigned)(tid + i * P);
+                const unsigned e = (unsigned)(tid + i * kScoreThreads);
                 if (e * 8u < nodes_end) {
                     uint2v n;
                     n.x = row_of(st_feat[i]); n.y = __float_as_uint(st_thr[i]);
                     lds_write_u2(nodes_at + e * 8u, n);
                 }
-                if (e * 4u < leaves_end) lds_write_f(leaves_at + e * 4u, st_leaf[i]);
             }
         }
     };
 
     float sum = f.base;
-    // W trees are walked side by side: a walk is a chain of dependent LDS reads (node, then feature value),
-    // and independent chains keep more of them in flight.  The leaves are still added in tree order.
-    auto walk_chunk = [&](int tc) {
-        const unsigned nodes_at = lds0 + xs_bytes;                             // LDS address of the node block
-        const unsigned leaves_at = nodes_at + node_bytes;
-        const unsigned tid4 = (unsigned)tid * 4u;
-        for (int t = 0; t < tc; t += W) {
+    // The leaf values of the group of trees walked last, on their way: a walk is a chain of dependent LDS reads, so W
+    // trees go side by side, and their leaves are picked up only when the next group has been walked.
+    float pend[W];
+    int pend_n = 0, pend_t = 0;                                                  // how many, and the first tree's place in the chunk
+    auto take_pending = [&]() {
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            if (w >= pend_n) break;
+            if constexpr (SL == 1) sum = sum + pend[w];
+            else *(__attribute__((address_space(3))) float *)(uintptr_t)(lv_at + (unsigned)((pend_t + w) * P + cfg) * 4u) = pend[w];
+        }
+    };
+    const unsigned cfg4 = (unsigned)cfg * 4u;
+    auto walk_chunk = [&](int t0, int tc) {
+        const char *const lc = reinterpret_cast<const char *>(f.leaf + (size_t)t0 * n_leaf);
+        for (int t = slice * W; t < tc; t += SL * W) {
             unsigned base[W], a[W], k_left[W], k_right[W];
 #pragma unroll
             for (int w = 0; w < W; ++w) {
@@ -172,15 +182,18 @@ __global__ void __launch_bounds__(P) gbt_score_kernel(ForestArgs f, const float 
                 for (int w = 0; w < W; ++w) nd[w] = lds_read_u2(a[w]);
                 float xv[W];
 #pragma unroll
-                for (int w = 0; w < W; ++w) xv[w] = lds_read_f(nd[w].x + tid4);
+                for (int w = 0; w < W; ++w) xv[w] = lds_read_f(nd[w].x + cfg4);
 #pragma unroll
                 for (int w = 0; w < W; ++w) a[w] = 2u * a[w] + ((xv[w] < __uint_as_float(nd[w].y)) ? k_left[w] : k_right[w]);
             }
-            // leaf l of tree t + w: the walk ends at a = base + 8 (n_int + l), the leaf sits at leaves_at + 4 ((t + w) n_leaf + l)
-            // = a / 2 + (leaves_at + 4 (t + w) n_leaf - 4 n_int - base / 2): one shift and one add of a scalar
+            take_pending();
+            // leaf l of tree t + w: the walk ends at a = base + 8 (n_int + l), the leaf is element (t + w) n_leaf + l of the
+            // chunk, at byte a / 2 + (4 (t + w) n_leaf - 4 n_int - base / 2): one shift and one add of a scalar
 #pragma unroll
             for (int w = 0; w < W; ++w)
-                if (t + w < tc) sum = sum + lds_read_f((a[w] >> 1) + (leaves_at + 4u * (unsigned)((t + w) * n_leaf - n_int) - (base[w] >> 1)));
+                pend[w] = *reinterpret_cast<const float *>(lc + ((a[w] >> 1) + (4u * (unsigned)(min(t + w, tc - 1) * n_leaf - n_int) - (base[w] >> 1))));
+            pend_n = min(W, tc - t);
+            pend_t = t;
         }
     };
     const int tpc = trees_per_chunk;
@@ -191,86 +204,108 @@ __global__ void __launch_bounds__(P) gbt_score_kernel(ForestArgs f, const float 
         const int tc = min(tpc, f.n_trees - t0);
         const int tc_next = min(tpc, f.n_trees - (t0 + tpc));
         if (tc_next > 0) fetch_chunk(t0 + tpc, tc_next);
-        walk_chunk(tc);
+        walk_chunk(t0, tc);
+        if constexpr (SL > 1) {
+            take_pending();
+            pend_n = 0;
+        }
         __syncthreads();   // every wave is done with this chunk
         if (tc_next > 0) store_chunk(tc_next);
+        if constexpr (SL > 1) {
+            if (slice == 0) {
+                const unsigned at = lv_at + cfg4;
+                for (int t = 0; t < tc; ++t) sum = sum + lds_read_f(at + (unsigned)(t * P) * 4u);
+            }
+        }
         __syncthreads();
     }
-    if (valid) score[row] = sum;
+    if constexpr (SL == 1) take_pending();
+    if (valid && slice == 0) score[(int64_t)blockIdx.y * N + row] = sum;
 }
 
-using Kernel = void (*)(ForestArgs, const float *, int64_t, int, int64_t, float *, int, int);
+using Kernel = void (*)(ForestBatch, const float *, int64_t, int, int64_t, int64_t, float *, int, int);
 
-// the kernels of one tile size: 4, 2, 1 trees side by side
+// the tiles, and the kernels of each for 4, 2, 1 trees side by side
 struct TileKernels {
-    int threads, groups;
+    int tile;
     Kernel kernel[3];
 };
-constexpr int kTileSizes = 2;
-static_assert(RLS_MAX_D * 896 * 4 + ((1 << RLS_MAX_DEPTH) - 1) * 8 + (1 << RLS_MAX_DEPTH) * 4 <= 160 * 1024,
-              "the deepest tree fits beside the smaller tile at the largest number of features");
 template <int P>
-TileKernels tile_kernels()
+constexpr TileKernels tile_kernels()
 {
-    constexpr int G = stage_groups(kForestChunkBytes, P);
-    return TileKernels{P, G, {gbt_score_kernel<P, G, 4>, gbt_score_kernel<P, G, 2>, gbt_score_kernel<P, G, 1>}};
+    return TileKernels{P, {gbt_score_kernel<P, 4>, gbt_score_kernel<P, 2>, gbt_score_kernel<P, 1>}};
 }
+static_assert(RLS_MAX_D * kScoreThreads * 4 + ((1 << RLS_MAX_DEPTH) - 1) * 8 <= kScoreLds,
+              "the deepest tree fits beside the largest tile at the largest number of features");
+
+struct ScorePlan {
+    const TileKernels *tile;
+    int side, tpc;           // trees side by side, trees per chunk
+    size_t lds;
+};
 
 }  // namespace
 
 hipError_t launch_gbt_score(const ForestArgs *forests_host, int32_t batch, const float *X, int64_t N, int32_t d,
                             int64_t ldx, int64_t x_batch_stride, float *score, hipStream_t s)
 {
-    // tiles, largest first: with up to 32 features and trees of depth up to 12 no smaller one ever holds more trees
-    static const TileKernels tiles[kTileSizes] = {tile_kernels<1024>(), tile_kernels<896>()};
+    static const TileKernels tiles[] = {tile_kernels<1024>(), tile_kernels<512>(), tile_kernels<256>(), tile_kernels<128>(),
+                                        tile_kernels<64>()};
     static std::once_flag attr_once;
     static hipError_t attr_status = hipSuccess;
     std::call_once(attr_once, [] {
         for (const TileKernels &t : tiles)
             for (const Kernel k : t.kernel)
                 if (attr_status == hipSuccess)
-                    attr_status = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
-                                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+                    attr_status = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kScoreLds);
     });
     if (attr_status != hipSuccess) return attr_status;
-    for (int32_t b = 0; b < batch; ++b) {
-        const ForestArgs &f = forests_host[b];
-        const int64_t tree_bytes = (((int64_t)1 << f.depth) - 1) * 8 + ((int64_t)1 << f.depth) * 4;
-        // The forest chunks take what the tile of configurations leaves of the 160 KB, at most kForestChunkBytes.  Every
-        // workgroup streams the whole forest, so the tile is the largest whose remainder still holds the trees a lane
-        // walks side by side (failing that, the largest among those that hold the most).
-        const TileKernels *tile = nullptr;
-        int64_t chunk_bytes = 0;
-        int best_side = 0;
-        for (const TileKernels &t : tiles) {
-            const int64_t space = std::min<int64_t>(kForestChunkBytes, 160 * 1024 - (int64_t)d * t.threads * 4);
-            const int64_t fit = space > 0 ? space / tree_bytes : 0;
-            const int side = fit >= kSideBySide ? kSideBySide : (fit >= 2 ? 2 : (fit >= 1 ? 1 : 0));
-            if (side > best_side) { best_side = side; tile = &t; chunk_bytes = space; }
+    for (int32_t b0 = 0; b0 < batch;) {
+        // one launch for the spaces that follow each other with forests of one shape
+        const int n_trees = forests_host[b0].n_trees, depth = forests_host[b0].depth;
+        int nb = 1;
+        while (b0 + nb < batch && nb < kScoreBatch && forests_host[b0 + nb].n_trees == n_trees && forests_host[b0 + nb].depth == depth) ++nb;
+        ForestBatch fb;
+        uintptr_t bits = 0;
+        for (int i = 0; i < kScoreBatch; ++i) {
+            fb.f[i] = forests_host[b0 + (i < nb ? i : 0)];
+            bits |= reinterpret_cast<uintptr_t>(fb.f[i].feat) | reinterpret_cast<uintptr_t>(fb.f[i].thr);
         }
-        if (tile == nullptr) return hipErrorInvalidValue;          // one tree does not fit beside any tile
-        const int P = tile->threads;
-        const int groups = tile->groups;
-        int tpc = (int)(chunk_bytes / tree_bytes);
-        // a thread stages 4 * groups entries of the next chunk: its leaves (the larger of the two arrays) must fit
-        const int64_t stage_cap = ((int64_t)4 * groups * P) >> f.depth;
-        if (tpc > stage_cap) tpc = (int)stage_cap;
-        if (tpc < 1) return hipErrorInvalidValue;                  // depth <= 12: cannot happen
-        const int side = tpc >= 4 ? 4 : (tpc >= 2 ? 2 : 1);
-        tpc -= tpc % side;
-        if (tpc > f.n_trees) tpc = f.n_trees;
-        const size_t lds = (size_t)d * P * 4 + (size_t)tpc * tree_bytes;
-        if (lds > 160 * 1024) return hipErrorInvalidValue;
-        // four entries at a time: every chunk starts at a multiple of four trees, the arrays at multiples of 16 bytes
-        const int quads = (tpc % 4 == 0 || tpc == f.n_trees) &&
-                          ((reinterpret_cast<uintptr_t>(f.feat) | reinterpret_cast<uintptr_t>(f.thr) |
-                            reinterpret_cast<uintptr_t>(f.leaf)) & 15) == 0;
-        const unsigned grid = (unsigned)((N + P - 1) / P);
-        const Kernel kernel = tile->kernel[side == 4 ? 0 : (side == 2 ? 1 : 2)];
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(P), lds, s, f, X + (int64_t)b * x_batch_stride, N, (int)d, ldx,
-                           score + (int64_t)b * N, tpc, quads);
-        hipError_t e = hipGetLastError();
+        const int64_t n_int = ((int64_t)1 << depth) - 1;
+        // The tile: a workgroup pays for moving the whole forest through LDS and for the walks of its tile, and there are
+        // as many turns as the workgroups fill the 256 compute units.  Times in ns, measured at depth 8 and 10: 0.15 per
+        // node moved, 0.045 per configuration and level walked, and a walk of one group of trees takes at least 150 per level.
+        ScorePlan best{nullptr, 0, 0, 0};
+        double best_ns = 0.0;
+        for (const TileKernels &t : tiles) {
+            const int P = t.tile, SL = kScoreThreads / P;
+            const int64_t space = kScoreLds - (int64_t)d * P * 4;
+            int64_t fit = std::min<int64_t>(space / (n_int * 8 + (SL > 1 ? P * 4 : 0)), kChunkNodes / n_int);
+            if (fit < 1) continue;
+            if (fit > n_trees) fit = n_trees;
+            const int side = fit >= 4 * SL ? 4 : (fit >= 2 * SL ? 2 : 1);
+            int tpc = (int)fit;
+            if (tpc > side * SL) tpc -= tpc % (side * SL);      // whole rounds of the slices ...
+            if (tpc > 4) tpc -= tpc % 4;                        // ... and chunks that start at a multiple of four trees
+            if (tpc < n_trees && tpc > 4 && tpc % 4 != 0) continue;
+            const double turns = (double)(((N + P - 1) / P * nb + 255) / 256);
+            const int busy = std::min(SL, (tpc + side - 1) / side);
+            const double walk = std::max(0.045 * P * (depth + 1), 150.0 * depth / (busy * side));
+            const double ns = turns * n_trees * (0.15 * (double)(n_int + 1) + walk);
+            if (best.tile == nullptr || ns < best_ns) {
+                best = ScorePlan{&t, side, tpc, (size_t)d * P * 4 + (size_t)tpc * (n_int * 8 + (SL > 1 ? P * 4 : 0))};
+                best_ns = ns;
+            }
+        }
+        if (best.tile == nullptr) return hipErrorInvalidValue;     // depth <= 12: cannot happen
+        const int quads = (best.tpc % 4 == 0 || best.tpc == n_trees) && (bits & 15) == 0;
+        const Kernel kernel = best.tile->kernel[best.side == 4 ? 0 : (best.side == 2 ? 1 : 2)];
+        const unsigned grid = (unsigned)((N + best.tile->tile - 1) / best.tile->tile);
+        hipLaunchKernelGGL(kernel, dim3(grid, (unsigned)nb), dim3(kScoreThreads), best.lds, s, fb, X + (int64_t)b0 * x_batch_stride, N, (int)d,
+                           ldx, x_batch_stride, score + (int64_t)b0 * N, best.tpc, quads);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
+        b0 += nb;
     }
     return hipSuccess;
 }

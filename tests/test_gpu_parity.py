@@ -60,6 +60,31 @@ def test_gbt_score_shapes(rls, orc, N, d, T, D):
     check_scores(rls, orc, f, X)
 
 
+@pytest.mark.parametrize("N,d,T,D", [
+    # tiles of 64 ... 1024 configurations (by the number of rows), full and with one configuration more or less
+    (63, 8, 64, 6), (64, 8, 65, 6), (2001, 7, 130, 6), (16385, 8, 33, 5), (32769, 16, 50, 7), (65535, 8, 256, 8), (131073, 5, 40, 4),
+    (262145, 32, 12, 6),
+    # trees that leave slices idle, fewer trees than slices, one tree, chunks that hold few deep trees
+    (200, 8, 1, 3), (300, 16, 5, 1), (500, 32, 21, 9), (130, 32, 37, 11), (70, 24, 18, 12)])
+def test_gbt_score_tiles_and_slices(rls, orc, N, d, T, D):
+    rng = np.random.default_rng(N + T)
+    X = rng.standard_normal((N, d)).astype(np.float32)
+    f = synth.random_forest(X, T, D, 0, rng)
+    f.base = -0.5
+    check_scores(rls, orc, f, X)
+
+
+def test_gbt_score_batched_forests_of_different_shapes(rls, orc):
+    """Spaces whose forests share a shape go into one launch (at most 64 of them), the others into launches of their own."""
+    rng = np.random.default_rng(5)
+    shapes = [(20, 5)] * 3 + [(20, 6)] + [(7, 6)] * 2 + [(20, 5)] * 66
+    X = rng.standard_normal((len(shapes), 333, 9)).astype(np.float32)
+    forests = [synth.random_forest(X[b], T, D, 0, rng) for b, (T, D) in enumerate(shapes)]
+    got = rls.gbt_score_batched([rls.DeviceForest.from_host(f) for f in forests], dev(X)).cpu().numpy()
+    for b, f in enumerate(forests):
+        np.testing.assert_array_equal(got[b], orc.gbt_score(f, X[b])[0])
+
+
 def test_gbt_score_feature_index_out_of_range_reads_the_border_column(rls, orc):
     """The library documents that a feature index outside [0, d) reads column 0 or d - 1 (the oracle rejects such a
     forest): the scores equal the oracle's on the forest with its indices brought inside."""
