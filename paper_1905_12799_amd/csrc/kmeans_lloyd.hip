@@ -1432,6 +1432,8 @@ struct ColPart {
     int pad2[2];
 };
 
+static_assert(kStatBlocks * 32 * sizeof(ColPart) >= kSeedExchangeBytes, "the seeding chain's exchange area lies in this block");
+
 __global__ void __launch_bounds__(kThreads) colstats_kernel(const float *__restrict__ X, int64_t N, int d, int dp, int64_t ldx,
                                                            int64_t x_bs, char *ws, int64_t ws_bs, int64_t off_part)
 {

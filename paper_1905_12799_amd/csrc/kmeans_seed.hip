@@ -7,11 +7,16 @@
 // with separately rounded multiply and add.  Sums are hierarchical (thread -> wave -> block ->
 // blocks) in a fixed order, so a chain is reproducible run to run.
 //
+// Two forms.  Up to about a million points the whole chain is one launch with the points in registers
+// (seed_chain_kernel).  More points, or more spaces than compute units, are walked in memory, one update and one draw
+// launch per centre:
 // Most rows are never read after the first steps: with each point the position a_i of its nearest centre is kept, and
 // when centre c is added a point with D_i <= |c_{a_i} - c|^2 / 4 cannot come closer to c than it is to c_{a_i}
 // (triangle inequality: |x_i - c| >= |c_{a_i} - c| - |x_i - c_{a_i}| >= sqrt(D_i)), so D_i stays and the row is not
 // fetched.  The bound carries a margin of 2^-30, far above the rounding of the fp64 sums, so every skipped point is one
 // whose computed distance would not have been smaller: D, the block sums and the chain are the same with and without it.
+#include <atomic>
+
 #include "rls_internal.h"
 
 namespace rls {
@@ -30,6 +35,9 @@ __device__ inline double uniform01(uint64_t seed, uint64_t j)
 {
     return (double)(splitmix64(seed, j) >> 11) * 0x1.0p-53;
 }
+
+// how long a workgroup of seed_chain_kernel waits for the others before it gives up (100 MHz clock: 50 ms)
+std::atomic<long long> g_wait_ticks{5000000};
 
 struct SeedList {
     uint64_t seed[64];
@@ -358,7 +366,441 @@ __global__ void __launch_bounds__(1024) seed_pick_kernel(SeedList seeds, int b0,
     }
 }
 
+// ---- the chain in one launch --------------------------------------------------------------------------------------
+// Up to one point per register slot of the chip (1M points at 16 features) the whole chain runs in one launch: a thread
+// keeps the rows and distances of its P points in registers for all steps, and per step the G workgroups of a space
+// exchange two messages through memory - every workgroup the sum of its D, then the workgroup that holds the drawn point
+// that point's row and index.  What bounds a step is the latency of these two exchanges and of the scans between them:
+// two launches per centre (an update of 7 to 12 us, a draw of 9 to 11 us and the ramp of each) took 17 to 23 us.
+// (One launch: 3.0 us per centre at 2000 x 8, 5.3 at 65,536 x 16, 8.5 at 1M x 16, against 13.6, 16.6 and 22.4.)
+//
+// A message is a word of 8 bytes that carries its own validity - the area is filled with kSlotEmpty before the launch,
+// every word is written once, and a row travels as words of (step, value) - so no flags, fences or counters are needed:
+// words are stored and polled with agent-scope atomics, which reach past the L2 of an XCD.
+//
+// No wait is unbounded: the workgroups need not be resident together (nothing guarantees that while other streams hold
+// compute units), so a workgroup that has waited `wait_ticks` gives up, the chain stays unfinished, and
+// seed_chain_rest_kernel, always launched behind, does it in one workgroup without any exchange.
+constexpr unsigned long long kSlotEmpty = ~0ull;
+constexpr int kChainWgs = 256;                                 // workgroups per space at most
+constexpr int kRowWords = RLS_MAX_D + 1;                       // row, then the index
+constexpr int kExRows = RLS_MAX_K * kChainWgs;                 // word offsets within the exchange area of a space
+constexpr int kExDone = kExRows + RLS_MAX_K * kRowWords;
+constexpr int kExWords = kExDone + 1;
+static_assert(kExWords * 8 <= kSeedExchangeBytes, "the exchange area must fit its place in the workspace");
+
+struct ChainArgs {
+    const float *X;
+    int64_t N;
+    int32_t d;
+    int64_t ldx, x_bs;
+    int32_t j_begin, k_max, groups;       // positions j_begin .. k_max - 1 are drawn by `groups` workgroups per space
+    double *mind;                         // [N]: read when j_begin > 1, written at the end (a later call may go on from here)
+    int64_t mind_bs;
+    int64_t *chain;
+    int64_t chain_bs;
+    unsigned long long *ex;               // exchange area
+    int64_t ex_bs;
+    long long wait_ticks;                 // of the 100 MHz clock
+};
+
+__global__ void __launch_bounds__(256) seed_begin_kernel(SeedList seeds, ChainArgs a)
+{
+    const int b = blockIdx.y;
+    unsigned long long *ex = a.ex + (int64_t)b * a.ex_bs;
+    const int t0 = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
+    for (int e = t0; e < a.k_max * kChainWgs; e += step)
+        if (e % kChainWgs < a.groups) ex[e] = kSlotEmpty;
+    for (int e = t0; e < a.k_max * kRowWords; e += step) ex[kExRows + e] = kSlotEmpty;
+    if (t0 == 0) {
+        ex[kExDone] = 0ull;
+        if (a.j_begin == 0) {
+            int64_t first = (int64_t)(uniform01(seeds.seed[b], 0) * (double)a.N);
+            if (first >= a.N) first = a.N - 1;
+            a.chain[(int64_t)b * a.chain_bs] = first;
+        }
+    }
+}
+
+// lane exchanges inside rows of 16 (shift right by 1, 2, 4, 8) and across them (broadcast of lanes 15 and 31): a lane
+// without a source, or in a row that is masked out, receives zero
+template <int CTRL, int ROWS>
+__device__ inline double dpp_or_zero(double v)
+{
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false));
+}
+// inclusive prefix sums over the wave; lane 63 holds the total
+__device__ inline double wave_scan_dpp(double v)
+{
+    v = __dadd_rn(v, dpp_or_zero<0x111, 0xf>(v));
+    v = __dadd_rn(v, dpp_or_zero<0x112, 0xf>(v));
+    v = __dadd_rn(v, dpp_or_zero<0x114, 0xf>(v));
+    v = __dadd_rn(v, dpp_or_zero<0x118, 0xf>(v));
+    v = __dadd_rn(v, dpp_or_zero<0x142, 0xa>(v));
+    v = __dadd_rn(v, dpp_or_zero<0x143, 0xc>(v));
+    return v;
+}
+__device__ inline double lane_value(double v, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+__device__ inline double lane_before(double v)      // the value of the lane below; 0 in lane 0
+{
+    const double o = __shfl_up(v, 1, 64);
+    return (threadIdx.x & 63) ? o : 0.0;
+}
+
+// Of E values per lane, numbered lane * E + e, with exclusive prefixes that start at `before` (`incl`: inclusive prefix
+// sums over the lanes): the first whose inclusive
+// prefix exceeds r (a value of zero is never taken), and the prefix before it; none (r rounded up to the sum): the last
+// positive one.  Same answer in every lane; -1 when no value is positive.
+template <int E>
+__device__ inline int wave_locate(const double (&v)[E], double incl, double before, double r, double &prefix)
+{
+    double run = __dadd_rn(before, lane_before(incl)), at = 0.0;
+    int hit = -1, last = -1;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const double nxt = __dadd_rn(run, v[e]);
+        if (v[e] > 0.0) {
+            if (hit < 0 && nxt > r) { hit = e; at = run; }
+            last = e;
+        }
+        run = nxt;
+    }
+    const unsigned long long hits = __ballot(hit >= 0);
+    if (hits) {
+        const int ln = __ffsll((long long)hits) - 1;
+        prefix = lane_value(at, ln);
+        return ln * E + __builtin_amdgcn_readlane(hit, ln);
+    }
+    const unsigned long long pos = __ballot(last >= 0);
+    prefix = r;                                    // nothing below exceeds it either: the last positive value again
+    if (!pos) return -1;
+    const int ln = 63 - __clzll((long long)pos);
+    return ln * E + __builtin_amdgcn_readlane(last, ln);
+}
+
+__device__ inline void post(unsigned long long *p, unsigned long long v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline unsigned long long peek(const unsigned long long *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// smallest index that is not among the j chosen ones (N >= k_max: it exists)
+__device__ inline int64_t first_not_chosen(const int64_t *chosen, int j)
+{
+    for (int64_t i = 0;; ++i) {
+        bool taken = false;
+        for (int m = 0; m < j; ++m) taken |= chosen[m] == i;
+        if (!taken) return i;
+    }
+}
+
+// DP: padded features (a padded feature is zero on both sides and adds +0), P: points per thread.
+template <int DP, int P>
+__global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainArgs a)
+{
+    constexpr int E = P > 4 ? P / 4 : 1;           // sums of 64 points that a lane of wave 0 looks at
+    __shared__ float cs[DP];
+    __shared__ double wsum[64 * E];
+    __shared__ int64_t chosen[RLS_MAX_K];
+    __shared__ int64_t s_pick;
+    __shared__ double s_before, s_r;
+    __shared__ int s_owner, s_entry, s_give_up;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int w = blockIdx.x, G = a.groups, b = blockIdx.y, d = a.d;
+    const float *Xb = a.X + (int64_t)b * a.x_bs;
+    double *mind = a.mind + (int64_t)b * a.mind_bs;
+    int64_t *chain = a.chain + (int64_t)b * a.chain_bs;
+    unsigned long long *ex = a.ex + (int64_t)b * a.ex_bs;
+    const uint64_t seed = seeds.seed[b];
+    const int j0 = a.j_begin > 1 ? a.j_begin : 1;
+
+    // this workgroup's points are base .. base + 1024 P - 1, point 1024 i + tid of them belongs to thread tid
+    const int64_t base = (int64_t)w * (1024 * P);
+    float x[P][DP];
+    double D[P];                                    // 0 for a point past the end: it is never drawn
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+        const int64_t p = base + 1024 * i + tid;
+        const float *row = Xb + min(p, a.N - 1) * a.ldx;
+#pragma unroll
+        for (int l = 0; l < DP; ++l) x[i][l] = l < d ? row[min(l, d - 1)] : 0.0f;
+        D[i] = a.j_begin > 1 && p < a.N ? mind[p] : 0.0;
+    }
+    if (tid < j0) chosen[tid] = chain[tid];
+    if (tid < 64 * E) wsum[tid] = 0.0;
+    if (tid == 0) s_give_up = 0;
+    __syncthreads();
+    if (tid < DP) cs[tid] = tid < d ? Xb[chosen[j0 - 1] * a.ldx + tid] : 0.0f;
+    __syncthreads();
+
+    for (int j = j0; j < a.k_max; ++j) {
+        // ---- the newest centre
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            double acc = 0.0;
+#pragma unroll
+            for (int l = 0; l < DP; ++l) {
+                const double diff = __dsub_rn((double)x[i][l], (double)cs[l]);
+                acc = __dadd_rn(acc, __dmul_rn(diff, diff));
+            }
+            if (base + 1024 * i + tid < a.N && (j == 1 || acc < D[i])) D[i] = acc;
+            const double incl = wave_scan_dpp(D[i]);
+            if (lane == 63) wsum[i * 16 + wave] = incl;
+        }
+        __syncthreads();
+        // ---- total, draw, and whose point it is: wave 0 of every workgroup finds the same answer
+        if (wave == 0) {
+            double own[E];
+            double loc = 0.0;
+#pragma unroll
+            for (int e = 0; e < E; ++e) { own[e] = wsum[lane * E + e]; loc = __dadd_rn(loc, own[e]); }
+            const double own_incl = wave_scan_dpp(loc), total = lane_value(own_incl, 63);
+            double v[4] = {0.0, 0.0, 0.0, 0.0};
+            bool lost = false;
+            if (G > 1) {
+                unsigned long long *slot = ex + j * kChainWgs;
+                if (lane == 0) {
+                    unsigned long long bits = (unsigned long long)__double_as_longlong(total);
+                    if (bits == kSlotEmpty) bits = 0x7ff8000000000000ull;
+                    post(slot + w, bits);
+                }
+                const long long t0 = wall_clock64();
+                for (;;) {
+                    bool miss = false;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        if (4 * lane + q < G) {
+                            const unsigned long long bits = peek(slot + 4 * lane + q);
+                            miss = miss || bits == kSlotEmpty;
+                            v[q] = __longlong_as_double((long long)bits);
+                        }
+                    }
+                    if (__ballot(miss) == 0ull) break;
+                    if (wall_clock64() - t0 > a.wait_ticks) { lost = true; break; }
+                }
+            } else if (lane == 0) {
+                v[0] = total;
+            }
+            if (lost) {
+                if (lane == 0) s_give_up = 1;
+            } else {
+                const double incl = wave_scan_dpp(__dadd_rn(__dadd_rn(__dadd_rn(v[0], v[1]), v[2]), v[3])), S = lane_value(incl, 63);
+                int owner = -1, entry = 0;
+                double before = 0.0, r = 0.0;
+                if (S > 0.0) {                      // else: every point coincides with a chosen centre
+                    r = __dmul_rn(uniform01(seed, (uint64_t)j), S);
+                    owner = wave_locate<4>(v, incl, 0.0, r, before);
+                    if (owner == w) {
+                        double at;
+                        entry = max(wave_locate<E>(own, own_incl, before, r, at), 0);
+                        before = at;
+                    }
+                }
+                if (lane == 0) { s_owner = owner; s_entry = entry; s_before = before; s_r = r; }
+            }
+        }
+        __syncthreads();
+        if (s_give_up) return;                      // same for the whole workgroup
+        const int owner = s_owner;
+        // ---- the drawn point: its workgroup hands out row and index
+        if (owner < 0) {
+            if (tid == 0) s_pick = first_not_chosen(chosen, j);
+            __syncthreads();
+            if (tid < DP) cs[tid] = tid < d ? Xb[s_pick * a.ldx + tid] : 0.0f;
+        } else if (owner == w) {
+            if (wave == (s_entry & 15)) {
+                const int ii = s_entry >> 4;
+                double v[1] = {D[0]};
+#pragma unroll
+                for (int i = 1; i < P; ++i)
+                    if (ii == i) v[0] = D[i];
+                double at;
+                const int ln = __builtin_amdgcn_readfirstlane(max(wave_locate<1>(v, wave_scan_dpp(v[0]), s_before, s_r, at), 0));
+                float mine = 0.0f;
+#pragma unroll
+                for (int l = 0; l < DP; ++l) {
+                    float val = x[0][l];
+#pragma unroll
+                    for (int i = 1; i < P; ++i)
+                        if (ii == i) val = x[i][l];
+                    const int got = __builtin_amdgcn_readlane(__float_as_int(val), ln);
+                    if (lane == l) mine = __int_as_float(got);
+                }
+                const int64_t pick = min(base + 1024 * ii + 64 * wave + ln, a.N - 1);
+                if (G > 1 && (lane < DP || lane == RLS_MAX_D)) {
+                    const unsigned val = lane < DP ? __float_as_uint(mine) : (unsigned)pick;
+                    post(ex + kExRows + j * kRowWords + lane, ((unsigned long long)j << 32) | val);
+                }
+                if (lane < DP) cs[lane] = mine;
+                if (lane == 0) s_pick = pick;
+            }
+        } else if (wave == 0) {
+            const bool mine = lane < DP || lane == RLS_MAX_D;
+            unsigned long long bits = 0ull;
+            bool lost = false;
+            const long long t0 = wall_clock64();
+            for (;;) {
+                if (mine) bits = peek(ex + kExRows + j * kRowWords + lane);
+                if (__ballot(mine && bits == kSlotEmpty) == 0ull) break;
+                if (wall_clock64() - t0 > a.wait_ticks) { lost = true; break; }
+            }
+            if (lost) {
+                if (lane == 0) s_give_up = 1;
+            } else {
+                if (lane < DP) cs[lane] = __uint_as_float((unsigned)bits);
+                if (lane == RLS_MAX_D) s_pick = (int64_t)(unsigned)bits;
+            }
+        }
+        __syncthreads();
+        if (s_give_up) return;
+        if (tid == 0) {
+            chosen[j] = s_pick;
+            if (w == 0) chain[j] = s_pick;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+        const int64_t p = base + 1024 * i + tid;
+        if (p < a.N) mind[p] = D[i];
+    }
+    if (w == 0 && tid == 0) ex[kExDone] = 1ull;
+}
+
+// The chain by one workgroup per space, with nothing to wait for: runs only where seed_chain_kernel gave up.  The
+// distances to the centres drawn by earlier calls are worked out again (some of them may be half updated).
+__global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, ChainArgs a)
+{
+    __shared__ float cs[RLS_MAX_D];
+    __shared__ int64_t chosen[RLS_MAX_K];
+    __shared__ double wtot[16];
+    __shared__ int s_first, s_last;
+    __shared__ int64_t s_pick;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, d = a.d;
+    const unsigned long long *ex = a.ex + (int64_t)b * a.ex_bs;
+    if (ex[kExDone] != 0ull) return;
+    const float *Xb = a.X + (int64_t)b * a.x_bs;
+    double *D = a.mind + (int64_t)b * a.mind_bs;
+    int64_t *chain = a.chain + (int64_t)b * a.chain_bs;
+    const int j0 = a.j_begin > 1 ? a.j_begin : 1;
+    if (tid < j0) chosen[tid] = chain[tid];
+    const int64_t len = (a.N + 1023) / 1024, p0 = min(tid * len, a.N), p1 = min(p0 + len, a.N);    // this thread's points
+    for (int j = 1; j < a.k_max; ++j) {
+        __syncthreads();
+        if (tid < d) cs[tid] = Xb[chosen[j - 1] * a.ldx + tid];
+        if (tid == 0) { s_first = 0x7fffffff; s_last = -1; }
+        __syncthreads();
+        double local = 0.0;
+        for (int64_t p = p0; p < p1; ++p) {
+            double acc = 0.0;
+            for (int l = 0; l < d; ++l) {
+                const double diff = __dsub_rn((double)Xb[p * a.ldx + l], (double)cs[l]);
+                acc = __dadd_rn(acc, __dmul_rn(diff, diff));
+            }
+            double cur = j == 1 ? acc : D[p];
+            if (acc < cur) cur = acc;
+            D[p] = cur;
+            local = __dadd_rn(local, cur);
+        }
+        if (j < j0) continue;
+        const double incl = wave_scan_dpp(local);
+        if (lane == 63) wtot[wave] = incl;
+        __syncthreads();
+        double before = 0.0, S = 0.0;
+        for (int v = 0; v < 16; ++v) {
+            if (v == wave) before = S;
+            S = __dadd_rn(S, wtot[v]);
+        }
+        double run = __dadd_rn(before, lane_before(incl));
+        const double r = __dmul_rn(uniform01(seeds.seed[b], (uint64_t)j), S);
+        if (local > 0.0) {
+            if (__dadd_rn(run, local) > r) atomicMin(&s_first, tid);
+            atomicMax(&s_last, tid);
+        }
+        __syncthreads();
+        if (!(S > 0.0) || s_last < 0) {
+            if (tid == 0) s_pick = first_not_chosen(chosen, j);
+        } else if (tid == (s_first != 0x7fffffff ? s_first : s_last)) {
+            int64_t pick = -1;
+            for (int64_t p = p0; p < p1; ++p) {
+                const double v = D[p];
+                run = __dadd_rn(run, v);
+                if (v > 0.0) {
+                    pick = p;
+                    if (run > r) break;
+                }
+            }
+            s_pick = pick;
+        }
+        __syncthreads();
+        if (tid == 0) { chosen[j] = s_pick; chain[j] = s_pick; }
+    }
+}
+
 }  // namespace
+
+void set_seed_wait_ticks(long long ticks) { g_wait_ticks.store(ticks, std::memory_order_relaxed); }
+
+// compute units of the current device, asked for once per device
+static int compute_units()
+{
+    constexpr int kMaxDevices = 64;
+    static std::atomic<int> known[kMaxDevices];
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
+    int n = known[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+        known[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
+// Points per thread of seed_chain_kernel: the fewest with which the workgroups of all spaces fit the compute units one
+// each (a workgroup of 1024 threads with up to 64 row registers fills one); 0: they do not fit, the points are walked in
+// memory, one update and one draw per centre.  Up to 4096 points of a space stay in one workgroup, which has nothing to exchange.
+static int chain_points_per_thread(int64_t N, int dp, int spaces, int *groups)
+{
+    const int most = 64 / dp;
+    const int cus = compute_units();
+    for (int p = 1; p <= most; p *= 2) {
+        const int64_t g = (N + 1024 * p - 1) / (1024 * p);
+        if (g > 1 && N <= 4096 && 2 * p <= most && p < 4) continue;
+        if (g * spaces > cus || g > kChainWgs) continue;
+        *groups = (int)g;
+        return p;
+    }
+    return 0;
+}
+
+static hipError_t launch_chain_in_one(int dp, int p, int spaces, const SeedList &sl, const ChainArgs &a, hipStream_t s)
+{
+    hipLaunchKernelGGL(seed_begin_kernel, dim3(16, spaces), dim3(256), 0, s, sl, a);
+    const dim3 grid(a.groups, spaces), block(1024);
+#define RLS_SEED_CHAIN(DPV, PV)                                                                                          \
+    case DPV * 16 + PV: hipLaunchKernelGGL((seed_chain_kernel<DPV, PV>), grid, block, 0, s, sl, a); break
+    switch (dp * 16 + p) {
+    RLS_SEED_CHAIN(8, 1);
+    RLS_SEED_CHAIN(8, 2);
+    RLS_SEED_CHAIN(8, 4);
+    RLS_SEED_CHAIN(8, 8);
+    RLS_SEED_CHAIN(16, 1);
+    RLS_SEED_CHAIN(16, 2);
+    RLS_SEED_CHAIN(16, 4);
+    RLS_SEED_CHAIN(32, 1);
+    RLS_SEED_CHAIN(32, 2);
+    default: return hipErrorInvalidValue;
+    }
+#undef RLS_SEED_CHAIN
+    if (a.groups > 1) hipLaunchKernelGGL(seed_chain_rest_kernel, dim3(spaces), dim3(1024), 0, s, sl, a);
+    return hipGetLastError();
+}
 
 hipError_t launch_seed_chain(const float *X, int64_t N, int32_t d, int64_t ldx, int64_t x_batch_stride, int32_t batch,
                              int32_t k_max, const uint64_t *seeds_host, int64_t *chain, int64_t chain_batch_stride,
@@ -372,6 +814,24 @@ hipError_t launch_seed_chain(const float *X, int64_t N, int32_t d, int64_t ldx, 
         SeedList sl;
         for (int i = 0; i < 64; ++i) sl.seed[i] = seeds_host[b0 + (i < nb ? i : 0)];
         char *wsb = ws + (int64_t)b0 * L.per_batch;
+        if (k_max <= 1) {
+            if (j_begin == 0) hipLaunchKernelGGL(seed_first_kernel, dim3(nb), dim3(64), 0, s, sl, b0, N, chain, chain_batch_stride);
+            continue;
+        }
+        const int dp = padded_d(d);
+        int groups = 0;
+        if (const int p = chain_points_per_thread(N, dp, nb, &groups)) {
+            ChainArgs ca;
+            ca.X = X + (int64_t)b0 * x_batch_stride; ca.N = N; ca.d = d; ca.ldx = ldx; ca.x_bs = x_batch_stride;
+            ca.j_begin = j_begin; ca.k_max = k_max; ca.groups = groups;
+            ca.mind = reinterpret_cast<double *>(wsb + L.mind); ca.mind_bs = L.per_batch / 8;
+            ca.chain = chain + (int64_t)b0 * chain_batch_stride; ca.chain_bs = chain_batch_stride;
+            ca.ex = reinterpret_cast<unsigned long long *>(wsb + L.colstat_part); ca.ex_bs = L.per_batch / 8;
+            ca.wait_ticks = g_wait_ticks.load(std::memory_order_relaxed);
+            const hipError_t e = launch_chain_in_one(dp, p, nb, sl, ca, s);
+            if (e != hipSuccess) return e;
+            continue;
+        }
         SeedState st;
         st.mind = reinterpret_cast<double *>(wsb + L.mind); st.mind_bs = L.per_batch / 8;
         st.bsum = reinterpret_cast<double *>(wsb + L.bsum); st.bsum_bs = L.per_batch / 8;

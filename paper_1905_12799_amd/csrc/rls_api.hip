@@ -90,6 +90,12 @@ int32_t rls_profile_enable(int32_t on)
     return RLS_OK;
 }
 
+int32_t rls_seed_wait_limit(int64_t ticks)
+{
+    set_seed_wait_ticks(ticks < 0 ? 5000000 : ticks);
+    return RLS_OK;
+}
+
 int32_t rls_profile_read(int32_t *n_launches, double *total_ms)
 {
     if (!n_launches || !total_ms) return RLS_ERR_NULL;

@@ -102,6 +102,8 @@ struct SweepLayout {
 };
 void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, int32_t batch, SweepLayout *L);
 
+// the column statistics' partial results come after the seeding chain: their place serves the chain's exchange area
+constexpr int kSeedExchangeBytes = 256 * 32 * 40;
 constexpr int kSeedBlock = 1024;   // points per block of the seeding kernels
 constexpr int kStatBlocks = 256;   // blocks of the column-statistics kernel
 
@@ -136,6 +138,9 @@ hipError_t launch_apply_actions(const int32_t *cfg, const signed char *action, i
 hipError_t launch_seed_chain(const float *X, int64_t N, int32_t d, int64_t ldx, int64_t x_batch_stride, int32_t batch,
                              int32_t k_max, const uint64_t *seeds_host, int64_t *chain, int64_t chain_batch_stride,
                              char *ws, const SweepLayout &L, hipStream_t s, int32_t j_begin = 0);
+
+// how long the workgroups of a chain wait for each other, in ticks of the 100 MHz clock (see rls_bench.h)
+void set_seed_wait_ticks(long long ticks);
 
 struct SweepArgs {
     const float *X;

@@ -5,6 +5,8 @@ two nearest centroids differ by less than 1e-6 relative, in the oracle's fp64 di
 for centroids (per column scale), inertia and tree scores (scores are also compared bit for bit with the
 oracle's fp32 tree-order sum).
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -308,6 +310,23 @@ def test_seeding_chain_lattice_points(rls, orc, N, d, span, stride):
     for seed in (1, 2):
         got = rls.kmeanspp_chain(Xd, k_max, seed).cpu().numpy()
         np.testing.assert_array_equal(got, orc.kmeanspp_chain(X, k_max, seed))
+
+
+@pytest.mark.parametrize("N,d,k_max", [(1, 3, 1), (2, 8, 2), (1024, 8, 5), (1025, 16, 9), (2049, 32, 128), (4097, 5, 6), (70001, 7, 12),
+                                       (300000, 17, 6), (1048577, 16, 4), (540000, 32, 4), (2000003, 6, 4)])
+def test_seeding_chain_one_launch(rls, orc, N, d, k_max):
+    """Edges of the chain that runs in one launch (one workgroup / several, points per thread, last sizes it takes and
+    the first it does not), and the kernel that takes over when its workgroups stop waiting for each other."""
+    rng = np.random.default_rng(N + d)
+    X = (rng.integers(0, 9, (N, d)) + rng.integers(0, 2, (N, 1)) * 0.25).astype(np.float32)
+    ref = orc.kmeanspp_chain(X, k_max, 21)
+    Xd = dev(X)
+    np.testing.assert_array_equal(rls.kmeanspp_chain(Xd, k_max, 21).cpu().numpy(), ref)
+    try:
+        rls.lib().rls_seed_wait_limit(ctypes.c_int64(0))
+        np.testing.assert_array_equal(rls.kmeanspp_chain(Xd, k_max, 21).cpu().numpy(), ref)
+    finally:
+        rls.lib().rls_seed_wait_limit(ctypes.c_int64(-1))
 
 
 def test_seeding_all_points_equal(rls, orc):
