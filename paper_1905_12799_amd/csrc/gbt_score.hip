@@ -273,8 +273,10 @@ hipError_t launch_gbt_score(const ForestArgs *forests_host, int32_t batch, const
         }
         const int64_t n_int = ((int64_t)1 << depth) - 1;
         // The tile: a workgroup pays for moving the whole forest through LDS and for the walks of its tile, and there are
-        // as many turns as the workgroups fill the 256 compute units.  Times in ns, measured at depth 8 and 10: 0.15 per
-        // node moved, 0.045 per configuration and level walked, and a walk of one group of trees takes at least 150 per level.
+        // as many turns as the workgroups fill the 256 compute units.  Times in ns per tree, fitted to depths 4 to 10 with
+        // tiles of 64 to 1024: 0.15 per node moved, 70 for a tree whatever the tile, 0.032 per configuration and level
+        // walked, and a walk of one group of trees takes at least 100 per level.  (141,494 x 8, 145 trees of depth 7: one
+        // turn of 1024 takes 50 us, three of 256 take 64.)
         ScorePlan best{nullptr, 0, 0, 0};
         double best_ns = 0.0;
         for (const TileKernels &t : tiles) {
@@ -290,7 +292,7 @@ hipError_t launch_gbt_score(const ForestArgs *forests_host, int32_t batch, const
             if (tpc < n_trees && tpc > 4 && tpc % 4 != 0) continue;
             const double turns = (double)(((N + P - 1) / P * nb + 255) / 256);
             const int busy = std::min(SL, (tpc + side - 1) / side);
-            const double walk = std::max(0.045 * P * (depth + 1), 150.0 * depth / (busy * side));
+            const double walk = 70.0 + std::max(0.032 * P * depth, 100.0 * depth / (busy * side));
             const double ns = turns * n_trees * (0.15 * (double)(n_int + 1) + walk);
             if (best.tile == nullptr || ns < best_ns) {
                 best = ScorePlan{&t, side, tpc, (size_t)d * P * 4 + (size_t)tpc * (n_int * 8 + (SL > 1 ? P * 4 : 0))};
