@@ -24,6 +24,7 @@
 //            equal a fresh sum in any order); per-chunk deltas go to global memory and lloyd_centroids_kernel
 //            adds them to the 128-bit totals, rounds once to fp64, divides by the count and rounds to fp32
 // The final pass replaces the update by the fp64 loss of every point and the label output.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -461,7 +462,6 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
     int mask = (int)0xffffff80;
     asm volatile("" : "+v"(mask));                  // keep the mask in a VGPR
 
-    const bool any_wide = c.wide_s[32] != 0;
     // this lane's copy of the accumulators
     unsigned long long *const sums_l = c.sums + (lane & (c.copies - 1)) * c.real_rows * (DP + 1);
     int *const cnts_l = c.cnts + (lane & (c.copies - 1)) * c.real_rows;
@@ -577,6 +577,9 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         if (lane == 0) v = atomicAdd(c.next_slab, 1);
         return __builtin_amdgcn_readfirstlane(v);
     };
+    int cur = wave;
+    fetch(c.chunk_begin + (int64_t)min(cur, n_slabs - 1) * SLAB);
+    const bool any_wide = c.wide_s[32] != 0;
     // part of the error bound that belongs to a run (the centroids' largest squared norm), per run this lane owns
     float tol_run[ST];
 #pragma unroll
@@ -666,10 +669,8 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         }
         log_head += nrec;
     };
-    int cur = wave;
-    if (cur >= n_slabs) return;
-    fetch(c.chunk_begin + (int64_t)cur * SLAB);
     settle();
+    if (cur >= n_slabs) return;
     int nxt = grab();
 
     while (cur < n_slabs) {
@@ -1259,30 +1260,42 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int TH = step_threads_of(DP), WV = TH / 64;
 
-    // Workgroup order: the chunks of all spaces of the batch, numbered space by space, are taken in blocks of
+    // Workgroup order.  Large inputs: the chunks of all spaces of the batch, numbered space by space, are taken in blocks of
     // plan.chunk_block; within a block the groups go heaviest first (the dispatcher hands workgroups out in index order,
     // light ones fill the end), and the workgroups of all groups for one chunk sit a multiple of eight apart - they run
     // at about the same time on the same XCD, so that what one of them reads of the chunk (its rows or its part of the
     // prepared copy) the others find in that XCD's L2.
+    // Small inputs (chunk_block 0): every group has chunks of its own, of about equal cost over all groups, one per compute
+    // unit; the chunks of a group that land on one XCD (every eighth workgroup) follow each other in the points.
     int gi, chunk, b;
-    {
+    if (plan.chunk_block > 0) {
         const int B = plan.chunk_block;
-        const int n_all = plan.n_chunks * a.batch;          // chunks of the whole batch
+        const int n_chunks = plan.g[0].n_chunks;
+        const int n_all = n_chunks * a.batch;               // chunks of the whole batch
         const int per_block = B * plan.n_groups;
         const int blk = blockIdx.x / per_block, rem = blockIdx.x % per_block;
         const int c0 = blk * B;
         const int bw = min(B, n_all - c0);                  // chunks of this block (the last one may be short)
         gi = plan.sched[rem / bw];
         const int vc = c0 + rem % bw;
-        b = vc / plan.n_chunks;
-        chunk = vc - b * plan.n_chunks;
-        // The division leaves these in vector registers although they are the same in every lane.  At d_pad 32 the
-        // kernel sits at the limit of 256 vector registers and spilled 35 of them over it (3% longer launches); as
-        // scalars they cost none.
-        b = __builtin_amdgcn_readfirstlane(b);
-        chunk = __builtin_amdgcn_readfirstlane(chunk);
-        gi = __builtin_amdgcn_readfirstlane(gi);
+        b = vc / n_chunks;
+        chunk = vc - b * n_chunks;
+    } else {
+        b = blockIdx.x / plan.n_wgs;
+        const int v = blockIdx.x - b * plan.n_wgs;
+        gi = 0;
+        while (gi + 1 < plan.n_groups && plan.g[gi + 1].wg0 <= v) ++gi;
+        const int r = v - plan.g[gi].wg0, nc = plan.g[gi].n_chunks;
+        const int first = blockIdx.x - r;                   // launch index of the group's first workgroup
+        chunk = r >> 3;
+        for (int q = 0; q < (int)(blockIdx.x & 7); ++q) chunk += (nc - ((q - first) & 7) + 7) >> 3;   // chunks of the XCDs before this one
     }
+    // The division leaves these in vector registers although they are the same in every lane.  At d_pad 32 the
+    // kernel sits at the limit of 256 vector registers and spilled 35 of them over it (3% longer launches); as
+    // scalars they cost none.
+    b = __builtin_amdgcn_readfirstlane(b);
+    chunk = __builtin_amdgcn_readfirstlane(chunk);
+    gi = __builtin_amdgcn_readfirstlane(gi);
     if (a.status[b] != 0) return;
     const GroupDesc g = plan.g[gi];
     const int d = a.d;
@@ -1309,40 +1322,63 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     const float *Xb = a.X + (int64_t)b * a.x_bs;
     const float *Cb = a.C + (int64_t)b * a.c_bs;
 
-    // group operands, centroids and column info into LDS; accumulators to zero
+    // group operands, centroids and column info into LDS; accumulators to zero.  Everything is requested in batches
+    // before anything is put down (ten trips to memory for the centroids, four for the operands and one per part of a run
+    // for the largest norms took 8 us of a launch of 42 at 65,536 x 16, k 1..64; now 6).
     {
         const float *colmean = reinterpret_cast<const float *>(wsb + a.off_colinfo);
         const int *colshift = reinterpret_cast<const int *>(wsb + a.off_colinfo + 128);
         const int *colwide = reinterpret_cast<const int *>(wsb + a.off_colinfo + 256);
-        if (tid < 32) {
-            mu_s[tid] = tid < DP ? colmean[tid] : 0.0f;                    // colmean: already negated and scaled
-            shift_s[tid] = colshift[tid];
-            pow2hi_s[tid] = (1023 + colshift[tid]) << 20;                 // 2^shift as a double: the high word
-        }
-        if (tid < 33) wide_s[tid] = colwide[tid];
-        const uint4 *src = reinterpret_cast<const uint4 *>(wsb + a.off_opA + (int64_t)g.tile0 * tile_bytes_of(DP));
-        for (int e = tid; e < g.n_tiles * (tile_bytes_of(DP) / 16); e += TH) opA_s[e] = src[e];
+        const float mean_v = colmean[tid & (DP - 1)];
+        const int shift_v = colshift[tid & 31], wide_v = colwide[min(tid, 32)];
+        // the largest squared norm of a run's centroids: the centroid kernel leaves one maximum per part of the run
+        static_assert(kMaxParts == 16 && TH >= 128, "sixteen lanes per run");
+        float pmax = 0.0f;
         {
-            const float *csrc = Cb + (int64_t)grow0 * d;
-            for (int e = tid; e < real_rows * DP; e += TH) {
-                const int j = e / DP, l = e % DP;
-                cs_lds[j * (DP + 4) + l] = l < d ? csrc[j * d + l] : 0.0f;
+            const int r = (tid >> 4) & 7, part = tid & 15;
+            if (r < g.n_runs && part < (k0 + r + kPartRows - 1) / kPartRows)
+                pmax = reinterpret_cast<const float *>(wsb + a.off_cnmax)[(g.run0 + r) * kMaxParts + part];
+        }
+        const uint4 *src = reinterpret_cast<const uint4 *>(wsb + a.off_opA + (int64_t)g.tile0 * tile_bytes_of(DP));
+        const float *csrc = Cb + (int64_t)grow0 * d;
+        const int n_op = g.n_tiles * (tile_bytes_of(DP) / 16), n_cs = real_rows * DP;
+        constexpr int UO = 6, UC = 12;
+        for (int i0 = 0; i0 * TH * UO < n_op || i0 * TH * UC < n_cs; ++i0) {
+            uint4 v[UO];
+#pragma unroll
+            for (int u = 0; u < UO; ++u) v[u] = src[min(tid + (i0 * UO + u) * TH, n_op - 1)];
+            float w[UC];
+#pragma unroll
+            for (int u = 0; u < UC; ++u) {
+                const int e = min(tid + (i0 * UC + u) * TH, n_cs - 1);
+                w[u] = csrc[(e / DP) * d + min(e % DP, d - 1)];
+            }
+            if (!FINAL && i0 == 0) {                     // (while the loads are on their way)
+                for (int e = tid; e < copies * real_rows * (DP + 1); e += TH) sums[e] = 0ull;
+                for (int e = tid; e < copies * real_rows; e += TH) cnts[e] = 0;
+            }
+#pragma unroll
+            for (int u = 0; u < UO; ++u) {
+                const int e = tid + (i0 * UO + u) * TH;
+                if (e < n_op) opA_s[e] = v[u];
+            }
+#pragma unroll
+            for (int u = 0; u < UC; ++u) {
+                const int e = tid + (i0 * UC + u) * TH;
+                if (e < n_cs) cs_lds[(e / DP) * (DP + 4) + e % DP] = e % DP < d ? w[u] : 0.0f;
             }
         }
+        if (tid < 32) {
+            mu_s[tid] = tid < DP ? mean_v : 0.0f;                          // colmean: already negated and scaled
+            shift_s[tid] = shift_v;
+            pow2hi_s[tid] = (1023 + shift_v) << 20;                        // 2^shift as a double: the high word
+        }
+        if (tid < 33) wide_s[tid] = wide_v;
         if (tid == 0) *next_slab = WV;
-        if (tid < 8) {
-            // the largest squared norm of the run's centroids: the centroid kernel leaves one maximum per part of the run
-            float m = 0.0f;
-            if (tid < g.n_runs) {
-                const float *parts = reinterpret_cast<const float *>(wsb + a.off_cnmax) + (g.run0 + tid) * kMaxParts;
-                const int n_parts = (plan.k_min + g.run0 + tid + kPartRows - 1) / kPartRows;
-                for (int p = 0; p < n_parts; ++p) m = fmaxf(m, parts[p]);
-            }
-            cnmax_s[tid] = m;
-        }
-        if (!FINAL) {
-            for (int e = tid; e < copies * real_rows * (DP + 1); e += TH) sums[e] = 0ull;
-            for (int e = tid; e < copies * real_rows; e += TH) cnts[e] = 0;
+        if (tid < 128) {
+#pragma unroll
+            for (int off = 8; off >= 1; off >>= 1) pmax = fmaxf(pmax, __shfl_xor(pmax, off, 64));
+            if ((tid & 15) == 0) cnmax_s[tid >> 4] = pmax;
         }
     }
     __syncthreads();
@@ -1354,13 +1390,13 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     c.sums = sums; c.cnts = cnts; c.copies = copies; c.real_rows = real_rows; c.mu_s = mu_s; c.shift_s = shift_s; c.pow2hi_s = pow2hi_s; c.wide_s = wide_s; c.cnmax_s = cnmax_s;
     c.scale = *reinterpret_cast<const float *>(wsb + a.off_colinfo + kColScaleOff);
     c.xp = reinterpret_cast<const uint4 *>(wsb + a.off_xp);
-    c.log = reinterpret_cast<unsigned long long *>(wsb + a.off_log) + ((int64_t)(gi * plan.n_chunks + chunk) * WV + (tid >> 6)) * kLogCap;
+    c.log = reinterpret_cast<unsigned long long *>(wsb + a.off_log) + ((int64_t)(g.wg0 + chunk) * WV + (tid >> 6)) * kLogCap;
     c.X = Xb; c.ldx = a.ldx; c.N = a.N; c.d = d; c.k0 = k0; c.n_runs = g.n_runs; c.n_tiles = g.n_tiles; c.grow0 = grow0;
     c.prev = reinterpret_cast<unsigned char *>(wsb + a.off_prev) + (int64_t)g.lab0 * ((a.N + 15) / 16 * 16);
     c.labels_out = (FINAL && a.labels) ? a.labels + (int64_t)b * a.lab_bs + (int64_t)g.run0 * a.N : nullptr;
     c.losum = reinterpret_cast<long long *>(wsb + a.off_losum);
-    c.chunk_begin = (int64_t)chunk * plan.chunk_len;
-    c.chunk_end = min(a.N, c.chunk_begin + plan.chunk_len);
+    c.chunk_begin = (int64_t)chunk * g.chunk_len;
+    c.chunk_end = min(a.N, c.chunk_begin + g.chunk_len);
     // 16-byte loads need whole quads of features and aligned rows
     c.first_round = a.first_round != 0;
     c.vec_x = (d % 4 == 0) && (a.ldx % 4 == 0) && ((reinterpret_cast<uintptr_t>(Xb) & 15) == 0);
@@ -1379,10 +1415,9 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
 #pragma unroll
     for (int i = 0; i < 8; ++i) jloc[i] = 0.0;
 
-    if (c.chunk_begin < c.chunk_end) {
-        if (c.vec_x) wave_loop_of<DP, FINAL, TRACE, true, PRE>(g.S, c, jloc);
-        else wave_loop_of<DP, FINAL, TRACE, false, PRE>(g.S, c, jloc);
-    }
+    // (a chunk is never empty)
+    if (c.vec_x) wave_loop_of<DP, FINAL, TRACE, true, PRE>(g.S, c, jloc);
+    else wave_loop_of<DP, FINAL, TRACE, false, PRE>(g.S, c, jloc);
 
     if (FINAL || TRACE) {
         const int lane = tid & 63, wave = tid >> 6;
@@ -1398,7 +1433,7 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
 
     if (!FINAL) {
         unsigned long long *psum = reinterpret_cast<unsigned long long *>(wsb + a.off_psum) +
-                                   ((int64_t)chunk * plan.total_rows + grow0) * d;
+                                   ((int64_t)g.part0 + (int64_t)chunk * real_rows) * d;
         for (int e = tid; e < real_rows * d; e += TH) {
             unsigned long long v = 0ull;
             long long rows_in = 0;     // rows that entered minus rows that left: each carried the bias once
@@ -1408,7 +1443,7 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
             }
             psum[e] = v - kFixBias * (unsigned long long)rows_in;
         }
-        int *pcnt = reinterpret_cast<int *>(wsb + a.off_pcnt) + (int64_t)chunk * plan.total_rows + grow0;
+        int *pcnt = reinterpret_cast<int *>(wsb + a.off_pcnt) + (int64_t)g.part0 + (int64_t)chunk * real_rows;
         for (int e = tid; e < real_rows; e += TH) {
             int v = 0;
             for (int cp = 0; cp < copies; ++cp) v += cnts[cp * real_rows + e];
@@ -1419,7 +1454,7 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
         if (tid < g.n_runs) {
             double v = 0.0;
             for (int w = 0; w < WV; ++w) v = __dadd_rn(v, jpart[tid * WV + w]);
-            reinterpret_cast<double *>(wsb + a.off_pj)[(int64_t)chunk * plan.n_runs + g.run0 + tid] = v;
+            reinterpret_cast<double *>(wsb + a.off_pj)[(int64_t)(g.wg0 + chunk) * 8 + tid] = v;
         }
     }
 }
@@ -1673,26 +1708,23 @@ __device__ inline void sum_chunks(const long long *pe, const int *pc, int64_t es
                                   long long &hi, unsigned long long &lo, long long &cnt)
 {
     constexpr int U = 8;
-    int c0 = c_begin;
-    for (; c0 + U <= c_end; c0 += U) {
+    for (int c0 = c_begin; c0 < c_end; c0 += U) {
         long long v[U];
         int m[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) { v[u] = pe[(c0 + u) * estride]; m[u] = pc[(c0 + u) * cstride]; }
+        for (int u = 0; u < U; ++u) {
+            const int c = min(c0 + u, c_end - 1);
+            v[u] = pe[c * estride];
+            m[u] = pc[c * cstride];
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            if (c0 + u >= c_end) { v[u] = 0; m[u] = 0; }
             const unsigned long long nlo = lo + (unsigned long long)v[u];
             hi += (v[u] >> 63) + (nlo < lo ? 1 : 0);
             lo = nlo;
             cnt += m[u];
         }
-    }
-    for (; c0 < c_end; ++c0) {
-        const long long v = pe[c0 * estride];
-        const unsigned long long nlo = lo + (unsigned long long)v;
-        hi += (v >> 63) + (nlo < lo ? 1 : 0);
-        lo = nlo;
-        cnt += pc[c0 * cstride];
     }
 }
 
@@ -1795,16 +1827,37 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
     // not read one after the other by a handful of threads; integer sums, any order.
     const int E = rows * DP;
     const int nsl = INIT ? 1 : kThreads / E;
+    // what the element's owner needs beside the deltas is requested first
+    long long tot_hi = 0, tot_lo = 0, tot_cnt = 0;
+    int col_shift = 0, col_wide = 0;
+    float col_mean = 0.0f, c_old = 0.0f;
+    if (tid < E && tid % DP < d) {
+        const int l = tid % DP;
+        const int64_t at = (int64_t)(row0 + j0 + tid / DP) * d + l;
+        col_mean = colmean[l];
+        if (!INIT) {
+            const long long *tot = reinterpret_cast<const long long *>(wsb + a.off_tot) + at * 2;
+            tot_hi = tot[0];
+            tot_lo = tot[1];
+            tot_cnt = reinterpret_cast<const long long *>(wsb + a.off_totcnt)[at];
+            col_shift = colshift[l];
+            col_wide = colwide[l];
+            c_old = Cb[at];
+        }
+    }
     if (!INIT) {
         const int e = tid % E, sl = tid / E;
         const int j = j0 + e / DP, l = e % DP;
         long long hi = 0, cnt = 0;
         unsigned long long lo = 0;
         if (sl < nsl && l < d) {
-            const long long *psum = reinterpret_cast<const long long *>(wsb + a.off_psum) + (int64_t)(row0 + j) * d + l;
-            const int *pcnt = reinterpret_cast<const int *>(wsb + a.off_pcnt) + row0 + j;
-            const int c_begin = (int)((int64_t)plan.n_chunks * sl / nsl), c_end = (int)((int64_t)plan.n_chunks * (sl + 1) / nsl);
-            sum_chunks(psum, pcnt, (int64_t)plan.total_rows * d, plan.total_rows, c_begin, c_end, hi, lo, cnt);
+            const int grow0 = rows_before(plan.k_min, g.run0);
+            const int grows = rows_before(plan.k_min, g.run0 + g.n_runs) - grow0;      // rows of the group
+            const int64_t at = (int64_t)g.part0 + row0 - grow0 + j;
+            const long long *psum = reinterpret_cast<const long long *>(wsb + a.off_psum) + at * d + l;
+            const int *pcnt = reinterpret_cast<const int *>(wsb + a.off_pcnt) + at;
+            const int c_begin = (int)((int64_t)g.n_chunks * sl / nsl), c_end = (int)((int64_t)g.n_chunks * (sl + 1) / nsl);
+            sum_chunks(psum, pcnt, (int64_t)grows * d, grows, c_begin, c_end, hi, lo, cnt);
         }
         part_hi[tid] = hi; part_lo[tid] = lo; part_cnt[tid] = cnt;
         __syncthreads();
@@ -1823,9 +1876,9 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
             } else {
                 long long *tot = reinterpret_cast<long long *>(wsb + a.off_tot) + ((int64_t)(row0 + j) * d + l) * 2;
                 long long *totcnt = reinterpret_cast<long long *>(wsb + a.off_totcnt) + (int64_t)(row0 + j) * d + l;
-                long long hi = tot[0];
-                unsigned long long lo = (unsigned long long)tot[1];
-                long long cnt = *totcnt;
+                long long hi = tot_hi;
+                unsigned long long lo = (unsigned long long)tot_lo;
+                long long cnt = tot_cnt;
                 for (int sl = 0; sl < nsl; ++sl) {
                     const unsigned long long nlo = lo + part_lo[sl * E + e];
                     hi += part_hi[sl * E + e] + (nlo < lo ? 1 : 0);
@@ -1835,8 +1888,8 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
                 tot[0] = hi;
                 tot[1] = (long long)lo;
                 *totcnt = cnt;
-                int shift = colshift[l];
-                if (colwide[l]) {
+                int shift = col_shift;
+                if (col_wide) {
                     // total = main * 2^kLowBits + low, on the scale 2^-(shift + kLowBits)
                     const long long low = reinterpret_cast<const long long *>(wsb + a.off_losum)[(int64_t)(row0 + j) * d + l];
                     hi = (long long)(((unsigned long long)hi << kLowBits) | (lo >> (64 - kLowBits)));
@@ -1850,10 +1903,10 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
                     c = (float)(fixed128_to_double(hi, lo, shift) / (double)cnt);
                     Cb[(int64_t)(row0 + j) * d + l] = c;
                 } else {
-                    c = Cb[(int64_t)(row0 + j) * d + l];     // a cluster without members keeps its centroid
+                    c = c_old;                               // a cluster without members keeps its centroid
                 }
             }
-            cp = fmaf(c, scale, colmean[l]);     // (c - mean) * scale, one rounding, as for the points
+            cp = fmaf(c, scale, col_mean);       // (c - mean) * scale, one rounding, as for the points
         }
         cs[jj * DP + l] = cp;
         // operand position of (centroid j, feature l)
@@ -1891,19 +1944,22 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
 }
 
 // sum of the per-chunk partial losses of every run, in chunk order
-__global__ void lloyd_loss_kernel(int n_runs, int n_chunks, const int32_t *status, const char *ws, int64_t ws_bs,
+__global__ void lloyd_loss_kernel(SweepPlan plan, const int32_t *status, const char *ws, int64_t ws_bs,
                                   int64_t off_pj, double *out, int64_t out_bs, int64_t out_stride, int64_t out_off)
 {
     const int b = blockIdx.x, r = threadIdx.x;
-    if (r >= n_runs || status[b] != 0) return;
-    const double *pj = reinterpret_cast<const double *>(ws + (int64_t)b * ws_bs + off_pj);
+    if (r >= plan.n_runs || status[b] != 0) return;
+    int gi = 0;
+    while (gi + 1 < plan.n_groups && plan.g[gi + 1].run0 <= r) ++gi;
+    const int n_chunks = plan.g[gi].n_chunks;
+    const double *pj = reinterpret_cast<const double *>(ws + (int64_t)b * ws_bs + off_pj) + (int64_t)plan.g[gi].wg0 * 8 + (r - plan.g[gi].run0);
     double v = 0.0;
     // eight loads in flight at a time (the walk is bound by their latency); the additions keep the chunk order
     constexpr int U = 8;
     for (int c0 = 0; c0 < n_chunks; c0 += U) {
         double t[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) t[u] = pj[(int64_t)min(c0 + u, n_chunks - 1) * n_runs + r];
+        for (int u = 0; u < U; ++u) t[u] = pj[(int64_t)min(c0 + u, n_chunks - 1) * 8];
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (c0 + u < n_chunks) v = __dadd_rn(v, t[u]);
@@ -1986,7 +2042,7 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
         const size_t need = (size_t)carve_lds(DP, a.d, g.n_tiles, rr, g.copies).total;
         if (need > lds) lds = need;
     }
-    const dim3 grid((unsigned)((int64_t)plan.n_groups * plan.n_chunks * batch), 1);
+    const dim3 grid((unsigned)((int64_t)plan.n_wgs * batch), 1);
     sa.batch = batch;
     const bool prof = profile_enabled();
     for (int t = 0; t < a.iters; ++t) {
@@ -1995,7 +2051,7 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
         if (trace) {
             hipLaunchKernelGGL((lloyd_step_kernel<DP, false, true, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
             if (prof) { hipError_t e = profile_mark(s, false); if (e != hipSuccess) return e; }
-            hipLaunchKernelGGL(lloyd_loss_kernel, dim3(batch), dim3(128), 0, s, plan.n_runs, plan.n_chunks, a.status, a.ws,
+            hipLaunchKernelGGL(lloyd_loss_kernel, dim3(batch), dim3(128), 0, s, plan, a.status, a.ws,
                                L.per_batch, L.pj, a.trace, (int64_t)plan.n_runs * (a.iters + 1), (int64_t)(a.iters + 1), (int64_t)t);
         } else {
             // the first round brings every row into a cluster and reads the rows themselves; later rounds take the
@@ -2007,10 +2063,10 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
         hipLaunchKernelGGL((lloyd_centroids_kernel<DP, false>), centroid_grid, dim3(kThreads), 0, s, plan, ca);
     }
     hipLaunchKernelGGL((lloyd_step_kernel<DP, true, false, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
-    hipLaunchKernelGGL(lloyd_loss_kernel, dim3(batch), dim3(128), 0, s, plan.n_runs, plan.n_chunks, a.status, a.ws, L.per_batch,
+    hipLaunchKernelGGL(lloyd_loss_kernel, dim3(batch), dim3(128), 0, s, plan, a.status, a.ws, L.per_batch,
                        L.pj, a.inertia, (int64_t)plan.n_runs, (int64_t)1, (int64_t)0);
     if (trace)
-        hipLaunchKernelGGL(lloyd_loss_kernel, dim3(batch), dim3(128), 0, s, plan.n_runs, plan.n_chunks, a.status, a.ws,
+        hipLaunchKernelGGL(lloyd_loss_kernel, dim3(batch), dim3(128), 0, s, plan, a.status, a.ws,
                            L.per_batch, L.pj, a.trace, (int64_t)plan.n_runs * (a.iters + 1), (int64_t)(a.iters + 1),
                            (int64_t)a.iters);
     return hipGetLastError();
@@ -2040,6 +2096,11 @@ int64_t lloyd_group_lds_bytes(int dp, int d, int n_tiles, int real_rows, int cop
 }
 
 constexpr int kFillWorkgroups = 256;   // one per compute unit
+constexpr int kSlabCost = 6;           // what a slab costs beside its tiles (operand loads, close calls, labels, log), in tiles
+// Longest launch, in the same unit (0.3 us), that is given one workgroup of equal cost per compute unit.  65,536 x 16, k 1..64
+// (80): 49 -> 42 us a launch; 1M x 16, k 8..23 (180): 81 -> 68 us; 1M x 16, k 1..64 (1100) is 3% better off with two
+// workgroups per compute unit that share their chunks' reads.
+constexpr int64_t kBalancedTime = 800;
 
 int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch, SweepPlan *plan)
 {
@@ -2101,34 +2162,76 @@ int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int3
         plan->sched[j] = v;
     }
     plan->total_rows = rows_before(k_min, plan->n_runs);
-    // chunks: enough workgroups over the whole batch to fill the chip twice over (a workgroup stages its
-    // group's rows once, so more and shorter chunks only add set-up); a chunk never exceeds 2^16 points (the accumulators
-    // would allow 2^17; with the groups of a chunk running side by side the shorter chunk measured 2% shorter launches at 8M x 32)
-    const int tp = geo.tile_points;
-    const int64_t tiles_total = (N + tp - 1) / tp;
-    const int64_t units = (int64_t)plan->n_groups * (batch > 0 ? batch : 1);
-    int64_t want = (512 + units - 1) / units;       // two workgroups per compute unit (1024 measured 4% longer launches at 1M x 16, 256 22% longer)
-    // a workgroup should have several slabs per wave to spread its set-up over: at least 4096 points per chunk
-    // but never fewer workgroups than fill the chip
-    int64_t most = (N + 4095) / 4096;
-    const int64_t fill = (kFillWorkgroups + units - 1) / units;
-    if (most < fill) most = fill;
-    if (want > most) want = most;
-    if (want > tiles_total) want = tiles_total;
-    if (want < 1) want = 1;
-    int64_t chunk_len = ((tiles_total + want - 1) / want) * tp;
-    const int64_t cap = (int64_t)1 << 16;
-    if (chunk_len > cap) chunk_len = cap / tp * tp;
-    plan->chunk_len = (int32_t)chunk_len;
-    plan->n_chunks = (int32_t)((N + chunk_len - 1) / chunk_len);
-    // chunks per block of the launch order: about one workgroup per compute unit in a block, a multiple of eight chunks
-    // (workgroups go to the eight XCDs in turn, so the groups of one chunk meet on one XCD)
-    int32_t cb = (kFillWorkgroups + plan->n_groups - 1) / plan->n_groups;
-    cb = (cb + 7) / 8 * 8;
-    const int64_t n_all = (int64_t)plan->n_chunks * (batch > 0 ? batch : 1);     // chunks of all spaces of the batch
-    if (cb > n_all) cb = (int32_t)n_all;
-    plan->chunk_block = cb;
-    if ((int64_t)plan->n_groups * n_all > 0x7fffffffLL) return RLS_ERR_INVALID_ARG;
+    if (batch < 1) batch = 1;
+    const int64_t units = (int64_t)plan->n_groups * batch;
+    const int64_t cap = (int64_t)1 << 16;      // points per chunk (the accumulators would allow 2^17)
+    plan->chunk_block = -1;
+    if (units <= kFillWorkgroups) {
+        // Small inputs: one workgroup per compute unit, so the heaviest one is what a launch takes, and every group gets
+        // chunks of its own length.  With r rounds of slabs for its waves, a workgroup of group g is busy for about
+        // r (tiles + kSlabCost): the shortest time is looked for with which the workgroups of all groups fit the compute
+        // units when every group takes as many whole rounds as that time allows.
+        const int64_t per_round = (int64_t)slab_blocks_of(dp, 1) * 32 * (step_threads_of(dp) / 64);
+        auto chunks_of = [&](const GroupDesc &g, int64_t time) {
+            const int64_t rounds = std::max<int64_t>(time / (g.n_tiles + kSlabCost), 1);
+            const int64_t len = std::min(rounds * per_round, cap);
+            return (N + len - 1) / len;
+        };
+        auto fits = [&](int64_t time) {
+            int64_t n = 0;
+            for (int gi = 0; gi < plan->n_groups; ++gi) n += chunks_of(plan->g[gi], time);
+            return n * batch <= kFillWorkgroups;
+        };
+        if (fits(kBalancedTime)) {
+            int64_t lo = 0, hi = kBalancedTime;
+            while (lo + 1 < hi) {
+                const int64_t mid = (lo + hi) / 2;
+                if (fits(mid)) hi = mid; else lo = mid;
+            }
+            for (int gi = 0; gi < plan->n_groups; ++gi) {
+                GroupDesc &g = plan->g[gi];
+                const int64_t nc = chunks_of(g, hi);
+                g.chunk_len = (int32_t)std::min<int64_t>(((N + nc - 1) / nc + 63) / 64 * 64, cap);     // spread evenly
+                g.n_chunks = (int32_t)((N + g.chunk_len - 1) / g.chunk_len);
+            }
+            plan->chunk_block = 0;
+        }
+    }
+    if (plan->chunk_block < 0) {
+        // Large inputs: the same chunks for every group, two workgroups per compute unit over the whole batch (a workgroup
+        // stages its group's rows once, so more and shorter chunks only add set-up: 1024 workgroups measured 4% longer
+        // launches at 1M x 16, 256 22% longer); a chunk never exceeds 2^16 points (with the groups of a chunk running side
+        // by side shorter chunks measured 2% shorter launches at 8M x 32)
+        const int tp = geo.tile_points;
+        const int64_t tiles_total = (N + tp - 1) / tp;
+        int64_t want = std::max<int64_t>(2 * kFillWorkgroups / units, 1);
+        if (want > tiles_total) want = tiles_total;
+        int64_t chunk_len = ((tiles_total + want - 1) / want) * tp;
+        if (chunk_len > cap) chunk_len = cap / tp * tp;
+        const int64_t n_chunks = (N + chunk_len - 1) / chunk_len;
+        for (int gi = 0; gi < plan->n_groups; ++gi) {
+            plan->g[gi].chunk_len = (int32_t)chunk_len;
+            plan->g[gi].n_chunks = (int32_t)n_chunks;
+        }
+        // chunks per block of the launch order: about one workgroup per compute unit in a block, a multiple of eight chunks
+        // (workgroups go to the eight XCDs in turn, so the groups of one chunk meet on one XCD)
+        int32_t cb = (kFillWorkgroups + plan->n_groups - 1) / plan->n_groups;
+        cb = (cb + 7) / 8 * 8;
+        const int64_t n_all = n_chunks * batch;                                  // chunks of all spaces of the batch
+        if (cb > n_all) cb = (int32_t)n_all;
+        plan->chunk_block = cb;
+    }
+    int64_t wgs = 0, parts = 0;
+    for (int gi = 0; gi < plan->n_groups; ++gi) {
+        GroupDesc &g = plan->g[gi];
+        g.wg0 = (int32_t)wgs;
+        g.part0 = (int32_t)parts;
+        wgs += g.n_chunks;
+        parts += (int64_t)g.n_chunks * (rows_before(k_min, g.run0 + g.n_runs) - rows_before(k_min, g.run0));
+    }
+    if (wgs * batch > 0x7fffffffLL || parts > 0x7fffffffLL) return RLS_ERR_INVALID_ARG;
+    plan->n_wgs = (int32_t)wgs;
+    plan->n_parts = (int32_t)parts;
     return RLS_OK;
 }
 
@@ -2150,14 +2253,14 @@ void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, in
     L->xp = take((N + 31) / 32 * prep_block_u4_of(plan.dp) * 16);     // (with the blocks above: the same place whatever the range of k)
     L->opA = take((int64_t)plan.total_tiles * tile_bytes_of(plan.dp));
     L->cnmax = take((int64_t)plan.n_runs * kMaxParts * 4);
-    L->psum = take((int64_t)plan.n_chunks * plan.total_rows * d * 8);
-    L->pcnt = take((int64_t)plan.n_chunks * plan.total_rows * 4);
-    L->pj = take((int64_t)plan.n_chunks * plan.n_runs * 8);
+    L->psum = take((int64_t)plan.n_parts * d * 8);
+    L->pcnt = take((int64_t)plan.n_parts * 4);
+    L->pj = take((int64_t)plan.n_wgs * 8 * 8);
     L->losum = take((int64_t)plan.total_rows * d * 8);
     L->tot = take((int64_t)plan.total_rows * d * 16);
     L->totcnt = take((int64_t)plan.total_rows * d * 8);
     L->prev = take((int64_t)plan.lab_slots * align_up(N, 16));
-    L->log = take((int64_t)plan.n_groups * plan.n_chunks * (step_threads_of(plan.dp) / 64) * kLogCap * 8);
+    L->log = take((int64_t)plan.n_wgs * (step_threads_of(plan.dp) / 64) * kLogCap * 8);
     L->per_batch = off;
     L->total = off * batch;
 }

@@ -38,9 +38,13 @@ struct GroupDesc {
     int16_t copies;    // copies of the LDS accumulators (a power of two up to 16)
     int16_t lab0;      // run slots (8 / S each) of all earlier groups: where this group's label bytes begin, in units of N rounded up to 16
     int32_t tile0;     // tiles of all earlier groups (offset of this group's operand block)
+    int32_t n_chunks;  // chunks the points are cut into for this group
+    int32_t chunk_len; // points per chunk (a multiple of 64)
+    int32_t wg0;       // chunks of all earlier groups
+    int32_t part0;     // per-chunk centroid rows of all earlier groups (n_chunks times rows each): where this group's deltas begin
 };
 
-constexpr int kMaxGroups = 128;
+constexpr int kMaxGroups = 64;       // (44 is the most any range of k and number of features needs)
 
 struct SweepPlan {
     int32_t n_groups;
@@ -49,9 +53,10 @@ struct SweepPlan {
     int32_t total_tiles;
     int32_t lab_slots;   // sum over the groups of their 8 / S run slots
     int32_t total_rows;  // sum of k over the runs
-    int32_t n_chunks;    // point chunks per group
-    int32_t chunk_len;   // points per chunk (multiple of the tile size)
-    int32_t chunk_block; // chunks per block of the step kernel's workgroup order (all groups of a block of chunks, then the next block)
+    int32_t n_wgs;       // chunks of all groups: workgroups of a step launch per space
+    int32_t n_parts;     // per-chunk centroid rows of all groups
+    int32_t chunk_block; // > 0: every group has the same chunks, and the step kernel's workgroup order takes this many at a time (all
+                         // groups of a block of chunks, then the next block); 0: the groups have chunks of their own, of equal cost
     int32_t dp;          // padded feature count: 8, 16 or 32
     GroupDesc g[kMaxGroups];
     uint8_t sched[kMaxGroups];   // launch order: group indices by falling cost
@@ -86,14 +91,14 @@ struct SweepLayout {
     int64_t seedthr;        // fp64 [k_max] per chosen centre: the bound below which a point's distance cannot improve
     int64_t opA;            // per 32-row tile: fp16 pieces of the centred, -2-scaled centroids and the bf16 bias slot, in MFMA operand order
     int64_t cnmax;          // fp32 [n_runs][parts of a run] maximum of cn over the centroids of a part
-    int64_t psum;           // int64 [n_chunks][total_rows][d] per-chunk changes of the fixed-point sums
-    int64_t pcnt;           // int32 [n_chunks][total_rows] per-chunk changes of the member counts
-    int64_t pj;             // fp64 [n_chunks][n_runs] partial losses
+    int64_t psum;           // int64 per group [n_chunks][rows of the group][d]: per-chunk changes of the fixed-point sums
+    int64_t pcnt;           // int32 per group [n_chunks][rows of the group]: per-chunk changes of the member counts
+    int64_t pj;             // fp64 [chunks of all groups][8] partial losses
     int64_t losum;          // int64 [total_rows][d] low-order fixed-point sums of wide columns (running)
     int64_t tot;            // int64 [total_rows][d][2] running 128-bit fixed-point sums (hi, lo)
     int64_t totcnt;         // int64 [total_rows][d] running member counts (one copy per feature)
     int64_t prev;           // uint8 per group [N rounded up to 16][8 / S]: label of every point in the last round (0xff: none yet)
-    int64_t log;            // uint64 [groups * chunks][waves][512] rings of moved-pair records, one per wave of the step kernel
+    int64_t log;            // uint64 [chunks of all groups][waves][512] rings of moved-pair records, one per wave of the step kernel
     int64_t xp;             // prepared copy of the points: per block of 32, the matrix operands and squared norms (kmeans_lloyd.hip)
     int64_t per_batch;      // bytes per batch element (multiple of 256)
     int64_t total;          // per_batch * batch
