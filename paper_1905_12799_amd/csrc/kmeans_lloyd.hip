@@ -2096,11 +2096,20 @@ int64_t lloyd_group_lds_bytes(int dp, int d, int n_tiles, int real_rows, int cop
 }
 
 constexpr int kFillWorkgroups = 256;   // one per compute unit
-constexpr int kSlabCost = 6;           // what a slab costs beside its tiles (operand loads, close calls, labels, log), in tiles
-// Longest launch, in the same unit (0.3 us), that is given one workgroup of equal cost per compute unit.  65,536 x 16, k 1..64
-// (80): 49 -> 42 us a launch; 1M x 16, k 8..23 (180): 81 -> 68 us; 1M x 16, k 1..64 (1100) is 3% better off with two
-// workgroups per compute unit that share their chunks' reads.
-constexpr int64_t kBalancedTime = 800;
+constexpr int kSlabCost = 6;
+// Workgroups per compute unit when the groups' chunks are cut to equal cost, by the work a compute unit has (0: the same
+// chunks for every group).  A workgroup pays some 9 us for its set-up and its last slabs, so a short launch gets one; a
+// long one gets several, so that the ends of its workgroups even out.  Measured, per sweep, against two workgroups per compute
+// unit with the same chunks for every group: 65,536 x 16, k 1..64 (per_cu 80): 2.19 -> 1.96 ms with one; 1M x 16, k 8..23 (200):
+// 3.1 -> 2.7 with one; 1M x 16, k 1..64 (1280): 12.6 -> 12.9 with two, the groups of a chunk no longer share its reads;
+// 1M x 32, k 1..100 (5300): 24.0 -> 19.8 with three; 2M x 16, k 1..128 (6500): 37.8 -> 34.6 with five.
+// (The spaces of a batch are many workgroups already: 0 is as good there or better from 700 on.)
+int workgroups_per_cu(int64_t per_cu, int batch)
+{
+    if (per_cu < (batch > 1 ? 700 : 800)) return 1;
+    if (batch > 1 || per_cu < 2000 || per_cu > 12000) return 0;
+    return (int)std::min<int64_t>((per_cu + 600) / 1200, 5);
+}
 
 int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch, SweepPlan *plan)
 {
@@ -2166,12 +2175,19 @@ int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int3
     const int64_t units = (int64_t)plan->n_groups * batch;
     const int64_t cap = (int64_t)1 << 16;      // points per chunk (the accumulators would allow 2^17)
     plan->chunk_block = -1;
-    if (units <= kFillWorkgroups) {
-        // Small inputs: one workgroup per compute unit, so the heaviest one is what a launch takes, and every group gets
-        // chunks of its own length.  With r rounds of slabs for its waves, a workgroup of group g is busy for about
-        // r (tiles + kSlabCost): the shortest time is looked for with which the workgroups of all groups fit the compute
-        // units when every group takes as many whole rounds as that time allows.
-        const int64_t per_round = (int64_t)slab_blocks_of(dp, 1) * 32 * (step_threads_of(dp) / 64);
+    // What a slab of 32 points costs: the tiles of its group, and about kSlabCost more for everything else (operand loads,
+    // close calls, labels, log).  `per_cu`: what one wave of a compute unit has to do when the work is spread evenly over the
+    // chip (in this unit, about 0.3 us).
+    const int waves = step_threads_of(dp) / 64;
+    const int64_t per_round = (int64_t)slab_blocks_of(dp, 1) * 32 * waves;
+    int64_t cost = 0;
+    for (int gi = 0; gi < plan->n_groups; ++gi) cost += plan->g[gi].n_tiles + kSlabCost;
+    const int64_t per_cu = (N + 31) / 32 * cost * batch / (kFillWorkgroups * waves);
+    const int per_cu_wgs = workgroups_per_cu(per_cu, batch);
+    if (per_cu_wgs > 0) {
+        // Every group gets chunks of its own length, so that all workgroups take about the same time.  With r rounds of slabs
+        // for its waves, a workgroup of group g is busy for r (tiles + kSlabCost): the shortest time is looked for with which
+        // the workgroups of all groups fit when every group takes as many whole rounds as that time allows.
         auto chunks_of = [&](const GroupDesc &g, int64_t time) {
             const int64_t rounds = std::max<int64_t>(time / (g.n_tiles + kSlabCost), 1);
             const int64_t len = std::min(rounds * per_round, cap);
@@ -2180,10 +2196,10 @@ int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int3
         auto fits = [&](int64_t time) {
             int64_t n = 0;
             for (int gi = 0; gi < plan->n_groups; ++gi) n += chunks_of(plan->g[gi], time);
-            return n * batch <= kFillWorkgroups;
+            return n * batch <= (int64_t)per_cu_wgs * kFillWorkgroups;
         };
-        if (fits(kBalancedTime)) {
-            int64_t lo = 0, hi = kBalancedTime;
+        int64_t lo = 0, hi = 2 * per_cu + 1000;
+        if (fits(hi)) {
             while (lo + 1 < hi) {
                 const int64_t mid = (lo + hi) / 2;
                 if (fits(mid)) hi = mid; else lo = mid;
