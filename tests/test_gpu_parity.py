@@ -542,6 +542,24 @@ def test_sweep_batched_block_order(rls, orc, batch, N, d, k_min, k_max, iters):
         compare_sweep(orc, X[b], one, ref, k_min, k_max)
 
 
+@pytest.mark.parametrize("N,d", [(769, 5), (24577, 16), (150001, 5), (300007, 13), (600011, 5), (600011, 32), (3200003, 5)])
+def test_sweep_chunks_per_group(rls, orc, N, d):
+    """k 1..128 over the sizes at which the step changes how it cuts the points: chunks of equal cost per group, one
+    workgroup per compute unit; the same chunks for every group; chunks per group, several per compute unit; and the same
+    chunks again.  A run does not depend on the others of its sweep: some k against the oracle."""
+    rng = np.random.default_rng(N + d)
+    centres = rng.uniform(-20, 20, size=(40, d)).astype(np.float32)
+    X = centres[rng.integers(0, 40, size=N)] + rng.standard_normal((N, d), dtype=np.float32)
+    Xd = dev(X)
+    init = rls.kmeanspp_chain(Xd, 128, 9)
+    res = rls.kmeans_sweep(Xd, 1, 128, 2, init_idx=init)
+    lab, J, st = res.labels.cpu(), res.inertia.cpu(), res.status.cpu()
+    for k in (1, 8, 63, 97, 128):
+        ref = orc.kmeans_sweep(X, k, k, 2, init_idx=init.cpu().numpy()[:k])
+        one = rls.SweepResult(k, k, d, lab[k - 1:k], res.centroids_of(k).cpu().reshape(-1), J[k - 1:k], None, st)
+        compare_sweep(orc, X, one, ref, k, k)
+
+
 def test_sweep_strided_unaligned_rows_and_small_d(rls, orc):
     # rows 11 floats apart and starting 4 bytes off a 16-byte boundary: the scalar load paths
     rng = np.random.default_rng(21)
