@@ -1,9 +1,9 @@
 /*
- * rls - timing aid for benchmarks.  NOT part of the library's interface proper (rls.h) and not part of the
- * paper's method: a benchmark program uses it to time the fused assign + update pass that dominates the
+ * rls - aids for benchmarks and tests.  NOT part of the library's interface proper (rls.h) and not part of the
+ * paper's method: a benchmark program uses rls_profile_* to time the fused assign + update pass that dominates the
  * k-means calls of Algorithm 1 (Sec. 4.2) on the stream the library launches it on.
  *
- * Unlike everything in rls.h these calls keep process-wide state (a flag and a pool of HIP events the
+ * Unlike everything in rls.h rls_profile_* keep process-wide state (a flag and a pool of HIP events the
  * library creates on first use); a mutex guards that state.  While enabled, every sweep of every host thread
  * records into the one pool, so the figures only mean something when one thread is sweeping.  Leave it
  * disabled (the default) anywhere else: a sweep that is being recorded into a HIP graph must not record events.
@@ -24,8 +24,8 @@ int32_t rls_profile_enable(int32_t on);
 int32_t rls_profile_read(int32_t *n_launches, double *total_ms);
 /* The seeding chain of up to about a million points runs in one launch whose workgroups wait for each other; one that has
  * waited this many ticks of the 100 MHz clock (default 5,000,000: 50 ms) gives up, and a second kernel, which waits for
- * nothing, does the chain.  0 makes every launch with more than one workgroup take that second path, for tests; a negative
- * value restores the default. */
+ * nothing, does the chain.  The limit holds for the calls of the host thread that sets it.  0 makes every launch with more
+ * than one workgroup take that second path, for tests; a negative value restores the default. */
 int32_t rls_seed_wait_limit(int64_t ticks);
 
 #ifdef __cplusplus

@@ -36,8 +36,10 @@ __device__ inline double uniform01(uint64_t seed, uint64_t j)
     return (double)(splitmix64(seed, j) >> 11) * 0x1.0p-53;
 }
 
-// how long a workgroup of seed_chain_kernel waits for the others before it gives up (100 MHz clock: 50 ms)
-std::atomic<long long> g_wait_ticks{5000000};
+// how long a workgroup of seed_chain_kernel waits for the others before it gives up (100 MHz clock: 50 ms); a test may
+// change it for the launches of its own host thread
+constexpr long long kWaitTicks = 5000000;
+thread_local long long t_wait_ticks = kWaitTicks;
 
 struct SeedList {
     uint64_t seed[64];
@@ -745,7 +747,7 @@ __global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, C
 
 }  // namespace
 
-void set_seed_wait_ticks(long long ticks) { g_wait_ticks.store(ticks, std::memory_order_relaxed); }
+void set_seed_wait_ticks(long long ticks) { t_wait_ticks = ticks < 0 ? kWaitTicks : ticks; }
 
 // compute units of the current device, asked for once per device
 static int compute_units()
@@ -827,7 +829,7 @@ hipError_t launch_seed_chain(const float *X, int64_t N, int32_t d, int64_t ldx, 
             ca.mind = reinterpret_cast<double *>(wsb + L.mind); ca.mind_bs = L.per_batch / 8;
             ca.chain = chain + (int64_t)b0 * chain_batch_stride; ca.chain_bs = chain_batch_stride;
             ca.ex = reinterpret_cast<unsigned long long *>(wsb + L.colstat_part); ca.ex_bs = L.per_batch / 8;
-            ca.wait_ticks = g_wait_ticks.load(std::memory_order_relaxed);
+            ca.wait_ticks = t_wait_ticks;
             const hipError_t e = launch_chain_in_one(dp, p, nb, sl, ca, s);
             if (e != hipSuccess) return e;
             continue;

@@ -92,7 +92,7 @@ int32_t rls_profile_enable(int32_t on)
 
 int32_t rls_seed_wait_limit(int64_t ticks)
 {
-    set_seed_wait_ticks(ticks < 0 ? 5000000 : ticks);
+    set_seed_wait_ticks(ticks);
     return RLS_OK;
 }
 

@@ -6,6 +6,7 @@ for centroids (per column scale), inertia and tree scores (scores are also compa
 oracle's fp32 tree-order sum).
 """
 import ctypes
+import threading
 
 import numpy as np
 import pytest
@@ -327,6 +328,41 @@ def test_seeding_chain_one_launch(rls, orc, N, d, k_max):
         np.testing.assert_array_equal(rls.kmeanspp_chain(Xd, k_max, 21).cpu().numpy(), ref)
     finally:
         rls.lib().rls_seed_wait_limit(ctypes.c_int64(-1))
+
+
+def exchange_words(ws, k_max):
+    """The words that the workgroups of a chain exchange, at the head of the workspace: the sums of step j are words
+    256 j + workgroup, and a word nobody has written is -1."""
+    base = (-ws.data_ptr()) % 256
+    return ws[base:base + 256 * k_max * 8].view(torch.int64).view(k_max, 256).cpu().numpy()
+
+
+def test_seeding_wait_limit_holds_for_one_host_thread(rls, orc):
+    """A limit set by one thread leaves the chains of another alone: that one's workgroups wait for each other to the end."""
+    rng = np.random.default_rng(31)
+    X = rng.standard_normal((20000, 8)).astype(np.float32)
+    Xd, k_max, groups = dev(X), 8, 20                       # 20 workgroups of 1024 points
+    ref = orc.kmeanspp_chain(X, k_max, 5)
+    seen = {}
+
+    def chain(name):
+        ws = torch.zeros(rls.kmeans_sweep_workspace_bytes(20000, 8, k_max, k_max) + 256, dtype=torch.uint8, device="cuda")
+        got = rls.kmeanspp_chain(Xd, k_max, 5, workspace=ws)
+        torch.cuda.synchronize()
+        seen[name] = (got.cpu().numpy(), exchange_words(ws, k_max)[k_max - 1, :groups])
+
+    try:
+        rls.lib().rls_seed_wait_limit(ctypes.c_int64(0))
+        chain("own")
+        other = threading.Thread(target=chain, args=("other",))
+        other.start()
+        other.join()
+    finally:
+        rls.lib().rls_seed_wait_limit(ctypes.c_int64(-1))
+    for name in ("own", "other"):
+        np.testing.assert_array_equal(seen[name][0], ref)
+    assert (seen["own"][1] == -1).any()                     # gave up before the last step
+    assert (seen["other"][1] != -1).all()
 
 
 def test_seeding_all_points_equal(rls, orc):
