@@ -27,6 +27,8 @@ int32_t rls_profile_read(int32_t *n_launches, double *total_ms);
  * nothing, does the chain.  The limit holds for the calls of the host thread that sets it.  0 makes every launch with more
  * than one workgroup take that second path, for tests; a negative value restores the default. */
 int32_t rls_seed_wait_limit(int64_t ticks);
+/* The same for the workgroups of a space from `first_workgroup` on; the ones before it wait the default time. */
+int32_t rls_seed_wait_limit_from(int32_t first_workgroup, int64_t ticks);
 
 #ifdef __cplusplus
 }

@@ -40,6 +40,7 @@ __device__ inline double uniform01(uint64_t seed, uint64_t j)
 // change it for the launches of its own host thread
 constexpr long long kWaitTicks = 5000000;
 thread_local long long t_wait_ticks = kWaitTicks;
+thread_local int t_wait_from = 0;                  // first workgroup of a space that the thread's limit holds for
 
 struct SeedList {
     uint64_t seed[64];
@@ -381,14 +382,16 @@ __global__ void __launch_bounds__(1024) seed_pick_kernel(SeedList seeds, int b0,
 // words are stored and polled with agent-scope atomics, which reach past the L2 of an XCD.
 //
 // No wait is unbounded: the workgroups need not be resident together (nothing guarantees that while other streams hold
-// compute units), so a workgroup that has waited `wait_ticks` gives up, the chain stays unfinished, and
-// seed_chain_rest_kernel, always launched behind, does it in one workgroup without any exchange.
+// compute units), so a workgroup that has waited `wait_ticks` gives up and leaves its finished word unset.  Any of them may
+// do so in the last step, when the others already have all they need from it, and its distances are then missing: so
+// seed_chain_rest_kernel, always launched behind, does the chain again, in one workgroup without any exchange, unless every
+// workgroup has finished.
 constexpr unsigned long long kSlotEmpty = ~0ull;
 constexpr int kChainWgs = 256;                                 // workgroups per space at most
 constexpr int kRowWords = RLS_MAX_D + 1;                       // row, then the index
 constexpr int kExRows = RLS_MAX_K * kChainWgs;                 // word offsets within the exchange area of a space
-constexpr int kExDone = kExRows + RLS_MAX_K * kRowWords;
-constexpr int kExWords = kExDone + 1;
+constexpr int kExDone = kExRows + RLS_MAX_K * kRowWords;        // one per workgroup: 1 when it has finished
+constexpr int kExWords = kExDone + kChainWgs;
 static_assert(kExWords * 8 <= kSeedExchangeBytes, "the exchange area must fit its place in the workspace");
 
 struct ChainArgs {
@@ -403,7 +406,8 @@ struct ChainArgs {
     int64_t chain_bs;
     unsigned long long *ex;               // exchange area
     int64_t ex_bs;
-    long long wait_ticks;                 // of the 100 MHz clock
+    long long wait_ticks;                 // of the 100 MHz clock; workgroups below wait_from wait kWaitTicks
+    int32_t wait_from;
 };
 
 __global__ void __launch_bounds__(256) seed_begin_kernel(SeedList seeds, ChainArgs a)
@@ -414,8 +418,8 @@ __global__ void __launch_bounds__(256) seed_begin_kernel(SeedList seeds, ChainAr
     for (int e = t0; e < a.k_max * kChainWgs; e += step)
         if (e % kChainWgs < a.groups) ex[e] = kSlotEmpty;
     for (int e = t0; e < a.k_max * kRowWords; e += step) ex[kExRows + e] = kSlotEmpty;
+    if (t0 < a.groups) ex[kExDone + t0] = 0ull;
     if (t0 == 0) {
-        ex[kExDone] = 0ull;
         if (a.j_begin == 0) {
             int64_t first = (int64_t)(uniform01(seeds.seed[b], 0) * (double)a.N);
             if (first >= a.N) first = a.N - 1;
@@ -522,6 +526,7 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
     unsigned long long *ex = a.ex + (int64_t)b * a.ex_bs;
     const uint64_t seed = seeds.seed[b];
     const int j0 = a.j_begin > 1 ? a.j_begin : 1;
+    const long long wait_ticks = w >= a.wait_from ? a.wait_ticks : kWaitTicks;
 
     // this workgroup's points are base .. base + 1024 P - 1, point 1024 i + tid of them belongs to thread tid
     const int64_t base = (int64_t)w * (1024 * P);
@@ -585,7 +590,7 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
                         }
                     }
                     if (__ballot(miss) == 0ull) break;
-                    if (wall_clock64() - t0 > a.wait_ticks) { lost = true; break; }
+                    if (wall_clock64() - t0 > wait_ticks) { lost = true; break; }
                 }
             } else if (lane == 0) {
                 v[0] = total;
@@ -651,7 +656,7 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
             for (;;) {
                 if (mine) bits = peek(ex + kExRows + j * kRowWords + lane);
                 if (__ballot(mine && bits == kSlotEmpty) == 0ull) break;
-                if (wall_clock64() - t0 > a.wait_ticks) { lost = true; break; }
+                if (wall_clock64() - t0 > wait_ticks) { lost = true; break; }
             }
             if (lost) {
                 if (lane == 0) s_give_up = 1;
@@ -672,10 +677,10 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
         const int64_t p = base + 1024 * i + tid;
         if (p < a.N) mind[p] = D[i];
     }
-    if (w == 0 && tid == 0) ex[kExDone] = 1ull;
+    if (tid == 0) ex[kExDone + w] = 1ull;
 }
 
-// The chain by one workgroup per space, with nothing to wait for: runs only where seed_chain_kernel gave up.  The
+// The chain by one workgroup per space, with nothing to wait for: runs only where a workgroup of seed_chain_kernel gave up.  The
 // distances to the centres drawn by earlier calls are worked out again (some of them may be half updated).
 __global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, ChainArgs a)
 {
@@ -686,7 +691,7 @@ __global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, C
     __shared__ int64_t s_pick;
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, d = a.d;
     const unsigned long long *ex = a.ex + (int64_t)b * a.ex_bs;
-    if (ex[kExDone] != 0ull) return;
+    if (!__syncthreads_or(tid < a.groups && ex[kExDone + tid] == 0ull)) return;
     const float *Xb = a.X + (int64_t)b * a.x_bs;
     double *D = a.mind + (int64_t)b * a.mind_bs;
     int64_t *chain = a.chain + (int64_t)b * a.chain_bs;
@@ -747,7 +752,11 @@ __global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, C
 
 }  // namespace
 
-void set_seed_wait_ticks(long long ticks) { t_wait_ticks = ticks < 0 ? kWaitTicks : ticks; }
+void set_seed_wait_ticks(int32_t first_workgroup, long long ticks)
+{
+    t_wait_ticks = ticks < 0 ? kWaitTicks : ticks;
+    t_wait_from = first_workgroup;
+}
 
 // compute units of the current device, asked for once per device
 static int compute_units()
@@ -829,7 +838,7 @@ hipError_t launch_seed_chain(const float *X, int64_t N, int32_t d, int64_t ldx, 
             ca.mind = reinterpret_cast<double *>(wsb + L.mind); ca.mind_bs = L.per_batch / 8;
             ca.chain = chain + (int64_t)b0 * chain_batch_stride; ca.chain_bs = chain_batch_stride;
             ca.ex = reinterpret_cast<unsigned long long *>(wsb + L.colstat_part); ca.ex_bs = L.per_batch / 8;
-            ca.wait_ticks = t_wait_ticks;
+            ca.wait_ticks = t_wait_ticks; ca.wait_from = t_wait_from;
             const hipError_t e = launch_chain_in_one(dp, p, nb, sl, ca, s);
             if (e != hipSuccess) return e;
             continue;

@@ -92,7 +92,14 @@ int32_t rls_profile_enable(int32_t on)
 
 int32_t rls_seed_wait_limit(int64_t ticks)
 {
-    set_seed_wait_ticks(ticks);
+    set_seed_wait_ticks(0, ticks);
+    return RLS_OK;
+}
+
+int32_t rls_seed_wait_limit_from(int32_t first_workgroup, int64_t ticks)
+{
+    if (first_workgroup < 0) return RLS_ERR_INVALID_ARG;
+    set_seed_wait_ticks(first_workgroup, ticks);
     return RLS_OK;
 }
 

@@ -365,6 +365,31 @@ def test_seeding_wait_limit_holds_for_one_host_thread(rls, orc):
     assert (seen["other"][1] != -1).all()
 
 
+@pytest.mark.parametrize("first", [0, 1, 5])
+def test_seeding_resume_after_workgroups_gave_up(rls, orc, first):
+    """Workgroups from `first` on give up in every step, those before wait: a workgroup may finish the last step of a call
+    (its draw needs the others' sums only) while another has left without its distances.  The wave that goes on from there
+    must still draw the oracle's centres.  The second centre is a point of workgroup 0, the third one is not."""
+    rng = np.random.default_rng(8)
+    N, d, k_max = 6000, 8, 5                                # six workgroups of 1024 points
+    X = (rng.integers(0, 30, (N, d)) + rng.standard_normal((N, d))).astype(np.float32)
+    chains = ((s, orc.kmeanspp_chain(X, k_max, s)) for s in range(1000))
+    seeds = [s for s, c in chains if c[1] < 1024 <= c[2]][:4]
+    assert len(seeds) == 4
+    Xd = dev(X)
+    ws = torch.empty(1 << 24, dtype=torch.uint8, device="cuda")
+    for seed in seeds:
+        ref = orc.kmeans_sweep(X, 1, k_max, 1, seed=seed)
+        ws.zero_()                                          # distances that nobody has written read as zero
+        try:
+            rls.lib().rls_seed_wait_limit_from(first, ctypes.c_int64(0))
+            _, n_done, part = rls.kmeans_sweep_until_knee(Xd, 1, k_max, 1, 1, 1e-9, seed=seed, workspace=ws)
+        finally:
+            rls.lib().rls_seed_wait_limit(ctypes.c_int64(-1))
+        assert n_done == k_max
+        compare_sweep(orc, X, part, ref, 1, k_max)
+
+
 def test_seeding_all_points_equal(rls, orc):
     X = np.full((300, 8), 3.0, dtype=np.float32)
     got = rls.kmeanspp_chain(dev(X), 5, 11).cpu().numpy()
