@@ -517,7 +517,8 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
     __shared__ int64_t chosen[RLS_MAX_K];
     __shared__ int64_t s_pick;
     __shared__ double s_before, s_r;
-    __shared__ int s_owner, s_entry, s_give_up;
+    __shared__ int s_owner, s_entry;
+    __shared__ int s_no_sums, s_no_row;             // a wait of this step ran out (a word each: set only before the barrier it is read behind)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int w = blockIdx.x, G = a.groups, b = blockIdx.y, d = a.d;
     const float *Xb = a.X + (int64_t)b * a.x_bs;
@@ -542,7 +543,7 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
     }
     if (tid < j0) chosen[tid] = chain[tid];
     if (tid < 64 * E) wsum[tid] = 0.0;
-    if (tid == 0) s_give_up = 0;
+    if (tid == 0) s_no_sums = s_no_row = 0;
     __syncthreads();
     if (tid < DP) cs[tid] = tid < d ? Xb[chosen[j0 - 1] * a.ldx + tid] : 0.0f;
     __syncthreads();
@@ -596,7 +597,7 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
                 v[0] = total;
             }
             if (lost) {
-                if (lane == 0) s_give_up = 1;
+                if (lane == 0) s_no_sums = 1;
             } else {
                 const double incl = wave_scan_dpp(__dadd_rn(__dadd_rn(__dadd_rn(v[0], v[1]), v[2]), v[3])), S = lane_value(incl, 63);
                 int owner = -1, entry = 0;
@@ -614,7 +615,7 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
             }
         }
         __syncthreads();
-        if (s_give_up) return;                      // same for the whole workgroup
+        if (s_no_sums) return;                      // same for the whole workgroup
         const int owner = s_owner;
         // ---- the drawn point: its workgroup hands out row and index
         if (owner < 0) {
@@ -659,14 +660,14 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
                 if (wall_clock64() - t0 > wait_ticks) { lost = true; break; }
             }
             if (lost) {
-                if (lane == 0) s_give_up = 1;
+                if (lane == 0) s_no_row = 1;
             } else {
                 if (lane < DP) cs[lane] = __uint_as_float((unsigned)bits);
                 if (lane == RLS_MAX_D) s_pick = (int64_t)(unsigned)bits;
             }
         }
         __syncthreads();
-        if (s_give_up) return;
+        if (s_no_row) return;
         if (tid == 0) {
             chosen[j] = s_pick;
             if (w == 0) chain[j] = s_pick;
