@@ -15,6 +15,7 @@
 // (triangle inequality: |x_i - c| >= |c_{a_i} - c| - |x_i - c_{a_i}| >= sqrt(D_i)), so D_i stays and the row is not
 // fetched.  The bound carries a margin of 2^-30, far above the rounding of the fp64 sums, so every skipped point is one
 // whose computed distance would not have been smaller: D, the block sums and the chain are the same with and without it.
+#include <algorithm>
 #include <atomic>
 
 #include "rls_internal.h"
@@ -36,10 +37,12 @@ __device__ inline double uniform01(uint64_t seed, uint64_t j)
     return (double)(splitmix64(seed, j) >> 11) * 0x1.0p-53;
 }
 
-// how long a workgroup of seed_chain_kernel waits for the others before it gives up (100 MHz clock: 50 ms); a test may
-// change it for the launches of its own host thread
+// How long a workgroup of seed_chain_kernel waits for the others before it gives up, in ticks of the 100 MHz clock: 2 ms in
+// its first exchange, which some workgroups may never reach while other streams hold compute units, then 50 ms, since
+// from there on all are running.  A test may change both for the launches of its own host thread.
+constexpr long long kArriveTicks = 200000;
 constexpr long long kWaitTicks = 5000000;
-thread_local long long t_wait_ticks = kWaitTicks;
+thread_local long long t_wait_ticks = -1;          // negative: the two limits above
 thread_local int t_wait_from = 0;                  // first workgroup of a space that the thread's limit holds for
 
 struct SeedList {
@@ -381,17 +384,22 @@ __global__ void __launch_bounds__(1024) seed_pick_kernel(SeedList seeds, int b0,
 // every word is written once, and a row travels as words of (step, value) - so no flags, fences or counters are needed:
 // words are stored and polled with agent-scope atomics, which reach past the L2 of an XCD.
 //
-// No wait is unbounded: the workgroups need not be resident together (nothing guarantees that while other streams hold
-// compute units), so a workgroup that has waited `wait_ticks` gives up and leaves its finished word unset.  Any of them may
-// do so in the last step, when the others already have all they need from it, and its distances are then missing: so
-// seed_chain_rest_kernel, always launched behind, does the chain again, in one workgroup without any exchange, unless every
-// workgroup has finished.
+// No wait is unbounded: the workgroups need not be resident together (two chains on two streams may each hold half of the
+// chip, a stream may be confined to a few compute units), so a workgroup that has waited too long gives up, tells the others,
+// and leaves its finished word unset.  Any of them may do so in the last step, when the others already have all they need
+// from it, and its distances are then missing: so seed_chain_rest_kernel, always launched behind, does the chain again
+// unless every workgroup has finished.
 constexpr unsigned long long kSlotEmpty = ~0ull;
 constexpr int kChainWgs = 256;                                 // workgroups per space at most
 constexpr int kRowWords = RLS_MAX_D + 1;                       // row, then the index
 constexpr int kExRows = RLS_MAX_K * kChainWgs;                 // word offsets within the exchange area of a space
 constexpr int kExDone = kExRows + RLS_MAX_K * kRowWords;        // one per workgroup: 1 when it has finished
-constexpr int kExWords = kExDone + kChainWgs;
+constexpr int kExQuit = kExDone + kChainWgs;                   // 1 when a workgroup has given up
+constexpr int kExTicket = kExQuit + 1;                         // seed_chain_rest_kernel: the next block of points to be worked on
+constexpr int kExSums = kExTicket + 1;                         //   sums of a step, one per block
+constexpr int kExCount = kExSums + kChainWgs;                  //   blocks of a step that are done, one per step
+constexpr int kExPick = kExCount + RLS_MAX_K;                  //   drawn index, one per step
+constexpr int kExWords = kExPick + RLS_MAX_K;
 static_assert(kExWords * 8 <= kSeedExchangeBytes, "the exchange area must fit its place in the workspace");
 
 struct ChainArgs {
@@ -406,7 +414,7 @@ struct ChainArgs {
     int64_t chain_bs;
     unsigned long long *ex;               // exchange area
     int64_t ex_bs;
-    long long wait_ticks;                 // of the 100 MHz clock; workgroups below wait_from wait kWaitTicks
+    long long wait_ticks;                 // limit of every wait in workgroups from wait_from on; negative: the default limits
     int32_t wait_from;
 };
 
@@ -418,12 +426,19 @@ __global__ void __launch_bounds__(256) seed_begin_kernel(SeedList seeds, ChainAr
     for (int e = t0; e < a.k_max * kChainWgs; e += step)
         if (e % kChainWgs < a.groups) ex[e] = kSlotEmpty;
     for (int e = t0; e < a.k_max * kRowWords; e += step) ex[kExRows + e] = kSlotEmpty;
+    int64_t *chain = a.chain + (int64_t)b * a.chain_bs;
     if (t0 < a.groups) ex[kExDone + t0] = 0ull;
+    if (t0 < a.k_max) {
+        ex[kExCount + t0] = 0ull;
+        ex[kExPick + t0] = kSlotEmpty;
+        if (t0 >= max(a.j_begin, 1)) chain[t0] = 0;
+    }
     if (t0 == 0) {
+        ex[kExQuit] = ex[kExTicket] = 0ull;
         if (a.j_begin == 0) {
             int64_t first = (int64_t)(uniform01(seeds.seed[b], 0) * (double)a.N);
             if (first >= a.N) first = a.N - 1;
-            a.chain[(int64_t)b * a.chain_bs] = first;
+            chain[0] = first;
         }
     }
 }
@@ -497,6 +512,20 @@ __device__ inline unsigned long long peek(const unsigned long long *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Looks again and again until everything is there (`look`: the same answer in every lane); false after `limit` ticks, or
+// soon after another workgroup has given up.  The clock is read before a look, so what is missing in the end is missing after the limit.
+template <class Look>
+__device__ inline bool wait_for(long long limit, const unsigned long long *quit, Look look)
+{
+    constexpr long long kUndisturbed = 2000;       // 20 us: no exchange lasts that long when all workgroups are running
+    const long long t0 = wall_clock64();
+    for (;;) {
+        const long long waited = wall_clock64() - t0;
+        if (look()) return true;
+        if (waited > limit || (quit && waited > kUndisturbed && peek(quit) != 0ull)) return false;
+    }
+}
+
 // smallest index that is not among the j chosen ones (N >= k_max: it exists)
 __device__ inline int64_t first_not_chosen(const int64_t *chosen, int j)
 {
@@ -527,7 +556,7 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
     unsigned long long *ex = a.ex + (int64_t)b * a.ex_bs;
     const uint64_t seed = seeds.seed[b];
     const int j0 = a.j_begin > 1 ? a.j_begin : 1;
-    const long long wait_ticks = w >= a.wait_from ? a.wait_ticks : kWaitTicks;
+    const bool own_limit = w >= a.wait_from && a.wait_ticks >= 0;
 
     // this workgroup's points are base .. base + 1024 P - 1, point 1024 i + tid of them belongs to thread tid
     const int64_t base = (int64_t)w * (1024 * P);
@@ -543,8 +572,12 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
     }
     if (tid < j0) chosen[tid] = chain[tid];
     if (tid < 64 * E) wsum[tid] = 0.0;
-    if (tid == 0) s_no_sums = s_no_row = 0;
+    if (tid == 0) {
+        s_no_sums = peek(ex + kExQuit) != 0ull;     // started when another had already given up
+        s_no_row = 0;
+    }
     __syncthreads();
+    if (s_no_sums) return;
     if (tid < DP) cs[tid] = tid < d ? Xb[chosen[j0 - 1] * a.ldx + tid] : 0.0f;
     __syncthreads();
 
@@ -579,8 +612,7 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
                     if (bits == kSlotEmpty) bits = 0x7ff8000000000000ull;
                     post(slot + w, bits);
                 }
-                const long long t0 = wall_clock64();
-                for (;;) {
+                lost = !wait_for(own_limit ? a.wait_ticks : (j == j0 ? kArriveTicks : kWaitTicks), ex + kExQuit, [&] {
                     bool miss = false;
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
@@ -590,14 +622,16 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
                             v[q] = __longlong_as_double((long long)bits);
                         }
                     }
-                    if (__ballot(miss) == 0ull) break;
-                    if (wall_clock64() - t0 > wait_ticks) { lost = true; break; }
-                }
+                    return __ballot(miss) == 0ull;
+                });
             } else if (lane == 0) {
                 v[0] = total;
             }
             if (lost) {
-                if (lane == 0) s_no_sums = 1;
+                if (lane == 0) {
+                    s_no_sums = 1;
+                    post(ex + kExQuit, 1ull);
+                }
             } else {
                 const double incl = wave_scan_dpp(__dadd_rn(__dadd_rn(__dadd_rn(v[0], v[1]), v[2]), v[3])), S = lane_value(incl, 63);
                 int owner = -1, entry = 0;
@@ -652,15 +686,15 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
         } else if (wave == 0) {
             const bool mine = lane < DP || lane == RLS_MAX_D;
             unsigned long long bits = 0ull;
-            bool lost = false;
-            const long long t0 = wall_clock64();
-            for (;;) {
+            const bool there = wait_for(own_limit ? a.wait_ticks : kWaitTicks, ex + kExQuit, [&] {
                 if (mine) bits = peek(ex + kExRows + j * kRowWords + lane);
-                if (__ballot(mine && bits == kSlotEmpty) == 0ull) break;
-                if (wall_clock64() - t0 > wait_ticks) { lost = true; break; }
-            }
-            if (lost) {
-                if (lane == 0) s_no_row = 1;
+                return __ballot(mine && bits == kSlotEmpty) == 0ull;
+            });
+            if (!there) {
+                if (lane == 0) {
+                    s_no_row = 1;
+                    post(ex + kExQuit, 1ull);
+                }
             } else {
                 if (lane < DP) cs[lane] = __uint_as_float((unsigned)bits);
                 if (lane == RLS_MAX_D) s_pick = (int64_t)(unsigned)bits;
@@ -681,73 +715,146 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
     if (tid == 0) ex[kExDone + w] = 1ull;
 }
 
-// The chain by one workgroup per space, with nothing to wait for: runs only where a workgroup of seed_chain_kernel gave up.  The
-// distances to the centres drawn by earlier calls are worked out again (some of them may be half updated).
-__global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, ChainArgs a)
+// The chain again, where a workgroup of seed_chain_kernel gave up.  It must not need its workgroups to be resident together,
+// so they own no points: a step is `groups` blocks of 1024 P points, and whoever is free takes the next block by a ticket.
+// A block waits for the draw of the step before, that is for blocks with smaller tickets, which workgroups hold that are
+// running and wait for smaller tickets still - so whatever number of workgroups is running, every wait ends.  Who finishes
+// the last block of a step draws.  The distances to the centres drawn by earlier calls are worked out again (some of them may be
+// half updated).  Distances, block sums and the draw are those of seed_chain_kernel.  Rows and distances come from memory in every step, and
+// between two steps lie a ticket, a count and a message: 14 us per centre at 65,536 x 16, 55 at 1M x 16, 167 at 524,288 x 32, against
+// 5.1, 10.5 and 11 undisturbed.  (One workgroup that walked all points: 631, 9970 and 8790.  All waves fencing in all three places
+// instead of one wave, acquire or release: 45, 175 and 313.)
+constexpr int kRestWgs = 256;                      // workgroups per space at most: launched for nothing almost always
+constexpr long long kRestTicks = 1000000000;       // 10 s.  Only another call that uses the same workspace at the same time can make a
+                                                   // wait last that long; its results are undefined then, but it ends
+template <int DP>
+__global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, ChainArgs a, int P)
 {
-    __shared__ float cs[RLS_MAX_D];
+    constexpr int E = 2;                           // sums of 64 points per lane of wave 0: P <= 8
+    __shared__ float cs[DP];
+    __shared__ double wsum[64 * E];
     __shared__ int64_t chosen[RLS_MAX_K];
-    __shared__ double wtot[16];
-    __shared__ int s_first, s_last;
     __shared__ int64_t s_pick;
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, d = a.d;
-    const unsigned long long *ex = a.ex + (int64_t)b * a.ex_bs;
-    if (!__syncthreads_or(tid < a.groups && ex[kExDone + tid] == 0ull)) return;
+    __shared__ double s_before, s_r;
+    __shared__ int s_ticket, s_last, s_owner, s_entry;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int G = a.groups, b = blockIdx.y, d = a.d;
+    unsigned long long *ex = a.ex + (int64_t)b * a.ex_bs;
+    if (!__syncthreads_or(tid < G && ex[kExDone + tid] == 0ull)) return;
     const float *Xb = a.X + (int64_t)b * a.x_bs;
     double *D = a.mind + (int64_t)b * a.mind_bs;
     int64_t *chain = a.chain + (int64_t)b * a.chain_bs;
     const int j0 = a.j_begin > 1 ? a.j_begin : 1;
     if (tid < j0) chosen[tid] = chain[tid];
-    const int64_t len = (a.N + 1023) / 1024, p0 = min(tid * len, a.N), p1 = min(p0 + len, a.N);    // this thread's points
-    for (int j = 1; j < a.k_max; ++j) {
+    if (tid < 64 * E) wsum[tid] = 0.0;
+    for (;;) {
+        if (tid == 0) s_ticket = (int)__hip_atomic_fetch_add(ex + kExTicket, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
-        if (tid < d) cs[tid] = Xb[chosen[j - 1] * a.ldx + tid];
-        if (tid == 0) { s_first = 0x7fffffff; s_last = -1; }
-        __syncthreads();
-        double local = 0.0;
-        for (int64_t p = p0; p < p1; ++p) {
-            double acc = 0.0;
-            for (int l = 0; l < d; ++l) {
-                const double diff = __dsub_rn((double)Xb[p * a.ldx + l], (double)cs[l]);
-                acc = __dadd_rn(acc, __dmul_rn(diff, diff));
+        const int j = j0 + s_ticket / G, blk = s_ticket % G;
+        if (j >= a.k_max) return;
+        if (j > j0) {
+            if (wave == 0) {
+                const bool there = wait_for(kRestTicks, nullptr, [&] { return peek(ex + kExPick + j - 1) != kSlotEmpty; });
+                if (lane == 0) s_last = there;
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");     // what others have written counts from the barrier on
             }
-            double cur = j == 1 ? acc : D[p];
-            if (acc < cur) cur = acc;
-            D[p] = cur;
-            local = __dadd_rn(local, cur);
+            __syncthreads();
+            if (!s_last) return;
+            if (tid >= j0 && tid < j) chosen[tid] = (int64_t)peek(ex + kExPick + tid);
         }
-        if (j < j0) continue;
-        const double incl = wave_scan_dpp(local);
-        if (lane == 63) wtot[wave] = incl;
-        __syncthreads();
-        double before = 0.0, S = 0.0;
-        for (int v = 0; v < 16; ++v) {
-            if (v == wave) before = S;
-            S = __dadd_rn(S, wtot[v]);
-        }
-        double run = __dadd_rn(before, lane_before(incl));
-        const double r = __dmul_rn(uniform01(seeds.seed[b], (uint64_t)j), S);
-        if (local > 0.0) {
-            if (__dadd_rn(run, local) > r) atomicMin(&s_first, tid);
-            atomicMax(&s_last, tid);
-        }
-        __syncthreads();
-        if (!(S > 0.0) || s_last < 0) {
-            if (tid == 0) s_pick = first_not_chosen(chosen, j);
-        } else if (tid == (s_first != 0x7fffffff ? s_first : s_last)) {
-            int64_t pick = -1;
-            for (int64_t p = p0; p < p1; ++p) {
-                const double v = D[p];
-                run = __dadd_rn(run, v);
-                if (v > 0.0) {
-                    pick = p;
-                    if (run > r) break;
+        // ---- the newest centre (the first time: all that are known)
+        const int64_t base = (int64_t)blk * 1024 * P;
+        for (int m = j == j0 ? 0 : j - 1; m < j; ++m) {
+            __syncthreads();
+            if (tid < DP) cs[tid] = tid < d ? Xb[chosen[m] * a.ldx + tid] : 0.0f;
+            __syncthreads();
+            for (int i = 0; i < P; ++i) {
+                const int64_t p = base + 1024 * i + tid;
+                double cur = 0.0;
+                if (p < a.N) {
+                    const float *row = Xb + p * a.ldx;
+                    float x[DP];
+#pragma unroll
+                    for (int l = 0; l < DP; ++l) x[l] = l < d ? row[min(l, d - 1)] : 0.0f;
+                    double acc = 0.0;
+#pragma unroll
+                    for (int l = 0; l < DP; ++l) {
+                        const double diff = __dsub_rn((double)x[l], (double)cs[l]);
+                        acc = __dadd_rn(acc, __dmul_rn(diff, diff));
+                    }
+                    cur = acc;
+                    if (m > 0) {
+                        const double old = D[p];
+                        if (!(acc < old)) cur = old;
+                    }
+                    D[p] = cur;
                 }
+                const double incl = wave_scan_dpp(cur);
+                if (lane == 63) wsum[i * 16 + wave] = incl;
             }
-            s_pick = pick;
+        }
+        __builtin_amdgcn_s_waitcnt(0x0f70);        // vmcnt(0): this wave's distances have left the compute unit ...
+        __syncthreads();
+        if (wave == 0) {
+            const double total = lane_value(wave_scan_dpp(__dadd_rn(wsum[lane * E], wsum[lane * E + 1])), 63);
+            if (lane == 0) {
+                post(ex + kExSums + blk, (unsigned long long)__double_as_longlong(total));
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");     // ... and are there for all, with the sum, before the block counts as done
+                s_last = __hip_atomic_fetch_add(ex + kExCount + j, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned long long)(G - 1);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         }
         __syncthreads();
-        if (tid == 0) { chosen[j] = s_pick; chain[j] = s_pick; }
+        if (!s_last) continue;
+        // ---- the draw
+        if (wave == 0) {
+            double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (4 * lane + q < G) v[q] = __longlong_as_double((long long)peek(ex + kExSums + 4 * lane + q));
+            const double incl = wave_scan_dpp(__dadd_rn(__dadd_rn(__dadd_rn(v[0], v[1]), v[2]), v[3])), S = lane_value(incl, 63);
+            int owner = -1;
+            double before = 0.0, r = 0.0;
+            if (S > 0.0) {
+                r = __dmul_rn(uniform01(seeds.seed[b], (uint64_t)j), S);
+                owner = wave_locate<4>(v, incl, 0.0, r, before);
+            }
+            if (lane == 0) { s_owner = owner; s_before = before; s_r = r; }
+        }
+        __syncthreads();
+        if (s_owner < 0) {
+            if (tid == 0) s_pick = first_not_chosen(chosen, j);
+        } else {
+            const int64_t from = (int64_t)s_owner * 1024 * P;
+            for (int i = 0; i < P; ++i) {
+                const int64_t p = from + 1024 * i + tid;
+                const double incl = wave_scan_dpp(p < a.N ? D[p] : 0.0);
+                if (lane == 63) wsum[i * 16 + wave] = incl;
+            }
+            __syncthreads();
+            if (wave == 0) {
+                double own[E];
+#pragma unroll
+                for (int e = 0; e < E; ++e) own[e] = wsum[lane * E + e];
+                double at;
+                const int entry = max(wave_locate<E>(own, wave_scan_dpp(__dadd_rn(own[0], own[1])), s_before, s_r, at), 0);
+                if (lane == 0) { s_entry = entry; s_before = at; }
+            }
+            __syncthreads();
+            if (wave == (s_entry & 15)) {
+                const int64_t first = from + 1024 * (s_entry >> 4) + 64 * wave;
+                const double v[1] = {first + lane < a.N ? D[first + lane] : 0.0};
+                double at;
+                const int ln = max(wave_locate<1>(v, wave_scan_dpp(v[0]), s_before, s_r, at), 0);
+                if (lane == 0) s_pick = min(first + ln, a.N - 1);
+            }
+        }
+        __syncthreads();
+        if (tid == 0) {
+            chain[j] = s_pick;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            post(ex + kExPick + j, (unsigned long long)s_pick);
+        }
     }
 }
 
@@ -755,7 +862,7 @@ __global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, C
 
 void set_seed_wait_ticks(int32_t first_workgroup, long long ticks)
 {
-    t_wait_ticks = ticks < 0 ? kWaitTicks : ticks;
+    t_wait_ticks = ticks;
     t_wait_from = first_workgroup;
 }
 
@@ -810,7 +917,12 @@ static hipError_t launch_chain_in_one(int dp, int p, int spaces, const SeedList 
     default: return hipErrorInvalidValue;
     }
 #undef RLS_SEED_CHAIN
-    if (a.groups > 1) hipLaunchKernelGGL(seed_chain_rest_kernel, dim3(spaces), dim3(1024), 0, s, sl, a);
+    if (a.groups > 1) {
+        const dim3 rest(std::min(a.groups, kRestWgs), spaces);
+        if (dp == 8) hipLaunchKernelGGL(seed_chain_rest_kernel<8>, rest, block, 0, s, sl, a, p);
+        else if (dp == 16) hipLaunchKernelGGL(seed_chain_rest_kernel<16>, rest, block, 0, s, sl, a, p);
+        else hipLaunchKernelGGL(seed_chain_rest_kernel<32>, rest, block, 0, s, sl, a, p);
+    }
     return hipGetLastError();
 }
 
