@@ -2251,7 +2251,7 @@ int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int3
     return RLS_OK;
 }
 
-void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, int32_t batch, SweepLayout *L)
+void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, int32_t batch, bool chain_grows, SweepLayout *L)
 {
     int64_t off = 0;
     auto take = [&](int64_t bytes) { const int64_t o = off; off += align_up(bytes, 256); return o; };
@@ -2259,13 +2259,22 @@ void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, in
     if (L->stat_blocks > kStatBlocks) L->stat_blocks = kStatBlocks;
     if (L->stat_blocks < 1) L->stat_blocks = 1;
     L->seed_blocks = (int32_t)((N + kSeedBlock - 1) / kSeedBlock);
+    // seeding state and partial column statistics: needed until the first round
     L->colstat_part = take((int64_t)kStatBlocks * 32 * sizeof(ColPart));
-    L->colinfo = take(512);
-    L->chain = take((int64_t)k_max * 8);
     L->mind = take(N * 8);
     L->bsum = take((int64_t)L->seed_blocks * 8);
     L->near = take(N);
     L->seedthr = take((int64_t)k_max * 8);
+    // The log, written from the second round on, takes their place, unless the chain is to grow: so what fitted the fixed
+    // workspace of rls_kmeans_sweep_static still fits with the up to 256 workgroups that chunks per group bring to sweeps
+    // of one or few k (12 MiB of log; chunks of at least 4096 points, as before, had 8 at the sizes in question).
+    const int64_t log_bytes = (int64_t)plan.n_wgs * (step_threads_of(plan.dp) / 64) * kLogCap * 8;
+    if (!chain_grows) {
+        L->log = L->colstat_part;
+        off = std::max(off, L->log + align_up(log_bytes, 256));
+    }
+    L->colinfo = take(512);
+    L->chain = take((int64_t)k_max * 8);
     L->xp = take((N + 31) / 32 * prep_block_u4_of(plan.dp) * 16);     // (with the blocks above: the same place whatever the range of k)
     L->opA = take((int64_t)plan.total_tiles * tile_bytes_of(plan.dp));
     L->cnmax = take((int64_t)plan.n_runs * kMaxParts * 4);
@@ -2276,7 +2285,7 @@ void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, in
     L->tot = take((int64_t)plan.total_rows * d * 16);
     L->totcnt = take((int64_t)plan.total_rows * d * 8);
     L->prev = take((int64_t)plan.lab_slots * align_up(N, 16));
-    L->log = take((int64_t)plan.n_wgs * (step_threads_of(plan.dp) / 64) * kLogCap * 8);
+    if (chain_grows) L->log = take(log_bytes);
     L->per_batch = off;
     L->total = off * batch;
 }

@@ -154,7 +154,7 @@ int64_t rls_kmeans_sweep_workspace_bytes(int64_t N, int32_t d, int32_t k_min, in
     const int32_t prc = make_sweep_plan(N, d, k_min, k_max, batch, &plan);
     if (prc != RLS_OK) return prc;
     SweepLayout L;
-    sweep_layout(plan, N, d, k_max, batch, &L);
+    sweep_layout(plan, N, d, k_max, batch, false, &L);
     return L.total;
 }
 
@@ -170,7 +170,7 @@ int32_t rls_kmeanspp_chain(const float *X_dev, int64_t N, int32_t d, int64_t ldx
     rc = make_sweep_plan(N, d, k_max, k_max, 1, &plan);
     if (rc != RLS_OK) return rc;
     SweepLayout L;
-    sweep_layout(plan, N, d, k_max, 1, &L);
+    sweep_layout(plan, N, d, k_max, 1, false, &L);
     if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < L.total) return RLS_ERR_WORKSPACE;
     char *ws = static_cast<char *>(workspace_dev);
     RLS_HIP_TRY(launch_seed_chain(X_dev, N, d, ldx, 0, 1, k_max, &seed, init_idx_dev, k_max, ws, L, (hipStream_t)stream));
@@ -196,7 +196,7 @@ int32_t rls_kmeans_sweep_batched(int32_t batch, const float *X_dev, int64_t N, i
     rc = make_sweep_plan(N, d, k_min, k_max, batch, &plan);
     if (rc != RLS_OK) return rc;
     SweepLayout L;
-    sweep_layout(plan, N, d, k_max, batch, &L);
+    sweep_layout(plan, N, d, k_max, batch, false, &L);
     if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < L.total) return RLS_ERR_WORKSPACE;
     char *ws = static_cast<char *>(workspace_dev);
     hipStream_t s = (hipStream_t)stream;
@@ -238,7 +238,7 @@ static int32_t until_knee_workspace(int64_t N, int32_t d, int32_t k_min, int32_t
         const int32_t rc = make_sweep_plan(N, d, k_lo, k_hi, 1, &plan);
         if (rc != RLS_OK) return rc;
         SweepLayout L;
-        sweep_layout(plan, N, d, k_max, 1, &L);     // chain sized for k_max: the leading blocks sit at the same offsets in every wave
+        sweep_layout(plan, N, d, k_max, 1, true, &L);     // chain sized for k_max: the leading blocks sit at the same offsets in every wave
         if (L.total > need) need = L.total;
     }
     *bytes = need;
@@ -284,7 +284,7 @@ int32_t rls_kmeans_sweep_until_knee(const float *X_dev, int64_t N, int32_t d, in
         rc = make_sweep_plan(N, d, k_lo, k_hi, 1, &plan);
         if (rc != RLS_OK) return rc;
         SweepLayout L;
-        sweep_layout(plan, N, d, k_max, 1, &L);
+        sweep_layout(plan, N, d, k_max, 1, true, &L);
         const int64_t *init = init_idx_dev;
         if (!init) {
             // the chain grows with the waves: centres chain_done .. k_hi-1 are drawn now, from the distance state of the earlier ones

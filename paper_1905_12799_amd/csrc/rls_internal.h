@@ -83,12 +83,12 @@ int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int3
 // unless noted).  Filled by sweep_layout().
 struct SweepLayout {
     int64_t colstat_part;   // per-block partial column statistics
-    int64_t colinfo;        // mean[32] fp32, shift[32] int32, wide[33] int32
-    int64_t chain;          // int64 [k_max] seeding chain
     int64_t mind;           // fp64 [N] squared distance to the nearest chosen centre
     int64_t bsum;           // fp64 [seed blocks] block sums of mind
     int64_t near;           // uint8 [N] chain position of the nearest chosen centre
     int64_t seedthr;        // fp64 [k_max] per chosen centre: the bound below which a point's distance cannot improve
+    int64_t colinfo;        // mean[32] fp32, shift[32] int32, wide[33] int32
+    int64_t chain;          // int64 [k_max] seeding chain
     int64_t opA;            // per 32-row tile: fp16 pieces of the centred, -2-scaled centroids and the bf16 bias slot, in MFMA operand order
     int64_t cnmax;          // fp32 [n_runs][parts of a run] maximum of cn over the centroids of a part
     int64_t psum;           // int64 per group [n_chunks][rows of the group][d]: per-chunk changes of the fixed-point sums
@@ -99,13 +99,15 @@ struct SweepLayout {
     int64_t totcnt;         // int64 [total_rows][d] running member counts (one copy per feature)
     int64_t prev;           // uint8 per group [N rounded up to 16][8 / S]: label of every point in the last round (0xff: none yet)
     int64_t log;            // uint64 [chunks of all groups][waves][512] rings of moved-pair records, one per wave of the step kernel
+                            // (in the place of colstat_part, mind, bsum, near and seedthr, unless the chain is to grow between sweeps)
     int64_t xp;             // prepared copy of the points: per block of 32, the matrix operands and squared norms (kmeans_lloyd.hip)
     int64_t per_batch;      // bytes per batch element (multiple of 256)
     int64_t total;          // per_batch * batch
     int32_t seed_blocks;
     int32_t stat_blocks;
 };
-void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, int32_t batch, SweepLayout *L);
+// `chain_grows`: a later call with the same workspace adds centres to the chain (the waves of a sweep until the knee)
+void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, int32_t batch, bool chain_grows, SweepLayout *L);
 
 // the column statistics' partial results come after the seeding chain: their place serves the chain's exchange area
 constexpr int kSeedExchangeBytes = 256 * 32 * 40;

@@ -60,3 +60,22 @@ def test_static_sweep_turns_down_what_does_not_fit(rls):
     rc = L.rls_kmeans_sweep_static(fake, N, d, d, 1, 64, 5, ctypes.c_uint64(1), None, None, fake, fake, None, fake, None)
     assert rc == -4
     assert L.rls_kmeans_sweep_static(fake, 0, d, d, 1, 64, 5, ctypes.c_uint64(1), None, None, fake, fake, None, fake, None) == -1
+
+
+# sizes close to the limit that the fixed workspace has always taken
+EDGE = [(665709, 13, 42, 42), (677843, 3, 10, 10), (676720, 5, 29, 29), (335816, 21, 121, 123), (338770, 22, 123, 125), (329472, 32, 25, 33),
+        (328672, 30, 64, 68), (377402, 18, 97, 97)]
+
+
+@pytest.mark.parametrize("N,d,k_min,k_max", EDGE[:1] + EDGE[3:4])
+def test_static_sweep_at_its_largest(rls, orc, N, d, k_min, k_max):
+    """The sweep with its own chain; the log of moved points lies where the chain's distances were."""
+    rng = np.random.default_rng(N)
+    X = (rng.uniform(-9, 9, (30, d))[rng.integers(0, 30, N)] + rng.standard_normal((N, d))).astype(np.float32)
+    got = rls.kmeans_sweep_static(torch.as_tensor(X).cuda(), k_min, k_max, 3, seed=4)
+    torch.cuda.synchronize()
+    ref = orc.kmeans_sweep(X, k_min, k_max, 3, seed=4)
+    assert int(got.status.item()) == 0
+    np.testing.assert_array_equal(got.labels.cpu().numpy(), ref["labels"])
+    np.testing.assert_array_equal(got.centroids.cpu().numpy(), ref["centroids"])
+    np.testing.assert_allclose(got.inertia.cpu().numpy(), ref["inertia"], rtol=1e-5)
