@@ -297,9 +297,8 @@ def test_seeding_chain(rls, orc, name, N, k_max):
 @pytest.mark.parametrize("N,d,span,stride", [(5000, 2, 6, None), (30011, 4, 3, None), (9000, 8, 2, 12), (7001, 5, 4, None),
                                              (20000, 16, 1, None), (3000, 32, 2, 40)])
 def test_seeding_chain_lattice_points(rls, orc, N, d, span, stride):
-    """Integer lattices: many duplicates, and many points exactly half way between two centres, where the bound
-    that lets the update skip a row (D_i against a quarter of the squared distance between centres) is met with
-    equality; rows that are not 16-byte multiples or are strided take the element-wise read path."""
+    """Integer lattices: many duplicates, many equal distances; rows that are strided or no multiple of 16 bytes.  (Sizes that
+    the chain in one launch takes; test_seeding_chain_walked_in_memory has the larger ones.)"""
     rng = np.random.default_rng(N + d)
     X = rng.integers(0, span + 1, size=(N, d)).astype(np.float32)
     Xd = dev(X)
@@ -311,6 +310,53 @@ def test_seeding_chain_lattice_points(rls, orc, N, d, span, stride):
     for seed in (1, 2):
         got = rls.kmeanspp_chain(Xd, k_max, seed).cpu().numpy()
         np.testing.assert_array_equal(got, orc.kmeanspp_chain(X, k_max, seed))
+
+
+@pytest.mark.parametrize("N,d,span,stride", [
+    # one size past the chain in one launch, per padded number of features; rows of 1 to 8 units of 16 bytes, dense and strided
+    (2097153, 4, 3, None), (2097999, 8, 2, 12), (1048577, 12, 2, None), (1050001, 16, 1, 20), (524289, 20, 1, None), (530001, 24, 2, None),
+    (525003, 28, 1, None), (524800, 32, 2, 40),
+    # element by element: rows that are no multiple of 16 bytes, or too far apart for that; more centres than distinct points
+    (2100001, 5, 4, None), (524300, 17, 2, None), (1049600, 12, 2, 13), (2097155, 2, 1, None)])
+def test_seeding_chain_walked_in_memory(rls, orc, N, d, span, stride):
+    """Chains with an update and a draw launch per centre.  Integer lattices: many duplicates, and many points exactly half way
+    between two centres, where the bound that lets the update skip a row (D_i against a quarter of the squared distance
+    between centres) is met with equality.  Drawn at once, and wave by wave from the distances, nearest centres and
+    bounds that the waves before left (with no rounds the centroids of a run are the rows of its first centres)."""
+    dp = 8 if d <= 8 else (16 if d <= 16 else 32)
+    assert N > torch.cuda.get_device_properties(0).multi_processor_count * 1024 * (64 // dp)
+    rng = np.random.default_rng(N + d)
+    X = rng.integers(0, span + 1, size=(N, d)).astype(np.float32)
+    Xd = dev(X)
+    if stride is not None:
+        wide = torch.zeros((N, stride), dtype=torch.float32, device="cuda")
+        wide[:, :d] = Xd
+        Xd = wide[:, :d]
+    k_max = min(40, (span + 1) ** d + 3)
+    ref = orc.kmeanspp_chain(X, k_max, 1)
+    np.testing.assert_array_equal(rls.kmeanspp_chain(Xd, k_max, 1).cpu().numpy(), ref)
+    for k_wave in (1, 4):
+        _, n_done, part = rls.kmeans_sweep_until_knee(Xd, 1, 7, k_wave, 0, 1e-9, seed=1, want_labels=False)
+        assert n_done == 7
+        np.testing.assert_array_equal(part.centroids_of(7).cpu().numpy(), X[ref[:7]])
+
+
+@pytest.mark.parametrize("N,d,gap", [(17001, 16, 0), (33000, 7, 0), (8200, 20, 8), (8200, 20, 6)])
+def test_seeding_chain_of_many_spaces(rls, orc, N, d, gap):
+    """64 spaces that do not fit the chip together are walked in memory, the six after them are one launch; rows that can
+    and (spaces 2 floats off) cannot be read 16 bytes at a time in every space."""
+    batch, k_max = 70, 6
+    rng = np.random.default_rng(N + gap)
+    X = rng.integers(0, 3, size=(batch, N, d)).astype(np.float32)
+    buf = torch.zeros((batch, N * d + gap), dtype=torch.float32, device="cuda")
+    buf[:, :N * d] = dev(X).view(batch, -1)
+    Xd = buf[:, :N * d].view(batch, N, d)
+    assert Xd.stride(0) == N * d + gap
+    seeds = [100 + b for b in range(batch)]
+    res = rls.kmeans_sweep_batched(Xd, k_max, k_max, 0, seeds=seeds)
+    got = res.centroids.cpu().numpy().reshape(batch, k_max, d)
+    for b in range(batch):
+        np.testing.assert_array_equal(got[b], X[b][orc.kmeanspp_chain(X[b], k_max, seeds[b])], err_msg=f"space {b}")
 
 
 @pytest.mark.parametrize("N,d,k_max", [(1, 3, 1), (2, 8, 2), (1024, 8, 5), (1025, 16, 9), (2049, 32, 128), (4097, 5, 6), (70001, 7, 12),
