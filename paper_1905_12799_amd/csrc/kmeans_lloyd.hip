@@ -2096,19 +2096,31 @@ int64_t lloyd_group_lds_bytes(int dp, int d, int n_tiles, int real_rows, int cop
 }
 
 constexpr int kFillWorkgroups = 256;   // one per compute unit
+// What a slab of 32 points costs beside the tiles of its group (operand loads, close calls, labels, log), in tiles.  Sweeps
+// at 65 shapes from 20,003 x 8 to 3.2M x 32 with 2, 4, 8 and 12 in its place: 2 up to 27% and 4 up to 12% slower, 8 and 12
+// within 5% either way.
 constexpr int kSlabCost = 6;
-// Workgroups per compute unit when the groups' chunks are cut to equal cost, by the work a compute unit has (0: the same
-// chunks for every group).  A workgroup pays some 9 us for its set-up and its last slabs, so a short launch gets one; a
-// long one gets several, so that the ends of its workgroups even out.  Measured, per sweep, against two workgroups per compute
-// unit with the same chunks for every group: 65,536 x 16, k 1..64 (per_cu 80): 2.19 -> 1.96 ms with one; 1M x 16, k 8..23 (200):
-// 3.1 -> 2.7 with one; 1M x 16, k 1..64 (1280): 12.6 -> 12.9 with two, the groups of a chunk no longer share its reads;
-// 1M x 32, k 1..100 (5300): 24.0 -> 19.8 with three; 2M x 16, k 1..128 (6500): 37.8 -> 34.6 with five.
-// (The spaces of a batch are many workgroups already: 0 is as good there or better from 700 on.)
-int workgroups_per_cu(int64_t per_cu, int batch)
+// Workgroups per compute unit when the groups' chunks are cut to equal cost (0: the same chunks for every group), by the work
+// `per_cu` that one wave of a compute unit has when all is spread evenly over the chip (tiles of 32 points, about 0.3 us each).
+// Equal cost pays where a launch is short or its groups are many; the same chunks let the groups of a chunk share its
+// reads.  A workgroup pays some 9 us for its set-up and its last slabs, so a short launch gets one per compute unit; in a long
+// one several even out each other's ends.  Sweeps of 8 rounds, time against the same chunks, geometric means over 396 shapes
+// of one space (40,003 to 12M points) with up to 4 / 5 to 8 / more than 8 groups:
+//   one     per_cu 100 .. 300: 0.86 / 0.87 / 0.87;  650 .. 800: 1.00 / 0.97 / 0.93;  800 .. 1000: 0.99 / 0.97 / 0.98;  1000 .. 2000: 1.02 / 0.99 / 0.98
+//   two     per_cu 800 .. 2000: 1.03 / 0.97 / 0.90;  2000 .. 4000: 1.04 / 1.00 / 0.90
+//   three   per_cu 2000 .. 4000: 1.05 / 1.00 / 0.89;  4000 .. 10,000: 1.03 / 0.93 / 0.89
+//   five    per_cu 4000 .. 10,000: 1.03 / 0.90 / 0.87;  12,000 .. 14,500: - / 1.00 / 0.92;  above: 1.00, chunks of at most 2^16
+//           points do not fit five any more
+// (5 to 8 groups, 800 .. 2000: 8..63 gains 5%, 1..64 loses 1 to 2%.)
+// A batch has at least as many workgroups as groups times spaces, and no freedom to even them out once these fill half of the
+// chip.  One per compute unit over 614 batches, per_cu 20 .. 100 / 100 .. 300 / 300 .. 700 / 700 .. 1200: below 64 of them 0.83 /
+// 0.91 / 0.98 / 1.03, 64 to 127: 0.88 / 0.95 / 1.00 / 1.08, 128 to 255: 1.02 / 1.11 / 1.13 / 1.18, more: 1.07 / 1.07 / 1.09 / 1.14.
+int workgroups_per_cu(int64_t per_cu, int n_groups, int batch)
 {
-    if (per_cu < (batch > 1 ? 700 : 800)) return 1;
-    if (batch > 1 || per_cu < 2000 || per_cu > 12000) return 0;
-    return (int)std::min<int64_t>((per_cu + 600) / 1200, 5);
+    if (batch > 1) return per_cu < 700 && n_groups * batch < kFillWorkgroups / 2 ? 1 : 0;
+    if (per_cu < (n_groups <= 4 ? 1000 : 800)) return 1;
+    if (n_groups <= 4 || (n_groups <= 8 && per_cu < 2000)) return 0;
+    return (int)std::min<int64_t>(std::max<int64_t>((per_cu + 600) / 1200, 2), 5);
 }
 
 int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch, SweepPlan *plan)
@@ -2175,15 +2187,12 @@ int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int3
     const int64_t units = (int64_t)plan->n_groups * batch;
     const int64_t cap = (int64_t)1 << 16;      // points per chunk (the accumulators would allow 2^17)
     plan->chunk_block = -1;
-    // What a slab of 32 points costs: the tiles of its group, and about kSlabCost more for everything else (operand loads,
-    // close calls, labels, log).  `per_cu`: what one wave of a compute unit has to do when the work is spread evenly over the
-    // chip (in this unit, about 0.3 us).
     const int waves = step_threads_of(dp) / 64;
     const int64_t per_round = (int64_t)slab_blocks_of(dp, 1) * 32 * waves;
     int64_t cost = 0;
     for (int gi = 0; gi < plan->n_groups; ++gi) cost += plan->g[gi].n_tiles + kSlabCost;
     const int64_t per_cu = (N + 31) / 32 * cost * batch / (kFillWorkgroups * waves);
-    const int per_cu_wgs = workgroups_per_cu(per_cu, batch);
+    const int per_cu_wgs = workgroups_per_cu(per_cu, plan->n_groups, batch);
     if (per_cu_wgs > 0) {
         // Every group gets chunks of its own length, so that all workgroups take about the same time.  With r rounds of slabs
         // for its waves, a workgroup of group g is busy for r (tiles + kSlabCost): the shortest time is looked for with which
@@ -2220,7 +2229,11 @@ int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int3
         // by side shorter chunks measured 2% shorter launches at 8M x 32)
         const int tp = geo.tile_points;
         const int64_t tiles_total = (N + tp - 1) / tp;
-        int64_t want = std::max<int64_t>(2 * kFillWorkgroups / units, 1);
+        int64_t want = 2 * kFillWorkgroups / units;
+        // More groups times spaces than compute units: rather a few workgroups too many than half of the chip idle in the last
+        // turn, but chunks of 4096 points at least (64 spaces of 65,537 x 16, k 8..63, 448 groups: one chunk of 2^16 points
+        // and one of a single point: 34.3 ms for 8 rounds, two halves 19.1).
+        if (units > kFillWorkgroups) want = std::min((2 * kFillWorkgroups + units - 1) / units, (N + 4095) / 4096);
         if (want > tiles_total) want = tiles_total;
         int64_t chunk_len = ((tiles_total + want - 1) / want) * tp;
         if (chunk_len > cap) chunk_len = cap / tp * tp;

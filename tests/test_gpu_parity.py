@@ -724,6 +724,25 @@ def test_sweep_batched_block_order(rls, orc, batch, N, d, k_min, k_max, iters):
         compare_sweep(orc, X[b], one, ref, k_min, k_max)
 
 
+@pytest.mark.parametrize("batch,N,d,k_min,k_max", [(128, 513, 5, 3, 3), (127, 513, 5, 3, 3), (43, 2049, 16, 8, 31), (42, 2049, 16, 8, 31),
+                                                   (37, 4097, 6, 8, 63), (36, 4095, 6, 8, 63), (37, 65537, 5, 8, 63), (520, 300, 5, 2, 2)])
+def test_sweep_batched_chunk_rule(rls, orc, batch, N, d, k_min, k_max):
+    """Both sides of the rules by which a batch cuts its points: groups times spaces up to half of the compute units (chunks of
+    equal cost per group), up to all of them, and more (one or two chunks per space, of 4096 points at least)."""
+    rng = np.random.default_rng(batch + N)
+    c = rng.uniform(-20, 20, size=(batch, 9, d)).astype(np.float32)
+    X = np.stack([c[b][rng.integers(0, 9, N)] for b in range(batch)]) + rng.standard_normal((batch, N, d), dtype=np.float32)
+    init = rng.integers(0, N, size=(batch, k_max))
+    res = rls.kmeans_sweep_batched(dev(X), k_min, k_max, 2, init_idx=dev(init))
+    lab, cen, J, st = res.labels.cpu(), res.centroids.cpu(), res.inertia.cpu(), res.status.cpu()
+    for b in (0, batch // 2, batch - 1):
+        for k in sorted({k_min, (k_min + k_max) // 2, k_max}):
+            ref = orc.kmeans_sweep(X[b], k, k, 2, init_idx=init[b, :k])
+            at = sum(range(k_min, k)) * d
+            one = rls.SweepResult(k, k, d, lab[b, k - k_min:k - k_min + 1], cen[b, at:at + k * d], J[b, k - k_min:k - k_min + 1], None, st[b:b + 1])
+            compare_sweep(orc, X[b], one, ref, k, k)
+
+
 @pytest.mark.parametrize("N,d", [(769, 5), (24577, 16), (150001, 5), (300007, 13), (600011, 5), (600011, 32), (3200003, 5)])
 def test_sweep_chunks_per_group(rls, orc, N, d):
     """k 1..128 over the sizes at which the step changes how it cuts the points: chunks of equal cost per group, one
