@@ -1342,32 +1342,39 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
         const uint4 *src = reinterpret_cast<const uint4 *>(wsb + a.off_opA + (int64_t)g.tile0 * tile_bytes_of(DP));
         const float *csrc = Cb + (int64_t)grow0 * d;
         const int n_op = g.n_tiles * (tile_bytes_of(DP) / 16), n_cs = real_rows * DP;
-        constexpr int UO = 6, UC = 12;
-        for (int i0 = 0; i0 * TH * UO < n_op || i0 * TH * UC < n_cs; ++i0) {
-            uint4 v[UO];
+        auto stage = [&](auto op_batch, auto cs_batch) {
+            constexpr int UO = decltype(op_batch)::value, UC = decltype(cs_batch)::value;
+            for (int i0 = 0; i0 * TH * UO < n_op || i0 * TH * UC < n_cs; ++i0) {
+                uint4 v[UO];
 #pragma unroll
-            for (int u = 0; u < UO; ++u) v[u] = src[min(tid + (i0 * UO + u) * TH, n_op - 1)];
-            float w[UC];
+                for (int u = 0; u < UO; ++u) v[u] = src[min(tid + (i0 * UO + u) * TH, n_op - 1)];
+                float w[UC];
 #pragma unroll
-            for (int u = 0; u < UC; ++u) {
-                const int e = min(tid + (i0 * UC + u) * TH, n_cs - 1);
-                w[u] = csrc[(e / DP) * d + min(e % DP, d - 1)];
-            }
-            if (!FINAL && i0 == 0) {                     // (while the loads are on their way)
-                for (int e = tid; e < copies * real_rows * (DP + 1); e += TH) sums[e] = 0ull;
-                for (int e = tid; e < copies * real_rows; e += TH) cnts[e] = 0;
-            }
+                for (int u = 0; u < UC; ++u) {
+                    const int e = min(tid + (i0 * UC + u) * TH, n_cs - 1);
+                    w[u] = csrc[(e / DP) * d + min(e % DP, d - 1)];
+                }
+                if (!FINAL && i0 == 0) {                 // (while the loads are on their way)
+                    for (int e = tid; e < copies * real_rows * (DP + 1); e += TH) sums[e] = 0ull;
+                    for (int e = tid; e < copies * real_rows; e += TH) cnts[e] = 0;
+                }
 #pragma unroll
-            for (int u = 0; u < UO; ++u) {
-                const int e = tid + (i0 * UO + u) * TH;
-                if (e < n_op) opA_s[e] = v[u];
-            }
+                for (int u = 0; u < UO; ++u) {
+                    const int e = tid + (i0 * UO + u) * TH;
+                    if (e < n_op) opA_s[e] = v[u];
+                }
 #pragma unroll
-            for (int u = 0; u < UC; ++u) {
-                const int e = tid + (i0 * UC + u) * TH;
-                if (e < n_cs) cs_lds[(e / DP) * (DP + 4) + e % DP] = e % DP < d ? w[u] : 0.0f;
+                for (int u = 0; u < UC; ++u) {
+                    const int e = tid + (i0 * UC + u) * TH;
+                    if (e < n_cs) cs_lds[(e / DP) * (DP + 4) + e % DP] = e % DP < d ? w[u] : 0.0f;
+                }
             }
-        }
+        };
+        // A batch takes the loads it is made for, whatever there is to load: small groups take one of their own (2003 x 8, k = 8: 9.8 -> 8.1 us
+        // a launch; sweeps of one group below 20,000 points 4% shorter), and skipping loads one by one made the compiler wait between
+        // them (65,536 x 16, k 1..64: 4% longer sweeps).
+        if (n_op <= TH && n_cs <= 2 * TH) stage(std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
+        else stage(std::integral_constant<int, 6>{}, std::integral_constant<int, 12>{});
         if (tid < 32) {
             mu_s[tid] = tid < DP ? mean_v : 0.0f;                          // colmean: already negated and scaled
             shift_s[tid] = shift_v;

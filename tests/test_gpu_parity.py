@@ -724,6 +724,16 @@ def test_sweep_batched_block_order(rls, orc, batch, N, d, k_min, k_max, iters):
         compare_sweep(orc, X[b], one, ref, k_min, k_max)
 
 
+@pytest.mark.parametrize("d,k_min,k_max", [(16, 96, 96), (16, 97, 97), (8, 128, 128), (9, 15, 22), (32, 32, 32), (25, 33, 33), (16, 8, 15)])
+def test_sweep_staging_of_small_groups(rls, orc, d, k_min, k_max):
+    """A group whose operands and centroids are one and two loads per thread is staged at once, a larger one in batches: the
+    last sizes of the one and the first of the other."""
+    rng = np.random.default_rng(d + k_max)
+    X = (rng.uniform(-15, 15, size=(11, d))[rng.integers(0, 11, 1500)] + rng.standard_normal((1500, d))).astype(np.float32)
+    res, ref = run_both(rls, orc, X, k_min, k_max, 3, seed=k_min)
+    compare_sweep(orc, X, res, ref, k_min, k_max)
+
+
 @pytest.mark.parametrize("batch,N,d,k_min,k_max", [(128, 513, 5, 3, 3), (127, 513, 5, 3, 3), (43, 2049, 16, 8, 31), (42, 2049, 16, 8, 31),
                                                    (37, 4097, 6, 8, 63), (36, 4095, 6, 8, 63), (37, 65537, 5, 8, 63), (520, 300, 5, 2, 2)])
 def test_sweep_batched_chunk_rule(rls, orc, batch, N, d, k_min, k_max):
