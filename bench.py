@@ -18,7 +18,7 @@ spaces of 262,144 x 16 as well, with their own step counts stated inside).  Each
                 the launch time over the dense fp16 MFMA peak; beside it the fraction of HBM peak the same launch
                 would need if every k read the trajectory on its own (`hbm_equivalent_ratio`, can exceed 1: one read
                 serves up to eight k), the matrix work actually issued, and - from rocprofv3 counters of this
-                library version, else null - the HBM bytes really moved and the vector-issue utilisation
+                very kernel source, else null - the HBM bytes really moved and the vector-issue utilisation
   cpu_baseline  the CPU oracle timed on a bounded sample of the same workload, with the scaling to the sweep's mix of k
   lloyd_step_per_k / early_exit / graph_replay   extra timings outside the timed steps (graph_replay: a short sweep
                 recorded into a HIP graph once and replayed, against the same sweep launched kernel by kernel)
@@ -26,8 +26,10 @@ and the line ends with `hbm_copy_measured`: what a plain 1 GiB device-to-device 
 (bytes read + written), the attainable figure next to the 8 TB/s that the HBM fractions are quoted against.
 """
 import argparse
+import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -43,14 +45,33 @@ VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4.0   # wave64 vector instructions per secon
 # rocprofv3 counters of one lloyd_step_kernel launch (mean over the rounds of a sweep), from the summaries under
 # profiles/ (lloyd_step_<workload>_hbm_counters.md: FETCH_SIZE / WRITE_SIZE in KiB per dispatch with the factors a
 # plain 1 GiB copy gives for each counter; lloyd_step_<workload>_sq_counters.md: SQ_INSTS_VALU).  Valid only for the
-# library version they were taken with; any other version reports null.
+# source they were taken with (step_source_digest); with any other the fields made from them are null.
 COUNTERS = {
     # mean over the 30 rounds of a sweep (first round included, like the launches the events time)
-    "whole_layer": {"version": 133, "fetch_kib": 190758.0, "write_kib": 44509.0, "fetch_scale": 2.0, "write_scale": 1.0,
+    "whole_layer": {"source": "", "fetch_kib": 190758.0, "write_kib": 44509.0, "fetch_scale": 2.0, "write_scale": 1.0,
                     "valu_insts": 1.482e8},
-    "large": {"version": 133, "fetch_kib": 7479002.0, "write_kib": 912506.0, "fetch_scale": 2.0, "write_scale": 1.0,
+    "large": {"source": "", "fetch_kib": 7479002.0, "write_kib": 912506.0, "fetch_scale": 2.0, "write_scale": 1.0,
               "valu_insts": 4.776e9},
 }
+
+
+def step_source_digest() -> str:
+    """What the Lloyd step is compiled from, without comments and white space: a change of the kernel or of its plan
+    changes this, a change of a comment does not."""
+    digest = hashlib.sha256()
+    for name in ("kmeans_lloyd.hip", "rls_internal.h"):
+        with open(os.path.join(ROOT, "paper_1905_12799_amd", "csrc", name)) as fh:
+            code = re.sub(r"//[^\n]*|/\*.*?\*/", "", fh.read(), flags=re.S)
+        digest.update("".join(code.split()).encode())
+    return digest.hexdigest()[:12]
+
+
+def counters_of(workload):
+    """The published counters of a workload if they belong to the kernel that is built here, else None."""
+    hc = COUNTERS.get(workload)
+    return hc if hc is not None and hc["source"] == step_source_digest() else None
+
+
 DEFAULT_STEPS = {"tiny": (50, 5), "mid": (20, 5), "whole_layer": (10, 3), "large": (5, 2), "batched": (5, 2)}
 
 
@@ -206,8 +227,8 @@ def run_workload(name, steps, warmup, args):
                              "the clock the chip holds under this load (valu_issue_frac counts the vector instructions alone, at "
                              "the nominal 2.4 GHz; profiles/lloyd_step_*_sq_counters.md)",
     }
-    hc = COUNTERS.get(w.name)
-    if hc is not None and hc["version"] == rls.version() and want_labels:
+    hc = counters_of(w.name)
+    if hc is not None and want_labels:
         hbm_bytes = (hc["fetch_kib"] * hc["fetch_scale"] + hc["write_kib"] * hc["write_scale"]) * 1024.0
         roofline["traffic"] = hbm_bytes                  # HBM bytes really moved per launch (rocprofv3 FETCH_SIZE, WRITE_SIZE)
         roofline["hbm_traffic_frac"] = hbm_bytes / kernel_s / 1e9 / HBM_PEAK_GBS
@@ -251,7 +272,7 @@ def run_workload(name, steps, warmup, args):
     if not batched and not args.no_graph and not (args.no_per_k and args.no_early_exit) and sweep_ms < 25.0:
         # A sweep enqueues kernels only, so a caller can record it into a HIP graph once and replay it on new rows of the
         # same shape.  Outside the timed steps: the recorded sweep replayed, against the same sweep launched kernel by
-        # kernel (short sweeps are bound by their launches: about 2 (k_max - 1) + 2 rounds + 8 of them).
+        # kernel (short sweeps are bound by their launches: two per round and about twelve more).
         side = torch.cuda.Stream()
         side.wait_stream(main_stream)
         graph = torch.cuda.CUDAGraph()
