@@ -48,10 +48,14 @@ VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4.0   # wave64 vector instructions per secon
 # source they were taken with (step_source_digest); with any other the fields made from them are null.
 COUNTERS = {
     # mean over the 30 rounds of a sweep (first round included, like the launches the events time)
-    "whole_layer": {"source": "", "fetch_kib": 190758.0, "write_kib": 44509.0, "fetch_scale": 2.0, "write_scale": 1.0,
-                    "valu_insts": 1.482e8},
-    "large": {"source": "", "fetch_kib": 7479002.0, "write_kib": 912506.0, "fetch_scale": 2.0, "write_scale": 1.0,
-              "valu_insts": 4.776e9},
+    "mid": {"source": "86e6a5b17b82", "fetch_kib": 8731.5, "write_kib": 11653.3, "fetch_scale": 2.0, "write_scale": 1.0,
+           "valu_insts": 1.165e+07},
+    "whole_layer": {"source": "86e6a5b17b82", "fetch_kib": 186281.9, "write_kib": 44490.2, "fetch_scale": 2.0, "write_scale": 1.0,
+                   "valu_insts": 1.494e+08},
+    "large": {"source": "86e6a5b17b82", "fetch_kib": 7429338.3, "write_kib": 914070.7, "fetch_scale": 2.0, "write_scale": 1.0,
+             "valu_insts": 4.781e+09},
+    "batched": {"source": "86e6a5b17b82", "fetch_kib": 2640160.5, "write_kib": 251775.6, "fetch_scale": 2.0, "write_scale": 1.0,
+               "valu_insts": 7.548e+08},
 }
 
 
