@@ -1715,6 +1715,16 @@ __device__ inline void sum_chunks(const long long *pe, const int *pc, int64_t es
                                   long long &hi, unsigned long long &lo, long long &cnt)
 {
     constexpr int U = 8;
+    if (c_end - c_begin <= 2) {                    // (eight loads for one or two: 44 instead of 37 us for 64 x (262,144 x 16), k 1..32)
+        for (int c = c_begin; c < c_end; ++c) {
+            const long long v = pe[c * estride];
+            const unsigned long long nlo = lo + (unsigned long long)v;
+            hi += (v >> 63) + (nlo < lo ? 1 : 0);
+            lo = nlo;
+            cnt += pc[c * cstride];
+        }
+        return;
+    }
     for (int c0 = c_begin; c0 < c_end; c0 += U) {
         long long v[U];
         int m[U];

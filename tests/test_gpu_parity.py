@@ -724,6 +724,19 @@ def test_sweep_batched_block_order(rls, orc, batch, N, d, k_min, k_max, iters):
         compare_sweep(orc, X[b], one, ref, k_min, k_max)
 
 
+@pytest.mark.parametrize("d", [5, 16, 32])
+@pytest.mark.parametrize("chunks", [1, 4, 8, 9, 16, 17, 24, 25])
+def test_sweep_few_chunks_per_sum(rls, orc, d, chunks):
+    """The centroid kernel's slices of one, two or more chunks each: one group whose chunks are one slab per wave."""
+    per_chunk = 32 * (8 if d == 32 else 12)
+    for N in (chunks * per_chunk, (chunks - 1) * per_chunk + 1):
+        rng = np.random.default_rng(N + d)
+        X = (rng.integers(0, 6, size=(N, d)) * 2.0 + rng.standard_normal((N, d))).astype(np.float32)
+        k = min(3, N)
+        res, ref = run_both(rls, orc, X, k, k, 3, seed=chunks)
+        compare_sweep(orc, X, res, ref, k, k)
+
+
 @pytest.mark.parametrize("d,k_min,k_max", [(16, 96, 96), (16, 97, 97), (8, 128, 128), (9, 15, 22), (32, 32, 32), (25, 33, 33), (16, 8, 15)])
 def test_sweep_staging_of_small_groups(rls, orc, d, k_min, k_max):
     """A group whose operands and centroids are one and two loads per thread is staged at once, a larger one in batches: the
