@@ -12,7 +12,7 @@
 // then meet in LDS, where one slice adds them.  Either way a configuration's leaves are added in fp32 in tree order, so
 // the result does not depend on the launch shape.  (Measured: 2000 x 8, 64 trees of depth 6: 23.9 -> 9.0 us a call with
 // 32 workgroups instead of two; 65,536 x 8, 256 of depth 8: 112 -> 41 us with tiles of 256; leaves in global memory
-// instead of LDS, which is what binds the large ones: 8M x 32, 512 of depth 10: 14.9 -> 11.9 ms.)
+// instead of LDS, which alone bound the large ones: 8M x 32, 512 of depth 10: 14.9 -> 11.9 ms.)
 //
 // A step of the walk is two dependent LDS reads and four vector instructions: the walk keeps the node's LDS
 // address a (node n of a tree at byte b sits at b + 8 n) and moves to child 2n + 1 + c by a <- 2 a + (8 + 8 c - b).
