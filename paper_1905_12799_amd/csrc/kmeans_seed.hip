@@ -38,8 +38,9 @@ __device__ inline double uniform01(uint64_t seed, uint64_t j)
 }
 
 // How long a workgroup of seed_chain_kernel waits for the others before it gives up, in ticks of the 100 MHz clock: 2 ms in
-// its first exchange, which some workgroups may never reach while other streams hold compute units, then 50 ms, since
-// from there on all are running.  A test may change both for the launches of its own host thread.
+// its first exchange, which some workgroups may never reach while other streams hold compute units (beside a tree scoring of 1M x 16
+// that fills the chip the last one arrives after 0.7 to 0.9 ms; giving up costs the chain again, 0.9 ms at 65,536 x 16 and 3.4 at
+// 1M x 16 with 64 centres), then 50 ms, since from there on all are running.  A test may change both for the launches of its own host thread.
 constexpr long long kArriveTicks = 200000;
 constexpr long long kWaitTicks = 5000000;
 thread_local long long t_wait_ticks = -1;          // negative: the two limits above
