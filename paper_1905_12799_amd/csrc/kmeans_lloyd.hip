@@ -77,24 +77,35 @@ __host__ __device__ constexpr int tile_bytes_of(int dp) { return tile_slots_of(d
 // pieces the bias slot wants (their sum, which is the norm cut off below 2^-24 of itself, serves the error bound).
 __host__ __device__ constexpr int prep_slots_of(int dp) { return 2 * ksteps_of(dp); }
 __host__ __device__ constexpr int prep_block_u4_of(int dp) { return prep_slots_of(dp) * 64 + 16; }   // 16-byte units per block
+// Tile lists of an ordered sweep.  A unit is 32 points (64 at d_pad = 32) that follow each other in the order; for every
+// unit, and each of the eight quad slots of a group's tiles, a list names the tiles whose quad in that slot may hold the
+// nearest centroid of one of the unit's points.  16 words per unit and group: eight of first words (one per slot: three tiles,
+// then the length of the longest of the eight lists, or kListAll when one does not fit), eight of second words (four more
+// tiles).  A list that ends before the longest one goes on with the tile of padding rows behind the real ones.
+__host__ __device__ constexpr int unit_blocks_of(int dp) { return dp == 32 ? 2 : 1; }
+constexpr int kListWords = 16, kListHead = 3, kListMax = 7, kListAll = 255;
+constexpr int kListMinTiles = 3, kListMaxTiles = 16;    // groups of fewer tiles meet them all (there is little to leave out), and groups of more
+
 // Moved pairs of the rounds that run on the prepared copy: every wave keeps a ring of records in global memory
 // (point within the chunk, accumulator row of the new label | row of the old label) and works it off 64 records at a time.
 constexpr int kLogCap = 512;                  // records per wave (a slab adds at most 4 x 64; 63 may be left over)
 
 // ---- LDS carve of lloyd_step_kernel (bytes), shared by the planner and the kernel ------------
 struct Carve {
-    int opA, cs, sums, cnts, misc, total;
+    int opA, cs, sums, cnts, rowpos, misc, total;
 };
-__host__ __device__ inline Carve carve_lds(int dp, int d, int n_tiles, int real_rows, int copies)
+__host__ __device__ inline Carve carve_lds(int dp, int d, int n_tiles, int real_rows, int copies, bool ordered)
 {
     Carve c;
     int off = 0;
-    c.opA = off;     off += n_tiles * tile_bytes_of(dp);       // MFMA operand rows of the group (fp16 pieces + bias slot)
+    // MFMA operand rows of the group (fp16 pieces + bias slot); with tile lists a tile of padding rows behind them
+    c.opA = off;     off += (n_tiles + (ordered ? 1 : 0)) * tile_bytes_of(dp);
     c.cs = off;      off += real_rows * (dp + 4) * 4;                   // centroids as given, rows of dp + 4 floats, zero-padded
     // accumulators: `copies` of them side by side (a lane adds to copy lane % copies, which spreads the lanes that
     // hit one cluster of a run with few clusters over several addresses; the copies are summed at the end)
-    c.sums = off;    off += copies * real_rows * (dp + 1) * 8;          // fixed-point sum deltas
+    c.sums = off;    off += (copies * real_rows * (dp + 1) * 8 + 15) / 16 * 16;   // fixed-point sum deltas
     c.cnts = off;    off += (copies * real_rows * 4 + 15) / 16 * 16;    // member count deltas
+    c.rowpos = off;  off += ordered ? (real_rows * 2 + 15) / 16 * 16 : 0;   // places of the centroids among the group's rows
     c.misc = off;    off += 2048;
     c.total = off;
     return c;
@@ -114,6 +125,8 @@ struct StepArgs {
     char *ws;                // workspace base
     int64_t ws_bs;           // bytes per batch element
     int64_t off_colinfo, off_opA, off_cnmax, off_psum, off_pcnt, off_pj, off_losum, off_prev, off_xp, off_log;
+    int64_t off_xs, off_inv, off_centres, off_radius, off_rowpos, off_lists;
+    int32_t ordered;         // 1: operand rows, accumulators and labels of the last round are in the order of the places
     int32_t first_round;     // 1: no point has a label yet (every pair enters a cluster, nothing leaves one)
     int32_t batch;           // spaces swept by the launch
 };
@@ -235,6 +248,26 @@ __device__ inline float wave_min_f32(float v)
     return v;
 }
 
+// sum and largest value over each half-wave, in all of its lanes
+__device__ inline float half_sum_f32(float v)
+{
+    v += __int_as_float(dpp_move<kDppSwap1>(__float_as_int(v)));
+    v += __int_as_float(dpp_move<kDppSwap2>(__float_as_int(v)));
+    v += __int_as_float(dpp_move<kDppHalfMirror>(__float_as_int(v)));
+    v += __int_as_float(dpp_move<kDppMirror>(__float_as_int(v)));
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ inline float half_max_f32(float v)
+{
+    v = fmaxf(v, __int_as_float(dpp_move<kDppSwap1>(__float_as_int(v))));
+    v = fmaxf(v, __int_as_float(dpp_move<kDppSwap2>(__float_as_int(v))));
+    v = fmaxf(v, __int_as_float(dpp_move<kDppHalfMirror>(__float_as_int(v))));
+    v = fmaxf(v, __int_as_float(dpp_move<kDppMirror>(__float_as_int(v))));
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 // The assignment as it is defined, by one whole wave: fp64 direct-form distances sum_l (x_l - c_l)^2, features in
 // rising order, of one point to the k centroids of a run (one or two per lane), then the lexicographic minimum of
 // (distance, index) over the wave.  Every lane returns the winner.  The point arrives as wave-uniform values (read
@@ -350,6 +383,8 @@ __device__ inline int key_index(int t, int a, int i)
     if (S == 4) return 16 * t + 4 * a + i;
     return 32 * t + 4 * a + i;   // S == 8: bit 4 (the half-wave) is added after the tile loop
 }
+// quads of a lane's four that differ in their indices (the others repeat them in another run)
+__host__ __device__ constexpr int index_quads_of(int s) { return s == 1 ? 1 : (s == 2 ? 2 : 4); }
 template <int S>
 __device__ inline int state_of(int a) { return S == 1 ? a : (S == 2 ? (a >> 1) : 0); }
 
@@ -386,15 +421,15 @@ __device__ inline void insert2x2(int a, int b, int &m1, int &m2)
 // fold the 16 results of one 32x32 tile (4 quads of 4 rows) into the per-run states: the two smallest keys
 // (five vector instructions per two distances: two and-or, min3, med3, min).  The second key shows whether the
 // first is a clear winner.
-template <int S, int ST>
-__device__ inline void fold_tile(const floatx16 &acc, const int (&kidx)[16], int mask, int (&m1)[ST], int (&m2)[ST])
+template <int S, int ST, int NKI>
+__device__ inline void fold_tile(const floatx16 &acc, const int (&kidx)[NKI], int mask, int (&m1)[ST], int (&m2)[ST])
 {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int st = state_of<S>(q);
 #pragma unroll
         for (int i = 0; i < 4; i += 2)
-            insert2x2(pack_key(acc[4 * q + i], mask, kidx[4 * q + i]), pack_key(acc[4 * q + i + 1], mask, kidx[4 * q + i + 1]),
+            insert2x2(pack_key(acc[4 * q + i], mask, kidx[(4 * q + i) % NKI]), pack_key(acc[4 * q + i + 1], mask, kidx[(4 * q + i + 1) % NKI]),
                       m1[st], m2[st]);
     }
 }
@@ -415,8 +450,11 @@ struct WaveCtx {
     const int *pow2hi_s;          // LDS: high words of the doubles 2^shift [32]
     const int *wide_s;            // LDS: wide-column flags [32], any at [32]
     const float *cnmax_s;         // LDS: per-run maximum squared norm of the centred centroids [8]
-    const float *X;               // this space's rows
+    const float *X;               // this space's rows (on the prepared copy of an ordered sweep: the rows in that order)
     const uint4 *xp;              // global: prepared copy of this space's points (see prep_block_u4_of)
+    const unsigned short *rowpos; // LDS: place of each of the group's centroids among its rows, or null (places = indices)
+    const int32_t *inv;           // global: place of each point (first round of an ordered sweep), or null
+    const unsigned *lists;        // global: the tile lists of the group's units, or null
     unsigned long long *log;      // global: this wave's ring of moved-pair records [kLogCap]
     int64_t ldx, N;
     int d, k0, n_runs, n_tiles, grow0;
@@ -435,10 +473,12 @@ struct WaveCtx {
 // cache look-ups (which bounds sweeps over few k).
 // PRE: the operands come from the prepared copy; the raw rows are read on demand (not in a pass that sums the loss,
 // which needs every row, and not in the first round, where every row enters a cluster).
-template <int DP, int S, bool FINAL, bool TRACE, bool VEC, bool PRE>
+template <int DP, int S, bool FINAL, bool TRACE, bool VEC, bool PRE, bool ORD>
 __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
 {
     static_assert(!PRE || (!FINAL && !TRACE), "the prepared copy serves the plain assign + update pass only");
+    static_assert(!ORD || (PRE && VEC), "the ordered copy is a prepared one, with rows of DP floats");
+    const int64_t ldx = ORD ? DP : c.ldx;
     constexpr int NB = slab_blocks_of(DP, S);       // blocks of 32 points per wave and slab
     // with 2 blocks at d_pad = 32 the rows of the next slab are requested after the tile loop, when the operand
     // registers are free again, instead of before it
@@ -453,6 +493,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
     constexpr int NM = 3 * NK + 1;                  // MFMAs per tile block
     constexpr int VPER = (40 + 16 + NM - 1) / NM;   // vector ops to slot in after each MFMA of a chain
     constexpr bool LOSS = FINAL || TRACE;
+    constexpr int NKI = 4 * index_quads_of(S);      // indices of a tile's rows that differ for this lane
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 31, hl = lane >> 5;
     const int d = c.d;
@@ -475,10 +516,10 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
     constexpr int NP = prep_slots_of(DP);            // operand slots per lane and block in the prepared copy
     uint4 pnext[PRE ? NB : 1][PRE ? NP : 1];          // PRE: the operand slots of the slab being fetched
     uint2 nnext[PRE ? NB : 1];                        // PRE: its norm entries
-    const unsigned ldx32 = (unsigned)c.ldx;          // checked on the host: 64 rows of ldx floats fit 32 bits
+    const unsigned ldx32 = (unsigned)ldx;          // checked on the host: 64 rows of ldx floats fit 32 bits
     // this lane's clamped feature offsets (fixed for the launch; with the prepared copy they are worked out where
     // a row is read, which is rare, instead of being kept in registers)
-    auto feat_off = [&](int s) { return (unsigned)(VEC ? min(f0 + (s & ~3), d - 4) + (s & 3) : min(f0 + s, d - 1)); };
+    auto feat_off = [&](int s) { return (unsigned)(ORD ? f0 + s : (VEC ? min(f0 + (s & ~3), d - 4) + (s & 3) : min(f0 + s, d - 1))); };
     unsigned foff[PRE ? 1 : H];
     if constexpr (!PRE) {
 #pragma unroll
@@ -501,26 +542,44 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
     for (int pb = 0; pb < NB; ++pb) oldn[pb] = 0xffffffffu;
     unsigned char *const prev_chunk = c.prev + c.chunk_begin * R;          // the chunk's first label byte
     const unsigned chunk_pts = (unsigned)(c.chunk_end - c.chunk_begin);   // points of the chunk (at most 2^17)
-    auto load_labels = [&](int64_t slab_base, unsigned li) -> unsigned {
-        const unsigned pt = (unsigned)(slab_base - c.chunk_begin) + li;   // point within the chunk
+    // tile lists: a lane feeds row lane % 32 of the tiles, which belongs to this slot of theirs
+    const unsigned a_slot = (unsigned)(((lane >> 3) & 3) + (lane & 4));
+    constexpr int kUnitShift = unit_blocks_of(DP) == 2 ? 6 : 5;
+    const unsigned *const lists = ORD && c.lists ? c.lists + (c.chunk_begin >> kUnitShift) * kListWords : nullptr;
+    const uint4 *const xp_chunk = PRE ? c.xp + (c.chunk_begin >> 5) * prep_block_u4_of(DP) : nullptr;    // chunks start on a block boundary
+    unsigned listn = 0u, list_moren = 0u;            // the list of the slab being fetched
+    int placen[PRE || FINAL ? 1 : NB];               // places of the points being fetched (first round of an ordered sweep)
+    auto load_labels = [&](unsigned pt) -> unsigned {                    // of a point within the chunk
         return (unsigned)*reinterpret_cast<const LabWord *>(prev_chunk + (pt * (unsigned)R + lab_off));
     };
-    auto fetch = [&](int64_t slab_base) {
-        const float *Xs = c.X + slab_base * c.ldx;
-        const unsigned last = (unsigned)min((int64_t)(SLAB_ - 1), c.chunk_end - 1 - slab_base);
+    auto fetch = [&](int slab) {
+        const unsigned first = (unsigned)slab * SLAB_;                   // the slab's first point within the chunk
+        const unsigned last = min((unsigned)(SLAB_ - 1), chunk_pts - 1u - first);
         if constexpr (PRE) {
-            const int64_t blk0 = slab_base >> 5, blk_last = (c.chunk_end - 1) >> 5;     // chunks start on a block boundary
+            const unsigned blk_last = (chunk_pts - 1u) >> 5;
 #pragma unroll
             for (int pb = 0; pb < NB; ++pb) {
-                const uint4 *bp = c.xp + min(blk0 + pb, blk_last) * prep_block_u4_of(DP);
+                const uint4 *bp = xp_chunk + min((first >> 5) + pb, blk_last) * (unsigned)prep_block_u4_of(DP);
 #pragma unroll
                 for (int sl = 0; sl < NP; ++sl) pnext[pb][sl] = bp[sl * 64 + lane];
                 nnext[pb] = reinterpret_cast<const uint2 *>(bp + NP * 64)[n];
                 const unsigned li = min((unsigned)(pb * 32 + n), last);
-                oldn[pb] = load_labels(slab_base, li);
+                oldn[pb] = load_labels(first + li);
+            }
+            if constexpr (ORD) {
+                if (lists) {
+                    // (a scalar base and a lane offset that is not folded into it: one register instead of two through the loop)
+                    const unsigned *const at = lists + (first >> kUnitShift) * kListWords;
+                    unsigned slot = a_slot;
+                    asm volatile("" : "+v"(slot));
+                    listn = at[slot];
+                    list_moren = at[slot + 8];
+                }
             }
             return;
         }
+        const int64_t slab_base = c.chunk_begin + first;
+        const float *Xs = c.X + slab_base * ldx;
 #pragma unroll
         for (int pb = 0; pb < NB; ++pb) {
             const unsigned li = min((unsigned)(pb * 32 + n), last);
@@ -536,7 +595,10 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 for (int s = 0; s < H; ++s) xnext[pb][s] = Xs[ro + foff[s]];
             }
             // labels these (point, run) pairs had in the previous round, 0xff before the first one
-            if (!FINAL) oldn[pb] = load_labels(slab_base, li);
+            if constexpr (!FINAL && !PRE) {
+                if (c.inv) placen[pb] = c.inv[slab_base + li];       // (first round: there are none yet)
+                else oldn[pb] = load_labels(first + li);
+            }
         }
     };
     // the outstanding loads of fetch() have to be complete here
@@ -549,15 +611,19 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                     asm volatile("" : "+v"(pnext[pb][sl].x), "+v"(pnext[pb][sl].y), "+v"(pnext[pb][sl].z), "+v"(pnext[pb][sl].w));
                 asm volatile("" : "+v"(nnext[pb].x), "+v"(nnext[pb].y));
             }
+            if constexpr (ORD) asm volatile("" : "+v"(listn), "+v"(list_moren));
         } else {
 #pragma unroll
             for (int pb = 0; pb < NB; ++pb)
 #pragma unroll
                 for (int s = 0; s < H; ++s) asm volatile("" : "+v"(xnext[pb][s]));
         }
-        if (!FINAL) {
+        if constexpr (!FINAL) {
 #pragma unroll
-            for (int pb = 0; pb < NB; ++pb) asm volatile("" : "+v"(oldn[pb]));
+            for (int pb = 0; pb < NB; ++pb) {
+                asm volatile("" : "+v"(oldn[pb]));
+                if constexpr (!PRE) asm volatile("" : "+v"(placen[pb]));
+            }
         }
     };
     // The chunk is handed out in slabs of SLAB points: one per wave statically, the rest from a counter in
@@ -578,12 +644,15 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         return __builtin_amdgcn_readfirstlane(v);
     };
     int cur = wave;
-    fetch(c.chunk_begin + (int64_t)min(cur, n_slabs - 1) * SLAB);
+    fetch(min(cur, n_slabs - 1));
     const bool any_wide = c.wide_s[32] != 0;
     // part of the error bound that belongs to a run (the centroids' largest squared norm), per run this lane owns
     float tol_run[ST];
 #pragma unroll
     for (int st = 0; st < ST; ++st) tol_run[st] = c.eps_a * c.cnmax_s[S == 8 ? 0 : hl * ST + st] + kTolFloor;
+    // accumulator rows of this lane's runs: run rl of the group begins at row rl k0 + rl (rl - 1) / 2
+    const unsigned rl0 = S == 8 ? 0u : (unsigned)(hl * ST);
+    const unsigned row0 = rl0 * (unsigned)c.k0 + rl0 * (rl0 - 1u) / 2u, row_step = (unsigned)c.k0 + rl0;
     double jown[ST];                                 // loss sums of the runs this lane owns
 #pragma unroll
     for (int st = 0; st < ST; ++st) jown[st] = 0.0;
@@ -604,21 +673,87 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         unsigned long long rec = 0ull;
         if (lane < nrec) rec = __hip_atomic_load(&c.log[(unsigned)(log_head + lane) & (kLogCap - 1)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        const int fq = FPL * (lane % LPR), g = lane / LPR;     // this lane's first feature, its record within a step
+        // (made opaque: what follows from the lane is worked out here, not kept in registers through the tile loop)
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        const int fq = FPL * (ln % LPR), g = ln / LPR;     // this lane's first feature, its record within a step
         // this lane's feature columns in its copy of the accumulators (the lane group picks the copy)
         const int cp = g & (c.copies - 1);
         unsigned long long *const scol = c.sums + (int64_t)cp * c.real_rows * (DP + 1) + fq;
-        const float *const xcol = c.X + c.chunk_begin * c.ldx + fq;
+        const float *const xcol = c.X + c.chunk_begin * ldx + fq;
         // member counts: the lane that holds a record moves its one member, once per flush
         if (lane < nrec) {
-            int *const ccol = c.cnts + (lane & (c.copies - 1)) * c.real_rows;
+            int *const ccol = c.cnts + (ln & (c.copies - 1)) * c.real_rows;
             const int nrow = (int)(((unsigned)rec >> 17) & 0xfffu), orow = (int)((unsigned)(rec >> 32) & 0xffffu);
             atomicAdd(ccol + nrow, 1);
-            if (orow != 0xffff) atomicAdd(ccol + orow, -1);
+            atomicAdd(ccol + orow, -1);                  // (a logged pair had a label: the first round logs nothing)
         }
-        int pow2hi[FPL];
+        if (!any_wide) {
+            // Every lane takes its features in an order of its own, feature j ^ (g mod FPL) in step j: neighbouring records move
+            // between the same clusters more often than not (always where the points lie in spatial order), and the lanes of one
+            // instruction would queue up at one address.  The quads are swapped by their addresses, the features inside a quad in
+            // registers.  All d_pad features are moved: past the last one they are zeros, and nobody reads those sums.
+            const int swz = g & (FPL - 1);
+            auto order4 = [&](auto &v0, auto &v1, auto &v2, auto &v3) {
+                const bool s1 = swz & 1, s2 = swz & 2;
+                auto a0 = s1 ? v1 : v0, a1 = s1 ? v0 : v1, a2 = s1 ? v3 : v2, a3 = s1 ? v2 : v3;
+                v0 = s2 ? a2 : a0; v1 = s2 ? a3 : a1; v2 = s2 ? a0 : a2; v3 = s2 ? a1 : a3;
+            };
+            const int q0 = FPL == 8 ? (swz & 4) : 0;             // first float of the quad that is taken first
+            int pow2hi[FPL];
 #pragma unroll
-        for (int j = 0; j < FPL; ++j) pow2hi[j] = c.pow2hi_s[fq + j];
+            for (int h = 0; h < FPL / 4; ++h) {
+                const int4 v = *reinterpret_cast<const int4 *>(c.pow2hi_s + fq + ((4 * h) ^ q0));
+                pow2hi[4 * h + 0] = v.x; pow2hi[4 * h + 1] = v.y; pow2hi[4 * h + 2] = v.z; pow2hi[4 * h + 3] = v.w;
+                order4(pow2hi[4 * h], pow2hi[4 * h + 1], pow2hi[4 * h + 2], pow2hi[4 * h + 3]);
+            }
+            for (int s0 = 0; s0 < STEPS && s0 * RPS < nrec; s0 += BATCH) {
+                unsigned lo[BATCH], hi[BATCH];
+                float xv[BATCH][FPL];
+#pragma unroll
+                for (int u = 0; u < BATCH; ++u) {
+                    const int src = (s0 + u) * RPS + g;
+                    lo[u] = (unsigned)__shfl((int)(unsigned)rec, src, 64);
+                    hi[u] = (unsigned)__shfl((int)(unsigned)(rec >> 32), src, 64);
+                    const bool ok = src < nrec;
+                    const float *const row = xcol + (int64_t)(lo[u] & 0x1ffffu) * ldx;
+#pragma unroll
+                    for (int h = 0; h < FPL / 4; ++h) {
+                        const int f = (4 * h) ^ q0;
+                        float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                        if (VEC) {
+                            if (ok && (ORD || fq + f < d)) v = *reinterpret_cast<const float4 *>(row + f);     // d is a multiple of four here
+                        } else if (ok) {
+                            if (fq + f + 0 < d) v.x = row[f + 0];
+                            if (fq + f + 1 < d) v.y = row[f + 1];
+                            if (fq + f + 2 < d) v.z = row[f + 2];
+                            if (fq + f + 3 < d) v.w = row[f + 3];
+                        }
+                        xv[u][4 * h + 0] = v.x; xv[u][4 * h + 1] = v.y; xv[u][4 * h + 2] = v.z; xv[u][4 * h + 3] = v.w;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < BATCH; ++u) {
+                    const int src = (s0 + u) * RPS + g;
+                    if (src < nrec) {
+                        unsigned long long *const srow_n = scol + ((lo[u] >> 17) & 0xfffu) * (DP + 1);
+                        unsigned long long *const srow_o = scol + (hi[u] & 0xffffu) * (DP + 1);
+#pragma unroll
+                        for (int h = 0; h < FPL / 4; ++h) order4(xv[u][4 * h], xv[u][4 * h + 1], xv[u][4 * h + 2], xv[u][4 * h + 3]);
+#pragma unroll
+                        for (int j = 0; j < FPL; ++j) {
+                            const unsigned long long v = fixed_biased(xv[u][j], pow2hi[j]);
+                            const int at = j ^ swz;
+                            atomicAdd(srow_n + at, v);
+                            __hip_atomic_fetch_sub(srow_o + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        }
+                    }
+                }
+            }
+            log_head += nrec;
+            return;
+        }
+        // some column has bits below its grid
         for (int s0 = 0; s0 < STEPS && s0 * RPS < nrec; s0 += BATCH) {
             unsigned lo[BATCH], hi[BATCH];
             float xv[BATCH][FPL];
@@ -628,7 +763,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 lo[u] = (unsigned)__shfl((int)(unsigned)rec, src, 64);
                 hi[u] = (unsigned)__shfl((int)(unsigned)(rec >> 32), src, 64);
                 const bool ok = src < nrec;
-                const float *const row = xcol + (int64_t)(lo[u] & 0x1ffffu) * c.ldx;
+                const float *const row = xcol + (int64_t)(lo[u] & 0x1ffffu) * ldx;
                 if (VEC) {
 #pragma unroll
                     for (int h = 0; h < FPL / 4; ++h) {
@@ -651,15 +786,14 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
 #pragma unroll
                     for (int j = 0; j < FPL; ++j) {
                         if (fq + j >= d) continue;
-                        const unsigned long long v = any_wide ? (unsigned long long)to_fixed(xv[u][j], c.shift_s[fq + j]) + kFixBias
-                                                              : fixed_biased(xv[u][j], pow2hi[j]);
+                        const unsigned long long v = (unsigned long long)to_fixed(xv[u][j], c.shift_s[fq + j]) + kFixBias;
                         atomicAdd(srow_n + j, v);
-                        if (orow != 0xffff) __hip_atomic_fetch_sub(srow_o + j, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        if (any_wide && c.wide_s[fq + j] != 0) {
+                        __hip_atomic_fetch_sub(srow_o + j, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        if (c.wide_s[fq + j] != 0) {
                             // bits below the grid of a wide column go to a global integer accumulator (rare)
                             const long long low = fixed_low(xv[u][j], c.shift_s[fq + j]);
                             if (low != 0) {
-                                if (orow != 0xffff) atomicAdd(reinterpret_cast<unsigned long long *>(&c.losum[(int64_t)(c.grow0 + orow) * d + fq + j]), (unsigned long long)(-low));
+                                atomicAdd(reinterpret_cast<unsigned long long *>(&c.losum[(int64_t)(c.grow0 + orow) * d + fq + j]), (unsigned long long)(-low));
                                 atomicAdd(reinterpret_cast<unsigned long long *>(&c.losum[(int64_t)(c.grow0 + nrow) * d + fq + j]), (unsigned long long)low);
                             }
                         }
@@ -702,6 +836,22 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         float xn[NB];
         int m1[NB][ST], m2[NB][ST];
         unsigned oldl[NB];                // labels in the previous round, one byte per run of this lane
+        int place[PRE || FINAL ? 1 : NB];
+        if constexpr (!PRE && !FINAL) {
+#pragma unroll
+            for (int pb = 0; pb < NB; ++pb) place[pb] = placen[pb];
+        }
+        // the tiles this slab meets: all of them in order, or those of its unit's list - this lane's slot meets its own ones
+        const unsigned list = listn, list_more = list_moren;
+        bool listed = false;
+        int n_it = c.n_tiles;
+        if constexpr (ORD) {
+            if (lists) {
+                const int len = __builtin_amdgcn_readfirstlane((int)(list >> 24));
+                listed = len != kListAll;
+                if (listed) n_it = len;
+            }
+        }
         auto old_of = [&](int pb, int st) -> int { return (int)((oldl[pb] >> (8 * st)) & 0xffu); };
         if constexpr (PRE) {
 #pragma unroll
@@ -748,15 +898,22 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         // The rows and previous labels of the next slab are asked for now and only needed when that slab starts, a
         // whole slab of work away.  Always issued - for the last slab it re-reads that slab - so that the number
         // of requests in flight is the same on every path.
-        if (!LATE_FETCH) fetch(c.chunk_begin + (int64_t)min(nxt, n_slabs - 1) * SLAB);
+        if (!LATE_FETCH) fetch(min(nxt, n_slabs - 1));
 
         // ---- distances tile by tile; the results of one block are folded while the matrix pipeline runs the next
         // (the tile loop is written out twice so that the operand buffers and accumulators alternate by name
         // instead of being copied)
         uint4 a_even[NS], a_odd[NS];
+        // operands of step t: tile t, or the tile that is next in the list of this lane's slot
         auto load_a = [&](uint4 (&dst)[NS], int t) {
+            unsigned at = (unsigned)t * (NS * 64);
+            if constexpr (ORD) {
+                const unsigned word = t < kListHead ? list : list_more;
+                const unsigned tile = listed ? (word >> (8 * (t < kListHead ? t : t - kListHead))) & 255u : (unsigned)t;
+                at = __umul24(tile, NS * 64);
+            }
 #pragma unroll
-            for (int sl = 0; sl < NS; ++sl) dst[sl] = opA_s[(t * NS + sl) * 64 + lane];
+            for (int sl = 0; sl < NS; ++sl) dst[sl] = opA_s[at + (unsigned)(sl * 64 + lane)];
         };
         load_a(a_even, 0);
         if constexpr (NB == 1) {
@@ -765,28 +922,28 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
             // and the two accumulators alternate by name.  The order is pinned: left to itself the compiler folds first
             // and then issues the chain into the same registers, and nothing of the wave overlaps.
             floatx16 acc_a, acc_b = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};     // (acc_b: never read before the second tile writes it)
-            int kidx_prev[16];
+            int kidx_prev[NKI];
             // `init`: the first tile of a slab - the first two keys of a run start its pair of smallest keys outright
             // (no sentinel values to set up and compare against)
-            auto fold_quad = [&](const floatx16 &acc, const int (&kidx)[16], int q, auto init) {
+            auto fold_quad = [&](const floatx16 &acc, const int (&kidx)[NKI], int q, auto init) {
                 const int st = state_of<S>(q);
                 const bool starts = decltype(init)::value && (S == 1 || (S == 2 && (q & 1) == 0) || (S >= 4 && q == 0));
-                const int ka = pack_key(acc[4 * q], mask, kidx[4 * q]), kb = pack_key(acc[4 * q + 1], mask, kidx[4 * q + 1]);
+                const int ka = pack_key(acc[4 * q], mask, kidx[(4 * q) % NKI]), kb = pack_key(acc[4 * q + 1], mask, kidx[(4 * q + 1) % NKI]);
                 if (starts) {
                     m1[0][st] = min(ka, kb);
                     m2[0][st] = max(ka, kb);
                 } else {
                     insert2x2(ka, kb, m1[0][st], m2[0][st]);
                 }
-                insert2x2(pack_key(acc[4 * q + 2], mask, kidx[4 * q + 2]), pack_key(acc[4 * q + 3], mask, kidx[4 * q + 3]),
+                insert2x2(pack_key(acc[4 * q + 2], mask, kidx[(4 * q + 2) % NKI]), pack_key(acc[4 * q + 3], mask, kidx[(4 * q + 3) % NKI]),
                           m1[0][st], m2[0][st]);
             };
             // `fold`: 0 nothing to fold (first tile), 1 the tile before is the slab's first, 2 any later tile
             auto tile_step = [&](const uint4 (&a_cur)[NS], uint4 (&a_nxt)[NS], int t, auto fold, floatx16 &acc_new, const floatx16 &acc_old) {
-                load_a(a_nxt, t + 1 < c.n_tiles ? t + 1 : t);
-                int kidx[16];
+                load_a(a_nxt, t + 1 < n_it ? t + 1 : t);
+                int kidx[NKI];
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
+                for (int e = 0; e < NKI; ++e) {
                     kidx[e] = key_index<S>(t, e >> 2, e & 3);
                     asm("" : "+s"(kidx[e]));
                 }
@@ -815,23 +972,23 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 if (kFold) fold_quad(acc_old, kidx_prev, 3, Init{});
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int e = 0; e < 16; ++e) kidx_prev[e] = kidx[e];
+                for (int e = 0; e < NKI; ++e) kidx_prev[e] = kidx[e];
             };
             using NoFold = std::integral_constant<int, 0>;
             using FoldFirst = std::integral_constant<int, 1>;
             using FoldLater = std::integral_constant<int, 2>;
             tile_step(a_even, a_odd, 0, NoFold{}, acc_a, acc_b);
-            if (c.n_tiles == 1) {
+            if (n_it == 1) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) fold_quad(acc_a, kidx_prev, q, std::true_type{});
             } else {
                 tile_step(a_odd, a_even, 1, FoldFirst{}, acc_b, acc_a);
                 int t = 2;
-                for (; t + 2 <= c.n_tiles; t += 2) {
+                for (; t + 2 <= n_it; t += 2) {
                     tile_step(a_even, a_odd, t, FoldLater{}, acc_a, acc_b);
                     tile_step(a_odd, a_even, t + 1, FoldLater{}, acc_b, acc_a);
                 }
-                if (t < c.n_tiles) {
+                if (t < n_it) {
                     tile_step(a_even, a_odd, t, FoldLater{}, acc_a, acc_b);
                     fold_tile<S, ST>(acc_a, kidx_prev, mask, m1[0], m2[0]);
                 } else {
@@ -840,14 +997,14 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
             }
         } else {
         floatx16 acc_prev;                 // results of the block before the current one, folded one block late
-            int kidx_old[16];
+            int kidx_old[NKI];
             // `first`: the very first block of the slab has no block before it to fold
             auto tile_step = [&](const uint4 (&a_cur)[NS], uint4 (&a_nxt)[NS], int t, auto first) {
-                load_a(a_nxt, t + 1 < c.n_tiles ? t + 1 : t);
+                load_a(a_nxt, t + 1 < n_it ? t + 1 : t);
                 // per-row key indices of this tile as opaque scalars (one scalar operand per and-or)
-                int kidx[16];
+                int kidx[NKI];
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
+                for (int e = 0; e < NKI; ++e) {
                     kidx[e] = key_index<S>(t, e >> 2, e & 3);
                     asm("" : "+s"(kidx[e]));
                 }
@@ -875,25 +1032,69 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                     acc_prev = acc;
                 }
 #pragma unroll
-                for (int e = 0; e < 16; ++e) kidx_old[e] = kidx[e];
+                for (int e = 0; e < NKI; ++e) kidx_old[e] = kidx[e];
             };
             {
                 tile_step(a_even, a_odd, 0, std::true_type{});
                 int t = 1;
-                for (; t + 2 <= c.n_tiles; t += 2) {
+                for (; t + 2 <= n_it; t += 2) {
                     tile_step(a_odd, a_even, t, std::false_type{});
                     tile_step(a_even, a_odd, t + 1, std::false_type{});
                 }
-                if (t < c.n_tiles) tile_step(a_odd, a_even, t, std::false_type{});
+                if (t < n_it) tile_step(a_odd, a_even, t, std::false_type{});
             }
             fold_tile<S, ST>(acc_prev, kidx_old, mask, m1[NB - 1], m2[NB - 1]);
         }
-        if (LATE_FETCH) fetch(c.chunk_begin + (int64_t)min(nxt, n_slabs - 1) * SLAB);
+        if constexpr (ORD) {
+            // The keys hold steps of the lists: the step becomes the tile that the winner's slot met there.  (The second
+            // key's index is not used.)
+            if (listed) {
+                // the words of this lane's slots 4 hl .. 4 hl + 3, from lanes that feed them
+                auto slots = [&](unsigned w, unsigned (&out)[4]) {
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) out[a] = (unsigned)__builtin_amdgcn_ds_bpermute(16 * hl + 32 * a, (int)w);
+                };
+                unsigned own[4];
+                slots(list, own);
+                constexpr int kStepShift = S == 1 ? 2 : (S == 2 ? 3 : (S == 4 ? 4 : 5));
+                constexpr int kStepMask = (127 >> kStepShift) << kStepShift;
+                // the word of the slot that a run's key came from (selects by bit masks: an index would put the words in memory)
+                auto either = [](unsigned w0, unsigned w1, int key, int bit) { return w0 ^ ((w0 ^ w1) & (0u - (((unsigned)key >> bit) & 1u))); };
+                auto pick = [&](const unsigned (&w)[4], int st, int key) -> unsigned {
+                    if (S == 1) return w[st];
+                    if (S == 2) return st == 0 ? either(w[0], w[1], key, 2) : either(w[2], w[3], key, 2);
+                    return either(either(w[0], w[1], key, 2), either(w[2], w[3], key, 2), key, 3);
+                };
+                if (n_it <= kListHead) {
+#pragma unroll
+                    for (int pb = 0; pb < NB; ++pb)
+#pragma unroll
+                        for (int st = 0; st < ST; ++st) {
+                            const int key = m1[pb][st];
+                            const unsigned step = ((unsigned)key & kStepMask) >> kStepShift;
+                            m1[pb][st] = (key & ~kStepMask) | (int)(((pick(own, st, key) >> (8 * step)) & 255u) << kStepShift);
+                        }
+                } else {
+                    unsigned more[4];
+                    slots(list_more, more);
+#pragma unroll
+                    for (int pb = 0; pb < NB; ++pb)
+#pragma unroll
+                        for (int st = 0; st < ST; ++st) {
+                            const int key = m1[pb][st];
+                            const int step = (key & kStepMask) >> kStepShift;
+                            const unsigned w = step < kListHead ? pick(own, st, key) : pick(more, st, key);
+                            m1[pb][st] = (key & ~kStepMask) | (int)(((w >> (8 * (step < kListHead ? step : step - kListHead))) & 255u) << kStepShift);
+                        }
+                }
+            }
+        }
+        if (LATE_FETCH) fetch(min(nxt, n_slabs - 1));
 
         // ---- labels, close calls, sums
         constexpr int NBST = NB * ST;               // (block, run) pairs a lane owns
         // this lane's points within the chunk, and whether they exist (the last slab of a chunk may be ragged)
-        const unsigned pt0 = (unsigned)(base - c.chunk_begin);
+        const unsigned pt0 = (unsigned)cur * SLAB;
         unsigned ptl[NB];
         bool pvalid[NB];
 #pragma unroll
@@ -933,7 +1134,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 any_close = any_close || closeb[pb][st];
             }
         }
-        if (__ballot(any_close) != 0ull) {
+        if (__builtin_amdgcn_ballot_w64(any_close) != 0ull) {
 #pragma unroll
             for (int pb = 0; pb < NB; ++pb)
 #pragma unroll
@@ -944,7 +1145,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         // data ties exactly) is settled by the whole wave with the exact arithmetic over the run.  The point's row is
         // read out of the registers of the two lanes that hold its halves.
         auto settle_close_calls = [&](const float (&xr)[NB][HP]) {
-            unsigned long long todo = __ballot(pend != 0u);
+            unsigned long long todo = __builtin_amdgcn_ballot_w64(pend != 0u);
             while (todo) {
                 const int src = __ffsll((long long)todo) - 1;
                 const unsigned sbits = (unsigned)__builtin_amdgcn_readlane((int)pend, src);
@@ -961,14 +1162,18 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                     xs[s] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src & 31));
                     xs[H + s] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), (src & 31) + 32));
                 }
-                const int arg = exact_argmin_wave<DP>(xs, crun, CS, c.k0 + srl);
+                int arg = exact_argmin_wave<DP>(xs, crun, CS, c.k0 + srl);
+                if constexpr (!FINAL && (ORD || !PRE)) {
+                    const int rowbase = srl * c.k0 + srl * (srl - 1) / 2;
+                    if (ORD || c.rowpos) arg = (int)c.rowpos[rowbase + arg] - rowbase;
+                }
                 if (lane == src) {
                     pend &= pend - 1u;
 #pragma unroll
                     for (int i = 0; i < NBST; ++i)
                         if (i == idx) m1[i / ST][i % ST] = arg;
                 }
-                todo = __ballot(pend != 0u);
+                todo = __builtin_amdgcn_ballot_w64(pend != 0u);
             }
         };
         if constexpr (PRE) {
@@ -977,7 +1182,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
             // whose label changed: those are read when the wave works off its log of moved pairs.)  Loads, wait and
             // scans sit in one branch, so that a slab without close calls never waits on the memory counter here: what
             // is in flight then are the operands of the next slab, wanted a whole slab later.
-            if (__ballot(pend != 0u) != 0ull) {
+            if (__builtin_amdgcn_ballot_w64(pend != 0u) != 0ull) {
                 unsigned need = pend;
                 need |= xchg32(need);
                 float xr[NB][HP];
@@ -985,7 +1190,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 for (int pb = 0; pb < NB; ++pb)
 #pragma unroll
                     for (int s = 0; s < HP; ++s) xr[pb][s] = 0.0f;
-                const float *Xs = c.X + base * c.ldx;
+                const float *Xs = c.X + base * ldx;
                 // (the row index is made opaque here so that the offsets below are worked out on the spot: hoisted out
                 // of the slab loop they would sit in registers, or in spill slots, through the tile loop)
                 unsigned nrow = (unsigned)n;
@@ -1004,7 +1209,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
 #pragma unroll
                             for (int s = 0; s < H; ++s) xr[pb][s] = Xs[ro + feat_off(s)];
                         }
-                        if (d < DP) {
+                        if (!ORD && d < DP) {                    // (the ordered copy's rows are padded with zeros)
 #pragma unroll
                             for (int s = 0; s < H; ++s)
                                 if (s >= nf) xr[pb][s] = 0.0f;
@@ -1042,11 +1247,11 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
             diffw[pb] = 0u;
             if (!FINAL) diffw[pb] = pvalid[pb] ? ((w ^ oldl[pb]) & actmask) : 0u;
         }
-        if (!FINAL) {
+        if constexpr (!FINAL && !PRE) {
             bool any = false;
 #pragma unroll
             for (int pb = 0; pb < NB; ++pb) any = any || diffw[pb] != 0u;
-            if (__ballot(any) != 0ull) {
+            if (__builtin_amdgcn_ballot_w64(any) != 0ull) {
 #pragma unroll
                 for (int pb = 0; pb < NB; ++pb)
 #pragma unroll
@@ -1057,28 +1262,36 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         if constexpr (PRE) {
             // Exact sums, later: the moved pairs go into this wave's log; 64 records at a time are worked off below.
             static_assert(64 * NBST + 63 <= kLogCap, "a slab's records and what an earlier flush left over must fit the ring");
+            unsigned any_diff = 0u;
+#pragma unroll
+            for (int pb = 0; pb < NB; ++pb) any_diff |= diffw[pb];
+            if (__builtin_amdgcn_ballot_w64(any_diff != 0u) != 0ull) {
 #pragma unroll
             for (int i = 0; i < NBST; ++i) {
-                const bool has = (mv >> i) & 1u;
-                const unsigned long long bal = __ballot(has);
+                const bool has = ((diffw[i / ST] >> (8 * (i % ST))) & 0xffu) != 0u;
+                const unsigned long long bal = __builtin_amdgcn_ballot_w64(has);
                 if (bal != 0ull) {
                     const int pb = i / ST, st = i % ST;
-                    const unsigned rl = S == 8 ? 0u : (unsigned)(hl * ST + st);
                     const unsigned pos = (unsigned)log_tail +
                                          __builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
                     if (has) {
                         // the record names the point and the two accumulator rows (within the group) outright, so
                         // that working it off takes no arithmetic on runs and labels
                         const unsigned pt = ptl[pb];                                                       // below 2^17
-                        const unsigned rowbase = rl * (unsigned)c.k0 + rl * (rl - 1u) / 2u;
+                        // the run's first row: row0 of this lane's first run, and k0 + rl0 + .. of them per run in between
+                        // (put together here: a row per run would sit in registers through the tile loop)
+                        unsigned step = row_step;
+                        asm volatile("" : "+v"(step));
+                        const unsigned rowbase = row0 + (unsigned)st * step + (unsigned)(st * (st - 1) / 2);
                         const unsigned lo = pt | ((rowbase + (unsigned)(m1[pb][st] & 127)) << 17);         // rows: below 2^12
-                        const unsigned hi = old_of(pb, st) == 0xff ? 0xffffu : rowbase + (unsigned)old_of(pb, st);
+                        const unsigned hi = rowbase + (unsigned)old_of(pb, st);
                         c.log[pos & (kLogCap - 1)] = ((unsigned long long)hi << 32) | lo;
                     }
                     log_tail += (int)__popcll(bal);
                 }
             }
             while (log_tail - log_head >= 64) log_flush(64);
+            }
         }
         if (!FINAL && !PRE) {
             // Exact sums: a point whose label changed moves its fixed-point row from the old cluster to the new
@@ -1224,7 +1437,12 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 }
             } else {
                 // a word with a changed byte is written back whole (bytes of run slots without a run are never looked at)
-                if (diffw[pb] != 0u) *reinterpret_cast<LabWord *>(prev_chunk + (ptl[pb] * (unsigned)R + lab_off)) = (LabWord)neww[pb];
+                if (diffw[pb] != 0u) {
+                    unsigned char *at = prev_chunk + (ptl[pb] * (unsigned)R + lab_off);
+                    if constexpr (!PRE && !FINAL)
+                        if (c.inv) at = c.prev + ((int64_t)place[pb] * R + lab_off);
+                    *reinterpret_cast<LabWord *>(at) = (LabWord)neww[pb];
+                }
             }
         }
         cur = nxt;
@@ -1243,18 +1461,109 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
     }
 }
 
-template <int DP, bool FINAL, bool TRACE, bool VEC, bool PRE>
-__device__ inline void wave_loop_of(int S, const WaveCtx &c, double (&jloc)[8])
+// The tile lists of the workgroup's units, 32 units per wave at a time: their centres take the place of 32 points.
+//
+// For a unit with centre b and radius r, and a run whose centroid nearest to b is m, every point x of the unit has
+// |x - c_m| <= |b - c_m| + r and |x - c_j| >= |b - c_j| - r: a centroid with |b - c_j| > |b - c_m| + 2 r is not the nearest of
+// any of them.  A quad of centroids stays when its smallest distance to b is within that bound; the distances are the
+// matrix pipeline's, so they enter with twice their error bound (which leaves a margin between the winner and what is left
+// out that no rounding of the exact arithmetic reaches).  The quads' distances stay in registers until the bound is known.
+// Cost: some 25 instructions per tile and 150 more for 32 units, where a tile left out saves a unit 50.
+template <int DP, int S>
+__device__ __forceinline__ void make_lists(const WaveCtx &c, const uint4 *centres, const float *radius, unsigned *lists)
 {
-    switch (S) {
-    case 1: wave_loop<DP, 1, FINAL, TRACE, VEC, PRE>(c, jloc); break;
-    case 2: wave_loop<DP, 2, FINAL, TRACE, VEC, PRE>(c, jloc); break;
-    case 4: wave_loop<DP, 4, FINAL, TRACE, VEC, PRE>(c, jloc); break;
-    default: wave_loop<DP, 8, FINAL, TRACE, VEC, PRE>(c, jloc); break;
+    constexpr int NK = ksteps_of(DP), NS = tile_slots_of(DP), NP = prep_slots_of(DP), UP = 32 * unit_blocks_of(DP);
+    constexpr int ST = S == 1 ? 4 : (S == 2 ? 2 : 1);
+    const int lane = threadIdx.x & 63, n = lane & 31, hl = lane >> 5;
+    const int u0 = (int)(c.chunk_begin / UP), u1 = (int)((c.chunk_end + UP - 1) / UP);
+    const floatx16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    for (int blk = (u0 >> 5) + (int)(threadIdx.x >> 6); blk * 32 < u1; blk += (int)(blockDim.x >> 6)) {
+        const uint4 *bp = centres + (int64_t)blk * prep_block_u4_of(DP);
+        f16x8 bh[NK], bl[NK];
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) {
+            bh[ks] = as_f16x8(bp[ks * 64 + lane]);
+            bl[ks] = as_f16x8(bp[(NK + ks) * 64 + lane]);
+        }
+        const uint2 nn = reinterpret_cast<const uint2 *>(bp + NP * 64)[n];
+        const float rad = radius[blk * 32 + n];
+        const float bn = (__uint_as_float(nn.x << 16) + __uint_as_float(nn.x & 0xffff0000u)) + __uint_as_float(nn.y << 16);
+        const bf16x8 bb = hl ? as_bf16x8(make_uint4(nn.x, nn.y, 0u, 0u)) : as_bf16x8(make_uint4(0x3f803f80u, 0x3f80u, 0u, 0u));
+        // the smallest distance of each quad of this lane's slots, and of each run
+        float quad[kListMaxTiles][4], lim[ST];
+#pragma unroll
+        for (int st = 0; st < ST; ++st) lim[st] = 2.0f * kPadNorm;
+#pragma unroll
+        for (int t = 0; t < kListMaxTiles; ++t) {
+            if (t >= c.n_tiles) continue;
+            const uint4 *at = c.opA_s + t * NS * 64 + lane;
+            floatx16 acc = zero;
+#pragma unroll
+            for (int ks = 0; ks < NK; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(at[(NK + ks) * 64]), bh[ks], acc, 0, 0, 0);
+#pragma unroll
+            for (int ks = 0; ks < NK; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(at[ks * 64]), bl[ks], acc, 0, 0, 0);
+#pragma unroll
+            for (int ks = 0; ks < NK; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(at[ks * 64]), bh[ks], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(at[2 * NK * 64]), bb, acc, 0, 0, 0);
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                quad[t][a] = fminf(fminf(acc[4 * a], acc[4 * a + 1]), fminf(acc[4 * a + 2], acc[4 * a + 3]));
+                lim[state_of<S>(a)] = fminf(lim[state_of<S>(a)], quad[t][a]);
+            }
+        }
+#pragma unroll
+        for (int st = 0; st < ST; ++st) {
+            if (S == 8) lim[st] = fminf(lim[st], xchg32(lim[st]));
+            const float err = fmaf(c.eps_a, bn + c.cnmax_s[S == 8 ? 0 : hl * ST + st], kTolFloor);
+            const float reach = sqrtf(fmaxf(lim[st], 0.0f) + err) + 2.0f * rad;
+            lim[st] = lim[st] < 0.5f * kPadNorm ? fmaf(reach, reach * 1.00001f, 2.0f * err) : -1.0f;     // (-1: a slot without a run)
+        }
+        unsigned in[4] = {0u, 0u, 0u, 0u};                   // bit t: tile t is on the slot's list
+#pragma unroll
+        for (int t = 0; t < kListMaxTiles; ++t) {
+            if (t >= c.n_tiles) continue;
+#pragma unroll
+            for (int a = 0; a < 4; ++a) in[a] |= quad[t][a] <= lim[state_of<S>(a)] ? 1u << t : 0u;
+        }
+        const unsigned pad = (unsigned)c.n_tiles;
+        int longest = max(max(__popc(in[0]), __popc(in[1])), max(__popc(in[2]), __popc(in[3])));
+        longest = max(max(longest, xchg32(longest)), 1);
+        const unsigned mark = (unsigned)(longest > kListMax ? kListAll : longest) << 24;
+        unsigned head[4], more[4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            head[a] = mark;
+            more[a] = 0u;
+#pragma unroll
+            for (int i = 0; i < kListMax; ++i) {
+                const unsigned t = in[a] != 0u ? (unsigned)(__ffs(in[a]) - 1) : pad;
+                in[a] &= in[a] - 1u;
+                if (i < kListHead) head[a] |= t << (8 * i);
+                else more[a] |= t << (8 * (i - kListHead));
+            }
+        }
+        const int u = blk * 32 + n;
+        if (u >= u0 && u < u1) {
+            uint4 *out = reinterpret_cast<uint4 *>(lists + (int64_t)u * kListWords) + hl;
+            out[0] = make_uint4(head[0], head[1], head[2], head[3]);
+            out[2] = make_uint4(more[0], more[1], more[2], more[3]);
+        }
     }
 }
 
-template <int DP, bool FINAL, bool TRACE, bool PRE>
+template <int DP, bool FINAL, bool TRACE, bool VEC, bool PRE, bool ORD>
+__device__ inline void wave_loop_of(int S, const WaveCtx &c, double (&jloc)[8])
+{
+    switch (S) {
+    case 1: wave_loop<DP, 1, FINAL, TRACE, VEC, PRE, ORD>(c, jloc); break;
+    case 2: wave_loop<DP, 2, FINAL, TRACE, VEC, PRE, ORD>(c, jloc); break;
+    case 4: wave_loop<DP, 4, FINAL, TRACE, VEC, PRE, ORD>(c, jloc); break;
+    default: wave_loop<DP, 8, FINAL, TRACE, VEC, PRE, ORD>(c, jloc); break;
+    }
+}
+
+// ORD: a round on the ordered copy of the points.  (The first round of an ordered sweep takes the points as they come.)
+template <int DP, bool FINAL, bool TRACE, bool PRE, bool ORD>
 __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPlan plan, StepArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1303,12 +1612,14 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     const int grow0 = rows_before(plan.k_min, g.run0);                    // first centroid row of the group
     const int real_rows = rows_before(plan.k_min, g.run0 + g.n_runs) - grow0;
     const int copies = g.copies;
-    const Carve cv = carve_lds(DP, d, g.n_tiles, real_rows, copies);
+    const bool ordered = ORD || (!PRE && a.ordered != 0);
+    const Carve cv = carve_lds(DP, d, g.n_tiles, real_rows, copies, ordered);
 
     uint4 *opA_s = reinterpret_cast<uint4 *>(smem + cv.opA);
     float *cs_lds = reinterpret_cast<float *>(smem + cv.cs);
     unsigned long long *sums = reinterpret_cast<unsigned long long *>(smem + cv.sums);
     int *cnts = reinterpret_cast<int *>(smem + cv.cnts);
+    unsigned short *rowpos_s = reinterpret_cast<unsigned short *>(smem + cv.rowpos);
     float *mu_s = reinterpret_cast<float *>(smem + cv.misc);              // [32]
     int *shift_s = reinterpret_cast<int *>(smem + cv.misc + 128);         // [32]
     int *wide_s = reinterpret_cast<int *>(smem + cv.misc + 256);          // [32] + any at [32]
@@ -1381,6 +1692,20 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
             pow2hi_s[tid] = (1023 + shift_v) << 20;                        // 2^shift as a double: the high word
         }
         if (tid < 33) wide_s[tid] = wide_v;
+        if (!FINAL && ordered) {
+            const unsigned short *rowpos = reinterpret_cast<const unsigned short *>(wsb + a.off_rowpos) + grow0;
+            for (int e = tid; e < real_rows; e += TH) rowpos_s[e] = rowpos[e];
+            // the tile of padding rows, as sweep_init_kernel makes them
+            unsigned ph, pm, pl;
+            split3(kPadNorm, ph, pm, pl);
+            constexpr int NSL = tile_slots_of(DP) * 64;
+            if (tid < NSL) {
+                uint4 v = make_uint4(0u, 0u, 0u, 0u);
+                if (tid >= NSL - 64) v = tid < NSL - 32 ? make_uint4(ph | (pm << 16), pl, 0u, 0u) : make_uint4(0x3f803f80u, 0x3f80u, 0u, 0u);
+                opA_s[g.n_tiles * NSL + tid] = v;
+            }
+            static_assert(NSL <= TH, "one thread per operand slot of a tile");
+        }
         if (tid == 0) *next_slab = WV;
         if (tid < 128) {
 #pragma unroll
@@ -1397,7 +1722,10 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     c.sums = sums; c.cnts = cnts; c.copies = copies; c.real_rows = real_rows; c.mu_s = mu_s; c.shift_s = shift_s; c.pow2hi_s = pow2hi_s; c.wide_s = wide_s; c.cnmax_s = cnmax_s;
     c.scale = *reinterpret_cast<const float *>(wsb + a.off_colinfo + kColScaleOff);
     c.xp = reinterpret_cast<const uint4 *>(wsb + a.off_xp);
-    c.log = reinterpret_cast<unsigned long long *>(wsb + a.off_log) + ((int64_t)(g.wg0 + chunk) * WV + (tid >> 6)) * kLogCap;
+    c.log = reinterpret_cast<unsigned long long *>(wsb + a.off_log) + ((int64_t)(g.wg0 + chunk) * WV + __builtin_amdgcn_readfirstlane(tid >> 6)) * kLogCap;
+    c.rowpos = !FINAL && ordered ? rowpos_s : nullptr;
+    c.inv = !PRE && !FINAL && ordered ? reinterpret_cast<const int32_t *>(wsb + a.off_inv) : nullptr;
+    c.lists = nullptr;
     c.X = Xb; c.ldx = a.ldx; c.N = a.N; c.d = d; c.k0 = k0; c.n_runs = g.n_runs; c.n_tiles = g.n_tiles; c.grow0 = grow0;
     c.prev = reinterpret_cast<unsigned char *>(wsb + a.off_prev) + (int64_t)g.lab0 * ((a.N + 15) / 16 * 16);
     c.labels_out = (FINAL && a.labels) ? a.labels + (int64_t)b * a.lab_bs + (int64_t)g.run0 * a.N : nullptr;
@@ -1407,6 +1735,10 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     // 16-byte loads need whole quads of features and aligned rows
     c.first_round = a.first_round != 0;
     c.vec_x = (d % 4 == 0) && (a.ldx % 4 == 0) && ((reinterpret_cast<uintptr_t>(Xb) & 15) == 0);
+    if constexpr (ORD) {
+        c.X = reinterpret_cast<const float *>(wsb + a.off_xs);
+        c.ldx = DP;
+    }
     // Bound on the summed error of two matrix-pipeline distances, relative to S = |x'|^2 + max |c'|^2 (centred and
     // scaled).  Per distance: what the two fp16 pieces per operand leave out - the product of the two low pieces and
     // the two remainders, each below 2^-20 of its element product - is at most 3 2^-20 |x'| |2c'| <= 24 2^-23 S; 4 or 7
@@ -1418,13 +1750,34 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     // shape is within 1.9 2^-24 of the sum of the magnitudes of its terms, against the five roundings charged.)
     c.eps_a = (float)(5 * ((DP < 16 ? 16 : DP) + 8)) * 1.1920928955078125e-07f;   // 5 (max(DP, 16) + 8) 2^-23
 
+    if constexpr (ORD) {
+        if (g.list0 >= 0) {
+            const int64_t n_units = (a.N + 32 * unit_blocks_of(DP) - 1) / (32 * unit_blocks_of(DP));
+            unsigned *lists = reinterpret_cast<unsigned *>(wsb + a.off_lists) + g.list0 * n_units * kListWords;
+            const uint4 *centres = reinterpret_cast<const uint4 *>(wsb + a.off_centres);
+            const float *radius = reinterpret_cast<const float *>(wsb + a.off_radius);
+            switch (g.S) {
+            case 1: make_lists<DP, 1>(c, centres, radius, lists); break;
+            case 2: make_lists<DP, 2>(c, centres, radius, lists); break;
+            case 4: make_lists<DP, 4>(c, centres, radius, lists); break;
+            default: make_lists<DP, 8>(c, centres, radius, lists); break;
+            }
+            c.lists = lists;
+            __syncthreads();
+        }
+    }
+
     double jloc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) jloc[i] = 0.0;
 
     // (a chunk is never empty)
-    if (c.vec_x) wave_loop_of<DP, FINAL, TRACE, true, PRE>(g.S, c, jloc);
-    else wave_loop_of<DP, FINAL, TRACE, false, PRE>(g.S, c, jloc);
+    if constexpr (ORD) {
+        wave_loop_of<DP, FINAL, TRACE, true, PRE, ORD>(g.S, c, jloc);
+    } else {
+        if (c.vec_x) wave_loop_of<DP, FINAL, TRACE, true, PRE, ORD>(g.S, c, jloc);
+        else wave_loop_of<DP, FINAL, TRACE, false, PRE, ORD>(g.S, c, jloc);
+    }
 
     if (FINAL || TRACE) {
         const int lane = tid & 63, wave = tid >> 6;
@@ -1444,16 +1797,18 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
         for (int e = tid; e < real_rows * d; e += TH) {
             unsigned long long v = 0ull;
             long long rows_in = 0;     // rows that entered minus rows that left: each carried the bias once
+            const int row = ordered ? rowpos_s[e / d] : e / d;
             for (int cp = 0; cp < copies; ++cp) {
-                v += sums[(cp * real_rows + e / d) * (DP + 1) + e % d];
-                rows_in += cnts[cp * real_rows + e / d];
+                v += sums[(cp * real_rows + row) * (DP + 1) + e % d];
+                rows_in += cnts[cp * real_rows + row];
             }
             psum[e] = v - kFixBias * (unsigned long long)rows_in;
         }
         int *pcnt = reinterpret_cast<int *>(wsb + a.off_pcnt) + (int64_t)g.part0 + (int64_t)chunk * real_rows;
         for (int e = tid; e < real_rows; e += TH) {
             int v = 0;
-            for (int cp = 0; cp < copies; ++cp) v += cnts[cp * real_rows + e];
+            const int row = ordered ? rowpos_s[e] : e;
+            for (int cp = 0; cp < copies; ++cp) v += cnts[cp * real_rows + row];
             pcnt[e] = v;
         }
     }
@@ -1471,7 +1826,7 @@ struct ColPart {
     double sum;
     int min_lsb, max_msb, bad, pad;
     float vmin, vmax;     // smallest and largest finite value
-    int pad2[2];
+    double sumsq;         // (for the order of the points only)
 };
 
 static_assert(kStatBlocks * 32 * sizeof(ColPart) >= kSeedExchangeBytes, "the seeding chain's exchange area lies in this block");
@@ -1486,7 +1841,7 @@ __global__ void __launch_bounds__(kThreads) colstats_kernel(const float *__restr
     const int l = tid % dp, pg = tid / dp, ppp = kThreads / dp;
     const int64_t per = (N + gridDim.x - 1) / gridDim.x;
     const int64_t r0 = (int64_t)blockIdx.x * per, r1 = min(N, r0 + per);
-    ColPart c = {0.0, 1 << 20, -(1 << 20), 0, 0, INFINITY, -INFINITY, {0, 0}};
+    ColPart c = {0.0, 1 << 20, -(1 << 20), 0, 0, INFINITY, -INFINITY, 0.0};
     if (l < d) {
         // eight rows of this thread's column in flight at a time (the walk is bound by their latency); the values
         // are taken in row order, so the sum does not depend on the depth
@@ -1504,6 +1859,7 @@ __global__ void __launch_bounds__(kThreads) colstats_kernel(const float *__restr
                 unsigned m = bits & 0x7fffffu;
                 if (e == 255) { c.bad = 1; continue; }
                 c.sum = __dadd_rn(c.sum, (double)x);
+                c.sumsq = fma((double)x, (double)x, c.sumsq);
                 c.vmin = fminf(c.vmin, x);
                 c.vmax = fmaxf(c.vmax, x);
                 if (e == 0) { if (m == 0) continue; e = 1; } else m |= 0x800000u;
@@ -1521,6 +1877,7 @@ __global__ void __launch_bounds__(kThreads) colstats_kernel(const float *__restr
         for (int g = 1; g < ppp; ++g) {
             const ColPart o = sh[g * dp + tid];
             t.sum = __dadd_rn(t.sum, o.sum);
+            t.sumsq += o.sumsq;
             t.min_lsb = min(t.min_lsb, o.min_lsb);
             t.max_msb = max(t.max_msb, o.max_msb);
             t.bad |= o.bad;
@@ -1532,17 +1889,19 @@ __global__ void __launch_bounds__(kThreads) colstats_kernel(const float *__restr
 }
 
 __global__ void __launch_bounds__(256) colstats_final_kernel(int64_t N, int d, int n_blocks, char *ws, int64_t ws_bs, int64_t off_part,
-                                                            int64_t off_colinfo, int32_t *status)
+                                                            int64_t off_colinfo, int64_t off_keyinfo, int32_t *status)
 {
     // 256 threads: eight walk the partial results of one column, every eighth block each, eight loads in flight (the
     // walk is bound by their latency); the eight are then combined in a fixed order, so the mean is the same in every run
     constexpr int G = 8, U = 8;
     __shared__ int flags;
     __shared__ ColPart comb[G][32];
+    __shared__ unsigned char place_s[32][12];
+    static_assert(kKeyColBits <= 12, "places of a column's bits");
     const int b = blockIdx.x, l = threadIdx.x & 31, g = threadIdx.x >> 5;
     if (threadIdx.x == 0) flags = 0;
     const ColPart *part = reinterpret_cast<const ColPart *>(ws + (int64_t)b * ws_bs + off_part);
-    ColPart t = {0.0, 1 << 20, -(1 << 20), 0, 0, INFINITY, -INFINITY, {0, 0}};
+    ColPart t = {0.0, 1 << 20, -(1 << 20), 0, 0, INFINITY, -INFINITY, 0.0};
     if (l < d) {
         for (int g0 = g; g0 < n_blocks; g0 += G * U) {
             ColPart o[U];
@@ -1552,6 +1911,7 @@ __global__ void __launch_bounds__(256) colstats_final_kernel(int64_t N, int d, i
             for (int u = 0; u < U; ++u) {
                 if (g0 + u * G >= n_blocks) continue;
                 t.sum = __dadd_rn(t.sum, o[u].sum);
+                t.sumsq += o[u].sumsq;
                 t.min_lsb = min(t.min_lsb, o[u].min_lsb);
                 t.max_msb = max(t.max_msb, o[u].max_msb);
                 t.bad |= o[u].bad;
@@ -1569,6 +1929,7 @@ __global__ void __launch_bounds__(256) colstats_final_kernel(int64_t N, int d, i
             for (int q = 1; q < G; ++q) {
                 const ColPart o = comb[q][l];
                 t.sum = __dadd_rn(t.sum, o.sum);
+                t.sumsq += o.sumsq;
                 t.min_lsb = min(t.min_lsb, o.min_lsb);
                 t.max_msb = max(t.max_msb, o.max_msb);
                 t.bad |= o.bad;
@@ -1610,6 +1971,39 @@ __global__ void __launch_bounds__(256) colstats_final_kernel(int64_t N, int d, i
         colwide[l] = wide;
         if (l == 0) *reinterpret_cast<float *>(ws + (int64_t)b * ws_bs + off_colinfo + kColScaleOff) = scale;
         if (wide) atomicOr(&flags, 1 << 16);
+        if (off_keyinfo >= 0) {
+            // bits of the ordering key: each goes to the column whose cells are the widest, against the column's spread
+            KeyInfo *ki = reinterpret_cast<KeyInfo *>(ws + (int64_t)b * ws_bs + off_keyinfo);
+            const double mu = t.sum / (double)N;
+            float width = l < d && !t.bad ? sqrtf((float)fmax(t.sumsq / (double)N - mu * mu, 0.0)) : 0.0f;
+            if (!(width < INFINITY)) width = 0.0f;
+            int nb = 0;
+            for (int s = 0; s < kKeyBits; ++s) {
+                const float top = half_max_f32(width);
+                const unsigned long long who = __ballot(width == top);
+                if (top > 0.0f && l == __ffsll((long long)who) - 1) {
+                    place_s[l][nb++] = (unsigned char)(kKeyBits - 1 - s);
+                    width = nb < kKeyColBits ? width * 0.5f : 0.0f;
+                }
+            }
+            const unsigned long long with = __ballot(nb > 0);
+            const float range = t.vmax - t.vmin;
+            int first = nb > 0 ? 1 << nb : 0;                     // inclusive, then exclusive sums over the columns
+            for (int off = 1; off < 32; off <<= 1) {
+                const int o = __shfl_up(first, off, 64);
+                if (l >= off) first += o;
+            }
+            if (nb > 0) {
+                const int at = __popcll(with & ((1ull << l) - 1ull));
+                ki->col[at] = l;
+                ki->bits[at] = nb;
+                ki->first[at] = first - (1 << nb);
+                ki->lo[at] = t.vmin;
+                ki->mul[at] = range > 0.0f && range < INFINITY ? (float)(1 << nb) / range : 0.0f;
+                for (int i = 0; i < nb; ++i) ki->place[at][i] = place_s[l][i];
+            }
+            if (l == 0) ki->n_cols = __popcll(with);
+        }
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -1668,6 +2062,147 @@ __global__ void __launch_bounds__(256) lloyd_prepare_kernel(const float *__restr
             reinterpret_cast<uint2 *>(bp + prep_slots_of(DP) * 64)[n] = make_uint2(nh | (nm << 16), nl);
         }
     }
+}
+
+// ---- the same for an ordered sweep: the copy is in the order of the places, the rows go along (padded with zeros to DP
+//      floats, so that rows of any length are read 16 bytes at a time later on), and every unit leaves its centre - the mean
+//      of its points as the operand pieces hold it - and an upper bound of the distance from there to its points.
+template <int DP>
+__global__ void __launch_bounds__(256) lloyd_prepare_ordered_kernel(const float *__restrict__ X, int64_t N, int d, int64_t ldx, int64_t x_bs,
+                                                                    const int32_t *__restrict__ status, char *ws, int64_t ws_bs,
+                                                                    int64_t off_colinfo, int64_t off_perm, int64_t off_xp, int64_t off_xs,
+                                                                    int64_t off_centres, int64_t off_radius)
+{
+    constexpr int H = DP / 2, NK = ksteps_of(DP), HP = 8 * NK, UB = unit_blocks_of(DP);
+    const int b = blockIdx.y;
+    if (status[b] != 0) return;
+    char *wsb = ws + (int64_t)b * ws_bs;
+    const float *Xb = X + (int64_t)b * x_bs;
+    const bool vec = (d % 4 == 0) && (ldx % 4 == 0) && ((reinterpret_cast<uintptr_t>(Xb) & 15) == 0);
+    const float *colmean = reinterpret_cast<const float *>(wsb + off_colinfo);      // -(mean * scale)
+    const float scale = *reinterpret_cast<const float *>(wsb + off_colinfo + kColScaleOff);
+    const int32_t *perm = reinterpret_cast<const int32_t *>(wsb + off_perm);
+    uint4 *xp = reinterpret_cast<uint4 *>(wsb + off_xp), *centres = reinterpret_cast<uint4 *>(wsb + off_centres);
+    float *xs = reinterpret_cast<float *>(wsb + off_xs), *radius = reinterpret_cast<float *>(wsb + off_radius);
+    const int64_t n_blocks = (N + 31) / 32, n_units = (n_blocks + UB - 1) / UB;
+    const int lane = threadIdx.x & 63, n = lane & 31, hl = lane >> 5;
+    const int f0 = hl * H;
+    float mean_h[H];
+#pragma unroll
+    for (int s = 0; s < H; ++s) mean_h[s] = f0 + s < d ? colmean[f0 + s] : 0.0f;
+    // operand pieces of one lane's half of a row, and the norm of the row
+    auto pieces = [&](const float (&xc)[HP], float norm, uint4 *bp, int at, bool store) {
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) {
+            unsigned ph[4], pl[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) split2_pair(xc[8 * ks + 2 * i], xc[8 * ks + 2 * i + 1], ph[i], pl[i]);
+            if (store) {
+                bp[(0 * NK + ks) * 64 + 32 * hl + at] = make_uint4(ph[0], ph[1], ph[2], ph[3]);
+                bp[(1 * NK + ks) * 64 + 32 * hl + at] = make_uint4(pl[0], pl[1], pl[2], pl[3]);
+            }
+        }
+        unsigned nh, nm, nl;
+        split3(norm, nh, nm, nl);
+        if (store && hl == 0) reinterpret_cast<uint2 *>(bp + prep_slots_of(DP) * 64)[at] = make_uint2(nh | (nm << 16), nl);
+    };
+    for (int64_t unit = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); unit < n_units;
+         unit += (int64_t)gridDim.x * (blockDim.x >> 6)) {
+        float xc[UB][HP];
+        float sum[H];
+#pragma unroll
+        for (int s = 0; s < H; ++s) sum[s] = 0.0f;
+#pragma unroll
+        for (int ub = 0; ub < UB; ++ub) {
+            const int64_t blk = unit * UB + ub, p = blk * 32 + n;
+            const bool valid = p < N;
+            float xr[H];
+            const float *row = Xb + (int64_t)(valid ? perm[p] : 0) * ldx;
+            if (vec) {
+#pragma unroll
+                for (int c4 = 0; c4 < H / 4; ++c4) {
+                    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    if (valid && f0 + 4 * c4 < d) v = *reinterpret_cast<const float4 *>(row + f0 + 4 * c4);
+                    xr[4 * c4 + 0] = v.x; xr[4 * c4 + 1] = v.y; xr[4 * c4 + 2] = v.z; xr[4 * c4 + 3] = v.w;
+                }
+            } else {
+#pragma unroll
+                for (int s = 0; s < H; ++s) xr[s] = valid && f0 + s < d ? row[f0 + s] : 0.0f;
+            }
+            float part = 0.0f;
+#pragma unroll
+            for (int s = 0; s < HP; ++s) {
+                // a point past the end and a padded feature count as a zero of the centred data
+                xc[ub][s] = s < H && valid && f0 + s < d ? fmaf(xr[s < H ? s : 0], scale, mean_h[s < H ? s : 0]) : 0.0f;
+                part = fmaf(xc[ub][s], xc[ub][s], part);
+            }
+            const float xn = part + xchg32(part);
+            if (blk < n_blocks) {
+#pragma unroll
+                for (int c4 = 0; c4 < H / 4; ++c4)
+                    *reinterpret_cast<float4 *>(xs + p * DP + f0 + 4 * c4) = make_float4(xr[4 * c4], xr[4 * c4 + 1], xr[4 * c4 + 2], xr[4 * c4 + 3]);
+            }
+            pieces(xc[ub], xn, xp + blk * prep_block_u4_of(DP), n, blk < n_blocks);
+#pragma unroll
+            for (int s = 0; s < H; ++s) sum[s] += xc[ub][s];
+        }
+        const float inv_n = 1.0f / (float)min(N - unit * (32 * UB), (int64_t)(32 * UB));
+        float bc[HP];
+        float norm = 0.0f;
+#pragma unroll
+        for (int s = 0; s < HP; ++s) bc[s] = s < H ? half_sum_f32(sum[s < H ? s : 0]) * inv_n : 0.0f;
+#pragma unroll
+        for (int s = 0; s < HP; s += 2) {                     // what the pieces hold of it, exactly
+            unsigned h, l;
+            split2_pair(bc[s], bc[s + 1], h, l);
+            const fp16x2 hh = __builtin_bit_cast(fp16x2, h), ll = __builtin_bit_cast(fp16x2, l);
+            bc[s] = (float)hh[0] + (float)ll[0];
+            bc[s + 1] = (float)hh[1] + (float)ll[1];
+            norm = fmaf(bc[s], bc[s], fmaf(bc[s + 1], bc[s + 1], norm));
+        }
+        norm += xchg32(norm);
+        float far = 0.0f;
+#pragma unroll
+        for (int ub = 0; ub < UB; ++ub) {
+            float r2 = 0.0f;
+#pragma unroll
+            for (int s = 0; s < H; ++s) {
+                const float diff = xc[ub][s] - bc[s];
+                r2 = fmaf(diff, diff, r2);
+            }
+            r2 += xchg32(r2);
+            if ((unit * UB + ub) * 32 + n < N) far = fmaxf(far, r2);
+        }
+        far = half_max_f32(far);
+        pieces(bc, norm, centres + (unit >> 5) * prep_block_u4_of(DP), (int)(unit & 31), n == 0);
+        if (lane == 0) radius[unit] = sqrtf(far) * 1.00001f + 1.0e-6f;     // (rounding of the differences: below d 2^-24 of it)
+    }
+}
+
+// Places of the centroids of every run, in the order of the points they start from: centroids that lie close together share
+// quads, and a unit meets fewer of them (1M x 16, k = 64: 3.3 tiles instead of 5.7).  The places stay for the whole sweep.
+__global__ void __launch_bounds__(RLS_MAX_K) lloyd_rowpos_kernel(SweepPlan plan, const int64_t *__restrict__ init_idx, int64_t init_bs,
+                                                                 const int32_t *__restrict__ status, char *ws, int64_t ws_bs,
+                                                                 int64_t off_inv, int64_t off_rowpos, OrderSpread sp)
+{
+    __shared__ int at[RLS_MAX_K];
+    const int b = blockIdx.y, run = blockIdx.x, k = plan.k_min + run, j = threadIdx.x;
+    if (status[b] != 0) return;
+    char *wsb = ws + (int64_t)b * ws_bs;
+    if (j < k) {
+        const uint32_t place = (uint32_t)reinterpret_cast<const int32_t *>(wsb + off_inv)[init_idx[(int64_t)b * init_bs + j]];
+        const uint32_t unit = place >> sp.unit_shift;                     // its place before the units were dealt out
+        const uint32_t sorted = unit < sp.n_full ? (uint32_t)((uint64_t)unit * sp.back % sp.n_full) : unit;
+        at[j] = (int)(sorted << sp.unit_shift | (place & ((1u << sp.unit_shift) - 1u)));
+    }
+    __syncthreads();
+    if (j >= k) return;
+    int pos = 0;
+    for (int i = 0; i < k; ++i) pos += at[i] < at[j] || (at[i] == at[j] && i < j) ? 1 : 0;
+    int gi = 0;
+    while (gi + 1 < plan.n_groups && plan.g[gi + 1].run0 <= run) ++gi;
+    const int row0 = rows_before(plan.k_min, run);
+    reinterpret_cast<unsigned short *>(wsb + off_rowpos)[row0 + j] = (unsigned short)(row0 - rows_before(plan.k_min, plan.g[gi].run0) + pos);
 }
 
 // ---- start of a sweep: padding operand rows are zero vectors with a huge norm; running totals are zero;
@@ -1803,6 +2338,8 @@ struct CentroidArgs {
     char *ws;
     int64_t ws_bs;
     int64_t off_colinfo, off_opA, off_cnmax, off_psum, off_pcnt, off_losum, off_tot, off_totcnt;
+    int64_t off_rowpos;          // places of the centroids among the rows of their group, or -1: by index
+    int32_t operands_by_index;   // 1: the operand rows made now are laid out by index all the same (for the final pass)
 };
 
 // One workgroup per run and part of kPartRows of its centroids: new centroids (from the seeding rows, or from the
@@ -1848,6 +2385,17 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
     long long tot_hi = 0, tot_lo = 0, tot_cnt = 0;
     int col_shift = 0, col_wide = 0;
     float col_mean = 0.0f, c_old = 0.0f;
+    const int run_row = row0 - rows_before(plan.k_min, g.run0);      // the run's first row in its group
+    const unsigned short *rowpos = a.off_rowpos >= 0 ? reinterpret_cast<const unsigned short *>(wsb + a.off_rowpos) + row0 + j0 : nullptr;
+    int place = j0 + tid / DP, place_n = j0 + tid;                   // of the element's centroid; of this thread's when it takes norms
+    int sum_place = place;                                           // of the element's low-order sum
+    if (rowpos) {
+        if (tid < E) sum_place = rowpos[tid / DP] - run_row;
+        if (!a.operands_by_index) {
+            place = sum_place;
+            if (tid < rows) place_n = rowpos[tid] - run_row;
+        }
+    }
     if (tid < E && tid % DP < d) {
         const int l = tid % DP;
         const int64_t at = (int64_t)(row0 + j0 + tid / DP) * d + l;
@@ -1908,7 +2456,7 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
                 int shift = col_shift;
                 if (col_wide) {
                     // total = main * 2^kLowBits + low, on the scale 2^-(shift + kLowBits)
-                    const long long low = reinterpret_cast<const long long *>(wsb + a.off_losum)[(int64_t)(row0 + j) * d + l];
+                    const long long low = reinterpret_cast<const long long *>(wsb + a.off_losum)[(int64_t)(row0 + sum_place) * d + l];
                     hi = (long long)(((unsigned long long)hi << kLowBits) | (lo >> (64 - kLowBits)));
                     lo = lo << kLowBits;
                     const unsigned long long nlo = lo + (unsigned long long)low;
@@ -1927,7 +2475,7 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
         }
         cs[jj * DP + l] = cp;
         // operand position of (centroid j, feature l)
-        const int qd = j >> 2, i = j & 3;
+        const int qd = place >> 2, i = place & 3;
         const int t = qd / g.S, slot = rl * g.S + qd % g.S;
         const int m = 8 * (slot & 3) + 4 * (slot >> 2) + i;
         const int h = l / (DP / 2), sf = l % (DP / 2);
@@ -1940,10 +2488,9 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
     __syncthreads();
     float mx = 0.0f;
     if (tid < rows) {
-        const int j = j0 + tid;
         float nrm = 0.0f;
         for (int l = 0; l < DP; ++l) nrm = fmaf(cs[tid * DP + l], cs[tid * DP + l], nrm);
-        const int qd = j >> 2, i = j & 3;
+        const int qd = place_n >> 2, i = place_n & 3;
         const int t = qd / g.S, slot = rl * g.S + qd % g.S;
         // bias slot, lower half-wave lane of this row: pieces of the squared norm
         unsigned ph, pm, pl;
@@ -1992,10 +2539,11 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
     static hipError_t attr_status = hipSuccess;
     std::call_once(attr_once, [] {
         const void *fns[] = {
-            reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, false, false>),
-            reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, false, true>),
-            reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, true, false>),
-            reinterpret_cast<const void *>(lloyd_step_kernel<DP, true, false, false>),
+            reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, false, false, false>),
+            reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, false, true, false>),
+            reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, false, true, true>),
+            reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, true, false, false>),
+            reinterpret_cast<const void *>(lloyd_step_kernel<DP, true, false, false, false>),
         };
         for (const void *fn : fns) {
             const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -2004,19 +2552,28 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
     });
     if (attr_status != hipSuccess) return attr_status;
     const int batch = a.batch;
-    // column statistics
-    if (!a.reuse_colstats) {
-        hipLaunchKernelGGL(colstats_kernel, dim3(L.stat_blocks, batch), dim3(kThreads), 0, s, a.X, a.N, (int)a.d, DP, a.ldx,
-                           a.x_batch_stride, a.ws, L.per_batch, L.colstat_part);
-        hipLaunchKernelGGL(colstats_final_kernel, dim3(batch), dim3(256), 0, s, a.N, (int)a.d, (int)L.stat_blocks, a.ws,
-                           L.per_batch, L.colstat_part, L.colinfo, a.status);
-    }
     // Rounds after the first run on the prepared copy of the points - unless the loss of every round is wanted (that
     // pass needs every row), or the sweep is so light in distance work (a single k up to 32: one tile of centroids per
     // group) that reading the rows is what it costs: the prepared copy is 6 to 12% larger than the rows.
     const bool trace = a.trace != nullptr;
     const bool use_pre = sweep_uses_prepared(plan, a.iters, trace);
-    if (use_pre && !a.reuse_prepared) {
+    const bool ordered = use_pre && plan.ordered;
+    // column statistics
+    if (!a.reuse_colstats) {
+        hipLaunchKernelGGL(colstats_kernel, dim3(L.stat_blocks, batch), dim3(kThreads), 0, s, a.X, a.N, (int)a.d, DP, a.ldx,
+                           a.x_batch_stride, a.ws, L.per_batch, L.colstat_part);
+        hipLaunchKernelGGL(colstats_final_kernel, dim3(batch), dim3(256), 0, s, a.N, (int)a.d, (int)L.stat_blocks, a.ws,
+                           L.per_batch, L.colstat_part, L.colinfo, plan.ordered ? L.keyinfo : (int64_t)-1, a.status);
+    }
+    if (ordered && !a.reuse_prepared) {
+        const hipError_t e = launch_order(a.X, a.N, a.ldx, a.x_batch_stride, batch, a.status, a.ws, L.per_batch, L.keyinfo, L.perm, L.inv, L.xs,
+                                          unit_blocks_of(DP) == 2 ? 6 : 5, s);
+        if (e != hipSuccess) return e;
+        const int64_t n_units = (a.N + 32 * unit_blocks_of(DP) - 1) / (32 * unit_blocks_of(DP));
+        const int64_t grid_x = std::min<int64_t>((n_units + 4 * 4 - 1) / (4 * 4), 4096);     // 4 waves per workgroup, ~4 units per wave
+        hipLaunchKernelGGL((lloyd_prepare_ordered_kernel<DP>), dim3((unsigned)grid_x, batch), dim3(256), 0, s, a.X, a.N, (int)a.d, a.ldx,
+                           a.x_batch_stride, a.status, a.ws, L.per_batch, L.colinfo, L.perm, L.xp, L.xs, L.centres, L.radius);
+    } else if (use_pre && !a.reuse_prepared) {
         // the prepared copy: one wave per block of 32 points, a few blocks per wave
         const int64_t n_blocks = (a.N + 31) / 32;
         int64_t grid_x = (n_blocks + 4 * 8 - 1) / (4 * 8);      // 4 waves per workgroup, ~8 blocks per wave
@@ -2032,6 +2589,9 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
     ia.n_losum = (int64_t)plan.total_rows * a.d; ia.n_tot = ia.n_losum * 2; ia.n_totcnt = ia.n_losum;
     ia.n_prev16 = (int64_t)plan.lab_slots * align_up(a.N, 16) / 16;
     hipLaunchKernelGGL(sweep_init_kernel, dim3(512, batch), dim3(256), 0, s, ia);
+    if (ordered)
+        hipLaunchKernelGGL(lloyd_rowpos_kernel, dim3(plan.n_runs, batch), dim3(RLS_MAX_K), 0, s, plan, a.init_idx, a.init_batch_stride, a.status,
+                           a.ws, L.per_batch, L.inv, L.rowpos, order_spread(a.N, unit_blocks_of(DP) == 2 ? 6 : 5));
 
     CentroidArgs ca;
     ca.X = a.X; ca.N = a.N; ca.d = a.d; ca.ldx = a.ldx; ca.x_bs = a.x_batch_stride;
@@ -2040,6 +2600,8 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
     ca.status = a.status; ca.ws = a.ws; ca.ws_bs = L.per_batch;
     ca.off_colinfo = L.colinfo; ca.off_opA = L.opA; ca.off_cnmax = L.cnmax;
     ca.off_psum = L.psum; ca.off_pcnt = L.pcnt; ca.off_losum = L.losum; ca.off_tot = L.tot; ca.off_totcnt = L.totcnt;
+    ca.off_rowpos = ordered ? L.rowpos : -1;
+    ca.operands_by_index = 0;
     const dim3 centroid_grid(parts_upto(plan.k_min + plan.n_runs - 1) - parts_upto(plan.k_min - 1), batch);
     hipLaunchKernelGGL((lloyd_centroids_kernel<DP, true>), centroid_grid, dim3(kThreads), 0, s, plan, ca);
 
@@ -2051,12 +2613,14 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
     sa.off_colinfo = L.colinfo; sa.off_opA = L.opA; sa.off_cnmax = L.cnmax;
     sa.off_psum = L.psum; sa.off_pcnt = L.pcnt; sa.off_pj = L.pj; sa.off_losum = L.losum; sa.off_prev = L.prev;
     sa.off_xp = L.xp; sa.off_log = L.log;
+    sa.off_xs = L.xs; sa.off_inv = L.inv; sa.off_centres = L.centres; sa.off_radius = L.radius; sa.off_rowpos = L.rowpos; sa.off_lists = L.lists;
+    sa.ordered = ordered ? 1 : 0;
 
     size_t lds = 0;
     for (int gi = 0; gi < plan.n_groups; ++gi) {
         const GroupDesc &g = plan.g[gi];
         const int rr = rows_before(plan.k_min, g.run0 + g.n_runs) - rows_before(plan.k_min, g.run0);
-        const size_t need = (size_t)carve_lds(DP, a.d, g.n_tiles, rr, g.copies).total;
+        const size_t need = (size_t)carve_lds(DP, a.d, g.n_tiles, rr, g.copies, ordered).total;
         if (need > lds) lds = need;
     }
     const dim3 grid((unsigned)((int64_t)plan.n_wgs * batch), 1);
@@ -2066,20 +2630,23 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
         sa.first_round = t == 0 ? 1 : 0;
         if (prof) { hipError_t e = profile_mark(s, true); if (e != hipSuccess) return e; }
         if (trace) {
-            hipLaunchKernelGGL((lloyd_step_kernel<DP, false, true, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
+            hipLaunchKernelGGL((lloyd_step_kernel<DP, false, true, false, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
             if (prof) { hipError_t e = profile_mark(s, false); if (e != hipSuccess) return e; }
             hipLaunchKernelGGL(lloyd_loss_kernel, dim3(batch), dim3(128), 0, s, plan, a.status, a.ws,
                                L.per_batch, L.pj, a.trace, (int64_t)plan.n_runs * (a.iters + 1), (int64_t)(a.iters + 1), (int64_t)t);
         } else {
             // the first round brings every row into a cluster and reads the rows themselves; later rounds take the
             // operands from the prepared copy and read a row only where a label is in doubt or has changed
-            if (t == 0 || !use_pre) hipLaunchKernelGGL((lloyd_step_kernel<DP, false, false, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
-            else hipLaunchKernelGGL((lloyd_step_kernel<DP, false, false, true>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
+            if (t == 0 || !use_pre) hipLaunchKernelGGL((lloyd_step_kernel<DP, false, false, false, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
+            else if (ordered) hipLaunchKernelGGL((lloyd_step_kernel<DP, false, false, true, true>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
+            else hipLaunchKernelGGL((lloyd_step_kernel<DP, false, false, true, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
             if (prof) { hipError_t e = profile_mark(s, false); if (e != hipSuccess) return e; }
         }
+        if (t == a.iters - 1) ca.operands_by_index = 1;    // the final pass takes points and centroids as they are numbered
         hipLaunchKernelGGL((lloyd_centroids_kernel<DP, false>), centroid_grid, dim3(kThreads), 0, s, plan, ca);
     }
-    hipLaunchKernelGGL((lloyd_step_kernel<DP, true, false, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
+    sa.ordered = 0;
+    hipLaunchKernelGGL((lloyd_step_kernel<DP, true, false, false, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
     hipLaunchKernelGGL(lloyd_loss_kernel, dim3(batch), dim3(128), 0, s, plan, a.status, a.ws, L.per_batch,
                        L.pj, a.inertia, (int64_t)plan.n_runs, (int64_t)1, (int64_t)0);
     if (trace)
@@ -2107,9 +2674,9 @@ LloydGeometry lloyd_geometry(int dp)
     return g;
 }
 
-int64_t lloyd_group_lds_bytes(int dp, int d, int n_tiles, int real_rows, int copies)
+int64_t lloyd_group_lds_bytes(int dp, int d, int n_tiles, int real_rows, int copies, bool ordered)
 {
-    return carve_lds(dp, d, n_tiles, real_rows, copies).total;
+    return carve_lds(dp, d, n_tiles, real_rows, copies, ordered).total;
 }
 
 constexpr int kFillWorkgroups = 256;   // one per compute unit
@@ -2140,10 +2707,34 @@ int workgroups_per_cu(int64_t per_cu, int n_groups, int batch)
     return (int)std::min<int64_t>(std::max<int64_t>((per_cu + 600) / 1200, 2), 5);
 }
 
-int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch, SweepPlan *plan)
+// An order of the points costs five launches (65 us up to some 100,000 points, 110 at 1M x 16, 1.5 ms at 8M x 32) and pays by
+// the tiles that a round leaves out: by the points times the tiles of the groups with lists.  Sweeps of 20 to 30 rounds, time
+// without against with an order: 100,003 x 16, k 1..32 (1760 in these units) 0.91; 65,536 x 16, 1..64 (4480) 1.00;
+// 1M x 16, 8..23 (9800) 1.04; 300,007 x 13, 8..63 (20,500) 1.14; 64 spaces of 262,144 x 16, 1..32 (295,000) 1.32;
+// 1M x 16, 1..64 (71,700) 1.45; 8M x 32, 1..128 (2.2M) 1.64.
+bool sweep_wants_order(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch)
+{
+    if (N < 16384 || k_max - k_min + 1 < 8) return false;
+    SweepPlan plan;
+    if (make_sweep_plan(N, d, k_min, k_max, 1, true, &plan) != RLS_OK) return false;
+    int64_t tiles = 0;
+    for (int gi = 0; gi < plan.n_groups; ++gi) tiles += plan.g[gi].list0 >= 0 ? plan.g[gi].n_tiles : 0;
+    return N / 1024 * tiles * batch >= 4600;
+}
+
+// What a slab of a group costs, in fifths of a tile: its tiles - with lists a fifth of them and one more - and the rest.
+static int slab_cost(const GroupDesc &g)
+{
+    return (g.list0 >= 0 ? 5 + g.n_tiles : 5 * g.n_tiles) + 5 * kSlabCost;
+}
+
+int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch, bool ordered, SweepPlan *plan)
 {
     const int dp = padded_d(d);
-    const LloydGeometry geo = lloyd_geometry(dp);
+    LloydGeometry geo = lloyd_geometry(dp);
+    if (ordered) geo.lds_budget = 160 * 1024;      // the tile of padding rows and the places have to fit as well
+    plan->ordered = ordered ? 1 : 0;
+    int n_lists = 0;
     plan->n_runs = k_max - k_min + 1;
     plan->k_min = k_min;
     plan->dp = dp;
@@ -2165,7 +2756,7 @@ int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int3
             const int n_tiles = (quads + S - 1) / S;
             const int real_rows = rows_before(k_min, run + nr) - rows_before(k_min, run);
             if (n_tiles > 32) continue;
-            if (lloyd_group_lds_bytes(dp, d, n_tiles, real_rows, 1) > geo.lds_budget) continue;
+            if (lloyd_group_lds_bytes(dp, d, n_tiles, real_rows, 1, ordered) > geo.lds_budget) continue;
             // cost per real row: padded rows and a fixed per-group overhead
             const double score = (n_tiles * 32.0 + 24.0) / real_rows;
             if (score < best_score - 1e-12 || (nr == best_nr && score < best_score + 1e-12)) {
@@ -2176,6 +2767,7 @@ int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int3
         GroupDesc &g = plan->g[plan->n_groups++];
         g.run0 = (int16_t)run; g.n_runs = (int16_t)best_nr; g.S = (int16_t)(8 / best_R); g.n_tiles = (int16_t)best_tiles;
         g.lab0 = (int16_t)lab_slots; g.tile0 = tiles;
+        g.list0 = ordered && best_tiles >= kListMinTiles && best_tiles <= kListMaxTiles ? n_lists++ : -1;
         lab_slots += best_R;
         // Runs with few clusters send many lanes of a wave to the same accumulator address (32 / k on average), which
         // the LDS works off one after the other: such groups keep several copies of their accumulators, LDS permitting.
@@ -2183,7 +2775,7 @@ int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int3
             const int kmax_g = k_min + run + best_nr - 1;
             const int real_rows = rows_before(k_min, run + best_nr) - rows_before(k_min, run);
             int copies = kmax_g <= 8 ? 16 : (kmax_g <= 16 ? 8 : (kmax_g <= 32 ? 4 : (kmax_g <= 64 ? 2 : 1)));
-            while (copies > 1 && lloyd_group_lds_bytes(dp, d, best_tiles, real_rows, copies) > geo.lds_budget) copies >>= 1;
+            while (copies > 1 && lloyd_group_lds_bytes(dp, d, best_tiles, real_rows, copies, ordered) > geo.lds_budget) copies >>= 1;
             g.copies = (int16_t)copies;
         }
         tiles += best_tiles;
@@ -2207,15 +2799,15 @@ int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int3
     const int waves = step_threads_of(dp) / 64;
     const int64_t per_round = (int64_t)slab_blocks_of(dp, 1) * 32 * waves;
     int64_t cost = 0;
-    for (int gi = 0; gi < plan->n_groups; ++gi) cost += plan->g[gi].n_tiles + kSlabCost;
-    const int64_t per_cu = (N + 31) / 32 * cost * batch / (kFillWorkgroups * waves);
+    for (int gi = 0; gi < plan->n_groups; ++gi) cost += slab_cost(plan->g[gi]);
+    const int64_t per_cu = (N + 31) / 32 * cost * batch / (5 * kFillWorkgroups * waves);
     const int per_cu_wgs = workgroups_per_cu(per_cu, plan->n_groups, batch);
     if (per_cu_wgs > 0) {
         // Every group gets chunks of its own length, so that all workgroups take about the same time.  With r rounds of slabs
         // for its waves, a workgroup of group g is busy for r (tiles + kSlabCost): the shortest time is looked for with which
         // the workgroups of all groups fit when every group takes as many whole rounds as that time allows.
         auto chunks_of = [&](const GroupDesc &g, int64_t time) {
-            const int64_t rounds = std::max<int64_t>(time / (g.n_tiles + kSlabCost), 1);
+            const int64_t rounds = std::max<int64_t>(5 * time / slab_cost(g), 1);
             const int64_t len = std::min(rounds * per_round, cap);
             return (N + len - 1) / len;
         };
@@ -2277,6 +2869,7 @@ int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int3
     }
     if (wgs * batch > 0x7fffffffLL || parts > 0x7fffffffLL) return RLS_ERR_INVALID_ARG;
     plan->n_wgs = (int32_t)wgs;
+    plan->n_lists = n_lists;
     plan->n_parts = (int32_t)parts;
     return RLS_OK;
 }
@@ -2306,6 +2899,19 @@ void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, in
     L->colinfo = take(512);
     L->chain = take((int64_t)k_max * 8);
     L->xp = take((N + 31) / 32 * prep_block_u4_of(plan.dp) * 16);     // (with the blocks above: the same place whatever the range of k)
+    const int64_t n_units = (N + 32 * unit_blocks_of(plan.dp) - 1) / (32 * unit_blocks_of(plan.dp));
+    L->keyinfo = L->perm = L->inv = L->xs = L->centres = L->radius = L->rowpos = L->lists = 0;
+    if (plan.ordered) {
+        L->keyinfo = take(sizeof(KeyInfo));
+        L->perm = take(N * 4);
+        L->inv = take(N * 4);
+        L->xs = take(std::max(align_up(N, 64) * plan.dp * 4, order_scratch_bytes(N)));
+        L->centres = take((n_units + 31) / 32 * prep_block_u4_of(plan.dp) * 16);
+        L->radius = take(align_up(n_units, 32) * 4);
+        // (from here on: a place that depends on the range of k)
+        L->rowpos = take((int64_t)plan.total_rows * 2);
+        L->lists = take((int64_t)plan.n_lists * n_units * kListWords * 4);
+    }
     L->opA = take((int64_t)plan.total_tiles * tile_bytes_of(plan.dp));
     L->cnmax = take((int64_t)plan.n_runs * kMaxParts * 4);
     L->psum = take((int64_t)plan.n_parts * d * 8);

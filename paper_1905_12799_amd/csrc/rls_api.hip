@@ -60,6 +60,30 @@ static int32_t check_sweep(int64_t N, int32_t d, int32_t k_min, int32_t k_max, i
     return RLS_OK;
 }
 
+// Plan and workspace of a sweep.  With an order of the points where that pays - unless the workspace at hand (bytes; negative:
+// any) holds the sweep without it only, so that a fixed workspace goes on taking what it has taken.
+static int32_t plan_sweep(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch, int64_t bytes, SweepPlan *plan, SweepLayout *L)
+{
+    for (int ordered = sweep_wants_order(N, d, k_min, k_max, batch) ? 1 : 0; ordered >= 0; --ordered) {
+        const int32_t rc = make_sweep_plan(N, d, k_min, k_max, batch, ordered != 0, plan);
+        if (rc != RLS_OK) return rc;
+        sweep_layout(*plan, N, d, k_max, batch, false, L);
+        if (bytes < 0 || L->total <= bytes) break;
+    }
+    return RLS_OK;
+}
+
+int64_t sweep_least_workspace(int64_t N, int32_t d, int32_t k_min, int32_t k_max)
+{
+    int32_t rc = check_sweep(N, d, k_min, k_max, 1);
+    SweepPlan plan;
+    if (rc == RLS_OK) rc = make_sweep_plan(N, d, k_min, k_max, 1, false, &plan);
+    if (rc != RLS_OK) return rc;
+    SweepLayout L;
+    sweep_layout(plan, N, d, k_max, 1, false, &L);
+    return L.total;
+}
+
 }  // namespace rls
 
 using namespace rls;
@@ -151,11 +175,9 @@ int64_t rls_kmeans_sweep_workspace_bytes(int64_t N, int32_t d, int32_t k_min, in
     const int32_t rc = check_sweep(N, d, k_min, k_max, batch);
     if (rc != RLS_OK) return rc;
     SweepPlan plan;
-    const int32_t prc = make_sweep_plan(N, d, k_min, k_max, batch, &plan);
-    if (prc != RLS_OK) return prc;
     SweepLayout L;
-    sweep_layout(plan, N, d, k_max, batch, false, &L);
-    return L.total;
+    const int32_t prc = plan_sweep(N, d, k_min, k_max, batch, -1, &plan, &L);
+    return prc != RLS_OK ? prc : L.total;
 }
 
 int32_t rls_kmeanspp_chain(const float *X_dev, int64_t N, int32_t d, int64_t ldx, int32_t k_max, uint64_t seed,
@@ -167,7 +189,7 @@ int32_t rls_kmeanspp_chain(const float *X_dev, int64_t N, int32_t d, int64_t ldx
     rc = check_sweep(N, d, k_max, k_max, 1);
     if (rc != RLS_OK) return rc;
     SweepPlan plan;
-    rc = make_sweep_plan(N, d, k_max, k_max, 1, &plan);
+    rc = make_sweep_plan(N, d, k_max, k_max, 1, false, &plan);
     if (rc != RLS_OK) return rc;
     SweepLayout L;
     sweep_layout(plan, N, d, k_max, 1, false, &L);
@@ -193,10 +215,9 @@ int32_t rls_kmeans_sweep_batched(int32_t batch, const float *X_dev, int64_t N, i
     if (ldx > RLS_MAX_LDX) return RLS_ERR_SHAPE;   // the step kernel addresses a slab of rows with 32-bit offsets
     if (batch > 1 && x_batch_stride < N * ldx - (ldx - d)) return RLS_ERR_SHAPE;
     SweepPlan plan;
-    rc = make_sweep_plan(N, d, k_min, k_max, batch, &plan);
-    if (rc != RLS_OK) return rc;
     SweepLayout L;
-    sweep_layout(plan, N, d, k_max, batch, false, &L);
+    rc = plan_sweep(N, d, k_min, k_max, batch, workspace_bytes, &plan, &L);
+    if (rc != RLS_OK) return rc;
     if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < L.total) return RLS_ERR_WORKSPACE;
     char *ws = static_cast<char *>(workspace_dev);
     hipStream_t s = (hipStream_t)stream;
@@ -229,13 +250,13 @@ int32_t rls_kmeans_sweep(const float *X_dev, int64_t N, int32_t d, int64_t ldx, 
                                     workspace_bytes, stream);
 }
 
-static int32_t until_knee_workspace(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t k_wave, int64_t *bytes)
+static int32_t until_knee_workspace(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t k_wave, bool ordered, int64_t *bytes)
 {
     int64_t need = 0;
     for (int32_t k_lo = k_min; k_lo <= k_max; k_lo += k_wave) {
         const int32_t k_hi = k_lo + k_wave - 1 < k_max ? k_lo + k_wave - 1 : k_max;
         SweepPlan plan;
-        const int32_t rc = make_sweep_plan(N, d, k_lo, k_hi, 1, &plan);
+        const int32_t rc = make_sweep_plan(N, d, k_lo, k_hi, 1, ordered, &plan);
         if (rc != RLS_OK) return rc;
         SweepLayout L;
         sweep_layout(plan, N, d, k_max, 1, true, &L);     // chain sized for k_max: the leading blocks sit at the same offsets in every wave
@@ -245,13 +266,19 @@ static int32_t until_knee_workspace(int64_t N, int32_t d, int32_t k_min, int32_t
     return RLS_OK;
 }
 
+// all waves of a call share the order, so it is decided once, by the first (often the only) one
+static bool until_knee_wants_order(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t k_wave)
+{
+    return sweep_wants_order(N, d, k_min, k_min + (k_wave < k_max - k_min + 1 ? k_wave : k_max - k_min + 1) - 1, 1);
+}
+
 int64_t rls_kmeans_sweep_until_knee_workspace_bytes(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t k_wave)
 {
     const int32_t rc = check_sweep(N, d, k_min, k_max, 1);
     if (rc != RLS_OK) return rc;
     if (k_wave < 1) return RLS_ERR_INVALID_ARG;
     int64_t bytes = 0;
-    const int32_t wrc = until_knee_workspace(N, d, k_min, k_max, k_wave, &bytes);
+    const int32_t wrc = until_knee_workspace(N, d, k_min, k_max, k_wave, until_knee_wants_order(N, d, k_min, k_max, k_wave), &bytes);
     return wrc != RLS_OK ? wrc : bytes;
 }
 
@@ -269,8 +296,14 @@ int32_t rls_kmeans_sweep_until_knee(const float *X_dev, int64_t N, int32_t d, in
     if (iters < 0 || k_wave < 1) return RLS_ERR_INVALID_ARG;
     if (ldx > RLS_MAX_LDX) return RLS_ERR_SHAPE;
     int64_t need = 0;
-    rc = until_knee_workspace(N, d, k_min, k_max, k_wave, &need);
+    bool ordered = until_knee_wants_order(N, d, k_min, k_max, k_wave);
+    rc = until_knee_workspace(N, d, k_min, k_max, k_wave, ordered, &need);
     if (rc != RLS_OK) return rc;
+    if (ordered && workspace_bytes < need) {
+        ordered = false;
+        rc = until_knee_workspace(N, d, k_min, k_max, k_wave, false, &need);
+        if (rc != RLS_OK) return rc;
+    }
     if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < need) return RLS_ERR_WORKSPACE;
     char *ws = static_cast<char *>(workspace_dev);
     hipStream_t s = (hipStream_t)stream;
@@ -281,7 +314,7 @@ int32_t rls_kmeans_sweep_until_knee(const float *X_dev, int64_t N, int32_t d, in
     for (int32_t k_lo = k_min; k_lo <= k_max && !fired; k_lo += k_wave) {
         const int32_t k_hi = k_lo + k_wave - 1 < k_max ? k_lo + k_wave - 1 : k_max;
         SweepPlan plan;
-        rc = make_sweep_plan(N, d, k_lo, k_hi, 1, &plan);
+        rc = make_sweep_plan(N, d, k_lo, k_hi, 1, ordered, &plan);
         if (rc != RLS_OK) return rc;
         SweepLayout L;
         sweep_layout(plan, N, d, k_max, 1, true, &L);

@@ -41,6 +41,7 @@ struct GroupDesc {
     int32_t n_chunks;  // chunks the points are cut into for this group
     int32_t chunk_len; // points per chunk (a multiple of 64)
     int32_t wg0;       // chunks of all earlier groups
+    int32_t list0;     // groups with tile lists before this one; -1: every unit meets every tile
     int32_t part0;     // per-chunk centroid rows of all earlier groups (n_chunks times rows each): where this group's deltas begin
 };
 
@@ -55,9 +56,12 @@ struct SweepPlan {
     int32_t total_rows;  // sum of k over the runs
     int32_t n_wgs;       // chunks of all groups: workgroups of a step launch per space
     int32_t n_parts;     // per-chunk centroid rows of all groups
+    int32_t n_lists;     // groups with tile lists
     int32_t chunk_block; // > 0: every group has the same chunks, and the step kernel's workgroup order takes this many at a time (all
                          // groups of a block of chunks, then the next block); 0: the groups have chunks of their own, of equal cost
     int32_t dp;          // padded feature count: 8, 16 or 32
+    int32_t ordered;     // 1: rounds after the first run on a spatially ordered copy of the points (kmeans_order.hip), whose blocks
+                         // meet only the tiles of centroids that can win there
     GroupDesc g[kMaxGroups];
     uint8_t sched[kMaxGroups];   // launch order: group indices by falling cost
 };
@@ -75,9 +79,11 @@ struct LloydGeometry {
 LloydGeometry lloyd_geometry(int dp);
 int padded_d(int d);
 // LDS bytes of a group: operand tiles + centroid copy + exact-sum accumulators + fixed part
-int64_t lloyd_group_lds_bytes(int dp, int d, int n_tiles, int real_rows, int copies);
+int64_t lloyd_group_lds_bytes(int dp, int d, int n_tiles, int real_rows, int copies, bool ordered);
+// whether sweeps over k_min .. k_max (the waves of a sweep until the knee: the whole range) are worth an order of the points
+bool sweep_wants_order(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch);
 // `batch`: spaces swept by the same launches (sizes the chunks so that the whole batch gives ~512 workgroups)
-int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch, SweepPlan *plan);
+int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch, bool ordered, SweepPlan *plan);
 
 // Workspace carving for one sweep (all offsets in bytes from the workspace base, per batch element
 // unless noted).  Filled by sweep_layout().
@@ -101,11 +107,21 @@ struct SweepLayout {
     int64_t log;            // uint64 [chunks of all groups][waves][512] rings of moved-pair records, one per wave of the step kernel
                             // (in the place of colstat_part, mind, bsum, near and seedthr, unless the chain is to grow between sweeps)
     int64_t xp;             // prepared copy of the points: per block of 32, the matrix operands and squared norms (kmeans_lloyd.hip)
+    // with an order of the points (plan.ordered); xp is in that order, and so are the labels of the last round
+    int64_t keyinfo;        // KeyInfo
+    int64_t perm, inv;      // int32 [N] place -> point, point -> place
+    int64_t xs;             // fp32 [N rounded up to 64][dp] rows in that order, zero past the last feature (before: the scratch of the ordering)
+    int64_t centres;        // prepared copy of the units' centres, as xp
+    int64_t radius;         // fp32 [units rounded up to 32] upper bound of a unit's radius, in scaled units
+    int64_t rowpos;         // uint16 [total_rows] place of a centroid among the rows of its group
+    int64_t lists;          // uint32 per group [units][16]: the tiles that a unit meets (see tile lists, kmeans_lloyd.hip)
     int64_t per_batch;      // bytes per batch element (multiple of 256)
     int64_t total;          // per_batch * batch
     int32_t seed_blocks;
     int32_t stat_blocks;
 };
+// workspace of a sweep of one space without an order of the points, or an error
+int64_t sweep_least_workspace(int64_t N, int32_t d, int32_t k_min, int32_t k_max);
 // `chain_grows`: a later call with the same workspace adds centres to the chain (the waves of a sweep until the knee)
 void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, int32_t batch, bool chain_grows, SweepLayout *L);
 
@@ -176,6 +192,25 @@ bool profile_enabled();
 hipError_t profile_mark(hipStream_t s, bool begin);
 
 hipError_t launch_sweep(const SweepPlan &plan, const SweepLayout &L, const SweepArgs &a, hipStream_t s);
+
+// ---- spatial order of the points (kmeans_order.hip)
+constexpr int kKeyBits = 24, kKeyColBits = 10;      // of a key, and of one column at most
+struct KeyInfo {
+    int32_t n_cols;                          // columns that have bits of the key
+    int32_t col[RLS_MAX_D], bits[RLS_MAX_D];
+    int32_t first[RLS_MAX_D];                // cells of all columns before
+    float lo[RLS_MAX_D], mul[RLS_MAX_D];     // cell of a value: (x - lo) mul, cut off
+    unsigned char place[RLS_MAX_D][12];      // where a column's bits go, the first is the cell's highest
+};
+// Whole units (of 2^unit_shift places) are dealt out: unit u of the sorted sequence is unit u * step mod n_full of the order
+struct OrderSpread {
+    int32_t unit_shift;
+    uint32_t n_full, step, back;             // back: the inverse of step
+};
+OrderSpread order_spread(int64_t N, int unit_shift);
+int64_t order_scratch_bytes(int64_t N);
+hipError_t launch_order(const float *X, int64_t N, int64_t ldx, int64_t x_batch_stride, int32_t batch, const int32_t *status, char *ws,
+                        int64_t ws_bs, int64_t off_keyinfo, int64_t off_perm, int64_t off_inv, int64_t off_scratch, int unit_shift, hipStream_t s);
 // whether the rounds after the first of such a sweep read the prepared copy of the points
 bool sweep_uses_prepared(const SweepPlan &plan, int32_t iters, bool trace);
 

@@ -1,0 +1,102 @@
+"""Sweeps on the spatially ordered copy of the points, whose blocks meet listed tiles of centroids only, against the same
+sweep on the points as they come (a sweep that also returns the loss of every round takes that route), bit for bit, and
+against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rls():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1905_12799_amd import binding
+    binding.lib()
+    return binding
+
+
+def clustered(rng, N, d, spread=1.0):
+    centres = rng.uniform(-40, 40, (24, d))
+    return np.rint(centres[rng.integers(0, 24, N)] + spread * rng.standard_normal((N, d))).astype(np.float32)
+
+
+def make(kind, N, d, seed):
+    rng = np.random.default_rng(seed)
+    if kind == "clusters":
+        X = clustered(rng, N, d, 4.0)
+    elif kind == "noise":                       # no structure: most units meet more tiles than a list holds
+        X = rng.standard_normal((N, d)).astype(np.float32)
+    elif kind == "grid":                        # few distinct rows: exact ties between centroids, long buckets
+        X = rng.integers(0, 3, (N, d)).astype(np.float32)
+    elif kind == "line":                        # one column carries nearly all of the key
+        X = clustered(rng, N, d, 0.01)
+        X[:, 0] = rng.uniform(0, 1e4, N)
+    elif kind == "same":                        # nothing to order by
+        X = np.full((N, d), 3.25, np.float32)
+    elif kind == "wide":                        # columns that span more bits than one accumulator keeps
+        X = clustered(rng, N, d, 3.0)
+        X[:, 1] = (rng.integers(1, 1 << 20, N) * 2.0 ** -30).astype(np.float32)
+        X[::7, 1] = 2.0 ** 21
+    return X
+
+
+# units and chunks that end raggedly, every padded width, groups of 1, 2, 4 and 8 slots per run, groups with fewer and with
+# more tiles than lists are kept for
+CASES = [("clusters", 180224, 16, 1, 40), ("clusters", 81921, 13, 8, 63), ("clusters", 90011, 5, 1, 64), ("clusters", 60017, 32, 1, 100),
+         ("clusters", 67000, 17, 97, 128), ("clusters", 50001, 8, 1, 110), ("clusters", 70001, 24, 10, 90), ("clusters", 66415, 3, 30, 90),
+         ("noise", 80000, 32, 1, 64), ("noise", 93333, 12, 20, 64), ("grid", 87017, 6, 1, 60), ("grid", 90480, 16, 20, 64),
+         ("line", 85000, 9, 1, 64), ("line", 76500, 1, 1, 64), ("same", 76400, 8, 1, 65), ("wide", 78000, 7, 1, 64), ("wide", 81000, 20, 10, 64)]
+
+
+@pytest.mark.parametrize("kind,N,d,k_min,k_max", CASES)
+def test_ordered_sweep_equals_plain_sweep(rls, kind, N, d, k_min, k_max):
+    X = torch.as_tensor(make(kind, N, d, N + d)).cuda()
+    got = rls.kmeans_sweep(X, k_min, k_max, 6, seed=3)
+    want = rls.kmeans_sweep(X, k_min, k_max, 6, seed=3, want_trace=True)
+    assert torch.equal(got.labels, want.labels)
+    assert torch.equal(got.centroids, want.centroids)
+    torch.testing.assert_close(got.inertia, want.inertia, rtol=1e-12, atol=0)
+
+
+def test_ordered_sweep_against_the_oracle(rls, orc):
+    X = make("clusters", 76999, 11, 5)
+    got = rls.kmeans_sweep(torch.as_tensor(X).cuda(), 9, 64, 3, seed=9)
+    ref = orc.kmeans_sweep(X, 9, 64, 3, seed=9)
+    np.testing.assert_array_equal(got.labels.cpu().numpy(), ref["labels"])
+    np.testing.assert_array_equal(got.centroids.cpu().numpy(), ref["centroids"])
+    np.testing.assert_allclose(got.inertia.cpu().numpy(), ref["inertia"], rtol=1e-12)
+
+
+def test_ordered_sweep_of_strided_rows_and_given_centres(rls):
+    """Rows further apart than they are long, initial centres that name one point twice; the same call again gives the same."""
+    full = torch.as_tensor(make("clusters", 100003, 16, 8)).cuda()
+    X = full[:, 1:14]
+    init = torch.arange(0, 100003, 1500, device="cuda", dtype=torch.int64)[:64].clone()
+    init[7] = init[3]
+    got = rls.kmeans_sweep(X, 1, 64, 5, init_idx=init)
+    again = rls.kmeans_sweep(X, 1, 64, 5, init_idx=init)
+    want = rls.kmeans_sweep(X.contiguous(), 1, 64, 5, init_idx=init, want_trace=True)
+    for r in (got, again):
+        assert torch.equal(r.labels, want.labels) and torch.equal(r.centroids, want.centroids)
+    assert torch.equal(got.inertia, again.inertia)
+
+
+def test_ordered_batch_and_smaller_workspace(rls):
+    """Spaces of a batch are ordered one by one; a workspace that only holds the sweep as it comes takes it without an order."""
+    X = torch.stack([torch.as_tensor(make(k, 82421, 10, i)) for i, k in enumerate(("clusters", "noise", "grid"))]).cuda()
+    got = rls.kmeans_sweep_batched(X, 1, 40, 5, seeds=[4, 5, 6])
+    need = rls.kmeans_sweep_workspace_bytes(82421, 10, 1, 40, 3)
+    tight = torch.empty(need - 3 * 82421 * 64, dtype=torch.uint8, device="cuda")         # without the ordered rows
+    plain = rls.kmeans_sweep_batched(X, 1, 40, 5, seeds=[4, 5, 6], workspace=tight)
+    assert torch.equal(got.labels, plain.labels) and torch.equal(got.centroids, plain.centroids)
+
+
+def test_waves_until_the_knee_share_the_order(rls):
+    X = torch.as_tensor(make("clusters", 500011, 14, 2)).cuda()
+    init = rls.kmeanspp_chain(X, 60, 11)
+    k, n_done, r = rls.kmeans_sweep_until_knee(X, 17, 60, 16, 5, 1e-9, seed=11)        # the knee never fires: all waves run
+    assert n_done == 44
+    want = rls.kmeans_sweep(X, 17, 60, 5, init_idx=init, want_trace=True)
+    assert torch.equal(r.labels, want.labels) and torch.equal(r.centroids, want.centroids)

@@ -127,3 +127,27 @@ def test_seeding_skip_rule_never_skips_a_point_that_would_improve():
             near = np.where(better, j, near)
             chain.append(pick)
     assert skipped_total > 100000        # the rule does fire on these inputs
+
+
+@pytest.mark.parametrize("kind", ["lattice", "gauss", "tight"])
+def test_ball_rule_keeps_every_nearest_centroid(kind):
+    """The tile lists of an ordered sweep: a centroid farther from a unit's centre than the nearest one plus twice the unit's
+    radius is left out; distances enter with their error bound either way, and no point's nearest centroid may be missing."""
+    rng = np.random.default_rng({"lattice": 1, "gauss": 2, "tight": 3}[kind])
+    for _ in range(200):
+        d, k = int(rng.integers(1, 33)), int(rng.integers(1, 129))
+        if kind == "lattice":
+            P, C = rng.integers(0, 4, (32, d)).astype(float), rng.integers(0, 4, (k, d)).astype(float)
+        elif kind == "gauss":
+            P, C = rng.standard_normal((32, d)) * 100, rng.standard_normal((k, d)) * 100
+        else:
+            P, C = 1000 + 1e-3 * rng.standard_normal((32, d)), 1000 + rng.standard_normal((k, d))
+        b = P.mean(axis=0)
+        err = 120 * 2.0 ** -23 * ((b ** 2).sum() + (C ** 2).sum(axis=1).max()) + 8
+        v = ((C - b) ** 2).sum(axis=1) + err / 2 * rng.uniform(-1, 1, k)          # the matrix pipeline's distances
+        radius = np.sqrt(((P - b) ** 2).sum(axis=1)).max()
+        reach = np.sqrt(max(v.min(), 0.0) + err) + 2 * radius
+        kept = v <= reach ** 2 + 2 * err
+        D = ((P[:, None, :] - C[None]) ** 2).sum(axis=2)
+        for i in range(32):
+            assert kept[D[i] == D[i].min()].all()
