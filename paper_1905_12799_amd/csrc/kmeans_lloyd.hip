@@ -92,7 +92,7 @@ constexpr int kLogCap = 512;                  // records per wave (a slab adds a
 
 // ---- LDS carve of lloyd_step_kernel (bytes), shared by the planner and the kernel ------------
 struct Carve {
-    int opA, cs, sums, cnts, rowpos, misc, total;
+    int opA, cs, sums, cnts, rowpos, rowidx, misc, total;
 };
 __host__ __device__ inline Carve carve_lds(int dp, int d, int n_tiles, int real_rows, int copies, bool ordered)
 {
@@ -106,6 +106,7 @@ __host__ __device__ inline Carve carve_lds(int dp, int d, int n_tiles, int real_
     c.sums = off;    off += (copies * real_rows * (dp + 1) * 8 + 15) / 16 * 16;   // fixed-point sum deltas
     c.cnts = off;    off += (copies * real_rows * 4 + 15) / 16 * 16;    // member count deltas
     c.rowpos = off;  off += ordered ? (real_rows * 2 + 15) / 16 * 16 : 0;   // places of the centroids among the group's rows
+    c.rowidx = off;  off += ordered ? (real_rows + 15) / 16 * 16 : 0;       // which centroid of its run has a place
     c.misc = off;    off += 2048;
     c.total = off;
     return c;
@@ -125,8 +126,7 @@ struct StepArgs {
     char *ws;                // workspace base
     int64_t ws_bs;           // bytes per batch element
     int64_t off_colinfo, off_opA, off_cnmax, off_psum, off_pcnt, off_pj, off_losum, off_prev, off_xp, off_log;
-    int64_t off_xs, off_inv, off_centres, off_radius, off_rowpos, off_lists;
-    int32_t ordered;         // 1: operand rows, accumulators and labels of the last round are in the order of the places
+    int64_t off_xs, off_centres, off_radius, off_rowpos, off_rowidx, off_lists;      // (ordered copy)
     int32_t first_round;     // 1: no point has a label yet (every pair enters a cluster, nothing leaves one)
     int32_t batch;           // spaces swept by the launch
 };
@@ -452,8 +452,8 @@ struct WaveCtx {
     const float *cnmax_s;         // LDS: per-run maximum squared norm of the centred centroids [8]
     const float *X;               // this space's rows (on the prepared copy of an ordered sweep: the rows in that order)
     const uint4 *xp;              // global: prepared copy of this space's points (see prep_block_u4_of)
-    const unsigned short *rowpos; // LDS: place of each of the group's centroids among its rows, or null (places = indices)
-    const int32_t *inv;           // global: place of each point (first round of an ordered sweep), or null
+    const unsigned short *rowpos; // LDS: place of each of the group's centroids among its rows (ordered copy; else places are indices)
+    const unsigned char *rowidx;  // LDS: the centroid of its run that has a place
     const unsigned *lists;        // global: the tile lists of the group's units, or null
     unsigned long long *log;      // global: this wave's ring of moved-pair records [kLogCap]
     int64_t ldx, N;
@@ -473,11 +473,14 @@ struct WaveCtx {
 // cache look-ups (which bounds sweeps over few k).
 // PRE: the operands come from the prepared copy; the raw rows are read on demand (not in a pass that sums the loss,
 // which needs every row, and not in the first round, where every row enters a cluster).
-template <int DP, int S, bool FINAL, bool TRACE, bool VEC, bool PRE, bool ORD>
+// ORD: a round on the ordered copy; FIRST: its first one, when no point has a label yet (other sweeps take the points as they come
+// in their first round).
+template <int DP, int S, bool FINAL, bool TRACE, bool VEC, bool PRE, bool ORD, bool FIRST>
 __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
 {
     static_assert(!PRE || (!FINAL && !TRACE), "the prepared copy serves the plain assign + update pass only");
     static_assert(!ORD || (PRE && VEC), "the ordered copy is a prepared one, with rows of DP floats");
+    static_assert(!FIRST || ORD, "a first round on the prepared copy is one of an ordered sweep");
     const int64_t ldx = ORD ? DP : c.ldx;
     constexpr int NB = slab_blocks_of(DP, S);       // blocks of 32 points per wave and slab
     // with 2 blocks at d_pad = 32 the rows of the next slab are requested after the tile loop, when the operand
@@ -548,7 +551,6 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
     const unsigned *const lists = ORD && c.lists ? c.lists + (c.chunk_begin >> kUnitShift) * kListWords : nullptr;
     const uint4 *const xp_chunk = PRE ? c.xp + (c.chunk_begin >> 5) * prep_block_u4_of(DP) : nullptr;    // chunks start on a block boundary
     unsigned listn = 0u, list_moren = 0u;            // the list of the slab being fetched
-    int placen[PRE || FINAL ? 1 : NB];               // places of the points being fetched (first round of an ordered sweep)
     auto load_labels = [&](unsigned pt) -> unsigned {                    // of a point within the chunk
         return (unsigned)*reinterpret_cast<const LabWord *>(prev_chunk + (pt * (unsigned)R + lab_off));
     };
@@ -564,7 +566,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 for (int sl = 0; sl < NP; ++sl) pnext[pb][sl] = bp[sl * 64 + lane];
                 nnext[pb] = reinterpret_cast<const uint2 *>(bp + NP * 64)[n];
                 const unsigned li = min((unsigned)(pb * 32 + n), last);
-                oldn[pb] = load_labels(first + li);
+                if constexpr (!FIRST) oldn[pb] = load_labels(first + li);
             }
             if constexpr (ORD) {
                 if (lists) {
@@ -595,10 +597,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 for (int s = 0; s < H; ++s) xnext[pb][s] = Xs[ro + foff[s]];
             }
             // labels these (point, run) pairs had in the previous round, 0xff before the first one
-            if constexpr (!FINAL && !PRE) {
-                if (c.inv) placen[pb] = c.inv[slab_base + li];       // (first round: there are none yet)
-                else oldn[pb] = load_labels(first + li);
-            }
+            if (!FINAL) oldn[pb] = load_labels(first + li);
         }
     };
     // the outstanding loads of fetch() have to be complete here
@@ -618,12 +617,9 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
 #pragma unroll
                 for (int s = 0; s < H; ++s) asm volatile("" : "+v"(xnext[pb][s]));
         }
-        if constexpr (!FINAL) {
+        if constexpr (!FINAL && !FIRST) {
 #pragma unroll
-            for (int pb = 0; pb < NB; ++pb) {
-                asm volatile("" : "+v"(oldn[pb]));
-                if constexpr (!PRE) asm volatile("" : "+v"(placen[pb]));
-            }
+            for (int pb = 0; pb < NB; ++pb) asm volatile("" : "+v"(oldn[pb]));
         }
     };
     // The chunk is handed out in slabs of SLAB points: one per wave statically, the rest from a counter in
@@ -686,7 +682,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
             int *const ccol = c.cnts + (ln & (c.copies - 1)) * c.real_rows;
             const int nrow = (int)(((unsigned)rec >> 17) & 0xfffu), orow = (int)((unsigned)(rec >> 32) & 0xffffu);
             atomicAdd(ccol + nrow, 1);
-            atomicAdd(ccol + orow, -1);                  // (a logged pair had a label: the first round logs nothing)
+            if (!FIRST || orow != 0xffff) atomicAdd(ccol + orow, -1);
         }
         if (!any_wide) {
             // Every lane takes its features in an order of its own, feature j ^ (g mod FPL) in step j: neighbouring records move
@@ -738,6 +734,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                     if (src < nrec) {
                         unsigned long long *const srow_n = scol + ((lo[u] >> 17) & 0xfffu) * (DP + 1);
                         unsigned long long *const srow_o = scol + (hi[u] & 0xffffu) * (DP + 1);
+                        const int enters = FIRST && (hi[u] & 0xffffu) == 0xffffu;         // nothing to take back
 #pragma unroll
                         for (int h = 0; h < FPL / 4; ++h) order4(xv[u][4 * h], xv[u][4 * h + 1], xv[u][4 * h + 2], xv[u][4 * h + 3]);
 #pragma unroll
@@ -745,7 +742,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                             const unsigned long long v = fixed_biased(xv[u][j], pow2hi[j]);
                             const int at = j ^ swz;
                             atomicAdd(srow_n + at, v);
-                            __hip_atomic_fetch_sub(srow_o + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                            if (!FIRST || enters == 0) __hip_atomic_fetch_sub(srow_o + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                         }
                     }
                 }
@@ -788,12 +785,12 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                         if (fq + j >= d) continue;
                         const unsigned long long v = (unsigned long long)to_fixed(xv[u][j], c.shift_s[fq + j]) + kFixBias;
                         atomicAdd(srow_n + j, v);
-                        __hip_atomic_fetch_sub(srow_o + j, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        if (!FIRST || orow != 0xffff) __hip_atomic_fetch_sub(srow_o + j, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                         if (c.wide_s[fq + j] != 0) {
                             // bits below the grid of a wide column go to a global integer accumulator (rare)
                             const long long low = fixed_low(xv[u][j], c.shift_s[fq + j]);
                             if (low != 0) {
-                                atomicAdd(reinterpret_cast<unsigned long long *>(&c.losum[(int64_t)(c.grow0 + orow) * d + fq + j]), (unsigned long long)(-low));
+                                if (!FIRST || orow != 0xffff) atomicAdd(reinterpret_cast<unsigned long long *>(&c.losum[(int64_t)(c.grow0 + orow) * d + fq + j]), (unsigned long long)(-low));
                                 atomicAdd(reinterpret_cast<unsigned long long *>(&c.losum[(int64_t)(c.grow0 + nrow) * d + fq + j]), (unsigned long long)low);
                             }
                         }
@@ -836,11 +833,6 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         float xn[NB];
         int m1[NB][ST], m2[NB][ST];
         unsigned oldl[NB];                // labels in the previous round, one byte per run of this lane
-        int place[PRE || FINAL ? 1 : NB];
-        if constexpr (!PRE && !FINAL) {
-#pragma unroll
-            for (int pb = 0; pb < NB; ++pb) place[pb] = placen[pb];
-        }
         // the tiles this slab meets: all of them in order, or those of its unit's list - this lane's slot meets its own ones
         const unsigned list = listn, list_more = list_moren;
         bool listed = false;
@@ -1163,9 +1155,9 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                     xs[H + s] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), (src & 31) + 32));
                 }
                 int arg = exact_argmin_wave<DP>(xs, crun, CS, c.k0 + srl);
-                if constexpr (!FINAL && (ORD || !PRE)) {
+                if constexpr (ORD) {
                     const int rowbase = srl * c.k0 + srl * (srl - 1) / 2;
-                    if (ORD || c.rowpos) arg = (int)c.rowpos[rowbase + arg] - rowbase;
+                    arg = (int)c.rowpos[rowbase + arg] - rowbase;
                 }
                 if (lane == src) {
                     pend &= pend - 1u;
@@ -1245,7 +1237,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
             }
             neww[pb] = w;
             diffw[pb] = 0u;
-            if (!FINAL) diffw[pb] = pvalid[pb] ? ((w ^ oldl[pb]) & actmask) : 0u;
+            if constexpr (!FINAL && !FIRST) diffw[pb] = pvalid[pb] ? ((w ^ oldl[pb]) & actmask) : 0u;
         }
         if constexpr (!FINAL && !PRE) {
             bool any = false;
@@ -1262,6 +1254,35 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         if constexpr (PRE) {
             // Exact sums, later: the moved pairs go into this wave's log; 64 records at a time are worked off below.
             static_assert(64 * NBST + 63 <= kLogCap, "a slab's records and what an earlier flush left over must fit the ring");
+            int from[FIRST ? NB : 1][FIRST ? ST : 1];           // FIRST: the row a point comes from, or 0xffff
+            if constexpr (FIRST) {
+                // No point has a label yet, so every one enters a cluster of every run - but the centroids of a run are those of
+                // the run before and one more, and most points keep the nearest one they had there.  Only the group's first
+                // run is filled point by point; a later run logs the points whose centroid is another one than in the run
+                // before it, as moves, and its sums are those of the run before plus what its own log moved (put together
+                // when the workgroup is done).  (Wide columns: their low-order sums are global, every run is filled.)
+#pragma unroll
+                for (int pb = 0; pb < NB; ++pb) {
+                    int idx[ST];                                // the labels as indices
+#pragma unroll
+                    for (int st = 0; st < ST; ++st) {
+                        const unsigned rb = row0 + (unsigned)st * row_step + (unsigned)(st * (st - 1) / 2);
+                        const bool real = ((actmask >> (8 * st)) & 0xffu) != 0u && pvalid[pb];
+                        idx[st] = real ? (int)c.rowidx[rb + (unsigned)(m1[pb][st] & 127)] : 0;
+                    }
+                    const int below = xchg32(idx[ST - 1]);      // the last run of the lower half-wave
+#pragma unroll
+                    for (int st = 0; st < ST; ++st) {
+                        const unsigned rb = row0 + (unsigned)st * row_step + (unsigned)(st * (st - 1) / 2);
+                        const bool real = ((actmask >> (8 * st)) & 0xffu) != 0u && pvalid[pb];
+                        const bool fills = any_wide || (hl == 0 && st == 0);
+                        const int before = st == 0 ? below : idx[st > 0 ? st - 1 : 0];
+                        const bool logs = real && (fills || before != idx[st]);
+                        from[pb][st] = logs && !fills ? (int)c.rowpos[rb + (unsigned)before] : 0xffff;
+                        diffw[pb] |= logs ? 0xffu << (8 * st) : 0u;
+                    }
+                }
+            }
             unsigned any_diff = 0u;
 #pragma unroll
             for (int pb = 0; pb < NB; ++pb) any_diff |= diffw[pb];
@@ -1284,7 +1305,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                         asm volatile("" : "+v"(step));
                         const unsigned rowbase = row0 + (unsigned)st * step + (unsigned)(st * (st - 1) / 2);
                         const unsigned lo = pt | ((rowbase + (unsigned)(m1[pb][st] & 127)) << 17);         // rows: below 2^12
-                        const unsigned hi = rowbase + (unsigned)old_of(pb, st);
+                        const unsigned hi = FIRST ? (unsigned)from[FIRST ? pb : 0][FIRST ? st : 0] : rowbase + (unsigned)old_of(pb, st);
                         c.log[pos & (kLogCap - 1)] = ((unsigned long long)hi << 32) | lo;
                     }
                     log_tail += (int)__popcll(bal);
@@ -1437,12 +1458,8 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 }
             } else {
                 // a word with a changed byte is written back whole (bytes of run slots without a run are never looked at)
-                if (diffw[pb] != 0u) {
-                    unsigned char *at = prev_chunk + (ptl[pb] * (unsigned)R + lab_off);
-                    if constexpr (!PRE && !FINAL)
-                        if (c.inv) at = c.prev + ((int64_t)place[pb] * R + lab_off);
-                    *reinterpret_cast<LabWord *>(at) = (LabWord)neww[pb];
-                }
+                if (FIRST ? pvalid[pb] && actmask != 0u : diffw[pb] != 0u)
+                    *reinterpret_cast<LabWord *>(prev_chunk + (ptl[pb] * (unsigned)R + lab_off)) = (LabWord)neww[pb];
             }
         }
         cur = nxt;
@@ -1551,19 +1568,18 @@ __device__ __forceinline__ void make_lists(const WaveCtx &c, const uint4 *centre
     }
 }
 
-template <int DP, bool FINAL, bool TRACE, bool VEC, bool PRE, bool ORD>
+template <int DP, bool FINAL, bool TRACE, bool VEC, bool PRE, bool ORD, bool FIRST>
 __device__ inline void wave_loop_of(int S, const WaveCtx &c, double (&jloc)[8])
 {
     switch (S) {
-    case 1: wave_loop<DP, 1, FINAL, TRACE, VEC, PRE, ORD>(c, jloc); break;
-    case 2: wave_loop<DP, 2, FINAL, TRACE, VEC, PRE, ORD>(c, jloc); break;
-    case 4: wave_loop<DP, 4, FINAL, TRACE, VEC, PRE, ORD>(c, jloc); break;
-    default: wave_loop<DP, 8, FINAL, TRACE, VEC, PRE, ORD>(c, jloc); break;
+    case 1: wave_loop<DP, 1, FINAL, TRACE, VEC, PRE, ORD, FIRST>(c, jloc); break;
+    case 2: wave_loop<DP, 2, FINAL, TRACE, VEC, PRE, ORD, FIRST>(c, jloc); break;
+    case 4: wave_loop<DP, 4, FINAL, TRACE, VEC, PRE, ORD, FIRST>(c, jloc); break;
+    default: wave_loop<DP, 8, FINAL, TRACE, VEC, PRE, ORD, FIRST>(c, jloc); break;
     }
 }
 
-// ORD: a round on the ordered copy of the points.  (The first round of an ordered sweep takes the points as they come.)
-template <int DP, bool FINAL, bool TRACE, bool PRE, bool ORD>
+template <int DP, bool FINAL, bool TRACE, bool PRE, bool ORD, bool FIRST>
 __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPlan plan, StepArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1612,14 +1628,14 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     const int grow0 = rows_before(plan.k_min, g.run0);                    // first centroid row of the group
     const int real_rows = rows_before(plan.k_min, g.run0 + g.n_runs) - grow0;
     const int copies = g.copies;
-    const bool ordered = ORD || (!PRE && a.ordered != 0);
-    const Carve cv = carve_lds(DP, d, g.n_tiles, real_rows, copies, ordered);
+    const Carve cv = carve_lds(DP, d, g.n_tiles, real_rows, copies, ORD);
 
     uint4 *opA_s = reinterpret_cast<uint4 *>(smem + cv.opA);
     float *cs_lds = reinterpret_cast<float *>(smem + cv.cs);
     unsigned long long *sums = reinterpret_cast<unsigned long long *>(smem + cv.sums);
     int *cnts = reinterpret_cast<int *>(smem + cv.cnts);
     unsigned short *rowpos_s = reinterpret_cast<unsigned short *>(smem + cv.rowpos);
+    unsigned char *rowidx_s = smem + cv.rowidx;
     float *mu_s = reinterpret_cast<float *>(smem + cv.misc);              // [32]
     int *shift_s = reinterpret_cast<int *>(smem + cv.misc + 128);         // [32]
     int *wide_s = reinterpret_cast<int *>(smem + cv.misc + 256);          // [32] + any at [32]
@@ -1692,9 +1708,13 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
             pow2hi_s[tid] = (1023 + shift_v) << 20;                        // 2^shift as a double: the high word
         }
         if (tid < 33) wide_s[tid] = wide_v;
-        if (!FINAL && ordered) {
+        if constexpr (ORD) {
             const unsigned short *rowpos = reinterpret_cast<const unsigned short *>(wsb + a.off_rowpos) + grow0;
-            for (int e = tid; e < real_rows; e += TH) rowpos_s[e] = rowpos[e];
+            const unsigned char *rowidx = reinterpret_cast<const unsigned char *>(wsb + a.off_rowidx) + grow0;
+            for (int e = tid; e < real_rows; e += TH) {
+                rowpos_s[e] = rowpos[e];
+                if (FIRST) rowidx_s[e] = rowidx[e];
+            }
             // the tile of padding rows, as sweep_init_kernel makes them
             unsigned ph, pm, pl;
             split3(kPadNorm, ph, pm, pl);
@@ -1723,8 +1743,8 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     c.scale = *reinterpret_cast<const float *>(wsb + a.off_colinfo + kColScaleOff);
     c.xp = reinterpret_cast<const uint4 *>(wsb + a.off_xp);
     c.log = reinterpret_cast<unsigned long long *>(wsb + a.off_log) + ((int64_t)(g.wg0 + chunk) * WV + __builtin_amdgcn_readfirstlane(tid >> 6)) * kLogCap;
-    c.rowpos = !FINAL && ordered ? rowpos_s : nullptr;
-    c.inv = !PRE && !FINAL && ordered ? reinterpret_cast<const int32_t *>(wsb + a.off_inv) : nullptr;
+    c.rowpos = rowpos_s;
+    c.rowidx = rowidx_s;
     c.lists = nullptr;
     c.X = Xb; c.ldx = a.ldx; c.N = a.N; c.d = d; c.k0 = k0; c.n_runs = g.n_runs; c.n_tiles = g.n_tiles; c.grow0 = grow0;
     c.prev = reinterpret_cast<unsigned char *>(wsb + a.off_prev) + (int64_t)g.lab0 * ((a.N + 15) / 16 * 16);
@@ -1773,10 +1793,10 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
 
     // (a chunk is never empty)
     if constexpr (ORD) {
-        wave_loop_of<DP, FINAL, TRACE, true, PRE, ORD>(g.S, c, jloc);
+        wave_loop_of<DP, FINAL, TRACE, true, PRE, ORD, FIRST>(g.S, c, jloc);
     } else {
-        if (c.vec_x) wave_loop_of<DP, FINAL, TRACE, true, PRE, ORD>(g.S, c, jloc);
-        else wave_loop_of<DP, FINAL, TRACE, false, PRE, ORD>(g.S, c, jloc);
+        if (c.vec_x) wave_loop_of<DP, FINAL, TRACE, true, PRE, ORD, FIRST>(g.S, c, jloc);
+        else wave_loop_of<DP, FINAL, TRACE, false, PRE, ORD, FIRST>(g.S, c, jloc);
     }
 
     if (FINAL || TRACE) {
@@ -1794,21 +1814,39 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     if (!FINAL) {
         unsigned long long *psum = reinterpret_cast<unsigned long long *>(wsb + a.off_psum) +
                                    ((int64_t)g.part0 + (int64_t)chunk * real_rows) * d;
+        // the accumulator rows that make up a centroid: its own; after a first round on the ordered copy also those of the same
+        // centroid in the group's earlier runs (see FIRST above)
+        const bool adds_up = FIRST && c.wide_s[32] == 0;
+        auto each_row = [&](int e, auto &&use) {
+            if (!ORD) {
+                use(e);
+            } else {
+                use((int)rowpos_s[e]);
+                if (FIRST && adds_up) {
+                    int r = 0;
+                    while (r + 1 < g.n_runs && (r + 1) * k0 + (r + 1) * r / 2 <= e) ++r;
+                    const int j = e - (r * k0 + r * (r - 1) / 2);
+                    for (int q = r - 1; q >= 0 && j < k0 + q; --q) use((int)rowpos_s[q * k0 + q * (q - 1) / 2 + j]);
+                }
+            }
+        };
         for (int e = tid; e < real_rows * d; e += TH) {
             unsigned long long v = 0ull;
             long long rows_in = 0;     // rows that entered minus rows that left: each carried the bias once
-            const int row = ordered ? rowpos_s[e / d] : e / d;
-            for (int cp = 0; cp < copies; ++cp) {
-                v += sums[(cp * real_rows + row) * (DP + 1) + e % d];
-                rows_in += cnts[cp * real_rows + row];
-            }
+            each_row(e / d, [&](int row) {
+                for (int cp = 0; cp < copies; ++cp) {
+                    v += sums[(cp * real_rows + row) * (DP + 1) + e % d];
+                    rows_in += cnts[cp * real_rows + row];
+                }
+            });
             psum[e] = v - kFixBias * (unsigned long long)rows_in;
         }
         int *pcnt = reinterpret_cast<int *>(wsb + a.off_pcnt) + (int64_t)g.part0 + (int64_t)chunk * real_rows;
         for (int e = tid; e < real_rows; e += TH) {
             int v = 0;
-            const int row = ordered ? rowpos_s[e] : e;
-            for (int cp = 0; cp < copies; ++cp) v += cnts[cp * real_rows + row];
+            each_row(e, [&](int row) {
+                for (int cp = 0; cp < copies; ++cp) v += cnts[cp * real_rows + row];
+            });
             pcnt[e] = v;
         }
     }
@@ -2064,6 +2102,46 @@ __global__ void __launch_bounds__(256) lloyd_prepare_kernel(const float *__restr
     }
 }
 
+// Sums in two doubles (the second holds what the first cannot): error-free sums and products of doubles, about 106 bits.
+struct Twofold {
+    double hi, lo;
+};
+__device__ inline Twofold twofold_sum(double a, double b)
+{
+    const double s = a + b, t = s - a;
+    return {s, (a - (s - t)) + (b - t)};
+}
+__device__ inline Twofold twofold_add(Twofold a, Twofold b)
+{
+    const Twofold s = twofold_sum(a.hi, b.hi);
+    const double lo = s.lo + (a.lo + b.lo), hi = s.hi + lo;
+    return {hi, lo - (hi - s.hi)};
+}
+__device__ inline Twofold twofold_product(double a, double b)
+{
+    const double p = a * b;
+    return {p, fma(a, b, -p)};
+}
+__device__ inline Twofold twofold_times(Twofold a, double b)
+{
+    const Twofold p = twofold_product(a.hi, b);
+    const double lo = fma(a.lo, b, p.lo), hi = p.hi + lo;
+    return {hi, lo - (hi - p.hi)};
+}
+__device__ inline Twofold twofold_wave_sum(Twofold v)
+{
+    for (int off = 32; off >= 1; off >>= 1) v = twofold_add(v, Twofold{__shfl_xor(v.hi, off, 64), __shfl_xor(v.lo, off, 64)});
+    return v;
+}
+// a 128-bit two's complement number, scaled by 2^-shift
+__device__ inline Twofold twofold_of_fixed(long long hi, unsigned long long lo, int shift)
+{
+    const Twofold low = twofold_sum((double)(lo >> 32) * 4294967296.0, (double)(lo & 0xffffffffull));       // both exact
+    const Twofold high = twofold_sum((double)(hi >> 32) * 4294967296.0 * 18446744073709551616.0, (double)((unsigned long long)hi & 0xffffffffull) * 18446744073709551616.0);
+    const Twofold v = twofold_add(high, low);
+    return {ldexp(v.hi, -shift), ldexp(v.lo, -shift)};
+}
+
 // ---- the same for an ordered sweep: the copy is in the order of the places, the rows go along (padded with zeros to DP
 //      floats, so that rows of any length are read 16 bytes at a time later on), and every unit leaves its centre - the mean
 //      of its points as the operand pieces hold it - and an upper bound of the distance from there to its points.
@@ -2071,7 +2149,7 @@ template <int DP>
 __global__ void __launch_bounds__(256) lloyd_prepare_ordered_kernel(const float *__restrict__ X, int64_t N, int d, int64_t ldx, int64_t x_bs,
                                                                     const int32_t *__restrict__ status, char *ws, int64_t ws_bs,
                                                                     int64_t off_colinfo, int64_t off_perm, int64_t off_xp, int64_t off_xs,
-                                                                    int64_t off_centres, int64_t off_radius)
+                                                                    int64_t off_centres, int64_t off_radius, int64_t off_rowsq)
 {
     constexpr int H = DP / 2, NK = ksteps_of(DP), HP = 8 * NK, UB = unit_blocks_of(DP);
     const int b = blockIdx.y;
@@ -2090,6 +2168,8 @@ __global__ void __launch_bounds__(256) lloyd_prepare_ordered_kernel(const float 
     float mean_h[H];
 #pragma unroll
     for (int s = 0; s < H; ++s) mean_h[s] = f0 + s < d ? colmean[f0 + s] : 0.0f;
+    const float back = -1.0f / scale;                 // (exact: a power of two)
+    Twofold sq = {0.0, 0.0};                          // squared distances of this thread's elements from the column means
     // operand pieces of one lane's half of a row, and the norm of the row
     auto pieces = [&](const float (&xc)[HP], float norm, uint4 *bp, int at, bool store) {
 #pragma unroll
@@ -2144,7 +2224,11 @@ __global__ void __launch_bounds__(256) lloyd_prepare_ordered_kernel(const float 
             }
             pieces(xc[ub], xn, xp + blk * prep_block_u4_of(DP), n, blk < n_blocks);
 #pragma unroll
-            for (int s = 0; s < H; ++s) sum[s] += xc[ub][s];
+            for (int s = 0; s < H; ++s) {
+                sum[s] += xc[ub][s];
+                const double off = valid && f0 + s < d ? (double)xr[s] - (double)(mean_h[s] * back) : 0.0;
+                sq = twofold_add(sq, twofold_product(off, off));
+            }
         }
         const float inv_n = 1.0f / (float)min(N - unit * (32 * UB), (int64_t)(32 * UB));
         float bc[HP];
@@ -2177,13 +2261,23 @@ __global__ void __launch_bounds__(256) lloyd_prepare_ordered_kernel(const float 
         pieces(bc, norm, centres + (unit >> 5) * prep_block_u4_of(DP), (int)(unit & 31), n == 0);
         if (lane == 0) radius[unit] = sqrtf(far) * 1.00001f + 1.0e-6f;     // (rounding of the differences: below d 2^-24 of it)
     }
+    __shared__ Twofold part[4];
+    sq = twofold_wave_sum(sq);
+    if (lane == 0) part[threadIdx.x >> 6] = sq;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        reinterpret_cast<Twofold *>(wsb + off_rowsq)[blockIdx.x] = twofold_add(twofold_add(part[0], part[1]), twofold_add(part[2], part[3]));
 }
+
+// workgroups of lloyd_prepare_ordered_kernel: 4 waves each, about 4 units per wave
+constexpr int kPrepareGrid = 4096;
+inline int64_t ordered_prepare_grid(int64_t n_units) { return std::min<int64_t>((n_units + 4 * 4 - 1) / (4 * 4), kPrepareGrid); }
 
 // Places of the centroids of every run, in the order of the points they start from: centroids that lie close together share
 // quads, and a unit meets fewer of them (1M x 16, k = 64: 3.3 tiles instead of 5.7).  The places stay for the whole sweep.
 __global__ void __launch_bounds__(RLS_MAX_K) lloyd_rowpos_kernel(SweepPlan plan, const int64_t *__restrict__ init_idx, int64_t init_bs,
                                                                  const int32_t *__restrict__ status, char *ws, int64_t ws_bs,
-                                                                 int64_t off_inv, int64_t off_rowpos, OrderSpread sp)
+                                                                 int64_t off_inv, int64_t off_rowpos, int64_t off_rowidx, OrderSpread sp)
 {
     __shared__ int at[RLS_MAX_K];
     const int b = blockIdx.y, run = blockIdx.x, k = plan.k_min + run, j = threadIdx.x;
@@ -2203,6 +2297,7 @@ __global__ void __launch_bounds__(RLS_MAX_K) lloyd_rowpos_kernel(SweepPlan plan,
     while (gi + 1 < plan.n_groups && plan.g[gi + 1].run0 <= run) ++gi;
     const int row0 = rows_before(plan.k_min, run);
     reinterpret_cast<unsigned short *>(wsb + off_rowpos)[row0 + j] = (unsigned short)(row0 - rows_before(plan.k_min, plan.g[gi].run0) + pos);
+    reinterpret_cast<unsigned char *>(wsb + off_rowidx)[row0 + pos] = (unsigned char)j;
 }
 
 // ---- start of a sweep: padding operand rows are zero vectors with a huge norm; running totals are zero;
@@ -2339,7 +2434,7 @@ struct CentroidArgs {
     int64_t ws_bs;
     int64_t off_colinfo, off_opA, off_cnmax, off_psum, off_pcnt, off_losum, off_tot, off_totcnt;
     int64_t off_rowpos;          // places of the centroids among the rows of their group, or -1: by index
-    int32_t operands_by_index;   // 1: the operand rows made now are laid out by index all the same (for the final pass)
+    int64_t off_losspart;        // (loss of an ordered sweep)
 };
 
 // One workgroup per run and part of kPartRows of its centroids: new centroids (from the seeding rows, or from the
@@ -2388,13 +2483,9 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
     const int run_row = row0 - rows_before(plan.k_min, g.run0);      // the run's first row in its group
     const unsigned short *rowpos = a.off_rowpos >= 0 ? reinterpret_cast<const unsigned short *>(wsb + a.off_rowpos) + row0 + j0 : nullptr;
     int place = j0 + tid / DP, place_n = j0 + tid;                   // of the element's centroid; of this thread's when it takes norms
-    int sum_place = place;                                           // of the element's low-order sum
     if (rowpos) {
-        if (tid < E) sum_place = rowpos[tid / DP] - run_row;
-        if (!a.operands_by_index) {
-            place = sum_place;
-            if (tid < rows) place_n = rowpos[tid] - run_row;
-        }
+        if (tid < E) place = rowpos[tid / DP] - run_row;
+        if (tid < rows) place_n = rowpos[tid] - run_row;
     }
     if (tid < E && tid % DP < d) {
         const int l = tid % DP;
@@ -2456,7 +2547,7 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
                 int shift = col_shift;
                 if (col_wide) {
                     // total = main * 2^kLowBits + low, on the scale 2^-(shift + kLowBits)
-                    const long long low = reinterpret_cast<const long long *>(wsb + a.off_losum)[(int64_t)(row0 + sum_place) * d + l];
+                    const long long low = reinterpret_cast<const long long *>(wsb + a.off_losum)[(int64_t)(row0 + place) * d + l];
                     hi = (long long)(((unsigned long long)hi << kLowBits) | (lo >> (64 - kLowBits)));
                     lo = lo << kLowBits;
                     const unsigned long long nlo = lo + (unsigned long long)low;
@@ -2507,6 +2598,158 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
     }
 }
 
+// ---- the end of an ordered sweep.  The loss of a run without a look at the points: with every coordinate taken from its
+//      column's mean m, the members of a cluster with centroid c, n members and exact sum S are at
+//         sum |x - c|^2 = sum |x - m|^2 - 2 (c - m).(S - n m) + n |c - m|^2,
+//      and the first sum over all clusters is that of all points (lloyd_prepare_ordered_kernel).  In two doubles, where what
+//      cancels between the terms is far below the last bit of the result.
+//      One workgroup per run and part of its centroids, as in lloyd_centroids_kernel: the sums after the final assignment.
+template <int DP>
+__global__ void __launch_bounds__(kThreads) lloyd_ordered_loss_kernel(SweepPlan plan, CentroidArgs a)
+{
+    __shared__ long long part_hi[kThreads], part_cnt[kThreads];
+    __shared__ unsigned long long part_lo[kThreads];
+    __shared__ Twofold wave_part[kThreads / 64];
+    const int b = blockIdx.y, tid = threadIdx.x;
+    if (a.status[b] != 0) return;
+    const int parts0 = parts_upto(plan.k_min - 1);
+    int run = 0;
+    for (int step = 64; step >= 1; step >>= 1)
+        if (run + step < plan.n_runs && parts_upto(plan.k_min + run + step - 1) - parts0 <= (int)blockIdx.x) run += step;
+    const int d = a.d, k = plan.k_min + run;
+    const int part = (int)blockIdx.x - (parts_upto(k - 1) - parts0);
+    const int j0 = part * kPartRows, rows = min(kPartRows, k - j0);
+    const int row0 = rows_before(plan.k_min, run);
+    int gi = 0;
+    while (gi + 1 < plan.n_groups && plan.g[gi + 1].run0 <= run) ++gi;
+    const GroupDesc g = plan.g[gi];
+    const int grow0 = rows_before(plan.k_min, g.run0), grows = rows_before(plan.k_min, g.run0 + g.n_runs) - grow0;
+    char *wsb = a.ws + (int64_t)b * a.ws_bs;
+    const int E = rows * DP, nsl = kThreads / E;
+    const int e = tid % E, sl = tid / E, j = j0 + e / DP, l = e % DP;
+    const int64_t at = (int64_t)(row0 + j) * d + l;
+    long long hi = 0, cnt = 0;
+    unsigned long long lo = 0;
+    if (sl < nsl && l < d) {
+        const int64_t first = (int64_t)g.part0 + row0 - grow0 + j;
+        const long long *psum = reinterpret_cast<const long long *>(wsb + a.off_psum) + first * d + l;
+        const int *pcnt = reinterpret_cast<const int *>(wsb + a.off_pcnt) + first;
+        const int c_begin = (int)((int64_t)g.n_chunks * sl / nsl), c_end = (int)((int64_t)g.n_chunks * (sl + 1) / nsl);
+        if (sl == 0) {
+            const long long *tot = reinterpret_cast<const long long *>(wsb + a.off_tot) + at * 2;
+            hi = tot[0];
+            lo = (unsigned long long)tot[1];
+            cnt = reinterpret_cast<const long long *>(wsb + a.off_totcnt)[at];
+        }
+        sum_chunks(psum, pcnt, (int64_t)grows * d, grows, c_begin, c_end, hi, lo, cnt);
+    }
+    part_hi[tid] = hi; part_lo[tid] = lo; part_cnt[tid] = cnt;
+    __syncthreads();
+    Twofold v = {0.0, 0.0};
+    if (tid < E && l < d) {
+        for (int s = 1; s < nsl; ++s) {
+            const unsigned long long nlo = lo + part_lo[s * E + e];
+            hi += part_hi[s * E + e] + (nlo < lo ? 1 : 0);
+            lo = nlo;
+            cnt += part_cnt[s * E + e];
+        }
+        int shift = reinterpret_cast<const int *>(wsb + a.off_colinfo + 128)[l];
+        if (reinterpret_cast<const int *>(wsb + a.off_colinfo + 256)[l] != 0) {
+            // total = main * 2^kLowBits + low, on the scale 2^-(shift + kLowBits)
+            const int place = (int)reinterpret_cast<const unsigned short *>(wsb + a.off_rowpos)[row0 + j];
+            const long long low = reinterpret_cast<const long long *>(wsb + a.off_losum)[(int64_t)(grow0 + place) * d + l];
+            hi = (long long)(((unsigned long long)hi << kLowBits) | (lo >> (64 - kLowBits)));
+            lo = lo << kLowBits;
+            const unsigned long long nlo = lo + (unsigned long long)low;
+            hi += (low >> 63) + (nlo < lo ? 1 : 0);
+            lo = nlo;
+            shift += kLowBits;
+        }
+        const float scale = *reinterpret_cast<const float *>(wsb + a.off_colinfo + kColScaleOff);
+        const double mean = (double)(reinterpret_cast<const float *>(wsb + a.off_colinfo)[l] * (-1.0f / scale)), n = (double)cnt;
+        const Twofold sum = twofold_add(twofold_of_fixed(hi, lo, shift), twofold_product(-n, mean));
+        const double c = (double)(a.C + (int64_t)b * a.c_bs)[at] - mean;
+        // c (n c - 2 S)
+        const Twofold nc = twofold_product(n, c);
+        v = twofold_times(twofold_add(nc, Twofold{-2.0 * sum.hi, -2.0 * sum.lo}), c);
+    }
+    v = twofold_wave_sum(v);
+    if ((tid & 63) == 0) wave_part[tid >> 6] = v;
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < kThreads / 64; ++w) v = twofold_add(v, wave_part[w]);
+        reinterpret_cast<Twofold *>(wsb + a.off_losspart)[run * kMaxParts + part] = v;
+    }
+}
+
+__global__ void __launch_bounds__(1024) lloyd_ordered_loss_final_kernel(SweepPlan plan, const int32_t *status, const char *ws, int64_t ws_bs, int64_t off_losspart,
+                                                                        int64_t off_rowsq, int n_rowsq, double *out, int64_t out_bs)
+{
+    __shared__ Twofold wave_part[16];
+    const int b = blockIdx.x, tid = threadIdx.x;
+    if (status[b] != 0) return;
+    const char *wsb = ws + (int64_t)b * ws_bs;
+    const Twofold *rowsq = reinterpret_cast<const Twofold *>(wsb + off_rowsq);
+    Twofold v = {0.0, 0.0};
+    for (int i = tid; i < n_rowsq; i += 1024) v = twofold_add(v, rowsq[i]);
+    v = twofold_wave_sum(v);
+    if ((tid & 63) == 0) wave_part[tid >> 6] = v;
+    __syncthreads();
+    if (tid >= plan.n_runs) return;
+    v = wave_part[0];
+    for (int w = 1; w < 16; ++w) v = twofold_add(v, wave_part[w]);
+    const Twofold *part = reinterpret_cast<const Twofold *>(wsb + off_losspart) + tid * kMaxParts;
+    const int n_parts = (plan.k_min + tid + kPartRows - 1) / kPartRows;
+    for (int p = 0; p < n_parts; ++p) v = twofold_add(v, part[p]);
+    out[(int64_t)b * out_bs + tid] = fmax(v.hi + v.lo, 0.0);
+}
+
+// The labels in the order of the points: every thread takes four points, looks up their places and, group by group, the label
+// bytes there (a read of up to eight bytes), and writes the labels of each run side by side.
+constexpr int kLabelPoints = 1024;
+__global__ void __launch_bounds__(256) lloyd_ordered_labels_kernel(SweepPlan plan, const int32_t *status, const char *ws, int64_t ws_bs, int64_t N,
+                                                                   int64_t off_inv, int64_t off_rowidx, int64_t off_prev, int32_t *labels, int64_t lab_bs)
+{
+    extern __shared__ unsigned char rowidx_s[];              // centroid of its run by place, all runs
+    constexpr int U = kLabelPoints / 256;
+    const int b = blockIdx.y, tid = threadIdx.x;
+    if (status[b] != 0) return;
+    const char *wsb = ws + (int64_t)b * ws_bs;
+    for (int e = tid; e < plan.total_rows; e += 256) rowidx_s[e] = reinterpret_cast<const unsigned char *>(wsb + off_rowidx)[e];
+    int64_t p[U];
+    int place[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        p[u] = (int64_t)blockIdx.x * kLabelPoints + u * 256 + tid;
+        place[u] = reinterpret_cast<const int32_t *>(wsb + off_inv)[min(p[u], N - 1)];
+    }
+    __syncthreads();
+    int32_t *const out = labels + (int64_t)b * lab_bs;
+    const int64_t n16 = (N + 15) / 16 * 16;
+    for (int gi = 0; gi < plan.n_groups; ++gi) {
+        const GroupDesc g = plan.g[gi];
+        const unsigned char *prev = reinterpret_cast<const unsigned char *>(wsb + off_prev) + g.lab0 * n16;
+        const int R = 8 / g.S;
+        uint2 w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const unsigned char *at = prev + (int64_t)place[u] * R;
+            w[u].y = 0u;
+            if (R == 8) w[u] = *reinterpret_cast<const uint2 *>(at);
+            else if (R == 4) w[u].x = *reinterpret_cast<const unsigned *>(at);
+            else if (R == 2) w[u].x = *reinterpret_cast<const unsigned short *>(at);
+            else w[u].x = *at;
+        }
+        for (int r = 0; r < g.n_runs; ++r) {
+            const int row0 = rows_before(plan.k_min, g.run0 + r);
+            int32_t *const run = out + (int64_t)(g.run0 + r) * N;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (p[u] < N) run[p[u]] = rowidx_s[row0 + (((r < 4 ? w[u].x : w[u].y) >> (8 * (r & 3))) & 127u)];
+        }
+    }
+}
+
 // sum of the per-chunk partial losses of every run, in chunk order
 __global__ void lloyd_loss_kernel(SweepPlan plan, const int32_t *status, const char *ws, int64_t ws_bs,
                                   int64_t off_pj, double *out, int64_t out_bs, int64_t out_stride, int64_t out_off)
@@ -2539,11 +2782,12 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
     static hipError_t attr_status = hipSuccess;
     std::call_once(attr_once, [] {
         const void *fns[] = {
-            reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, false, false, false>),
-            reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, false, true, false>),
-            reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, false, true, true>),
-            reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, true, false, false>),
-            reinterpret_cast<const void *>(lloyd_step_kernel<DP, true, false, false, false>),
+            reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, false, false, false, false>),
+            reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, false, true, false, false>),
+            reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, false, true, true, true>),
+            reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, false, true, true, false>),
+            reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, true, false, false, false>),
+            reinterpret_cast<const void *>(lloyd_step_kernel<DP, true, false, false, false, false>),
         };
         for (const void *fn : fns) {
             const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -2558,6 +2802,7 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
     const bool trace = a.trace != nullptr;
     const bool use_pre = sweep_uses_prepared(plan, a.iters, trace);
     const bool ordered = use_pre && plan.ordered;
+    const int64_t n_units = (a.N + 32 * unit_blocks_of(DP) - 1) / (32 * unit_blocks_of(DP));
     // column statistics
     if (!a.reuse_colstats) {
         hipLaunchKernelGGL(colstats_kernel, dim3(L.stat_blocks, batch), dim3(kThreads), 0, s, a.X, a.N, (int)a.d, DP, a.ldx,
@@ -2569,10 +2814,8 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
         const hipError_t e = launch_order(a.X, a.N, a.ldx, a.x_batch_stride, batch, a.status, a.ws, L.per_batch, L.keyinfo, L.perm, L.inv, L.xs,
                                           unit_blocks_of(DP) == 2 ? 6 : 5, s);
         if (e != hipSuccess) return e;
-        const int64_t n_units = (a.N + 32 * unit_blocks_of(DP) - 1) / (32 * unit_blocks_of(DP));
-        const int64_t grid_x = std::min<int64_t>((n_units + 4 * 4 - 1) / (4 * 4), 4096);     // 4 waves per workgroup, ~4 units per wave
-        hipLaunchKernelGGL((lloyd_prepare_ordered_kernel<DP>), dim3((unsigned)grid_x, batch), dim3(256), 0, s, a.X, a.N, (int)a.d, a.ldx,
-                           a.x_batch_stride, a.status, a.ws, L.per_batch, L.colinfo, L.perm, L.xp, L.xs, L.centres, L.radius);
+        hipLaunchKernelGGL((lloyd_prepare_ordered_kernel<DP>), dim3((unsigned)ordered_prepare_grid(n_units), batch), dim3(256), 0, s, a.X, a.N,
+                           (int)a.d, a.ldx, a.x_batch_stride, a.status, a.ws, L.per_batch, L.colinfo, L.perm, L.xp, L.xs, L.centres, L.radius, L.rowsq);
     } else if (use_pre && !a.reuse_prepared) {
         // the prepared copy: one wave per block of 32 points, a few blocks per wave
         const int64_t n_blocks = (a.N + 31) / 32;
@@ -2587,11 +2830,11 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
     ia.off_opA = L.opA; ia.off_losum = L.losum; ia.off_tot = L.tot; ia.off_totcnt = L.totcnt; ia.off_prev = L.prev;
     ia.n_tiles = plan.total_tiles; ia.dp = DP;
     ia.n_losum = (int64_t)plan.total_rows * a.d; ia.n_tot = ia.n_losum * 2; ia.n_totcnt = ia.n_losum;
-    ia.n_prev16 = (int64_t)plan.lab_slots * align_up(a.N, 16) / 16;
+    ia.n_prev16 = ordered ? 0 : (int64_t)plan.lab_slots * align_up(a.N, 16) / 16;      // (an ordered first round writes them all)
     hipLaunchKernelGGL(sweep_init_kernel, dim3(512, batch), dim3(256), 0, s, ia);
     if (ordered)
         hipLaunchKernelGGL(lloyd_rowpos_kernel, dim3(plan.n_runs, batch), dim3(RLS_MAX_K), 0, s, plan, a.init_idx, a.init_batch_stride, a.status,
-                           a.ws, L.per_batch, L.inv, L.rowpos, order_spread(a.N, unit_blocks_of(DP) == 2 ? 6 : 5));
+                           a.ws, L.per_batch, L.inv, L.rowpos, L.rowidx, order_spread(a.N, unit_blocks_of(DP) == 2 ? 6 : 5));
 
     CentroidArgs ca;
     ca.X = a.X; ca.N = a.N; ca.d = a.d; ca.ldx = a.ldx; ca.x_bs = a.x_batch_stride;
@@ -2600,8 +2843,7 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
     ca.status = a.status; ca.ws = a.ws; ca.ws_bs = L.per_batch;
     ca.off_colinfo = L.colinfo; ca.off_opA = L.opA; ca.off_cnmax = L.cnmax;
     ca.off_psum = L.psum; ca.off_pcnt = L.pcnt; ca.off_losum = L.losum; ca.off_tot = L.tot; ca.off_totcnt = L.totcnt;
-    ca.off_rowpos = ordered ? L.rowpos : -1;
-    ca.operands_by_index = 0;
+    ca.off_rowpos = ordered ? L.rowpos : -1; ca.off_losspart = L.losspart;
     const dim3 centroid_grid(parts_upto(plan.k_min + plan.n_runs - 1) - parts_upto(plan.k_min - 1), batch);
     hipLaunchKernelGGL((lloyd_centroids_kernel<DP, true>), centroid_grid, dim3(kThreads), 0, s, plan, ca);
 
@@ -2613,8 +2855,7 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
     sa.off_colinfo = L.colinfo; sa.off_opA = L.opA; sa.off_cnmax = L.cnmax;
     sa.off_psum = L.psum; sa.off_pcnt = L.pcnt; sa.off_pj = L.pj; sa.off_losum = L.losum; sa.off_prev = L.prev;
     sa.off_xp = L.xp; sa.off_log = L.log;
-    sa.off_xs = L.xs; sa.off_inv = L.inv; sa.off_centres = L.centres; sa.off_radius = L.radius; sa.off_rowpos = L.rowpos; sa.off_lists = L.lists;
-    sa.ordered = ordered ? 1 : 0;
+    sa.off_xs = L.xs; sa.off_centres = L.centres; sa.off_radius = L.radius; sa.off_rowpos = L.rowpos; sa.off_rowidx = L.rowidx; sa.off_lists = L.lists;
 
     size_t lds = 0;
     for (int gi = 0; gi < plan.n_groups; ++gi) {
@@ -2630,23 +2871,33 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
         sa.first_round = t == 0 ? 1 : 0;
         if (prof) { hipError_t e = profile_mark(s, true); if (e != hipSuccess) return e; }
         if (trace) {
-            hipLaunchKernelGGL((lloyd_step_kernel<DP, false, true, false, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
+            hipLaunchKernelGGL((lloyd_step_kernel<DP, false, true, false, false, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
             if (prof) { hipError_t e = profile_mark(s, false); if (e != hipSuccess) return e; }
             hipLaunchKernelGGL(lloyd_loss_kernel, dim3(batch), dim3(128), 0, s, plan, a.status, a.ws,
                                L.per_batch, L.pj, a.trace, (int64_t)plan.n_runs * (a.iters + 1), (int64_t)(a.iters + 1), (int64_t)t);
         } else {
             // the first round brings every row into a cluster and reads the rows themselves; later rounds take the
             // operands from the prepared copy and read a row only where a label is in doubt or has changed
-            if (t == 0 || !use_pre) hipLaunchKernelGGL((lloyd_step_kernel<DP, false, false, false, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
-            else if (ordered) hipLaunchKernelGGL((lloyd_step_kernel<DP, false, false, true, true>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
-            else hipLaunchKernelGGL((lloyd_step_kernel<DP, false, false, true, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
+            if (ordered && t == 0) hipLaunchKernelGGL((lloyd_step_kernel<DP, false, false, true, true, true>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
+            else if (t == 0 || !use_pre) hipLaunchKernelGGL((lloyd_step_kernel<DP, false, false, false, false, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
+            else if (ordered) hipLaunchKernelGGL((lloyd_step_kernel<DP, false, false, true, true, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
+            else hipLaunchKernelGGL((lloyd_step_kernel<DP, false, false, true, false, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
             if (prof) { hipError_t e = profile_mark(s, false); if (e != hipSuccess) return e; }
         }
-        if (t == a.iters - 1) ca.operands_by_index = 1;    // the final pass takes points and centroids as they are numbered
         hipLaunchKernelGGL((lloyd_centroids_kernel<DP, false>), centroid_grid, dim3(kThreads), 0, s, plan, ca);
     }
-    sa.ordered = 0;
-    hipLaunchKernelGGL((lloyd_step_kernel<DP, true, false, false, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
+    if (ordered) {
+        // the final assignment is a round like the others; the losses come from its sums, the labels go back to their points
+        hipLaunchKernelGGL((lloyd_step_kernel<DP, false, false, true, true, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
+        hipLaunchKernelGGL((lloyd_ordered_loss_kernel<DP>), centroid_grid, dim3(kThreads), 0, s, plan, ca);
+        hipLaunchKernelGGL(lloyd_ordered_loss_final_kernel, dim3(batch), dim3(1024), 0, s, plan, a.status, a.ws, L.per_batch, L.losspart, L.rowsq,
+                           (int)ordered_prepare_grid(n_units), a.inertia, (int64_t)plan.n_runs);
+        if (a.labels)
+            hipLaunchKernelGGL(lloyd_ordered_labels_kernel, dim3((unsigned)((a.N + kLabelPoints - 1) / kLabelPoints), batch), dim3(256),
+                               (size_t)plan.total_rows, s, plan, a.status, a.ws, L.per_batch, a.N, L.inv, L.rowidx, L.prev, a.labels, sa.lab_bs);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL((lloyd_step_kernel<DP, true, false, false, false, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
     hipLaunchKernelGGL(lloyd_loss_kernel, dim3(batch), dim3(128), 0, s, plan, a.status, a.ws, L.per_batch,
                        L.pj, a.inertia, (int64_t)plan.n_runs, (int64_t)1, (int64_t)0);
     if (trace)
@@ -2900,7 +3151,7 @@ void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, in
     L->chain = take((int64_t)k_max * 8);
     L->xp = take((N + 31) / 32 * prep_block_u4_of(plan.dp) * 16);     // (with the blocks above: the same place whatever the range of k)
     const int64_t n_units = (N + 32 * unit_blocks_of(plan.dp) - 1) / (32 * unit_blocks_of(plan.dp));
-    L->keyinfo = L->perm = L->inv = L->xs = L->centres = L->radius = L->rowpos = L->lists = 0;
+    L->keyinfo = L->perm = L->inv = L->xs = L->centres = L->radius = L->rowsq = L->rowpos = L->rowidx = L->losspart = L->lists = 0;
     if (plan.ordered) {
         L->keyinfo = take(sizeof(KeyInfo));
         L->perm = take(N * 4);
@@ -2908,8 +3159,11 @@ void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, in
         L->xs = take(std::max(align_up(N, 64) * plan.dp * 4, order_scratch_bytes(N)));
         L->centres = take((n_units + 31) / 32 * prep_block_u4_of(plan.dp) * 16);
         L->radius = take(align_up(n_units, 32) * 4);
+        L->rowsq = take((int64_t)kPrepareGrid * sizeof(Twofold));
         // (from here on: a place that depends on the range of k)
         L->rowpos = take((int64_t)plan.total_rows * 2);
+        L->rowidx = take((int64_t)plan.total_rows);
+        L->losspart = take((int64_t)plan.n_runs * kMaxParts * sizeof(Twofold));
         L->lists = take((int64_t)plan.n_lists * n_units * kListWords * 4);
     }
     L->opA = take((int64_t)plan.total_tiles * tile_bytes_of(plan.dp));

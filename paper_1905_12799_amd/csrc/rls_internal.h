@@ -113,7 +113,10 @@ struct SweepLayout {
     int64_t xs;             // fp32 [N rounded up to 64][dp] rows in that order, zero past the last feature (before: the scratch of the ordering)
     int64_t centres;        // prepared copy of the units' centres, as xp
     int64_t radius;         // fp32 [units rounded up to 32] upper bound of a unit's radius, in scaled units
+    int64_t rowsq;          // two doubles per workgroup of the preparation: squared distances of the points from the column means
+    int64_t losspart;       // two doubles [n_runs][parts of a run]
     int64_t rowpos;         // uint16 [total_rows] place of a centroid among the rows of its group
+    int64_t rowidx;         // uint8 [total_rows] centroid of its run that has a place
     int64_t lists;          // uint32 per group [units][16]: the tiles that a unit meets (see tile lists, kmeans_lloyd.hip)
     int64_t per_batch;      // bytes per batch element (multiple of 256)
     int64_t total;          // per_batch * batch
