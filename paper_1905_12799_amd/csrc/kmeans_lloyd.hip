@@ -674,7 +674,8 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         asm volatile("" : "+v"(ln));
         const int fq = FPL * (ln % LPR), g = ln / LPR;     // this lane's first feature, its record within a step
         // this lane's feature columns in its copy of the accumulators (the lane group picks the copy)
-        const int cp = g & (c.copies - 1);
+        // (other bits of the record's number than those that order its features)
+        const int cp = ((g >> 3) | (g << 2)) & (c.copies - 1);
         unsigned long long *const scol = c.sums + (int64_t)cp * c.real_rows * (DP + 1) + fq;
         const float *const xcol = c.X + c.chunk_begin * ldx + fq;
         // member counts: the lane that holds a record moves its one member, once per flush
@@ -1131,6 +1132,62 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
             for (int pb = 0; pb < NB; ++pb)
 #pragma unroll
                 for (int st = 0; st < ST; ++st) pend |= (unsigned)closeb[pb][st] << (pb * ST + st);
+            if constexpr (ORD && S <= 2) {
+                // Where points lie close together their close calls come together as well (on knob data whole blocks of points tie
+                // exactly), and a wave that settles 256 of them one by one holds up its launch.  Many at a time are settled by the
+                // lanes that own them, each its own pair: the exact arithmetic over the centroids that the unit's lists name.
+                constexpr int kMany = 8;                 // (one by one: 100 to 350 instructions each; together: 75 per listed centroid)
+                if (listed && __popcll(__builtin_amdgcn_ballot_w64(pend != 0u)) >= kMany) {
+                int half = hl;                           // (opaque: nothing of this is worked out ahead of the branch)
+                asm volatile("" : "+v"(half));
+#pragma unroll
+                for (int i = 0; i < NBST; ++i) {
+                    const int pb = i / ST, st = i % ST;
+                    const bool mine = (pend >> i) & 1u;
+                    if (__popcll(__builtin_amdgcn_ballot_w64(mine)) < kMany) continue;
+                    if (mine) {
+                        float x[DP];
+                        const float *const row = c.X + c.chunk_begin * DP + ptl[pb] * (unsigned)DP;
+#pragma unroll
+                        for (int l = 0; l < DP; l += 4) {
+                            const float4 v = *reinterpret_cast<const float4 *>(row + l);
+                            x[l] = v.x; x[l + 1] = v.y; x[l + 2] = v.z; x[l + 3] = v.w;
+                        }
+                        const int rl = half * ST + st, k = c.k0 + rl, rowbase = rl * c.k0 + rl * (rl - 1) / 2;
+                        double best = INFINITY;
+                        int arg = 0, at = 0;             // the nearest so far: its index, its place
+                        for (int a = 0; a < S; ++a) {
+                            const unsigned slot = (unsigned)(half * 4 + st * S + a);
+                            const unsigned head = lists[(pt0 >> kUnitShift) * kListWords + slot], more = lists[(pt0 >> kUnitShift) * kListWords + 8 + slot];
+                            for (int q = 0; q < 4 * n_it; ++q) {
+                                const int step = q >> 2;
+                                const int tile = (int)(((step < kListHead ? head : more) >> (8 * (step < kListHead ? step : step - kListHead))) & 255u);
+                                const int place = 4 * (S * tile + a) + (q & 3);
+                                if (place >= k) continue;                        // padding
+                                const int j = (int)c.rowidx[rowbase + place];
+                                const float *const crow = c.cs + (rowbase + j) * CS;
+                                double dist = 0.0;
+#pragma unroll
+                                for (int l = 0; l < DP; l += 4) {
+                                    const float4 cv = *reinterpret_cast<const float4 *>(crow + l);
+                                    double diff = __dsub_rn((double)x[l], (double)cv.x);
+                                    dist = __dadd_rn(dist, __dmul_rn(diff, diff));
+                                    diff = __dsub_rn((double)x[l + 1], (double)cv.y);
+                                    dist = __dadd_rn(dist, __dmul_rn(diff, diff));
+                                    diff = __dsub_rn((double)x[l + 2], (double)cv.z);
+                                    dist = __dadd_rn(dist, __dmul_rn(diff, diff));
+                                    diff = __dsub_rn((double)x[l + 3], (double)cv.w);
+                                    dist = __dadd_rn(dist, __dmul_rn(diff, diff));
+                                }
+                                if (dist < best || (dist == best && j < arg)) { best = dist; arg = j; at = place; }
+                            }
+                        }
+                        m1[pb][st] = at;
+                        pend &= ~(1u << i);
+                    }
+                }
+                }
+            }
         }
 
         // A close call (about one pair in a thousand on knob data; every pair where centroids coincide or integer
@@ -1713,7 +1770,7 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
             const unsigned char *rowidx = reinterpret_cast<const unsigned char *>(wsb + a.off_rowidx) + grow0;
             for (int e = tid; e < real_rows; e += TH) {
                 rowpos_s[e] = rowpos[e];
-                if (FIRST) rowidx_s[e] = rowidx[e];
+                rowidx_s[e] = rowidx[e];
             }
             // the tile of padding rows, as sweep_init_kernel makes them
             unsigned ph, pm, pl;
