@@ -63,8 +63,9 @@ def step_source_digest() -> str:
     """What the Lloyd step is compiled from, without comments and white space: a change of the kernel or of its plan
     changes this, a change of a comment does not."""
     digest = hashlib.sha256()
-    for name in ("kmeans_lloyd.hip", "kmeans_order.hip", "lloyd_device.h", "rls_internal.h"):
-        with open(os.path.join(ROOT, "paper_1905_12799_amd", "csrc", name)) as fh:
+    csrc = os.path.join(ROOT, "paper_1905_12799_amd", "csrc")
+    for name in sorted(set(os.listdir(csrc)) & {"kmeans_lloyd.hip", "kmeans_order.hip", "lloyd_device.h", "rls_internal.h"}):
+        with open(os.path.join(csrc, name)) as fh:
             code = re.sub(r"//[^\n]*|/\*.*?\*/", "", fh.read(), flags=re.S)
         digest.update("".join(code.split()).encode())
     return digest.hexdigest()[:12]
