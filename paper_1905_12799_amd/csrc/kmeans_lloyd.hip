@@ -44,19 +44,6 @@ __host__ __device__ inline int parts_upto(int k)
     return kPartRows * q * (q + 1) / 2 + (k - kPartRows * q) * (q + 1);
 }
 __host__ __device__ constexpr int tile_points_of(int dp) { return dp == 32 ? 256 : 512; }
-// 32-point blocks a wave takes per slab.  Up to d_pad = 16: one, which keeps a wave under 168 registers so that three
-// waves fit a SIMD (measured: 6% shorter launches than two waves with two blocks each).  At d_pad = 32 three waves do
-// not fit; there a wave takes two blocks, except with eight runs side by side, where the best keys of 4 runs x 2 blocks
-// would not fit the registers next to the operands.
-__host__ __device__ constexpr int slab_blocks_of(int dp, int s) { return dp <= 16 ? 1 : (s < 2 ? 1 : 2); }
-// threads of a step workgroup: up to d_pad = 16 one block per slab leaves room for three waves per SIMD
-__host__ __device__ constexpr int step_threads_of(int dp) { return dp <= 16 ? 768 : 512; }
-// Prepared copy of the points (written once per sweep by lloyd_prepare_kernel): per block of 32 points the B operands
-// of the distance tiles in the lane order of the step kernel - 2 * ksteps slots (high pieces, then low pieces, per
-// K-step) of 64 lanes x 16 bytes - followed by 32 entries of 8 bytes with the point's squared norm as the three bf16
-// pieces the bias slot wants (their sum, which is the norm cut off below 2^-24 of itself, serves the error bound).
-__host__ __device__ constexpr int prep_slots_of(int dp) { return 2 * ksteps_of(dp); }
-__host__ __device__ constexpr int prep_block_u4_of(int dp) { return prep_slots_of(dp) * 64 + 16; }   // 16-byte units per block
 // Tile lists of an ordered sweep.  A unit is 32 points (64 at d_pad = 32) that follow each other in the order; for every
 // unit, and each of the eight quad slots of a group's tiles, a list names the tiles whose quad in that slot may hold the
 // nearest centroid of one of the unit's points.  16 words per unit and group: eight of first words (one per slot: three tiles,
@@ -2491,7 +2478,7 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
     // group) that reading the rows is what it costs: the prepared copy is 6 to 12% larger than the rows.
     const bool trace = a.trace != nullptr;
     const bool use_pre = sweep_uses_prepared(plan, a.iters, trace);
-    const bool ordered = use_pre && plan.ordered;
+    const bool ordered = use_pre && plan.ordered, small = sweep_is_small(plan, a.N, batch, a.iters, trace);
     const int64_t n_units = (a.N + 32 * unit_blocks_of(DP) - 1) / (32 * unit_blocks_of(DP));
     // column statistics
     if (!a.reuse_colstats) {
@@ -2506,7 +2493,7 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((lloyd_prepare_ordered_kernel<DP>), dim3((unsigned)ordered_prepare_grid(n_units), batch), dim3(256), 0, s, a.X, a.N,
                            (int)a.d, a.ldx, a.x_batch_stride, a.status, a.ws, L.per_batch, L.colinfo, L.perm, L.xp, L.xs, L.centres, L.radius, L.rowsq);
-    } else if (use_pre && !a.reuse_prepared) {
+    } else if (small || (use_pre && !a.reuse_prepared)) {
         // the prepared copy: one wave per block of 32 points, a few blocks per wave
         const int64_t n_blocks = (a.N + 31) / 32;
         int64_t grid_x = (n_blocks + 4 * 8 - 1) / (4 * 8);      // 4 waves per workgroup, ~8 blocks per wave
@@ -2515,6 +2502,7 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
         hipLaunchKernelGGL((lloyd_prepare_kernel<DP>), dim3((unsigned)grid_x, batch), dim3(256), 0, s, a.X, a.N, (int)a.d, a.ldx,
                            a.x_batch_stride, a.status, a.ws, L.per_batch, L.colinfo, L.xp);
     }
+    if (small) return launch_small_sweep(plan, L, a, s);
     InitArgs ia;
     ia.ws = a.ws; ia.ws_bs = L.per_batch;
     ia.off_opA = L.opA; ia.off_losum = L.losum; ia.off_tot = L.tot; ia.off_totcnt = L.totcnt; ia.off_prev = L.prev;

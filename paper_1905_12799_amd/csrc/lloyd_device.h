@@ -27,6 +27,20 @@ __host__ __device__ constexpr int ksteps_of(int dp) { return dp == 32 ? 2 : 1; }
 __host__ __device__ constexpr int tile_slots_of(int dp) { return 2 * ksteps_of(dp) + 1; }          // 16-byte slots per lane
 __host__ __device__ constexpr int tile_bytes_of(int dp) { return tile_slots_of(dp) * 64 * 16; }    // per 32-row tile
 
+// 32-point blocks a wave takes per slab.  Up to d_pad = 16: one, which keeps a wave under 168 registers so that three
+// waves fit a SIMD (measured: 6% shorter launches than two waves with two blocks each).  At d_pad = 32 three waves do
+// not fit; there a wave takes two blocks, except with eight runs side by side, where the best keys of 4 runs x 2 blocks
+// would not fit the registers next to the operands.
+__host__ __device__ constexpr int slab_blocks_of(int dp, int s) { return dp <= 16 ? 1 : (s < 2 ? 1 : 2); }
+// threads of a step workgroup: up to d_pad = 16 one block per slab leaves room for three waves per SIMD
+__host__ __device__ constexpr int step_threads_of(int dp) { return dp <= 16 ? 768 : 512; }
+
+// Prepared copy of the points (written once per sweep by lloyd_prepare_kernel): per block of 32 points the B operands
+// of the distance tiles in the lane order of the step kernel - 2 * ksteps slots (high pieces, then low pieces, per
+// K-step) of 64 lanes x 16 bytes - followed by 32 entries of 8 bytes with the point's squared norm as the three bf16
+// pieces the bias slot wants (their sum, which is the norm cut off below 2^-24 of itself, serves the error bound).
+__host__ __device__ constexpr int prep_slots_of(int dp) { return 2 * ksteps_of(dp); }
+__host__ __device__ constexpr int prep_block_u4_of(int dp) { return prep_slots_of(dp) * 64 + 16; }   // 16-byte units per block
 // x * 2^shift truncated toward zero, |x * 2^shift| < 2^kGridBits; exact whenever x is a multiple of 2^-shift.
 // The scaling is exact in fp64; adding 2^52 + 2^51 leaves the integer in the low bits of the significand.
 __device__ inline long long to_fixed(float x, int shift)

@@ -196,6 +196,10 @@ hipError_t profile_mark(hipStream_t s, bool begin);
 
 hipError_t launch_sweep(const SweepPlan &plan, const SweepLayout &L, const SweepArgs &a, hipStream_t s);
 
+// sweeps of few points: one workgroup per run, one launch (kmeans_small.hip)
+bool sweep_is_small(const SweepPlan &plan, int64_t N, int32_t batch, int32_t iters, bool trace);
+hipError_t launch_small_sweep(const SweepPlan &plan, const SweepLayout &L, const SweepArgs &a, hipStream_t s);
+
 // ---- spatial order of the points (kmeans_order.hip)
 constexpr int kKeyBits = 24, kKeyColBits = 10;      // of a key, and of one column at most
 struct KeyInfo {
