@@ -11,7 +11,7 @@
 // 512 ... 64 configurations and split the trees of a chunk over the 1024 / P slices of the workgroup; the leaf values
 // then meet in LDS, where one slice adds them.  Either way a configuration's leaves are added in fp32 in tree order, so
 // the result does not depend on the launch shape.  (Measured: 2000 x 8, 64 trees of depth 6: 23.9 -> 9.0 us a call with
-// 32 workgroups instead of two; 65,536 x 8, 256 of depth 8: 112 -> 41 us with tiles of 256; leaves in global memory
+// 32 workgroups instead of two; 65,536 x 8, 256 of depth 8: 112 -> 43 us with tiles of 256; leaves in global memory
 // instead of LDS, which alone bound the large ones: 8M x 32, 512 of depth 10: 14.9 -> 11.9 ms.)
 //
 // A step of the walk is two dependent LDS reads and four vector instructions: the walk keeps the node's LDS
@@ -214,7 +214,15 @@ __global__ void __launch_bounds__(kScoreThreads) gbt_score_kernel(ForestBatch fb
         if constexpr (SL > 1) {
             if (slice == 0) {
                 const unsigned at = lv_at + cfg4;
-                for (int t = 0; t < tc; ++t) sum = sum + lds_read_f(at + (unsigned)(t * P) * 4u);
+                // (eight reads under way at a time, added in tree order: one by one every tree waited for its read, 70 ns)
+                constexpr int U = 8;
+                for (int t = 0; t < tc; t += U) {
+                    float v[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) v[u] = lds_read_f(at + (unsigned)(min(t + u, tc - 1) * P) * 4u);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) sum = sum + (t + u < tc ? v[u] : -0.0f);       // (-0 changes no sum)
+                }
             }
         }
         __syncthreads();
@@ -225,15 +233,15 @@ __global__ void __launch_bounds__(kScoreThreads) gbt_score_kernel(ForestBatch fb
 
 using Kernel = void (*)(ForestBatch, const float *, int64_t, int, int64_t, int64_t, float *, int, int);
 
-// the tiles, and the kernels of each for 4, 2, 1 trees side by side
+// the tiles, and the kernels of each for 8 (the largest tile only), 4, 2, 1 trees side by side
 struct TileKernels {
     int tile;
-    Kernel kernel[3];
+    Kernel kernel[4];
 };
 template <int P>
 constexpr TileKernels tile_kernels()
 {
-    return TileKernels{P, {gbt_score_kernel<P, 4>, gbt_score_kernel<P, 2>, gbt_score_kernel<P, 1>}};
+    return TileKernels{P, {gbt_score_kernel<P, P == kScoreThreads ? 8 : 4>, gbt_score_kernel<P, 4>, gbt_score_kernel<P, 2>, gbt_score_kernel<P, 1>}};
 }
 static_assert(RLS_MAX_D * kScoreThreads * 4 + ((1 << RLS_MAX_DEPTH) - 1) * 8 <= kScoreLds,
               "the deepest tree fits beside the largest tile at the largest number of features");
@@ -285,7 +293,9 @@ hipError_t launch_gbt_score(const ForestArgs *forests_host, int32_t batch, const
             int64_t fit = std::min<int64_t>(space / (n_int * 8 + (SL > 1 ? P * 4 : 0)), kChunkNodes / n_int);
             if (fit < 1) continue;
             if (fit > n_trees) fit = n_trees;
-            const int side = fit >= 4 * SL ? 4 : (fit >= 2 * SL ? 2 : 1);
+            // (eight side by side hide more of the chains' latency where a thread walks whole chunks: 1M x 16, 512 trees of depth 5
+            // 508 -> 482 us, of depth 8 794 -> 782; split over slices they leave more of a chunk's last round idle)
+            const int side = SL == 1 && fit >= 8 ? 8 : (fit >= 4 * SL ? 4 : (fit >= 2 * SL ? 2 : 1));
             int tpc = (int)fit;
             if (tpc > side * SL) tpc -= tpc % (side * SL);      // whole rounds of the slices ...
             if (tpc > 4) tpc -= tpc % 4;                        // ... and chunks that start at a multiple of four trees
@@ -301,7 +311,7 @@ hipError_t launch_gbt_score(const ForestArgs *forests_host, int32_t batch, const
         }
         if (best.tile == nullptr) return hipErrorInvalidValue;     // depth <= 12: cannot happen
         const int quads = (best.tpc % 4 == 0 || best.tpc == n_trees) && (bits & 15) == 0;
-        const Kernel kernel = best.tile->kernel[best.side == 4 ? 0 : (best.side == 2 ? 1 : 2)];
+        const Kernel kernel = best.tile->kernel[best.side == 8 ? 0 : (best.side == 4 ? 1 : (best.side == 2 ? 2 : 3))];
         const unsigned grid = (unsigned)((N + best.tile->tile - 1) / best.tile->tile);
         hipLaunchKernelGGL(kernel, dim3(grid, (unsigned)nb), dim3(kScoreThreads), best.lds, s, fb, X + (int64_t)b0 * x_batch_stride, N, (int)d,
                            ldx, x_batch_stride, score + (int64_t)b0 * N, best.tpc, quads);
