@@ -1301,6 +1301,16 @@ __device__ inline void wave_loop_of(int S, const WaveCtx &c, double (&jloc)[8])
     }
 }
 
+// The last group whose `first` is at most `v`: all groups are looked at together, one per lane.  (One after the other every
+// group was a trip to the kernel's arguments, which no cache holds when a launch begins.)
+template <typename First>
+__device__ inline int group_of(const SweepPlan &plan, First first, int v)
+{
+    static_assert(kMaxGroups <= 64, "one group per lane");
+    const int lane = threadIdx.x & 63;
+    return __popcll(__builtin_amdgcn_ballot_w64(lane < plan.n_groups && first(plan.g[lane]) <= v)) - 1;
+}
+
 template <int DP, bool FINAL, bool TRACE, bool PRE, bool ORD, bool FIRST>
 __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPlan plan, StepArgs a)
 {
@@ -1330,8 +1340,7 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     } else {
         b = blockIdx.x / plan.n_wgs;
         const int v = blockIdx.x - b * plan.n_wgs;
-        gi = 0;
-        while (gi + 1 < plan.n_groups && plan.g[gi + 1].wg0 <= v) ++gi;
+        gi = group_of(plan, [](const GroupDesc &g) { return g.wg0; }, v);
         const int r = v - plan.g[gi].wg0, nc = plan.g[gi].n_chunks;
         const int first = blockIdx.x - r;                   // launch index of the group's first workgroup
         chunk = r >> 3;
@@ -1343,7 +1352,7 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     b = __builtin_amdgcn_readfirstlane(b);
     chunk = __builtin_amdgcn_readfirstlane(chunk);
     gi = __builtin_amdgcn_readfirstlane(gi);
-    if (a.status[b] != 0) return;
+    const int bad = a.status[b];                    // (looked at below, when it has come with everything else)
     const GroupDesc g = plan.g[gi];
     const int d = a.d;
     const int k0 = plan.k_min + g.run0;                                   // k of the group's first run
@@ -1449,6 +1458,7 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
             static_assert(NSL <= TH, "one thread per operand slot of a tile");
         }
         if (tid == 0) *next_slab = WV;
+        if (bad != 0) return;
         if (tid < 128) {
 #pragma unroll
             for (int off = 8; off >= 1; off >>= 1) pmax = fmaxf(pmax, __shfl_xor(pmax, off, 64));
@@ -2125,7 +2135,8 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
     __shared__ long long part_hi[INIT ? 1 : kThreads], part_cnt[INIT ? 1 : kThreads];
     __shared__ unsigned long long part_lo[INIT ? 1 : kThreads];
     const int b = blockIdx.y, tid = threadIdx.x;
-    if (a.status[b] != 0) return;
+    const int bad = a.status[b];                    // (looked at before the first store, when it has come with everything else)
+    if (INIT && bad != 0) return;                   // (the seeding's choices are not there)
     // blockIdx.x counts the parts of all runs in run order: the run is the last one that starts at or before it
     const int parts0 = parts_upto(plan.k_min - 1);
     int run = 0;
@@ -2135,8 +2146,7 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
     const int part = (int)blockIdx.x - (parts_upto(k - 1) - parts0);
     const int j0 = part * kPartRows, rows = min(kPartRows, k - j0);
     const int row0 = rows_before(plan.k_min, run);
-    int gi = 0;
-    while (gi + 1 < plan.n_groups && plan.g[gi + 1].run0 <= run) ++gi;
+    const int gi = group_of(plan, [](const GroupDesc &g) { return (int)g.run0; }, run);
     const GroupDesc g = plan.g[gi];
     const int rl = run - g.run0;
     char *wsb = a.ws + (int64_t)b * a.ws_bs;
@@ -2192,6 +2202,7 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
             const int c_begin = (int)((int64_t)g.n_chunks * sl / nsl), c_end = (int)((int64_t)g.n_chunks * (sl + 1) / nsl);
             sum_chunks(psum, pcnt, (int64_t)grows * d, grows, c_begin, c_end, hi, lo, cnt);
         }
+        if (bad != 0) return;
         part_hi[tid] = hi; part_lo[tid] = lo; part_cnt[tid] = cnt;
         __syncthreads();
     }
