@@ -1301,14 +1301,26 @@ __device__ inline void wave_loop_of(int S, const WaveCtx &c, double (&jloc)[8])
     }
 }
 
-// The last group whose `first` is at most `v`: all groups are looked at together, one per lane.  (One after the other every
-// group was a trip to the kernel's arguments, which no cache holds when a launch begins.)
-template <typename First>
-__device__ inline int group_of(const SweepPlan &plan, First first, int v)
+// The groups, one per lane: all are asked for together, and the one that a workgroup belongs to is found and taken from the
+// lane that has it.  (Walked one by one every group was a trip to the kernel's arguments, which no cache holds when a launch
+// begins: step and centroid launches 0.3 to 0.8 us longer.)
+static_assert(kMaxGroups <= 64, "one group per lane");
+static_assert(sizeof(GroupDesc) % 4 == 0, "taken over word by word");
+__device__ inline GroupDesc group_of_lane(const SweepPlan &plan) { return plan.g[min((int)(threadIdx.x & 63), kMaxGroups - 1)]; }
+// the number of groups in the front that satisfy `holds` in their lanes, less one
+__device__ inline int last_group(const SweepPlan &plan, bool holds)
 {
-    static_assert(kMaxGroups <= 64, "one group per lane");
-    const int lane = threadIdx.x & 63;
-    return __popcll(__builtin_amdgcn_ballot_w64(lane < plan.n_groups && first(plan.g[lane]) <= v)) - 1;
+    return __popcll(__builtin_amdgcn_ballot_w64((int)(threadIdx.x & 63) < plan.n_groups && holds)) - 1;
+}
+__device__ inline GroupDesc take_group(const GroupDesc &mine, int gi)
+{
+    int w[sizeof(GroupDesc) / 4];
+    __builtin_memcpy(w, &mine, sizeof(w));
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(GroupDesc) / 4; ++i) w[i] = __builtin_amdgcn_readlane(w[i], gi);
+    GroupDesc g;
+    __builtin_memcpy(&g, w, sizeof(w));
+    return g;
 }
 
 template <int DP, bool FINAL, bool TRACE, bool PRE, bool ORD, bool FIRST>
@@ -1325,6 +1337,7 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     // Small inputs (chunk_block 0): every group has chunks of its own, of about equal cost over all groups, one per compute
     // unit; the chunks of a group that land on one XCD (every eighth workgroup) follow each other in the points.
     int gi, chunk, b;
+    const GroupDesc mine = group_of_lane(plan);
     if (plan.chunk_block > 0) {
         const int B = plan.chunk_block;
         const int n_chunks = plan.g[0].n_chunks;
@@ -1340,8 +1353,9 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     } else {
         b = blockIdx.x / plan.n_wgs;
         const int v = blockIdx.x - b * plan.n_wgs;
-        gi = group_of(plan, [](const GroupDesc &g) { return g.wg0; }, v);
-        const int r = v - plan.g[gi].wg0, nc = plan.g[gi].n_chunks;
+        gi = last_group(plan, mine.wg0 <= v);
+        const GroupDesc g = take_group(mine, gi);
+        const int r = v - g.wg0, nc = g.n_chunks;
         const int first = blockIdx.x - r;                   // launch index of the group's first workgroup
         chunk = r >> 3;
         for (int q = 0; q < (int)(blockIdx.x & 7); ++q) chunk += (nc - ((q - first) & 7) + 7) >> 3;   // chunks of the XCDs before this one
@@ -1353,7 +1367,7 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     chunk = __builtin_amdgcn_readfirstlane(chunk);
     gi = __builtin_amdgcn_readfirstlane(gi);
     const int bad = a.status[b];                    // (looked at below, when it has come with everything else)
-    const GroupDesc g = plan.g[gi];
+    const GroupDesc g = take_group(mine, gi);
     const int d = a.d;
     const int k0 = plan.k_min + g.run0;                                   // k of the group's first run
     const int grow0 = rows_before(plan.k_min, g.run0);                    // first centroid row of the group
@@ -1546,40 +1560,78 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     if (!FINAL) {
         unsigned long long *psum = reinterpret_cast<unsigned long long *>(wsb + a.off_psum) +
                                    ((int64_t)g.part0 + (int64_t)chunk * real_rows) * d;
-        // the accumulator rows that make up a centroid: its own; after a first round on the ordered copy also those of the same
-        // centroid in the group's earlier runs (see FIRST above)
-        const bool adds_up = FIRST && c.wide_s[32] == 0;
-        auto each_row = [&](int e, auto &&use) {
-            if (!ORD) {
-                use(e);
-            } else {
+        int *pcnt = reinterpret_cast<int *>(wsb + a.off_pcnt) + (int64_t)g.part0 + (int64_t)chunk * real_rows;
+        if constexpr (FIRST) {
+            // the accumulator rows that make up a centroid after a first round on the ordered copy: its own and, unless a column is
+            // wide, those of the same centroid in the group's earlier runs (see FIRST above)
+            const bool adds_up = c.wide_s[32] == 0;
+            auto each_row = [&](int e, auto &&use) {
                 use((int)rowpos_s[e]);
-                if (FIRST && adds_up) {
+                if (adds_up) {
                     int r = 0;
                     while (r + 1 < g.n_runs && (r + 1) * k0 + (r + 1) * r / 2 <= e) ++r;
                     const int j = e - (r * k0 + r * (r - 1) / 2);
                     for (int q = r - 1; q >= 0 && j < k0 + q; --q) use((int)rowpos_s[q * k0 + q * (q - 1) / 2 + j]);
                 }
+            };
+            for (int e = tid; e < real_rows * d; e += TH) {
+                unsigned long long v = 0ull;
+                long long rows_in = 0;     // rows that entered minus rows that left: each carried the bias once
+                each_row(e / d, [&](int row) {
+                    for (int cp = 0; cp < copies; ++cp) {
+                        v += sums[(cp * real_rows + row) * (DP + 1) + e % d];
+                        rows_in += cnts[cp * real_rows + row];
+                    }
+                });
+                psum[e] = v - kFixBias * (unsigned long long)rows_in;
             }
-        };
-        for (int e = tid; e < real_rows * d; e += TH) {
-            unsigned long long v = 0ull;
-            long long rows_in = 0;     // rows that entered minus rows that left: each carried the bias once
-            each_row(e / d, [&](int row) {
-                for (int cp = 0; cp < copies; ++cp) {
-                    v += sums[(cp * real_rows + row) * (DP + 1) + e % d];
-                    rows_in += cnts[cp * real_rows + row];
+            for (int e = tid; e < real_rows; e += TH) {
+                int v = 0;
+                each_row(e, [&](int row) {
+                    for (int cp = 0; cp < copies; ++cp) v += cnts[cp * real_rows + row];
+                });
+                pcnt[e] = v;
+            }
+        } else {
+            // Several elements or copies at a time, whose reads are under way together (one by one, the flush of 484 rows of 16
+            // took 6200 cycles, now 1500).  The count of a row's members is read with each of its features.
+            static_assert(TH % DP == 0, "a thread keeps its feature");
+            const int l = tid % DP;
+            auto flush = [&](auto elements, auto copies_at_once) {
+                constexpr int U = decltype(elements)::value, Q = decltype(copies_at_once)::value;
+                for (int row0 = tid / DP; row0 < real_rows; row0 += U * (TH / DP)) {
+                    unsigned long long v[U];
+                    int rows_in[U], at[U];     // rows that entered minus rows that left: each carried the bias once
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int row = min(row0 + u * (TH / DP), real_rows - 1);
+                        at[u] = ORD ? (int)rowpos_s[row] : row;
+                        v[u] = 0ull;
+                        rows_in[u] = 0;
+                    }
+                    for (int cp = 0; cp < copies; cp += Q) {           // (both are powers of two: Q copies are there)
+#pragma unroll
+                        for (int q = 0; q < Q; ++q)
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                const int row = (cp + q) * real_rows + at[u];
+                                v[u] += sums[row * (DP + 1) + l];
+                                rows_in[u] += cnts[row];
+                            }
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int row = row0 + u * (TH / DP);
+                        if (row < real_rows && l < d) {
+                            psum[row * d + l] = v[u] - kFixBias * (unsigned long long)(long long)rows_in[u];
+                            if (l == 0) pcnt[row] = rows_in[u];
+                        }
+                    }
                 }
-            });
-            psum[e] = v - kFixBias * (unsigned long long)rows_in;
-        }
-        int *pcnt = reinterpret_cast<int *>(wsb + a.off_pcnt) + (int64_t)g.part0 + (int64_t)chunk * real_rows;
-        for (int e = tid; e < real_rows; e += TH) {
-            int v = 0;
-            each_row(e, [&](int row) {
-                for (int cp = 0; cp < copies; ++cp) v += cnts[cp * real_rows + row];
-            });
-            pcnt[e] = v;
+            };
+            if (copies == 1) flush(std::integral_constant<int, 4>{}, std::integral_constant<int, 1>{});
+            else if (copies == 2) flush(std::integral_constant<int, 2>{}, std::integral_constant<int, 2>{});
+            else flush(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
         }
     }
     if (FINAL || TRACE) {
@@ -2146,8 +2198,8 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
     const int part = (int)blockIdx.x - (parts_upto(k - 1) - parts0);
     const int j0 = part * kPartRows, rows = min(kPartRows, k - j0);
     const int row0 = rows_before(plan.k_min, run);
-    const int gi = group_of(plan, [](const GroupDesc &g) { return (int)g.run0; }, run);
-    const GroupDesc g = plan.g[gi];
+    const GroupDesc mine = group_of_lane(plan);
+    const GroupDesc g = take_group(mine, last_group(plan, mine.run0 <= run));
     const int rl = run - g.run0;
     char *wsb = a.ws + (int64_t)b * a.ws_bs;
     const float *colmean = reinterpret_cast<const float *>(wsb + a.off_colinfo);   // -(mean * scale)
