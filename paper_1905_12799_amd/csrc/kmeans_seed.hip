@@ -379,7 +379,8 @@ __global__ void __launch_bounds__(1024) seed_pick_kernel(SeedList seeds, int b0,
 // exchange two messages through memory - every workgroup the sum of its D, then the workgroup that holds the drawn point
 // that point's row and index.  What bounds a step is the latency of these two exchanges and of the scans between them:
 // two launches per centre (an update of 7 to 12 us, a draw of 9 to 11 us and the ramp of each) took 17 to 23 us.
-// (One launch: 3.0 us per centre at 2000 x 8, 5.3 at 65,536 x 16, 8.5 at 1M x 16, against 13.6, 16.6 and 22.4.)
+// (One launch: 2.5 us per centre at 2000 x 8 - where a single workgroup skips the scan over the others, with it 2.7 -, 5.0 at
+// 65,536 x 16, 8.5 at 1M x 16, against 13.6, 16.6 and 22.4.)
 //
 // A message is a word of 8 bytes that carries its own validity - the area is filled with kSlotEmpty before the launch,
 // every word is written once, and a row travels as words of (step, value) - so no flags, fences or counters are needed:
@@ -583,6 +584,7 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
     __syncthreads();
 
     for (int j = j0; j < a.k_max; ++j) {
+        const double u01 = uniform01(seed, (uint64_t)j);
         // ---- the newest centre
 #pragma unroll
         for (int i = 0; i < P; ++i) {
@@ -625,10 +627,18 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
                     }
                     return __ballot(miss) == 0ull;
                 });
-            } else if (lane == 0) {
-                v[0] = total;
             }
-            if (lost) {
+            if (G == 1) {
+                // nothing to exchange: the same draw without the scan over the workgroups
+                int owner = -1, entry = 0;
+                double before = 0.0, r = 0.0;
+                if (total > 0.0) {                  // else: every point coincides with a chosen centre
+                    r = __dmul_rn(u01, total);
+                    owner = w;
+                    entry = max(wave_locate<E>(own, own_incl, total > r ? 0.0 : r, r, before), 0);
+                }
+                if (lane == 0) { s_owner = owner; s_entry = entry; s_before = before; s_r = r; }
+            } else if (lost) {
                 if (lane == 0) {
                     s_no_sums = 1;
                     post(ex + kExQuit, 1ull);
@@ -638,7 +648,7 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
                 int owner = -1, entry = 0;
                 double before = 0.0, r = 0.0;
                 if (S > 0.0) {                      // else: every point coincides with a chosen centre
-                    r = __dmul_rn(uniform01(seed, (uint64_t)j), S);
+                    r = __dmul_rn(u01, S);
                     owner = wave_locate<4>(v, incl, 0.0, r, before);
                     if (owner == w) {
                         double at;
