@@ -100,3 +100,38 @@ def test_waves_until_the_knee_share_the_order(rls):
     assert n_done == 44
     want = rls.kmeans_sweep(X, 17, 60, 5, init_idx=init, want_trace=True)
     assert torch.equal(r.labels, want.labels) and torch.equal(r.centroids, want.centroids)
+
+
+def test_ordered_sweep_in_a_graph(rls):
+    """Recorded once and replayed with eager work in between: every replay gives the eager result."""
+    X = torch.as_tensor(make("clusters", 90011, 16, 4)).cuda()
+    ws = torch.empty(rls.kmeans_sweep_workspace_bytes(90011, 16, 1, 64, 1) + 256, dtype=torch.uint8, device="cuda")
+    init = rls.kmeanspp_chain(X, 64, 5)
+    sweep = lambda: rls.kmeans_sweep(X, 1, 64, 5, init_idx=init, workspace=ws, check_status=False)
+    want = [t.clone() for t in (lambda r: (r.labels, r.centroids, r.inertia))(sweep())]
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        sweep()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            res = sweep()
+    torch.cuda.current_stream().wait_stream(side)
+    for rep in range(3):
+        for t in (res.labels, res.centroids, res.inertia):
+            t.zero_()
+        rls.kmeans_sweep(X[:30000], 2, 20, 2, seed=rep)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert int(res.status.item()) == 0
+        for got, exp in zip((res.labels, res.centroids, res.inertia), want):
+            assert torch.equal(got, exp), f"replay {rep}"
+
+
+def test_ordered_sweep_turns_down_bad_data(rls):
+    X = torch.as_tensor(make("clusters", 90011, 16, 4)).cuda()
+    X[80000, 3] = float("inf")
+    assert int(rls.kmeans_sweep(X, 1, 64, 2, seed=1, check_status=False).status.item()) & rls.RLS_STATUS_NONFINITE
