@@ -17,8 +17,8 @@ spaces of 262,144 x 16 as well, with their own step counts stated inside).  Each
                 pipeline, so `frac` is the method's distance arithmetic (2 d k flop per point and (k, round)) over
                 the launch time over the dense fp16 MFMA peak; beside it the fraction of HBM peak the same launch
                 would need if every k read the trajectory on its own (`hbm_equivalent_ratio`, can exceed 1: one read
-                serves up to eight k), the matrix work actually issued, and - from rocprofv3 counters of this
-                very kernel source, else null - the HBM bytes really moved and the vector-issue utilisation
+                serves up to eight k), and - from rocprofv3 counters of this very kernel source, else null - the matrix
+                work actually issued, the HBM bytes really moved and the vector-issue utilisation
   cpu_baseline  the CPU oracle timed on a bounded sample of the same workload, with the scaling to the sweep's mix of k
   lloyd_step_per_k / early_exit / graph_replay   extra timings outside the timed steps (graph_replay: a short sweep
                 recorded into a HIP graph once and replayed, against the same sweep launched kernel by kernel)
@@ -207,13 +207,12 @@ def run_workload(name, steps, warmup, args):
     score_ms = stage_ms["score"] / steps
 
     # ---- dominant kernel: the Lloyd step (assign + update for every k in one launch) -------------------------
-    kernel_s = kernel_ms_total / max(n_launch, 1) * 1e-3
+    # (a sweep of a few thousand points is one launch of another kernel: no step launches to time, no roofline)
+    kernel_s = kernel_ms_total / n_launch * 1e-3 if n_launch else float("inf")
     sum_k = sum(range(w.k_min, w.k_max + 1))
     alg_bytes = 4.0 * w.d * w.N * B * n_k                 # 4 d bytes per point and (k, round): every k reads the row
     alg_flops = 2.0 * w.d * sum_k * w.N * B               # 2 d k flop per point and (k, round)
-    # matrix work as issued: per distance three products of fp16 pieces over the padded features plus one bias step of 16
     d_pad = 8 if w.d <= 8 else (16 if w.d <= 16 else 32)
-    issued_flops = 2.0 * (3.0 * max(d_pad, 16) + 16.0) * sum_k * w.N * B
     tflops = alg_flops / kernel_s / 1e12
     roofline = {
         # The launch is bound by vector-instruction issue beside the matrix pipeline (the fold of the distance tiles
@@ -223,7 +222,7 @@ def run_workload(name, steps, warmup, args):
         "frac": tflops / MFMA_F16_PEAK_TFLOPS, "traffic": None,
         "kernel": "lloyd_step_kernel", "launches_timed": n_launch, "avg_launch_ms": kernel_s * 1e3,
         "algorithmic_flops_per_launch": alg_flops, "algorithmic_bytes_per_launch": alg_bytes,
-        "mfma_issued_frac": issued_flops / kernel_s / 1e12 / MFMA_F16_PEAK_TFLOPS,
+        "mfma_issued_frac": None,
         "fp32_mfma_equivalent_ratio": tflops / MFMA_F32_PEAK_TFLOPS,   # against the fp32 matrix peak an fp32 contraction would have had
         "hbm_equivalent_GBps": alg_bytes / kernel_s / 1e9,
         "hbm_equivalent_ratio": alg_bytes / kernel_s / 1e9 / HBM_PEAK_GBS,   # can pass 1: one read of a row serves up to eight k
@@ -238,6 +237,12 @@ def run_workload(name, steps, warmup, args):
         roofline["traffic"] = hbm_bytes                  # HBM bytes really moved per launch (rocprofv3 FETCH_SIZE, WRITE_SIZE)
         roofline["hbm_traffic_frac"] = hbm_bytes / kernel_s / 1e9 / HBM_PEAK_GBS
         roofline["valu_issue_frac"] = hc["valu_insts"] / kernel_s / VALU_ISSUE_PEAK
+        # matrix work as issued: three products of fp16 pieces over the padded features plus one bias step per distance, of the
+        # tiles that the points' lists name (an MFMA is 32 x 32 x 16)
+        roofline["mfma_issued_frac"] = hc["mfma_insts"] * 32768.0 / kernel_s / 1e12 / MFMA_F16_PEAK_TFLOPS
+
+    if not n_launch:
+        roofline = None
 
     visits = float(w.N) * B * w.n_trees * w.depth
     out = {
