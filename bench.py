@@ -44,18 +44,18 @@ VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4.0   # wave64 vector instructions per secon
 
 # rocprofv3 counters of one lloyd_step_kernel launch (mean over the rounds of a sweep), from the summaries under
 # profiles/ (lloyd_step_<workload>_hbm_counters.md: FETCH_SIZE / WRITE_SIZE in KiB per dispatch with the factors a
-# plain 1 GiB copy gives for each counter; lloyd_step_<workload>_sq_counters.md: SQ_INSTS_VALU).  Valid only for the
+# plain 1 GiB copy gives for each counter; lloyd_step_<workload>_sq_counters.md: SQ_INSTS_VALU, SQ_INSTS_MFMA).  Valid only for the
 # source they were taken with (step_source_digest); with any other the fields made from them are null.
 COUNTERS = {
     # mean over the 30 rounds of a sweep (first round included, like the launches the events time)
-    "mid": {"source": "a164148e0d37", "fetch_kib": 8732.4, "write_kib": 11653.3, "fetch_scale": 2.0, "write_scale": 1.0,
-           "valu_insts": 1.165e+07},
-    "whole_layer": {"source": "a164148e0d37", "fetch_kib": 187376.0, "write_kib": 44479.5, "fetch_scale": 2.0, "write_scale": 1.0,
-                   "valu_insts": 1.494e+08},
-    "large": {"source": "a164148e0d37", "fetch_kib": 7435421.5, "write_kib": 913996.2, "fetch_scale": 2.0, "write_scale": 1.0,
-             "valu_insts": 4.781e+09},
-    "batched": {"source": "a164148e0d37", "fetch_kib": 2639848.1, "write_kib": 251768.2, "fetch_scale": 2.0, "write_scale": 1.0,
-               "valu_insts": 7.548e+08},
+    "mid": {"source": "b943046e8c46", "fetch_kib": 8656.7, "write_kib": 11653.5, "fetch_scale": 2.0, "write_scale": 1.0,
+           "valu_insts": 1.056e+07, "mfma_insts": 5.898e+05},
+    "whole_layer": {"source": "b943046e8c46", "fetch_kib": 316818.4, "write_kib": 50230.0, "fetch_scale": 2.0, "write_scale": 1.0,
+                   "valu_insts": 8.092e+07, "mfma_insts": 2.86e+06},
+    "large": {"source": "b943046e8c46", "fetch_kib": 7881477.7, "write_kib": 1250588.4, "fetch_scale": 2.0, "write_scale": 1.0,
+             "valu_insts": 2.882e+09, "mfma_insts": 1.869e+08},
+    "batched": {"source": "b943046e8c46", "fetch_kib": 2565900.0, "write_kib": 341002.8, "fetch_scale": 2.0, "write_scale": 1.0,
+               "valu_insts": 5.367e+08, "mfma_insts": 1.971e+07},
 }
 
 
@@ -325,7 +325,9 @@ def run_workload(name, steps, warmup, args):
             rls.kmeans_sweep(X, k, k, w.iters, seed=seeds[0], want_labels=False, workspace=ws)
             n_l, ms_l = rls.profile_read()
             rls.profile_enable(False)
-            t_l = ms_l / max(n_l, 1) * 1e-3
+            if not n_l:
+                continue                                 # all rounds in one launch
+            t_l = ms_l / n_l * 1e-3
             flops_k = 2.0 * (3.0 * max(d_pad, 16) + 16.0) * max(k, 32) * w.N       # issued: tiles of 32 centroids
             per_k.append({"k": k, "launch_ms": t_l * 1e3, "config_iter_per_s": w.N / t_l,
                           "hbm_frac": 4.0 * w.d * w.N / t_l / 1e9 / HBM_PEAK_GBS,
