@@ -294,8 +294,9 @@ hipError_t launch_gbt_score(const ForestArgs *forests_host, int32_t batch, const
             if (fit < 1) continue;
             if (fit > n_trees) fit = n_trees;
             // (eight side by side hide more of the chains' latency where a thread walks whole chunks: 1M x 16, 512 trees of depth 5
-            // 508 -> 482 us, of depth 8 794 -> 782; split over slices they leave more of a chunk's last round idle)
-            const int side = SL == 1 && fit >= 8 ? 8 : (fit >= 4 * SL ? 4 : (fit >= 2 * SL ? 2 : 1));
+            // 508 -> 482 us, of depth 8 794 -> 782; split over slices they leave more of a chunk's last round idle,
+            // and chunks of 8 trees where 12 fit cost more than that: 6.8M x 16, 67 trees of depth 10 1141 -> 1255 us)
+            const int side = SL == 1 && fit >= 8 && fit % 8 < 4 ? 8 : (fit >= 4 * SL ? 4 : (fit >= 2 * SL ? 2 : 1));
             int tpc = (int)fit;
             if (tpc > side * SL) tpc -= tpc % (side * SL);      // whole rounds of the slices ...
             if (tpc > 4) tpc -= tpc % 4;                        // ... and chunks that start at a multiple of four trees

@@ -20,7 +20,7 @@ def rls():
 
 # small: slices, trees 1 .. two chunks and a remainder; large: groups of eight, the last one of 1, 7 or all
 @pytest.mark.parametrize("N,d,T,D", [(1, 8, 1, 3), (65, 5, 7, 4), (1000, 8, 8, 6), (3001, 16, 9, 6), (4000, 8, 129, 8), (20001, 12, 65, 5), (50001, 16, 95, 9),
-                                     (262145, 8, 8, 4), (300001, 16, 9, 6), (262145, 32, 23, 7), (270001, 5, 55, 8), (262145, 16, 25, 10)])
+                                     (262145, 8, 8, 4), (300001, 16, 9, 6), (262145, 32, 23, 7), (270001, 5, 55, 8), (262145, 16, 25, 10), (262145, 8, 12, 7)])
 def test_trees_that_do_not_divide(rls, orc, N, d, T, D):
     rng = np.random.default_rng(N + T)
     X = rng.standard_normal((N, d)).astype(np.float32)
