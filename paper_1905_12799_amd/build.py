@@ -4,6 +4,8 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -27,22 +29,30 @@ def is_stale() -> bool:
 
 
 def build_library(verbose: bool = False) -> str:
-    """Compile every kernel file for gfx950 and link the shared library. Always compiles."""
+    """Compile every kernel file for gfx950, side by side, and link the shared library. Always compiles."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
-           "-ffp-contract=off", "-mllvm", "-amdgpu-mfma-vgpr-form",
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-           "-o", LIB] + sources()
-    if verbose:
-        print(" ".join(cmd))
-    res = subprocess.run(cmd, capture_output=True, text=True)
+    flags = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-ffp-contract=off", "-mllvm", "-amdgpu-mfma-vgpr-form",
+             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+    # the Lloyd kernels of the larger padded numbers of features are objects of their own (they take longest and go first)
+    lloyd = os.path.join(CSRC, "kmeans_lloyd.hip")
+    units = [(lloyd, ["-DRLS_LLOYD_DPAD=32"]), (lloyd, ["-DRLS_LLOYD_DPAD=16"]), (lloyd, [])] + [(s, []) for s in sources() if s != lloyd]
     noise = "is not a recognized feature for this target"
-    err = "\n".join(line for line in res.stderr.splitlines() if noise not in line)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + err)
-    if verbose and err.strip():
-        print(err, file=sys.stderr)
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        err = "\n".join(line for line in res.stderr.splitlines() if noise not in line)
+        if res.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + err)
+        if verbose and err.strip():
+            print(err, file=sys.stderr)
+
+    with tempfile.TemporaryDirectory() as tmp:
+        objects = [os.path.join(tmp, f"{i}.o") for i in range(len(units))]
+        with ThreadPoolExecutor(min(8, os.cpu_count() or 1)) as pool:
+            list(pool.map(lambda unit, obj: run([hipcc] + flags + unit[1] + ["-c", "-o", obj, unit[0]]), units, objects))
+        run([hipcc, "--offload-arch=gfx950", "-fPIC", "-shared", "-o", LIB] + objects)
     return LIB
 
 

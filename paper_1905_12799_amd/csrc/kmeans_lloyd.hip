@@ -24,6 +24,10 @@
 //            equal a fresh sum in any order); per-chunk deltas go to global memory and lloyd_centroids_kernel
 //            adds them to the 128-bit totals, rounds once to fp64, divides by the count and rounds to fp32
 // The final pass replaces the update by the fp64 loss of every point and the label output.
+//
+// Two other forms share this file's plan and arithmetic, and give the same labels, centroids and sums: sweeps with much distance
+// work run on a copy of the points in spatial order (kmeans_order.hip), where a unit of neighbouring points meets only the
+// tiles of centroids that can win there (ORD, make_lists); sweeps of a few thousand points are one launch (kmeans_small.hip).
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
@@ -2650,6 +2654,17 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
 
 }  // namespace
 
+// The kernels take minutes to compile: the file is compiled once for each padded number of features, 16 and 32 with
+// RLS_LLOYD_DPAD set to it (nothing but that launch), 8 together with everything else.
+hipError_t launch_sweep_dpad16(const SweepPlan &plan, const SweepLayout &L, const SweepArgs &a, hipStream_t s);
+hipError_t launch_sweep_dpad32(const SweepPlan &plan, const SweepLayout &L, const SweepArgs &a, hipStream_t s);
+#if defined(RLS_LLOYD_DPAD) && RLS_LLOYD_DPAD == 16
+hipError_t launch_sweep_dpad16(const SweepPlan &plan, const SweepLayout &L, const SweepArgs &a, hipStream_t s) { return launch_sweep_dp<16>(plan, L, a, s); }
+#elif defined(RLS_LLOYD_DPAD) && RLS_LLOYD_DPAD == 32
+hipError_t launch_sweep_dpad32(const SweepPlan &plan, const SweepLayout &L, const SweepArgs &a, hipStream_t s) { return launch_sweep_dp<32>(plan, L, a, s); }
+#else
+
+
 int padded_d(int d) { return d <= 8 ? 8 : (d <= 16 ? 16 : 32); }
 
 bool sweep_uses_prepared(const SweepPlan &plan, int32_t iters, bool trace)
@@ -2926,9 +2941,10 @@ hipError_t launch_sweep(const SweepPlan &plan, const SweepLayout &L, const Sweep
 {
     switch (plan.dp) {
     case 8: return launch_sweep_dp<8>(plan, L, a, s);
-    case 16: return launch_sweep_dp<16>(plan, L, a, s);
-    default: return launch_sweep_dp<32>(plan, L, a, s);
+    case 16: return launch_sweep_dpad16(plan, L, a, s);
+    default: return launch_sweep_dpad32(plan, L, a, s);
     }
 }
+#endif
 
 }  // namespace rls
