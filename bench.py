@@ -48,13 +48,13 @@ VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4.0   # wave64 vector instructions per secon
 # source they were taken with (step_source_digest); with any other the fields made from them are null.
 COUNTERS = {
     # mean over the 30 rounds of a sweep (first round included, like the launches the events time)
-    "mid": {"source": "f4dd567622e2", "fetch_kib": 8647.7, "write_kib": 11653.4, "fetch_scale": 2.0, "write_scale": 1.0,
+    "mid": {"source": "dbb502bc6f87", "fetch_kib": 8647.4, "write_kib": 11653.4, "fetch_scale": 2.0, "write_scale": 1.0,
            "valu_insts": 1.056e+07, "mfma_insts": 5.898e+05},
-    "whole_layer": {"source": "f4dd567622e2", "fetch_kib": 316770.9, "write_kib": 50231.8, "fetch_scale": 2.0, "write_scale": 1.0,
+    "whole_layer": {"source": "dbb502bc6f87", "fetch_kib": 316760.3, "write_kib": 50230.0, "fetch_scale": 2.0, "write_scale": 1.0,
                    "valu_insts": 8.092e+07, "mfma_insts": 2.86e+06},
-    "large": {"source": "f4dd567622e2", "fetch_kib": 7896888.3, "write_kib": 1250652.2, "fetch_scale": 2.0, "write_scale": 1.0,
+    "large": {"source": "dbb502bc6f87", "fetch_kib": 7898241.5, "write_kib": 1250672.1, "fetch_scale": 2.0, "write_scale": 1.0,
              "valu_insts": 2.882e+09, "mfma_insts": 1.869e+08},
-    "batched": {"source": "f4dd567622e2", "fetch_kib": 2564613.6, "write_kib": 340979.3, "fetch_scale": 2.0, "write_scale": 1.0,
+    "batched": {"source": "dbb502bc6f87", "fetch_kib": 2565126.8, "write_kib": 341002.6, "fetch_scale": 2.0, "write_scale": 1.0,
                "valu_insts": 5.367e+08, "mfma_insts": 1.971e+07},
 }
 
