@@ -1,4 +1,5 @@
 // Host entry points of the C ABI declared in rls.h: argument checks, workspace carving, launches.
+#include <algorithm>
 #include <math.h>
 #include <string.h>
 
@@ -60,28 +61,36 @@ static int32_t check_sweep(int64_t N, int32_t d, int32_t k_min, int32_t k_max, i
     return RLS_OK;
 }
 
-// Plan and workspace of a sweep.  With an order of the points where that pays - unless the workspace at hand (bytes; negative:
-// any) holds the sweep without it only, so that a fixed workspace goes on taking what it has taken.
-static int32_t plan_sweep(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch, int64_t bytes, SweepPlan *plan, SweepLayout *L)
+// Plan and workspace of a sweep.  With an order of the points where that pays - unless nothing would read it (a loss trace, fewer
+// than two rounds), or the workspace at hand holds the sweep without it only, so that a fixed workspace goes on taking what it
+// has taken.
+static int32_t plan_sweep(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch, int32_t iters, bool trace, int64_t bytes,
+                          SweepPlan *plan, SweepLayout *L)
 {
     for (int ordered = sweep_wants_order(N, d, k_min, k_max, batch) ? 1 : 0; ordered >= 0; --ordered) {
         const int32_t rc = make_sweep_plan(N, d, k_min, k_max, batch, ordered != 0, plan);
         if (rc != RLS_OK) return rc;
+        if (ordered != 0 && !sweep_uses_prepared(*plan, iters, trace)) continue;
         sweep_layout(*plan, N, d, k_max, batch, false, L);
-        if (bytes < 0 || L->total <= bytes) break;
+        if (L->total <= bytes) break;
     }
     return RLS_OK;
 }
 
-int64_t sweep_least_workspace(int64_t N, int32_t d, int32_t k_min, int32_t k_max)
+static int64_t form_workspace(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch, bool ordered)
 {
-    int32_t rc = check_sweep(N, d, k_min, k_max, 1);
     SweepPlan plan;
-    if (rc == RLS_OK) rc = make_sweep_plan(N, d, k_min, k_max, 1, false, &plan);
+    const int32_t rc = make_sweep_plan(N, d, k_min, k_max, batch, ordered, &plan);
     if (rc != RLS_OK) return rc;
     SweepLayout L;
-    sweep_layout(plan, N, d, k_max, 1, false, &L);
+    sweep_layout(plan, N, d, k_max, batch, false, &L);
     return L.total;
+}
+
+int64_t sweep_least_workspace(int64_t N, int32_t d, int32_t k_min, int32_t k_max)
+{
+    const int32_t rc = check_sweep(N, d, k_min, k_max, 1);
+    return rc != RLS_OK ? rc : form_workspace(N, d, k_min, k_max, 1, false);
 }
 
 }  // namespace rls
@@ -174,10 +183,11 @@ int64_t rls_kmeans_sweep_workspace_bytes(int64_t N, int32_t d, int32_t k_min, in
 {
     const int32_t rc = check_sweep(N, d, k_min, k_max, batch);
     if (rc != RLS_OK) return rc;
-    SweepPlan plan;
-    SweepLayout L;
-    const int32_t prc = plan_sweep(N, d, k_min, k_max, batch, -1, &plan, &L);
-    return prc != RLS_OK ? prc : L.total;
+    // (whichever form the call then takes)
+    const int64_t plain = form_workspace(N, d, k_min, k_max, batch, false);
+    if (plain < 0 || !sweep_wants_order(N, d, k_min, k_max, batch)) return plain;
+    const int64_t ordered = form_workspace(N, d, k_min, k_max, batch, true);
+    return ordered < 0 ? ordered : std::max(plain, ordered);
 }
 
 int32_t rls_kmeanspp_chain(const float *X_dev, int64_t N, int32_t d, int64_t ldx, int32_t k_max, uint64_t seed,
@@ -216,7 +226,7 @@ int32_t rls_kmeans_sweep_batched(int32_t batch, const float *X_dev, int64_t N, i
     if (batch > 1 && x_batch_stride < N * ldx - (ldx - d)) return RLS_ERR_SHAPE;
     SweepPlan plan;
     SweepLayout L;
-    rc = plan_sweep(N, d, k_min, k_max, batch, workspace_bytes, &plan, &L);
+    rc = plan_sweep(N, d, k_min, k_max, batch, iters, inertia_trace_dev != nullptr, workspace_bytes, &plan, &L);
     if (rc != RLS_OK) return rc;
     if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < L.total) return RLS_ERR_WORKSPACE;
     char *ws = static_cast<char *>(workspace_dev);
@@ -250,17 +260,27 @@ int32_t rls_kmeans_sweep(const float *X_dev, int64_t N, int32_t d, int64_t ldx, 
                                     workspace_bytes, stream);
 }
 
+// The plan of a wave: a last, short one that would not read the order (see sweep_uses_prepared) does without
+static int32_t plan_wave(int64_t N, int32_t d, int32_t k_lo, int32_t k_hi, int32_t iters, bool ordered, SweepPlan *plan)
+{
+    int32_t rc = make_sweep_plan(N, d, k_lo, k_hi, 1, ordered, plan);
+    if (rc == RLS_OK && ordered && !sweep_uses_prepared(*plan, iters, false)) rc = make_sweep_plan(N, d, k_lo, k_hi, 1, false, plan);
+    return rc;
+}
+
 static int32_t until_knee_workspace(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t k_wave, bool ordered, int64_t *bytes)
 {
     int64_t need = 0;
     for (int32_t k_lo = k_min; k_lo <= k_max; k_lo += k_wave) {
         const int32_t k_hi = k_lo + k_wave - 1 < k_max ? k_lo + k_wave - 1 : k_max;
-        SweepPlan plan;
-        const int32_t rc = make_sweep_plan(N, d, k_lo, k_hi, 1, ordered, &plan);
-        if (rc != RLS_OK) return rc;
-        SweepLayout L;
-        sweep_layout(plan, N, d, k_max, 1, true, &L);     // chain sized for k_max: the leading blocks sit at the same offsets in every wave
-        if (L.total > need) need = L.total;
+        for (int form = ordered ? 1 : 0; form >= 0; --form) {     // (whichever form a wave takes)
+            SweepPlan plan;
+            const int32_t rc = make_sweep_plan(N, d, k_lo, k_hi, 1, form != 0, &plan);
+            if (rc != RLS_OK) return rc;
+            SweepLayout L;
+            sweep_layout(plan, N, d, k_max, 1, true, &L);     // chain sized for k_max: the leading blocks sit at the same offsets in every wave
+            if (L.total > need) need = L.total;
+        }
     }
     *bytes = need;
     return RLS_OK;
@@ -314,7 +334,7 @@ int32_t rls_kmeans_sweep_until_knee(const float *X_dev, int64_t N, int32_t d, in
     for (int32_t k_lo = k_min; k_lo <= k_max && !fired; k_lo += k_wave) {
         const int32_t k_hi = k_lo + k_wave - 1 < k_max ? k_lo + k_wave - 1 : k_max;
         SweepPlan plan;
-        rc = make_sweep_plan(N, d, k_lo, k_hi, 1, ordered, &plan);
+        rc = plan_wave(N, d, k_lo, k_hi, iters, ordered, &plan);
         if (rc != RLS_OK) return rc;
         SweepLayout L;
         sweep_layout(plan, N, d, k_max, 1, true, &L);

@@ -42,6 +42,19 @@ def make(kind, N, d, seed):
     return X
 
 
+def as_they_come(rls, X, k_min, k_max, iters, **kw):
+    """The sweep with a workspace that is short of the ordered rows.  The library turns that down where it would not have taken
+    an order anyway, so no comparison with it passes for want of an ordered sweep."""
+    batch, (N, d) = (X.shape[0] if X.dim() == 3 else 1), X.shape[-2:]
+    short = rls.kmeans_sweep_workspace_bytes(N, d, k_min, k_max, batch) - batch * N * (8 if d <= 8 else 16 if d <= 16 else 32) * 4
+    workspace = torch.empty(short, dtype=torch.uint8, device="cuda")
+    return (rls.kmeans_sweep_batched if X.dim() == 3 else rls.kmeans_sweep)(X, k_min, k_max, iters, workspace=workspace, **kw)
+
+
+def equal(a, b):
+    return torch.equal(a.labels, b.labels) and torch.equal(a.centroids, b.centroids) and torch.equal(a.inertia, b.inertia)
+
+
 # units and chunks that end raggedly, every padded width, groups of 1, 2, 4 and 8 slots per run, groups with fewer and with
 # more tiles than lists are kept for
 CASES = [("clusters", 180224, 16, 1, 40), ("clusters", 81921, 13, 8, 63), ("clusters", 90011, 5, 1, 64), ("clusters", 60017, 32, 1, 100),
@@ -129,6 +142,16 @@ def test_ordered_sweep_in_a_graph(rls):
         assert int(res.status.item()) == 0
         for got, exp in zip((res.labels, res.centroids, res.inertia), want):
             assert torch.equal(got, exp), f"replay {rep}"
+
+
+@pytest.mark.parametrize("iters,want_trace", [(0, False), (1, False), (4, True)])
+def test_sweeps_that_would_not_read_the_order_do_without(rls, iters, want_trace):
+    """A loss trace, or fewer than two rounds: the same sweep, to the last bit of its losses, as without an order at hand."""
+    X = torch.as_tensor(make("noise", 90011, 16, 6)).cuda()
+    got = rls.kmeans_sweep(X, 1, 64, iters, seed=5, want_trace=want_trace)
+    want = as_they_come(rls, X, 1, 64, iters, seed=5, want_trace=want_trace)
+    assert equal(got, want)
+    assert not want_trace or torch.equal(got.trace, want.trace)
 
 
 def test_ordered_sweep_turns_down_bad_data(rls):
