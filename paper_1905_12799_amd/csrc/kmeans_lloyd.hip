@@ -1890,46 +1890,6 @@ __global__ void __launch_bounds__(256) lloyd_prepare_kernel(const float *__restr
     }
 }
 
-// Sums in two doubles (the second holds what the first cannot): error-free sums and products of doubles, about 106 bits.
-struct Twofold {
-    double hi, lo;
-};
-__device__ inline Twofold twofold_sum(double a, double b)
-{
-    const double s = a + b, t = s - a;
-    return {s, (a - (s - t)) + (b - t)};
-}
-__device__ inline Twofold twofold_add(Twofold a, Twofold b)
-{
-    const Twofold s = twofold_sum(a.hi, b.hi);
-    const double lo = s.lo + (a.lo + b.lo), hi = s.hi + lo;
-    return {hi, lo - (hi - s.hi)};
-}
-__device__ inline Twofold twofold_product(double a, double b)
-{
-    const double p = a * b;
-    return {p, fma(a, b, -p)};
-}
-__device__ inline Twofold twofold_times(Twofold a, double b)
-{
-    const Twofold p = twofold_product(a.hi, b);
-    const double lo = fma(a.lo, b, p.lo), hi = p.hi + lo;
-    return {hi, lo - (hi - p.hi)};
-}
-__device__ inline Twofold twofold_wave_sum(Twofold v)
-{
-    for (int off = 32; off >= 1; off >>= 1) v = twofold_add(v, Twofold{__shfl_xor(v.hi, off, 64), __shfl_xor(v.lo, off, 64)});
-    return v;
-}
-// a 128-bit two's complement number, scaled by 2^-shift
-__device__ inline Twofold twofold_of_fixed(long long hi, unsigned long long lo, int shift)
-{
-    const Twofold low = twofold_sum((double)(lo >> 32) * 4294967296.0, (double)(lo & 0xffffffffull));       // both exact
-    const Twofold high = twofold_sum((double)(hi >> 32) * 4294967296.0 * 18446744073709551616.0, (double)((unsigned long long)hi & 0xffffffffull) * 18446744073709551616.0);
-    const Twofold v = twofold_add(high, low);
-    return {ldexp(v.hi, -shift), ldexp(v.lo, -shift)};
-}
-
 // ---- the same for an ordered sweep: the copy is in the order of the places, the rows go along (padded with zeros to DP
 //      floats, so that rows of any length are read 16 bytes at a time later on), and every unit leaves its centre - the mean
 //      of its points as the operand pieces hold it - and an upper bound of the distance from there to its points.
@@ -1937,7 +1897,7 @@ template <int DP>
 __global__ void __launch_bounds__(256) lloyd_prepare_ordered_kernel(const float *__restrict__ X, int64_t N, int d, int64_t ldx, int64_t x_bs,
                                                                     const int32_t *__restrict__ status, char *ws, int64_t ws_bs,
                                                                     int64_t off_colinfo, int64_t off_perm, int64_t off_xp, int64_t off_xs,
-                                                                    int64_t off_centres, int64_t off_radius, int64_t off_rowsq)
+                                                                    int64_t off_centres, int64_t off_radius)
 {
     constexpr int H = DP / 2, NK = ksteps_of(DP), HP = 8 * NK, UB = unit_blocks_of(DP);
     const int b = blockIdx.y;
@@ -1956,8 +1916,6 @@ __global__ void __launch_bounds__(256) lloyd_prepare_ordered_kernel(const float 
     float mean_h[H];
 #pragma unroll
     for (int s = 0; s < H; ++s) mean_h[s] = f0 + s < d ? colmean[f0 + s] : 0.0f;
-    const float back = -1.0f / scale;                 // (exact: a power of two)
-    Twofold sq = {0.0, 0.0};                          // squared distances of this thread's elements from the column means
     // operand pieces of one lane's half of a row, and the norm of the row
     auto pieces = [&](const float (&xc)[HP], float norm, uint4 *bp, int at, bool store) {
 #pragma unroll
@@ -2012,11 +1970,7 @@ __global__ void __launch_bounds__(256) lloyd_prepare_ordered_kernel(const float 
             }
             pieces(xc[ub], xn, xp + blk * prep_block_u4_of(DP), n, blk < n_blocks);
 #pragma unroll
-            for (int s = 0; s < H; ++s) {
-                sum[s] += xc[ub][s];
-                const double off = valid && f0 + s < d ? (double)xr[s] - (double)(mean_h[s] * back) : 0.0;
-                sq = twofold_add(sq, twofold_product(off, off));
-            }
+            for (int s = 0; s < H; ++s) sum[s] += xc[ub][s];
         }
         const float inv_n = 1.0f / (float)min(N - unit * (32 * UB), (int64_t)(32 * UB));
         float bc[HP];
@@ -2049,12 +2003,6 @@ __global__ void __launch_bounds__(256) lloyd_prepare_ordered_kernel(const float 
         pieces(bc, norm, centres + (unit >> 5) * prep_block_u4_of(DP), (int)(unit & 31), n == 0);
         if (lane == 0) radius[unit] = sqrtf(far) * 1.00001f + 1.0e-6f;     // (rounding of the differences: below d 2^-24 of it)
     }
-    __shared__ Twofold part[4];
-    sq = twofold_wave_sum(sq);
-    if (lane == 0) part[threadIdx.x >> 6] = sq;
-    __syncthreads();
-    if (threadIdx.x == 0)
-        reinterpret_cast<Twofold *>(wsb + off_rowsq)[blockIdx.x] = twofold_add(twofold_add(part[0], part[1]), twofold_add(part[2], part[3]));
 }
 
 // workgroups of lloyd_prepare_ordered_kernel: 4 waves each, about 4 units per wave
@@ -2177,7 +2125,6 @@ struct CentroidArgs {
     int64_t ws_bs;
     int64_t off_colinfo, off_opA, off_cnmax, off_psum, off_pcnt, off_losum, off_tot, off_totcnt;
     int64_t off_rowpos;          // places of the centroids among the rows of their group, or -1: by index
-    int64_t off_losspart;        // (loss of an ordered sweep)
 };
 
 // One workgroup per run and part of kPartRows of its centroids: new centroids (from the seeding rows, or from the
@@ -2342,156 +2289,203 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
     }
 }
 
-// ---- the end of an ordered sweep.  The loss of a run without a look at the points: with every coordinate taken from its
-//      column's mean m, the members of a cluster with centroid c, n members and exact sum S are at
-//         sum |x - c|^2 = sum |x - m|^2 - 2 (c - m).(S - n m) + n |c - m|^2,
-//      and the first sum over all clusters is that of all points (lloyd_prepare_ordered_kernel).  In two doubles, where what
-//      cancels between the terms is far below the last bit of the result.
-//      One workgroup per run and part of its centroids, as in lloyd_centroids_kernel: the sums after the final assignment.
-template <int DP>
-__global__ void __launch_bounds__(kThreads) lloyd_ordered_loss_kernel(SweepPlan plan, CentroidArgs a)
+// ---- the end of an ordered sweep: the labels go back to the points' own order, and every point's exact distance to its centroid
+//      is added up.  The additions are those of the final pass over the points as they come (lloyd_step_kernel), one by one and
+//      in the same order - lanes over their slabs of a chunk, the lanes of a wave, the waves, the chunks (lloyd_loss_kernel) -, so
+//      that a sweep has the same losses to the last bit whichever form it takes.  (Losses from the exact sums of the clusters and
+//      the squares of all points cost next to nothing, but where a column spans many binary digits next to nothing is left of them:
+//      their terms agree in more digits than two doubles hold.)
+//      `plan` is the plan of that other form.  A workgroup takes one of its chunks and the runs of a span: runs whose chunks are
+//      the same there and whose label bytes lie side by side here.  Where a wave of the step takes 32 points at a time, 32 lanes do
+//      so here: up to d_pad 16 in two half-waves, each every other run of the span (1M x 16, k 1..64: 230 us, one half-wave for all
+//      runs 250); at d_pad 32, where spans have down to two runs, one for all of them, which converts the row to fp64 once (4M x 32,
+//      k 1..128: 5.0 ms, two 5.8).  Bound by vector issue: per point, run and feature a conversion (8 cycles a wave) and three fp64
+//      operations (4 each), three quarters of the time at 1M x 16; the labels alone took 94 us there.
+struct RunSpan {
+    int16_t run0, lab0;                    // first run; the label bytes' place (see GroupDesc::lab0)
+    uint8_t n_runs, group;                 // runs; the group of `plan`
+    uint8_t slots, first;                  // label bytes of a point, and which of them is that of the first run
+};
+struct RunSpans {
+    int32_t n;
+    RunSpan s[RLS_MAX_K];
+};
+static_assert(sizeof(SweepPlan) + sizeof(RunSpans) + 256 <= 4096, "kernel arguments");
+struct EndArgs {
+    const float *X;
+    int64_t N, ldx, x_bs;
+    int32_t d;
+    const float *C;
+    int64_t c_bs;
+    int32_t *labels;                       // or null
+    int64_t lab_bs;
+    const int32_t *status;
+    char *ws;
+    int64_t ws_bs;
+    int64_t off_inv, off_rowidx, off_prev, off_pj;
+    int32_t batch, wgs;                    // spaces; chunks of all spans
+};
+constexpr int end_lds_bytes(int dp, int rows) { return rows * (dp + 4) * 4 + (step_threads_of(dp) / 64) * 8 * 8 + rows; }
+
+constexpr int end_halves_of(int dp) { return dp <= 16 ? 2 : 1; }
+constexpr int end_threads_of(int dp) { return step_threads_of(dp) / 2 * end_halves_of(dp); }
+
+template <int DP, bool VEC>
+__global__ void __launch_bounds__(end_threads_of(DP)) lloyd_ordered_end_kernel(SweepPlan plan, RunSpans spans, EndArgs a)
 {
-    __shared__ long long part_hi[kThreads], part_cnt[kThreads];
-    __shared__ unsigned long long part_lo[kThreads];
-    __shared__ Twofold wave_part[kThreads / 64];
-    const int b = blockIdx.y, tid = threadIdx.x;
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int HS = end_halves_of(DP), TH = end_threads_of(DP), WV = step_threads_of(DP) / 64, CS = DP + 4, NR = 8 / HS;
+    const int tid = threadIdx.x, n = tid & 31, hl = (tid >> 5) & (HS - 1), w = tid / (32 * HS);
+    int b, chunk, span;
+    if (plan.chunk_block > 0) {
+        // the same chunks for every span: the spans of a chunk follow each other on one XCD, they read the same rows
+        const int turn = (int)(blockIdx.x >> 3), at = turn / spans.n * 8 + (int)(blockIdx.x & 7);
+        span = turn % spans.n;
+        b = at / plan.g[0].n_chunks;
+        chunk = at - b * plan.g[0].n_chunks;
+        if (b >= a.batch) return;
+    } else {
+        // chunks of their own, hardly more than compute units: no workgroup without one, which would leave another compute unit
+        // two of them (1,000,003 x 16, k 8..23: 106 us with such, 75 without).  Two spans per lane find where theirs begin.
+        b = blockIdx.x / a.wgs;
+        const int v = blockIdx.x - b * a.wgs, lane = tid & 63;
+        const int c0 = 2 * lane < spans.n ? plan.g[spans.s[2 * lane].group].n_chunks : 0;
+        const int c1 = 2 * lane + 1 < spans.n ? plan.g[spans.s[2 * lane + 1].group].n_chunks : 0;
+        int before = c0 + c1;                            // inclusive, then exclusive sums
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(before, off, 64);
+            if (lane >= off) before += o;
+        }
+        before -= c0 + c1;
+        const int from = __popcll(__builtin_amdgcn_ballot_w64(before <= v)) - 1;        // (behind the last span: the sum of all, above v)
+        chunk = v - __shfl(before, from, 64);
+        const int first = __shfl(c0, from, 64);
+        span = 2 * from + (chunk >= first ? 1 : 0);
+        if (chunk >= first) chunk -= first;
+        b = __builtin_amdgcn_readfirstlane(b); chunk = __builtin_amdgcn_readfirstlane(chunk); span = __builtin_amdgcn_readfirstlane(span);
+    }
+    const RunSpan sp = spans.s[span];
+    const GroupDesc g = plan.g[sp.group];
     if (a.status[b] != 0) return;
-    const int parts0 = parts_upto(plan.k_min - 1);
-    int run = 0;
-    for (int step = 64; step >= 1; step >>= 1)
-        if (run + step < plan.n_runs && parts_upto(plan.k_min + run + step - 1) - parts0 <= (int)blockIdx.x) run += step;
-    const int d = a.d, k = plan.k_min + run;
-    const int part = (int)blockIdx.x - (parts_upto(k - 1) - parts0);
-    const int j0 = part * kPartRows, rows = min(kPartRows, k - j0);
-    const int row0 = rows_before(plan.k_min, run);
-    int gi = 0;
-    while (gi + 1 < plan.n_groups && plan.g[gi + 1].run0 <= run) ++gi;
-    const GroupDesc g = plan.g[gi];
-    const int grow0 = rows_before(plan.k_min, g.run0), grows = rows_before(plan.k_min, g.run0 + g.n_runs) - grow0;
-    char *wsb = a.ws + (int64_t)b * a.ws_bs;
-    const int E = rows * DP, nsl = kThreads / E;
-    const int e = tid % E, sl = tid / E, j = j0 + e / DP, l = e % DP;
-    const int64_t at = (int64_t)(row0 + j) * d + l;
-    long long hi = 0, cnt = 0;
-    unsigned long long lo = 0;
-    if (sl < nsl && l < d) {
-        const int64_t first = (int64_t)g.part0 + row0 - grow0 + j;
-        const long long *psum = reinterpret_cast<const long long *>(wsb + a.off_psum) + first * d + l;
-        const int *pcnt = reinterpret_cast<const int *>(wsb + a.off_pcnt) + first;
-        const int c_begin = (int)((int64_t)g.n_chunks * sl / nsl), c_end = (int)((int64_t)g.n_chunks * (sl + 1) / nsl);
-        if (sl == 0) {
-            const long long *tot = reinterpret_cast<const long long *>(wsb + a.off_tot) + at * 2;
-            hi = tot[0];
-            lo = (unsigned long long)tot[1];
-            cnt = reinterpret_cast<const long long *>(wsb + a.off_totcnt)[at];
-        }
-        sum_chunks(psum, pcnt, (int64_t)grows * d, grows, c_begin, c_end, hi, lo, cnt);
+    const int d = a.d, k0 = plan.k_min + sp.run0;
+    const int grow0 = rows_before(plan.k_min, sp.run0), rows = rows_before(plan.k_min, sp.run0 + sp.n_runs) - grow0;
+    float *cs_s = reinterpret_cast<float *>(smem);
+    double *jpart_s = reinterpret_cast<double *>(smem + rows * CS * 4);          // [WV][8]
+    unsigned char *rowidx_s = smem + rows * CS * 4 + WV * 8 * 8;
+    const char *wsb = a.ws + (int64_t)b * a.ws_bs;
+    const float *Xb = a.X + (int64_t)b * a.x_bs, *Cb = a.C + (int64_t)b * a.c_bs + (int64_t)grow0 * d;
+    const int32_t *inv = reinterpret_cast<const int32_t *>(wsb + a.off_inv);
+    const unsigned char *prev = reinterpret_cast<const unsigned char *>(wsb + a.off_prev) + (int64_t)sp.lab0 * ((a.N + 15) / 16 * 16);
+    static_assert(TH % DP == 0, "a thread keeps its feature");
+    for (int r0 = tid / DP; r0 < rows; r0 += 8 * (TH / DP)) {            // (eight on their way at a time)
+        const int l = tid % DP;
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = Cb[min(r0 + u * (TH / DP), rows - 1) * d + min(l, d - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (r0 + u * (TH / DP) < rows) cs_s[(r0 + u * (TH / DP)) * CS + l] = l < d ? v[u] : 0.0f;
     }
-    part_hi[tid] = hi; part_lo[tid] = lo; part_cnt[tid] = cnt;
+    for (int e = tid; e < rows; e += TH) rowidx_s[e] = reinterpret_cast<const unsigned char *>(wsb + a.off_rowidx)[grow0 + e];
     __syncthreads();
-    Twofold v = {0.0, 0.0};
-    if (tid < E && l < d) {
-        for (int s = 1; s < nsl; ++s) {
-            const unsigned long long nlo = lo + part_lo[s * E + e];
-            hi += part_hi[s * E + e] + (nlo < lo ? 1 : 0);
-            lo = nlo;
-            cnt += part_cnt[s * E + e];
+
+    const int begin = chunk * g.chunk_len, end = (int)min(a.N, (int64_t)begin + g.chunk_len);
+    const int twice = slab_blocks_of(DP, g.S) - 1;                     // a slab is one block of 32 points, or two
+    const int n_slabs = (end - begin + (32 << twice) - 1) / (32 << twice);
+    const int steps = n_slabs > w ? ((n_slabs - w + WV - 1) / WV) << twice : 0;
+    auto point = [&](int t) { return begin + ((((t >> twice) * WV + w) << twice) + (t & twice)) * 32 + n; };
+    // (past the end: the chunk's last point)
+    auto place_of = [&](int t) { return inv[min(point(t), end - 1)]; };
+    auto fetch = [&](int t, int place, float (&x)[DP], uint2 &word) {
+        const unsigned char *at = prev + (int64_t)place * sp.slots;
+        word = make_uint2(0u, 0u);
+        if (sp.slots == 8) word = *reinterpret_cast<const uint2 *>(at);
+        else if (sp.slots == 4) word.x = *reinterpret_cast<const unsigned *>(at);
+        else if (sp.slots == 2) word.x = *reinterpret_cast<const unsigned short *>(at);
+        else word.x = *at;
+        const float *row = Xb + (int64_t)min(point(t), end - 1) * a.ldx;
+#pragma unroll
+        for (int l = 0; l < DP; l += 4) {
+            float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (VEC) {
+                if (l < d) v = *reinterpret_cast<const float4 *>(row + l);
+            } else {
+                if (l + 0 < d) v.x = row[l + 0];
+                if (l + 1 < d) v.y = row[l + 1];
+                if (l + 2 < d) v.z = row[l + 2];
+                if (l + 3 < d) v.w = row[l + 3];
+            }
+            x[l] = v.x; x[l + 1] = v.y; x[l + 2] = v.z; x[l + 3] = v.w;
         }
-        int shift = reinterpret_cast<const int *>(wsb + a.off_colinfo + 128)[l];
-        if (reinterpret_cast<const int *>(wsb + a.off_colinfo + 256)[l] != 0) {
-            // total = main * 2^kLowBits + low, on the scale 2^-(shift + kLowBits)
-            const int place = (int)reinterpret_cast<const unsigned short *>(wsb + a.off_rowpos)[row0 + j];
-            const long long low = reinterpret_cast<const long long *>(wsb + a.off_losum)[(int64_t)(grow0 + place) * d + l];
-            hi = (long long)(((unsigned long long)hi << kLowBits) | (lo >> (64 - kLowBits)));
-            lo = lo << kLowBits;
-            const unsigned long long nlo = lo + (unsigned long long)low;
-            hi += (low >> 63) + (nlo < lo ? 1 : 0);
-            lo = nlo;
-            shift += kLowBits;
-        }
-        const float scale = *reinterpret_cast<const float *>(wsb + a.off_colinfo + kColScaleOff);
-        const double mean = (double)(reinterpret_cast<const float *>(wsb + a.off_colinfo)[l] * (-1.0f / scale)), n = (double)cnt;
-        const Twofold sum = twofold_add(twofold_of_fixed(hi, lo, shift), twofold_product(-n, mean));
-        const double c = (double)(a.C + (int64_t)b * a.c_bs)[at] - mean;
-        // c (n c - 2 S)
-        const Twofold nc = twofold_product(n, c);
-        v = twofold_times(twofold_add(nc, Twofold{-2.0 * sum.hi, -2.0 * sum.lo}), c);
+    };
+    // runs hl, hl + HS, ... of the span: their first rows and label bytes (one of the last runs twice, rather than one that is not there)
+    double sum[NR];
+    int row[NR], byte[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const int r = min(HS * i + hl, sp.n_runs - 1);
+        sum[i] = 0.0;
+        row[i] = r * k0 + r * (r - 1) / 2;
+        byte[i] = sp.first + r;
     }
-    v = twofold_wave_sum(v);
-    if ((tid & 63) == 0) wave_part[tid >> 6] = v;
+    // (requested ahead: a point's place by two steps, its row and label bytes by one; further ahead measured the same)
+    float xn[DP];
+    uint2 wordn;
+    fetch(0, place_of(0), xn, wordn);
+    int placen = place_of(1);
+    for (int t = 0; t < steps; ++t) {
+        const int p = point(t);
+        const bool valid = p < end;
+        const uint2 word = wordn;
+        int label[NR];
+#pragma unroll
+        for (int i = 0; i < NR; ++i) label[i] = rowidx_s[row[i] + (int)(((byte[i] < 4 ? word.x : word.y) >> (8 * (byte[i] & 3))) & 127u)];
+        if (valid && a.labels) {
+            int32_t *const out = a.labels + (int64_t)b * a.lab_bs + (int64_t)sp.run0 * a.N + p;
+#pragma unroll
+            for (int i = 0; i < NR; ++i)
+                if (HS * i + hl < sp.n_runs) out[(HS * i + hl) * a.N] = label[i];
+        }
+        float x[DP];
+#pragma unroll
+        for (int l = 0; l < DP; ++l) x[l] = xn[l];
+        fetch(t + 1, placen, xn, wordn);
+        placen = place_of(t + 2);
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            if (HS * i >= sp.n_runs) continue;
+            const double dist = exact_distance<DP>(x, cs_s + (row[i] + label[i]) * CS);
+            sum[i] = __dadd_rn(sum[i], valid ? dist : 0.0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const double v = half_sum_f64(sum[i]);
+        if (n == 0) jpart_s[w * 8 + HS * i + hl] = v;
+    }
     __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < kThreads / 64; ++w) v = twofold_add(v, wave_part[w]);
-        reinterpret_cast<Twofold *>(wsb + a.off_losspart)[run * kMaxParts + part] = v;
+    if (tid < sp.n_runs) {
+        double v = 0.0;
+        for (int q = 0; q < WV; ++q) v = __dadd_rn(v, jpart_s[q * 8 + tid]);
+        reinterpret_cast<double *>(const_cast<char *>(wsb) + a.off_pj)[(int64_t)(g.wg0 + chunk) * 8 + (sp.run0 - g.run0) + tid] = v;
     }
 }
 
-__global__ void __launch_bounds__(1024) lloyd_ordered_loss_final_kernel(SweepPlan plan, const int32_t *status, const char *ws, int64_t ws_bs, int64_t off_losspart,
-                                                                        int64_t off_rowsq, int n_rowsq, double *out, int64_t out_bs)
+// the spans of an ordered sweep: every run lies in one
+inline RunSpans run_spans(const SweepPlan &plan, const SweepPlan &plain)
 {
-    __shared__ Twofold wave_part[16];
-    const int b = blockIdx.x, tid = threadIdx.x;
-    if (status[b] != 0) return;
-    const char *wsb = ws + (int64_t)b * ws_bs;
-    const Twofold *rowsq = reinterpret_cast<const Twofold *>(wsb + off_rowsq);
-    Twofold v = {0.0, 0.0};
-    for (int i = tid; i < n_rowsq; i += 1024) v = twofold_add(v, rowsq[i]);
-    v = twofold_wave_sum(v);
-    if ((tid & 63) == 0) wave_part[tid >> 6] = v;
-    __syncthreads();
-    if (tid >= plan.n_runs) return;
-    v = wave_part[0];
-    for (int w = 1; w < 16; ++w) v = twofold_add(v, wave_part[w]);
-    const Twofold *part = reinterpret_cast<const Twofold *>(wsb + off_losspart) + tid * kMaxParts;
-    const int n_parts = (plan.k_min + tid + kPartRows - 1) / kPartRows;
-    for (int p = 0; p < n_parts; ++p) v = twofold_add(v, part[p]);
-    out[(int64_t)b * out_bs + tid] = fmax(v.hi + v.lo, 0.0);
-}
-
-// The labels in the order of the points: every thread takes four points, looks up their places and, group by group, the label
-// bytes there (a read of up to eight bytes), and writes the labels of each run side by side.
-constexpr int kLabelPoints = 1024;
-__global__ void __launch_bounds__(256) lloyd_ordered_labels_kernel(SweepPlan plan, const int32_t *status, const char *ws, int64_t ws_bs, int64_t N,
-                                                                   int64_t off_inv, int64_t off_rowidx, int64_t off_prev, int32_t *labels, int64_t lab_bs)
-{
-    extern __shared__ unsigned char rowidx_s[];              // centroid of its run by place, all runs
-    constexpr int U = kLabelPoints / 256;
-    const int b = blockIdx.y, tid = threadIdx.x;
-    if (status[b] != 0) return;
-    const char *wsb = ws + (int64_t)b * ws_bs;
-    for (int e = tid; e < plan.total_rows; e += 256) rowidx_s[e] = reinterpret_cast<const unsigned char *>(wsb + off_rowidx)[e];
-    int64_t p[U];
-    int place[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        p[u] = (int64_t)blockIdx.x * kLabelPoints + u * 256 + tid;
-        place[u] = reinterpret_cast<const int32_t *>(wsb + off_inv)[min(p[u], N - 1)];
+    RunSpans r;
+    r.n = 0;
+    int gi = 0, pi = 0;
+    for (int run = 0; run < plan.n_runs;) {
+        while (gi + 1 < plan.n_groups && plan.g[gi + 1].run0 <= run) ++gi;
+        while (pi + 1 < plain.n_groups && plain.g[pi + 1].run0 <= run) ++pi;
+        const GroupDesc &g = plan.g[gi], &p = plain.g[pi];
+        const int end = std::min(g.run0 + g.n_runs, p.run0 + p.n_runs);
+        r.s[r.n++] = RunSpan{(int16_t)run, g.lab0, (uint8_t)(end - run), (uint8_t)pi, (uint8_t)(8 / g.S), (uint8_t)(run - g.run0)};
+        run = end;
     }
-    __syncthreads();
-    int32_t *const out = labels + (int64_t)b * lab_bs;
-    const int64_t n16 = (N + 15) / 16 * 16;
-    for (int gi = 0; gi < plan.n_groups; ++gi) {
-        const GroupDesc g = plan.g[gi];
-        const unsigned char *prev = reinterpret_cast<const unsigned char *>(wsb + off_prev) + g.lab0 * n16;
-        const int R = 8 / g.S;
-        uint2 w[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const unsigned char *at = prev + (int64_t)place[u] * R;
-            w[u].y = 0u;
-            if (R == 8) w[u] = *reinterpret_cast<const uint2 *>(at);
-            else if (R == 4) w[u].x = *reinterpret_cast<const unsigned *>(at);
-            else if (R == 2) w[u].x = *reinterpret_cast<const unsigned short *>(at);
-            else w[u].x = *at;
-        }
-        for (int r = 0; r < g.n_runs; ++r) {
-            const int row0 = rows_before(plan.k_min, g.run0 + r);
-            int32_t *const run = out + (int64_t)(g.run0 + r) * N;
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (p[u] < N) run[p[u]] = rowidx_s[row0 + (((r < 4 ? w[u].x : w[u].y) >> (8 * (r & 3))) & 127u)];
-        }
-    }
+    return r;
 }
 
 // sum of the per-chunk partial losses of every run, in chunk order
@@ -2532,6 +2526,8 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
             reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, false, true, true, false>),
             reinterpret_cast<const void *>(lloyd_step_kernel<DP, false, true, false, false, false>),
             reinterpret_cast<const void *>(lloyd_step_kernel<DP, true, false, false, false, false>),
+            reinterpret_cast<const void *>(lloyd_ordered_end_kernel<DP, false>),
+            reinterpret_cast<const void *>(lloyd_ordered_end_kernel<DP, true>),
         };
         for (const void *fn : fns) {
             const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -2545,7 +2541,7 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
     // group) that reading the rows is what it costs: the prepared copy is 6 to 12% larger than the rows.
     const bool trace = a.trace != nullptr;
     const bool use_pre = sweep_uses_prepared(plan, a.iters, trace);
-    const bool ordered = use_pre && plan.ordered, small = sweep_is_small(plan, a.N, batch, a.iters, trace);
+    const bool ordered = plan.ordered != 0, small = sweep_is_small(plan, a.N, batch, a.iters, trace);
     const int64_t n_units = (a.N + 32 * unit_blocks_of(DP) - 1) / (32 * unit_blocks_of(DP));
     // column statistics
     if (!a.reuse_colstats) {
@@ -2559,7 +2555,7 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
                                           unit_blocks_of(DP) == 2 ? 6 : 5, s);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((lloyd_prepare_ordered_kernel<DP>), dim3((unsigned)ordered_prepare_grid(n_units), batch), dim3(256), 0, s, a.X, a.N,
-                           (int)a.d, a.ldx, a.x_batch_stride, a.status, a.ws, L.per_batch, L.colinfo, L.perm, L.xp, L.xs, L.centres, L.radius, L.rowsq);
+                           (int)a.d, a.ldx, a.x_batch_stride, a.status, a.ws, L.per_batch, L.colinfo, L.perm, L.xp, L.xs, L.centres, L.radius);
     } else if (small || (use_pre && !a.reuse_prepared)) {
         // the prepared copy: a wave takes a block of 32 points at a time, 4 waves per workgroup; one block as long as the chip has
         // room for all of them, then about 8 (8 throughout: 2000 x 8 7.0 instead of 4.8 us, 65,536 x 16 13.1 instead of 5.6)
@@ -2588,7 +2584,7 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
     ca.status = a.status; ca.ws = a.ws; ca.ws_bs = L.per_batch;
     ca.off_colinfo = L.colinfo; ca.off_opA = L.opA; ca.off_cnmax = L.cnmax;
     ca.off_psum = L.psum; ca.off_pcnt = L.pcnt; ca.off_losum = L.losum; ca.off_tot = L.tot; ca.off_totcnt = L.totcnt;
-    ca.off_rowpos = ordered ? L.rowpos : -1; ca.off_losspart = L.losspart;
+    ca.off_rowpos = ordered ? L.rowpos : -1;
     const dim3 centroid_grid(parts_upto(plan.k_min + plan.n_runs - 1) - parts_upto(plan.k_min - 1), batch);
     hipLaunchKernelGGL((lloyd_centroids_kernel<DP, true>), centroid_grid, dim3(kThreads), 0, s, plan, ca);
 
@@ -2632,14 +2628,29 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
         hipLaunchKernelGGL((lloyd_centroids_kernel<DP, false>), centroid_grid, dim3(kThreads), 0, s, plan, ca);
     }
     if (ordered) {
-        // the final assignment is a round like the others; the losses come from its sums, the labels go back to their points
+        // the final assignment is a round like the others; its labels go back to the points, and with them come the losses
         hipLaunchKernelGGL((lloyd_step_kernel<DP, false, false, true, true, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
-        hipLaunchKernelGGL((lloyd_ordered_loss_kernel<DP>), centroid_grid, dim3(kThreads), 0, s, plan, ca);
-        hipLaunchKernelGGL(lloyd_ordered_loss_final_kernel, dim3(batch), dim3(1024), 0, s, plan, a.status, a.ws, L.per_batch, L.losspart, L.rowsq,
-                           (int)ordered_prepare_grid(n_units), a.inertia, (int64_t)plan.n_runs);
-        if (a.labels)
-            hipLaunchKernelGGL(lloyd_ordered_labels_kernel, dim3((unsigned)((a.N + kLabelPoints - 1) / kLabelPoints), batch), dim3(256),
-                               (size_t)plan.total_rows, s, plan, a.status, a.ws, L.per_batch, a.N, L.inv, L.rowidx, L.prev, a.labels, sa.lab_bs);
+        SweepPlan plain;
+        if (make_sweep_plan(a.N, a.d, plan.k_min, plan.k_min + plan.n_runs - 1, batch, false, &plain) != RLS_OK) return hipErrorInvalidValue;
+        int rows = 0;
+        const RunSpans spans = run_spans(plan, plain);
+        for (int i = 0; i < spans.n; ++i)
+            rows = std::max(rows, rows_before(plan.k_min, spans.s[i].run0 + spans.s[i].n_runs) - rows_before(plan.k_min, spans.s[i].run0));
+        EndArgs ea;
+        ea.X = a.X; ea.N = a.N; ea.ldx = a.ldx; ea.x_bs = a.x_batch_stride; ea.d = a.d;
+        ea.C = a.centroids; ea.c_bs = ca.c_bs; ea.labels = a.labels; ea.lab_bs = sa.lab_bs;
+        ea.status = a.status; ea.ws = a.ws; ea.ws_bs = L.per_batch;
+        ea.off_inv = L.inv; ea.off_rowidx = L.rowidx; ea.off_prev = L.prev; ea.off_pj = L.pj;
+        ea.batch = batch; ea.wgs = 0;
+        const bool vec = a.d % 4 == 0 && a.ldx % 4 == 0 && (a.x_batch_stride % 4 == 0 || batch == 1) && (reinterpret_cast<uintptr_t>(a.X) & 15) == 0;
+        for (int i = 0; i < spans.n; ++i) ea.wgs += plain.g[spans.s[i].group].n_chunks;
+        const int64_t end_wgs = plain.chunk_block > 0 ? ((int64_t)plain.g[0].n_chunks * batch + 7) / 8 * 8 * spans.n : (int64_t)ea.wgs * batch;
+        const dim3 end_grid((unsigned)end_wgs), end_block(end_threads_of(DP));
+        const size_t end_lds = (size_t)end_lds_bytes(DP, rows);
+        if (vec) hipLaunchKernelGGL((lloyd_ordered_end_kernel<DP, true>), end_grid, end_block, end_lds, s, plain, spans, ea);
+        else hipLaunchKernelGGL((lloyd_ordered_end_kernel<DP, false>), end_grid, end_block, end_lds, s, plain, spans, ea);
+        hipLaunchKernelGGL(lloyd_loss_kernel, dim3(batch), dim3(128), 0, s, plain, a.status, a.ws, L.per_batch,
+                           L.pj, a.inertia, (int64_t)plan.n_runs, (int64_t)1, (int64_t)0);
         return hipGetLastError();
     }
     hipLaunchKernelGGL((lloyd_step_kernel<DP, true, false, false, false, false>), grid, dim3(step_threads_of(DP)), lds, s, plan, sa);
@@ -2876,7 +2887,13 @@ int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int3
         parts += (int64_t)g.n_chunks * (rows_before(k_min, g.run0 + g.n_runs) - rows_before(k_min, g.run0));
     }
     if (wgs * batch > 0x7fffffffLL || parts > 0x7fffffffLL) return RLS_ERR_INVALID_ARG;
-    plan->n_wgs = (int32_t)wgs;
+    plan->n_wgs = plan->loss_wgs = (int32_t)wgs;
+    if (ordered) {
+        SweepPlan plain;                       // (its chunks are those of the losses)
+        const int32_t rc = make_sweep_plan(N, d, k_min, k_max, batch, false, &plain);
+        if (rc != RLS_OK) return rc;
+        plan->loss_wgs = plain.n_wgs;
+    }
     plan->n_lists = n_lists;
     plan->n_parts = (int32_t)parts;
     return RLS_OK;
@@ -2908,7 +2925,7 @@ void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, in
     L->chain = take((int64_t)k_max * 8);
     L->xp = take((N + 31) / 32 * prep_block_u4_of(plan.dp) * 16);     // (with the blocks above: the same place whatever the range of k)
     const int64_t n_units = (N + 32 * unit_blocks_of(plan.dp) - 1) / (32 * unit_blocks_of(plan.dp));
-    L->keyinfo = L->perm = L->inv = L->xs = L->centres = L->radius = L->rowsq = L->rowpos = L->rowidx = L->losspart = L->lists = 0;
+    L->keyinfo = L->perm = L->inv = L->xs = L->centres = L->radius = L->rowpos = L->rowidx = L->lists = 0;
     if (plan.ordered) {
         L->keyinfo = take(sizeof(KeyInfo));
         L->perm = take(N * 4);
@@ -2916,18 +2933,16 @@ void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, in
         L->xs = take(std::max(align_up(N, 64) * plan.dp * 4, order_scratch_bytes(N)));
         L->centres = take((n_units + 31) / 32 * prep_block_u4_of(plan.dp) * 16);
         L->radius = take(align_up(n_units, 32) * 4);
-        L->rowsq = take((int64_t)kPrepareGrid * sizeof(Twofold));
         // (from here on: a place that depends on the range of k)
         L->rowpos = take((int64_t)plan.total_rows * 2);
         L->rowidx = take((int64_t)plan.total_rows);
-        L->losspart = take((int64_t)plan.n_runs * kMaxParts * sizeof(Twofold));
         L->lists = take((int64_t)plan.n_lists * n_units * kListWords * 4);
     }
     L->opA = take((int64_t)plan.total_tiles * tile_bytes_of(plan.dp));
     L->cnmax = take((int64_t)plan.n_runs * kMaxParts * 4);
     L->psum = take((int64_t)plan.n_parts * d * 8);
     L->pcnt = take((int64_t)plan.n_parts * 4);
-    L->pj = take((int64_t)plan.n_wgs * 8 * 8);
+    L->pj = take((int64_t)plan.loss_wgs * 8 * 8);
     L->losum = take((int64_t)plan.total_rows * d * 8);
     L->tot = take((int64_t)plan.total_rows * d * 16);
     L->totcnt = take((int64_t)plan.total_rows * d * 8);

@@ -178,6 +178,40 @@ __device__ inline float half_max_f32(float v)
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// sum over each half-wave, in all of its lanes: partners 16, 8, 4, 2, 1 lanes apart
+__device__ inline double half_sum_f64(double v)
+{
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const auto rl = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto rh = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    v = __dadd_rn(__hiloint2double((int)rh[0], (int)rl[0]), __hiloint2double((int)rh[1], (int)rl[1]));
+    v = __dadd_rn(v, dpp_move<0x128>(v));          // turned by 8, 4, 2, 1 lanes of 16
+    v = __dadd_rn(v, dpp_move<0x124>(v));
+    v = __dadd_rn(v, dpp_move<0x122>(v));
+    v = __dadd_rn(v, dpp_move<0x121>(v));
+    return v;
+}
+
+// the exact squared distance: fp64, features in rising order, products and sums rounded one by one
+template <int DP>
+__device__ inline double exact_distance(const float (&x)[DP], const float *crow)
+{
+    double dist = 0.0;
+#pragma unroll
+    for (int l = 0; l < DP; l += 4) {
+        const float4 c = *reinterpret_cast<const float4 *>(crow + l);
+        double diff = __dsub_rn((double)x[l], (double)c.x);
+        dist = __dadd_rn(dist, __dmul_rn(diff, diff));
+        diff = __dsub_rn((double)x[l + 1], (double)c.y);
+        dist = __dadd_rn(dist, __dmul_rn(diff, diff));
+        diff = __dsub_rn((double)x[l + 2], (double)c.z);
+        dist = __dadd_rn(dist, __dmul_rn(diff, diff));
+        diff = __dsub_rn((double)x[l + 3], (double)c.w);
+        dist = __dadd_rn(dist, __dmul_rn(diff, diff));
+    }
+    return dist;
+}
+
 // The assignment as it is defined, by one whole wave: fp64 direct-form distances sum_l (x_l - c_l)^2, features in
 // rising order, of one point to the k centroids of a run (one or two per lane), then the lexicographic minimum of
 // (distance, index) over the wave.  Every lane returns the winner.  The point arrives as wave-uniform values (read

@@ -55,6 +55,7 @@ struct SweepPlan {
     int32_t lab_slots;   // sum over the groups of their 8 / S run slots
     int32_t total_rows;  // sum of k over the runs
     int32_t n_wgs;       // chunks of all groups: workgroups of a step launch per space
+    int32_t loss_wgs;    // the same of the plan by which the losses are added up: that of the sweep without an order of the points
     int32_t n_parts;     // per-chunk centroid rows of all groups
     int32_t n_lists;     // groups with tile lists
     int32_t chunk_block; // > 0: every group has the same chunks, and the step kernel's workgroup order takes this many at a time (all
@@ -99,7 +100,7 @@ struct SweepLayout {
     int64_t cnmax;          // fp32 [n_runs][parts of a run] maximum of cn over the centroids of a part
     int64_t psum;           // int64 per group [n_chunks][rows of the group][d]: per-chunk changes of the fixed-point sums
     int64_t pcnt;           // int32 per group [n_chunks][rows of the group]: per-chunk changes of the member counts
-    int64_t pj;             // fp64 [chunks of all groups][8] partial losses
+    int64_t pj;             // fp64 [chunks of all groups (loss_wgs)][8] partial losses
     int64_t losum;          // int64 [total_rows][d] low-order fixed-point sums of wide columns (running)
     int64_t tot;            // int64 [total_rows][d][2] running 128-bit fixed-point sums (hi, lo)
     int64_t totcnt;         // int64 [total_rows][d] running member counts (one copy per feature)
@@ -113,8 +114,6 @@ struct SweepLayout {
     int64_t xs;             // fp32 [N rounded up to 64][dp] rows in that order, zero past the last feature (before: the scratch of the ordering)
     int64_t centres;        // prepared copy of the units' centres, as xp
     int64_t radius;         // fp32 [units rounded up to 32] upper bound of a unit's radius, in scaled units
-    int64_t rowsq;          // two doubles per workgroup of the preparation: squared distances of the points from the column means
-    int64_t losspart;       // two doubles [n_runs][parts of a run]
     int64_t rowpos;         // uint16 [total_rows] place of a centroid among the rows of its group
     int64_t rowidx;         // uint8 [total_rows] centroid of its run that has a place
     int64_t lists;          // uint32 per group [units][16]: the tiles that a unit meets (see tile lists, kmeans_lloyd.hip)

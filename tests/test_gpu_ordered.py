@@ -1,6 +1,6 @@
 """Sweeps on the spatially ordered copy of the points, whose blocks meet listed tiles of centroids only, against the same
-sweep on the points as they come (a sweep that also returns the loss of every round takes that route), bit for bit, and
-against the oracle."""
+sweep on the points as they come (taken with a workspace that holds nothing else, and by a sweep that also returns the loss of
+every round), bit for bit, losses included, and against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -39,6 +39,9 @@ def make(kind, N, d, seed):
         X = clustered(rng, N, d, 3.0)
         X[:, 1] = (rng.integers(1, 1 << 20, N) * 2.0 ** -30).astype(np.float32)
         X[::7, 1] = 2.0 ** 21
+    elif kind == "islands":                     # every column spans 61 binary digits; whoever isolates the far rows has a tiny loss
+        X = (rng.integers(0, 1 << 20, (N, d)) * 2.0 ** -40).astype(np.float32)
+        X[::7] = 2.0 ** 21
     return X
 
 
@@ -57,29 +60,43 @@ def equal(a, b):
 
 # units and chunks that end raggedly, every padded width, groups of 1, 2, 4 and 8 slots per run, groups with fewer and with
 # more tiles than lists are kept for
-CASES = [("clusters", 180224, 16, 1, 40), ("clusters", 81921, 13, 8, 63), ("clusters", 90011, 5, 1, 64), ("clusters", 60017, 32, 1, 100),
+CASES = [("clusters", 212992, 16, 1, 40), ("clusters", 81921, 13, 8, 63), ("clusters", 90011, 5, 1, 64), ("clusters", 60017, 32, 1, 100),
          ("clusters", 67000, 17, 97, 128), ("clusters", 50001, 8, 1, 110), ("clusters", 70001, 24, 10, 90), ("clusters", 66415, 3, 30, 90),
-         ("noise", 80000, 32, 1, 64), ("noise", 93333, 12, 20, 64), ("grid", 87017, 6, 1, 60), ("grid", 90480, 16, 20, 64),
-         ("line", 85000, 9, 1, 64), ("line", 76500, 1, 1, 64), ("same", 76400, 8, 1, 65), ("wide", 78000, 7, 1, 64), ("wide", 81000, 20, 10, 64)]
+         ("noise", 80000, 32, 1, 64), ("noise", 93333, 12, 20, 64), ("grid", 97017, 6, 1, 60), ("grid", 96480, 16, 20, 64),
+         ("line", 85000, 9, 1, 64), ("line", 86500, 1, 1, 64), ("same", 82400, 8, 1, 65), ("wide", 87000, 7, 1, 64), ("wide", 81000, 20, 10, 64),
+         ("islands", 87003, 8, 1, 64), ("islands", 84001, 11, 8, 70), ("islands", 82000, 18, 2, 64)]
 
 
 @pytest.mark.parametrize("kind,N,d,k_min,k_max", CASES)
 def test_ordered_sweep_equals_plain_sweep(rls, kind, N, d, k_min, k_max):
     X = torch.as_tensor(make(kind, N, d, N + d)).cuda()
     got = rls.kmeans_sweep(X, k_min, k_max, 6, seed=3)
-    want = rls.kmeans_sweep(X, k_min, k_max, 6, seed=3, want_trace=True)
-    assert torch.equal(got.labels, want.labels)
-    assert torch.equal(got.centroids, want.centroids)
-    torch.testing.assert_close(got.inertia, want.inertia, rtol=1e-12, atol=0)
+    assert equal(got, as_they_come(rls, X, k_min, k_max, 6, seed=3))
+    assert equal(got, rls.kmeans_sweep(X, k_min, k_max, 6, seed=3, want_trace=True))
+    without = rls.kmeans_sweep(X, k_min, k_max, 6, seed=3, want_labels=False)
+    assert torch.equal(got.inertia, without.inertia)
 
 
-def test_ordered_sweep_against_the_oracle(rls, orc):
-    X = make("clusters", 76999, 11, 5)
-    got = rls.kmeans_sweep(torch.as_tensor(X).cuda(), 9, 64, 3, seed=9)
-    ref = orc.kmeans_sweep(X, 9, 64, 3, seed=9)
+@pytest.mark.parametrize("kind,N,d,k_min,k_max", [("clusters", 87999, 11, 9, 64), ("islands", 90001, 8, 1, 64), ("grid", 62003, 19, 30, 64)])
+def test_ordered_sweep_against_the_oracle(rls, orc, kind, N, d, k_min, k_max):
+    X = make(kind, N, d, 5)
+    got = rls.kmeans_sweep(torch.as_tensor(X).cuda(), k_min, k_max, 3, seed=9)
+    as_they_come(rls, torch.as_tensor(X).cuda(), k_min, k_max, 1, seed=9)               # (an order is taken)
+    ref = orc.kmeans_sweep(X, k_min, k_max, 3, seed=9)
     np.testing.assert_array_equal(got.labels.cpu().numpy(), ref["labels"])
     np.testing.assert_array_equal(got.centroids.cpu().numpy(), ref["centroids"])
-    np.testing.assert_allclose(got.inertia.cpu().numpy(), ref["inertia"], rtol=1e-12)
+    # (the oracle adds the N distances up one after the other: its sum may be N 2^-53 off, 1e-11, and is 1.2e-12)
+    np.testing.assert_allclose(got.inertia.cpu().numpy(), ref["inertia"], rtol=N * 2.0 ** -53)
+
+
+def test_knee_of_an_ordered_sweep_over_columns_of_many_digits(rls, orc):
+    """The k at which Algorithm 1 stops, where the losses it compares are 2^-100 of the points' squares."""
+    X = make("islands", 90001, 8, 12)
+    k, n_done, r = rls.kmeans_sweep_until_knee(torch.as_tensor(X).cuda(), 1, 64, 64, 5, 1.05, seed=7)
+    ref = orc.kmeans_sweep(X, 1, 64, 5, seed=7)
+    assert n_done == 64
+    np.testing.assert_allclose(r.inertia.cpu().numpy(), ref["inertia"], rtol=90001 * 2.0 ** -53)
+    assert k == orc.pick_knee(ref["inertia"], 1, 64, 1.05)
 
 
 def test_ordered_sweep_of_strided_rows_and_given_centres(rls):
@@ -90,20 +107,15 @@ def test_ordered_sweep_of_strided_rows_and_given_centres(rls):
     init[7] = init[3]
     got = rls.kmeans_sweep(X, 1, 64, 5, init_idx=init)
     again = rls.kmeans_sweep(X, 1, 64, 5, init_idx=init)
-    want = rls.kmeans_sweep(X.contiguous(), 1, 64, 5, init_idx=init, want_trace=True)
-    for r in (got, again):
-        assert torch.equal(r.labels, want.labels) and torch.equal(r.centroids, want.centroids)
-    assert torch.equal(got.inertia, again.inertia)
+    want = as_they_come(rls, X.contiguous(), 1, 64, 5, init_idx=init)
+    assert equal(got, want) and equal(again, want)
 
 
 def test_ordered_batch_and_smaller_workspace(rls):
     """Spaces of a batch are ordered one by one; a workspace that only holds the sweep as it comes takes it without an order."""
     X = torch.stack([torch.as_tensor(make(k, 82421, 10, i)) for i, k in enumerate(("clusters", "noise", "grid"))]).cuda()
     got = rls.kmeans_sweep_batched(X, 1, 40, 5, seeds=[4, 5, 6])
-    need = rls.kmeans_sweep_workspace_bytes(82421, 10, 1, 40, 3)
-    tight = torch.empty(need - 3 * 82421 * 64, dtype=torch.uint8, device="cuda")         # without the ordered rows
-    plain = rls.kmeans_sweep_batched(X, 1, 40, 5, seeds=[4, 5, 6], workspace=tight)
-    assert torch.equal(got.labels, plain.labels) and torch.equal(got.centroids, plain.centroids)
+    assert equal(got, as_they_come(rls, X, 1, 40, 5, seeds=[4, 5, 6]))
 
 
 def test_waves_until_the_knee_share_the_order(rls):
@@ -111,8 +123,12 @@ def test_waves_until_the_knee_share_the_order(rls):
     init = rls.kmeanspp_chain(X, 60, 11)
     k, n_done, r = rls.kmeans_sweep_until_knee(X, 17, 60, 16, 5, 1e-9, seed=11)        # the knee never fires: all waves run
     assert n_done == 44
-    want = rls.kmeans_sweep(X, 17, 60, 5, init_idx=init, want_trace=True)
-    assert torch.equal(r.labels, want.labels) and torch.equal(r.centroids, want.centroids)
+    for k_lo in (17, 33, 49):                                  # (the losses are added up by the plan of a wave)
+        k_hi = min(k_lo + 15, 60)
+        want = as_they_come(rls, X, k_lo, k_hi, 5, init_idx=init[:k_hi])
+        rows = slice(14 * sum(range(17, k_lo)), 14 * sum(range(17, k_hi + 1)))
+        assert torch.equal(r.labels[k_lo - 17:k_hi - 16], want.labels) and torch.equal(r.centroids[rows], want.centroids)
+        assert torch.equal(r.inertia[k_lo - 17:k_hi - 16], want.inertia)
 
 
 def test_ordered_sweep_in_a_graph(rls):
