@@ -131,6 +131,16 @@ def test_waves_until_the_knee_share_the_order(rls):
         assert torch.equal(r.inertia[k_lo - 17:k_hi - 16], want.inertia)
 
 
+def test_last_wave_of_one_small_k_does_without_the_order(rls):
+    X = torch.as_tensor(make("clusters", 1440011, 5, 3)).cuda()
+    init = rls.kmeanspp_chain(X, 16, 2)
+    as_they_come(rls, X, 8, 15, 1, init_idx=init)              # (the first wave takes an order)
+    k, n_done, r = rls.kmeans_sweep_until_knee(X, 8, 16, 8, 3, 1e-9, seed=2)
+    assert n_done == 9
+    want = rls.kmeans_sweep(X, 16, 16, 3, init_idx=init)
+    assert torch.equal(r.labels[8:], want.labels) and torch.equal(r.centroids[-16 * 5:], want.centroids) and torch.equal(r.inertia[8:], want.inertia)
+
+
 def test_ordered_sweep_in_a_graph(rls):
     """Recorded once and replayed with eager work in between: every replay gives the eager result."""
     X = torch.as_tensor(make("clusters", 90011, 16, 4)).cuda()
