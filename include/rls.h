@@ -110,8 +110,17 @@ int32_t rls_gbt_score_batched(const rls_forest *forests, int32_t batch, const fl
 int32_t rls_kmeanspp_chain(const float *X_dev, int64_t N, int32_t d, int64_t ldx, int32_t k_max, uint64_t seed,
                            int64_t *init_idx_dev, void *workspace_dev, int64_t workspace_bytes, void *stream);
 
-/* Bytes of workspace rls_kmeans_sweep[_batched] needs (a multiple of 256), or a negative RLS_ERR_* code. */
+/*
+ * Bytes of workspace (a multiple of 256) with which rls_kmeans_sweep[_batched] takes the form that its shape is fastest
+ * in, or a negative RLS_ERR_* code.  For sweeps with much distance work that includes a copy of the points in spatial
+ * order, and the value is up to 1.7 times the least one.
+ */
 int64_t rls_kmeans_sweep_workspace_bytes(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch);
+/*
+ * The least it needs.  With a workspace between the two the sweep takes the points as they come: slower as a rule, faster
+ * where the rows have no structure at all (independent columns); labels, centroids and losses are the same to the last bit.
+ */
+int64_t rls_kmeans_sweep_least_workspace_bytes(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch);
 
 /*
  * The loop over k of Algorithm 1 (Sec. 4.2) without its early break: Lloyd's k-means for
@@ -136,7 +145,8 @@ int64_t rls_kmeans_sweep_workspace_bytes(int64_t N, int32_t d, int32_t k_min, in
  *                     precondition, in which case all other outputs are unspecified.  Exact sums
  *                     need, per feature column, the lowest set bit of every value to lie at most
  *                     79 binary places below the highest set bit of the column.
- *   workspace_dev     256-byte aligned, at least rls_kmeans_sweep_workspace_bytes(...) bytes
+ *   workspace_dev     256-byte aligned, rls_kmeans_sweep_workspace_bytes(...) bytes, or fewer down to
+ *                     rls_kmeans_sweep_least_workspace_bytes(...)
  */
 int32_t rls_kmeans_sweep(const float *X_dev, int64_t N, int32_t d, int64_t ldx,
                          int32_t k_min, int32_t k_max, int32_t iters, uint64_t seed,
@@ -149,7 +159,7 @@ int32_t rls_kmeans_sweep(const float *X_dev, int64_t N, int32_t d, int64_t ldx,
  * loops, harnesses that forbid hipMalloc): same arguments, results and status bits, but the workspace is a fixed
  * array of RLS_STATIC_WORKSPACE_BYTES inside the library's device image (each GPU the library runs on holds its
  * own copy until the process ends).  The call allocates nothing and frees nothing.
- *   - RLS_ERR_WORKSPACE when rls_kmeans_sweep_workspace_bytes(N, d, k_min, k_max, 1) exceeds
+ *   - RLS_ERR_WORKSPACE when rls_kmeans_sweep_least_workspace_bytes(N, d, k_min, k_max, 1) exceeds
  *     RLS_STATIC_WORKSPACE_BYTES (nothing is enqueued); that query tells beforehand whether a shape fits.
  *   - All calls on one GPU share that GPU's array: two such sweeps that overlap in time on one GPU (different
  *     streams or host threads) race.  Successive calls on one stream are fine; every call initialises the parts
@@ -188,7 +198,7 @@ int32_t rls_kmeans_sweep_batched(int32_t batch, const float *X_dev, int64_t N, i
  *   inertia_host  [k_max-k_min+1] fp64 (host), first *n_done_out entries written
  *   k_out         the chosen k (k_max when the test never fires; 0 when *status_dev != 0)
  *   n_done_out    how many k were computed (a whole number of waves, or all)
- * Workspace: rls_kmeans_sweep_until_knee_workspace_bytes.
+ * Workspace: rls_kmeans_sweep_until_knee_workspace_bytes; fewer bytes are taken as by rls_kmeans_sweep.
  */
 int64_t rls_kmeans_sweep_until_knee_workspace_bytes(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t k_wave);
 int32_t rls_kmeans_sweep_until_knee(const float *X_dev, int64_t N, int32_t d, int64_t ldx, int32_t k_min, int32_t k_max,

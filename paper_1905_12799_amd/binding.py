@@ -53,6 +53,8 @@ def lib() -> ctypes.CDLL:
         L.rls_kmeans_sweep_workspace_bytes.restype = ctypes.c_int64
         L.rls_kmeans_sweep_workspace_bytes.argtypes = [ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32,
                                                        ctypes.c_int32]
+        L.rls_kmeans_sweep_least_workspace_bytes.restype = ctypes.c_int64
+        L.rls_kmeans_sweep_least_workspace_bytes.argtypes = L.rls_kmeans_sweep_workspace_bytes.argtypes
         i32, i64, u64, vp, f64 = ctypes.c_int32, ctypes.c_int64, ctypes.c_uint64, ctypes.c_void_p, ctypes.c_double
         L.rls_gbt_score.restype = i32
         L.rls_gbt_score.argtypes = [ctypes.POINTER(_Forest), vp, i64, i32, i64, vp, vp]
@@ -192,6 +194,13 @@ def kmeans_sweep_workspace_bytes(N: int, d: int, k_min: int, k_max: int, batch: 
     n = int(lib().rls_kmeans_sweep_workspace_bytes(N, d, k_min, k_max, batch))
     if n < 0:
         raise RlsError(n, "rls_kmeans_sweep_workspace_bytes")
+    return n
+
+
+def kmeans_sweep_least_workspace_bytes(N: int, d: int, k_min: int, k_max: int, batch: int = 1) -> int:
+    n = int(lib().rls_kmeans_sweep_least_workspace_bytes(N, d, k_min, k_max, batch))
+    if n < 0:
+        raise RlsError(n, "rls_kmeans_sweep_least_workspace_bytes")
     return n
 
 

@@ -87,12 +87,6 @@ static int64_t form_workspace(int64_t N, int32_t d, int32_t k_min, int32_t k_max
     return L.total;
 }
 
-int64_t sweep_least_workspace(int64_t N, int32_t d, int32_t k_min, int32_t k_max)
-{
-    const int32_t rc = check_sweep(N, d, k_min, k_max, 1);
-    return rc != RLS_OK ? rc : form_workspace(N, d, k_min, k_max, 1, false);
-}
-
 }  // namespace rls
 
 using namespace rls;
@@ -188,6 +182,12 @@ int64_t rls_kmeans_sweep_workspace_bytes(int64_t N, int32_t d, int32_t k_min, in
     if (plain < 0 || !sweep_wants_order(N, d, k_min, k_max, batch)) return plain;
     const int64_t ordered = form_workspace(N, d, k_min, k_max, batch, true);
     return ordered < 0 ? ordered : std::max(plain, ordered);
+}
+
+int64_t rls_kmeans_sweep_least_workspace_bytes(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch)
+{
+    const int32_t rc = check_sweep(N, d, k_min, k_max, batch);
+    return rc != RLS_OK ? rc : form_workspace(N, d, k_min, k_max, batch, false);
 }
 
 int32_t rls_kmeanspp_chain(const float *X_dev, int64_t N, int32_t d, int64_t ldx, int32_t k_max, uint64_t seed,

@@ -122,8 +122,6 @@ struct SweepLayout {
     int32_t seed_blocks;
     int32_t stat_blocks;
 };
-// workspace of a sweep of one space without an order of the points, or an error
-int64_t sweep_least_workspace(int64_t N, int32_t d, int32_t k_min, int32_t k_max);
 // `chain_grows`: a later call with the same workspace adds centres to the chain (the waves of a sweep until the knee)
 void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, int32_t batch, bool chain_grows, SweepLayout *L);
 

@@ -41,7 +41,7 @@ extern "C" int32_t rls_kmeans_sweep_static(const float *X_dev, int64_t N, int32_
                                            double *inertia_trace_dev, int32_t *status_dev, void *stream)
 {
     // sizes beyond the fixed workspace are turned down before anything is enqueued
-    const int64_t need = rls::sweep_least_workspace(N, d, k_min, k_max);
+    const int64_t need = rls_kmeans_sweep_least_workspace_bytes(N, d, k_min, k_max, 1);
     if (need < 0) return (int32_t)need;
     if (need > (int64_t)RLS_STATIC_WORKSPACE_BYTES) return RLS_ERR_WORKSPACE;
     void *ws = nullptr;

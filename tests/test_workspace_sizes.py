@@ -8,16 +8,38 @@ from tests.test_zz_no_alloc import EDGE
 
 
 @pytest.fixture(scope="module")
-def query():
+def library():
     from paper_1905_12799_amd import build
     if not os.path.exists(build.LIB):
         build.build_library()
-    fn = ctypes.CDLL(build.LIB).rls_kmeans_sweep_workspace_bytes
-    fn.restype = ctypes.c_int64
-    fn.argtypes = [ctypes.c_int64] + [ctypes.c_int32] * 4
-    return fn
+    lib = ctypes.CDLL(build.LIB)
+    for fn in (lib.rls_kmeans_sweep_workspace_bytes, lib.rls_kmeans_sweep_least_workspace_bytes):
+        fn.restype = ctypes.c_int64
+        fn.argtypes = [ctypes.c_int64] + [ctypes.c_int32] * 4
+    return lib
 
 
 @pytest.mark.parametrize("N,d,k_min,k_max", EDGE)
-def test_fits_the_fixed_workspace(query, N, d, k_min, k_max):
-    assert 0 < query(N, d, k_min, k_max, 1) <= 64 << 20
+def test_fits_the_fixed_workspace(library, N, d, k_min, k_max):
+    assert 0 < library.rls_kmeans_sweep_workspace_bytes(N, d, k_min, k_max, 1) <= 64 << 20
+
+
+@pytest.mark.parametrize("N,d,k_min,k_max,batch,ordered", [
+    (2000, 8, 1, 16, 1, False), (65536, 16, 1, 64, 1, False), (1048576, 16, 32, 32, 1, False),
+    (300007, 13, 8, 63, 1, True), (1048576, 16, 1, 64, 1, True), (262144, 16, 1, 32, 64, True), (8388608, 32, 1, 128, 1, True)])
+def test_least_workspace(library, N, d, k_min, k_max, batch, ordered):
+    """Equal where the points are taken as they come anyway; less where the larger one holds a copy of the rows in order."""
+    best = library.rls_kmeans_sweep_workspace_bytes(N, d, k_min, k_max, batch)
+    least = library.rls_kmeans_sweep_least_workspace_bytes(N, d, k_min, k_max, batch)
+    assert 0 < least <= best and least % 256 == 0 and best % 256 == 0
+    assert best - least >= batch * N * d * 4 if ordered else best == least
+
+
+def test_least_workspace_refuses_what_the_other_refuses(library):
+    for shape in ((0, 8, 1, 16, 1), (1000, 33, 1, 16, 1), (1000, 8, 5, 4, 1), (10, 8, 1, 16, 1), (1000, 8, 1, 129, 1), (1000, 8, 1, 16, 0)):
+        assert library.rls_kmeans_sweep_least_workspace_bytes(*shape) == library.rls_kmeans_sweep_workspace_bytes(*shape) == -1
+
+
+def test_fixed_workspace_goes_by_the_least(library):
+    """A shape that fits the fixed workspace as the points come, and not with their order."""
+    assert library.rls_kmeans_sweep_least_workspace_bytes(300007, 13, 8, 63, 1) <= 64 << 20 < library.rls_kmeans_sweep_workspace_bytes(300007, 13, 8, 63, 1)

@@ -79,3 +79,13 @@ def test_static_sweep_at_its_largest(rls, orc, N, d, k_min, k_max):
     np.testing.assert_array_equal(got.labels.cpu().numpy(), ref["labels"])
     np.testing.assert_array_equal(got.centroids.cpu().numpy(), ref["centroids"])
     np.testing.assert_allclose(got.inertia.cpu().numpy(), ref["inertia"], rtol=1e-5)
+
+
+def test_static_sweep_of_a_shape_whose_order_does_not_fit(rls):
+    """The fixed workspace takes what the least one holds; with the larger one the same sweep runs on ordered points."""
+    rng = np.random.default_rng(3)
+    X = torch.as_tensor((rng.integers(-9, 9, (30, 13))[rng.integers(0, 30, 300007)] + rng.standard_normal((300007, 13))).astype(np.float32)).cuda()
+    assert rls.kmeans_sweep_least_workspace_bytes(300007, 13, 8, 63) <= rls.STATIC_WORKSPACE_BYTES < rls.kmeans_sweep_workspace_bytes(300007, 13, 8, 63)
+    got = rls.kmeans_sweep_static(X, 8, 63, 4, seed=6)
+    torch.cuda.synchronize()
+    same(got, rls.kmeans_sweep(X, 8, 63, 4, seed=6))
