@@ -2725,12 +2725,17 @@ int workgroups_per_cu(int64_t per_cu, int n_groups, int batch)
     return (int)std::min<int64_t>(std::max<int64_t>((per_cu + 600) / 1200, 2), 5);
 }
 
-// An order of the points costs five launches and the copying of the rows (60 us up to some 100,000 points, 130 at 1M x 16, 1.4 ms
-// at 8M x 32) and pays by the tiles that the rounds leave out: by the points times the tiles of the groups with lists, a tile
-// of 32 features for two.  Sweeps of 20 rounds, time without against with an order, by thousands of points times tiles:
-//   8 to 16 features   1700 .. 1800: 0.82 .. 0.87;  3300 .. 3500: 0.85 .. 0.96;  4500: 0.97;  5000: 1.00;  6800 .. 7000: 1.00 .. 1.06;
-//                      10,200: 1.14 .. 1.17;  13,700: 1.17 .. 1.26;  27,300: 1.32 .. 1.49
-//   29 and 32          2700: 0.87 .. 0.91;  5500: 0.98 .. 1.02;  8400: 1.01 .. 1.05;  10,900: 1.09 .. 1.13;  12,900: 1.07 .. 1.12;  25,800: 1.21 .. 1.27
+// An order of the points costs five launches, the copying of the rows, a dearer last pass and some 6 us a round for the lists, and
+// pays by the tiles that the rounds leave out: all but one of a group at most.  The measure: thousands of points times (the tiles
+// of the groups with lists, less one for every group, less two).  Time without against with an order, geometric means over 590
+// sweeps of one to 64 spaces of knob configurations after 10 / 20 / 30 rounds, by that measure:
+//   up to 16 features   1500 .. 3000: 0.90 / 0.96 / 0.98;  3000 .. 4000: 0.92 / 0.98 / 1.00;  4000 .. 5000: 0.96 / 1.01 / 1.04;
+//                       5000 .. 7000: 1.01 / 1.06 / 1.09;  7000 .. 9000: 1.05 / 1.11 / 1.14;  9000 .. 16,000: 1.14 / 1.21 / 1.24
+//   17 to 32            1500 .. 3000: 0.90 / 0.95 / 0.97;  3000 .. 4000: 0.97 / 1.02 / 1.04;  4000 .. 5000: 1.01 / 1.06 / 1.08;
+//                       5000 .. 7000: 1.05 / 1.09 / 1.10;  7000 .. 12,000: 1.12 / 1.17 / 1.20
+// Rows without any structure gain nothing by it, and that cannot be told from the sizes: independent normal deviates take 1.25 times
+// as long with an order at 100,003 x 16, k 1..64, 1.16 at 1M, 1.03 at 2M x 32 (20 rounds).  A caller with such rows hands in the
+// least workspace.
 bool sweep_wants_order(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch)
 {
     if (N < 16384 || k_max - k_min + 1 < 8) return false;
@@ -2738,7 +2743,7 @@ bool sweep_wants_order(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32
     if (make_sweep_plan(N, d, k_min, k_max, 1, true, &plan) != RLS_OK) return false;
     int64_t tiles = 0;
     for (int gi = 0; gi < plan.n_groups; ++gi) tiles += plan.g[gi].list0 >= 0 ? plan.g[gi].n_tiles : 0;
-    return N / 1024 * tiles * batch * (plan.dp == 32 ? 2 : 1) >= 5600;
+    return N * batch / 1024 * (tiles - plan.n_groups - 2) >= 4500;
 }
 
 // What a slab of a group costs, in fifths of a tile: its tiles - with lists a fifth of them and one more - and the rest.
