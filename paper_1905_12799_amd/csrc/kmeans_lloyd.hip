@@ -1786,11 +1786,12 @@ __global__ void __launch_bounds__(256) colstats_final_kernel(int64_t N, int d, i
         int *colwide = reinterpret_cast<int *>(ws + (int64_t)b * ws_bs + off_colinfo + 256);
         // One power of two for all columns (distances keep their order): with |x - mean| < 2^(M+1) in every column the
         // centred values obey |x - mean| * 2^(kScaledMsb - M - 2) < 2^(kScaledMsb - 1), one bit inside what fp16 holds for
-        // 2 c'.  The exponent is kept inside the fp32 range; data that small only makes every comparison a close call.
+        // 2 c'.  The exponent is kept inside the fp32 range: no distance from the mean reaches 2^129 (an infinite one, rounded up, counts
+        // as that), and data that asks for more than 2^100 is so small that every comparison is a close call.
         // (the 32 threads of the columns are the lower half of one wave: the exchange stays among them)
         for (int off = 16; off >= 1; off >>= 1) msb = max(msb, __shfl_xor(msb, off, 64));
         int e = kScaledMsb - 2 - (msb > -(1 << 20) ? msb : 0);
-        e = min(max(e, -100), 100);
+        e = min(max(e, kScaledMsb - 2 - 128), 100);
         const float scale = ldexpf(1.0f, e);
         colmean[l] = -(mean * scale);      // what the kernels add after multiplying by the scale
         colshift[l] = shift;

@@ -142,6 +142,19 @@ def test_last_wave_of_one_small_k_does_without_the_order(rls):
     assert torch.equal(r.labels[16:], want.labels) and torch.equal(r.centroids[-32 * 5:], want.centroids) and torch.equal(r.inertia[16:], want.inertia)
 
 
+@pytest.mark.parametrize("N,d,k_min,k_max", [(3000, 8, 1, 20), (40003, 16, 1, 24), (90011, 12, 1, 64), (60017, 32, 1, 100)])
+def test_rows_scaled_by_a_power_of_two(rls, N, d, k_min, k_max):
+    """Nothing rounds differently, up to the largest floats and their differences (which no float holds)."""
+    X = torch.as_tensor(make("clusters", N, d, 8)).cuda()
+    X[0], X[1] = 63.0, -63.0
+    want = rls.kmeans_sweep(X, k_min, k_max, 4, seed=3)
+    for s in (-60, 90, 110, 112, 116, 122):
+        got = rls.kmeans_sweep(X * 2.0 ** s, k_min, k_max, 4, seed=3)
+        assert torch.equal(got.labels, want.labels)
+        assert torch.equal(got.centroids, want.centroids * 2.0 ** s)
+        assert torch.equal(got.inertia, want.inertia * 2.0 ** (2 * s))
+
+
 def test_ordered_sweep_in_a_graph(rls):
     """Recorded once and replayed with eager work in between: every replay gives the eager result."""
     X = torch.as_tensor(make("clusters", 90011, 16, 4)).cuda()
