@@ -834,20 +834,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                                 const int place = 4 * (S * tile + a) + (q & 3);
                                 if (place >= k) continue;                        // padding
                                 const int j = (int)c.rowidx[rowbase + place];
-                                const float *const crow = c.cs + (rowbase + j) * CS;
-                                double dist = 0.0;
-#pragma unroll
-                                for (int l = 0; l < DP; l += 4) {
-                                    const float4 cv = *reinterpret_cast<const float4 *>(crow + l);
-                                    double diff = __dsub_rn((double)x[l], (double)cv.x);
-                                    dist = __dadd_rn(dist, __dmul_rn(diff, diff));
-                                    diff = __dsub_rn((double)x[l + 1], (double)cv.y);
-                                    dist = __dadd_rn(dist, __dmul_rn(diff, diff));
-                                    diff = __dsub_rn((double)x[l + 2], (double)cv.z);
-                                    dist = __dadd_rn(dist, __dmul_rn(diff, diff));
-                                    diff = __dsub_rn((double)x[l + 3], (double)cv.w);
-                                    dist = __dadd_rn(dist, __dmul_rn(diff, diff));
-                                }
+                                const double dist = exact_distance<DP>(x, c.cs + (rowbase + j) * CS);
                                 if (dist < best || (dist == best && j < arg)) { best = dist; arg = j; at = place; }
                             }
                         }
@@ -1150,20 +1137,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                     const int rl = S == 8 ? 0 : hl * ST + st;
                     const bool active = ((S == 8) ? (hl == 0) : true) && rl < c.n_runs && pvalid[pb];
                     const int row = active ? rl * c.k0 + rl * (rl - 1) / 2 + (m1[pb][st] & 127) : 0;
-                    const float *crow = c.cs + row * CS;
-                    double dist = 0.0;
-#pragma unroll
-                    for (int l = 0; l < DP; l += 4) {
-                        const float4 cv = *reinterpret_cast<const float4 *>(crow + l);
-                        double diff = __dsub_rn((double)xf[l], (double)cv.x);
-                        dist = __dadd_rn(dist, __dmul_rn(diff, diff));
-                        diff = __dsub_rn((double)xf[l + 1], (double)cv.y);
-                        dist = __dadd_rn(dist, __dmul_rn(diff, diff));
-                        diff = __dsub_rn((double)xf[l + 2], (double)cv.z);
-                        dist = __dadd_rn(dist, __dmul_rn(diff, diff));
-                        diff = __dsub_rn((double)xf[l + 3], (double)cv.w);
-                        dist = __dadd_rn(dist, __dmul_rn(diff, diff));
-                    }
+                    const double dist = exact_distance<DP>(xf, c.cs + row * CS);
                     if (active) jown[st] = __dadd_rn(jown[st], dist);
                 }
             }

@@ -191,24 +191,6 @@ __global__ void __launch_bounds__(small_threads_of(DP)) lloyd_small_kernel(Sweep
             for (int l = 0; l < DP; ++l) x[l] = l < d ? row[l] : 0.0f;
         }
     };
-    // the exact squared distance: fp64, features in rising order, products and sums rounded one by one
-    auto exact_distance = [&](const float (&x)[DP], int j) -> double {
-        const float *crow = cs_s + j * CS;
-        double dist = 0.0;
-#pragma unroll
-        for (int l = 0; l < DP; l += 4) {
-            const float4 c = *reinterpret_cast<const float4 *>(crow + l);
-            double diff = __dsub_rn((double)x[l], (double)c.x);
-            dist = __dadd_rn(dist, __dmul_rn(diff, diff));
-            diff = __dsub_rn((double)x[l + 1], (double)c.y);
-            dist = __dadd_rn(dist, __dmul_rn(diff, diff));
-            diff = __dsub_rn((double)x[l + 2], (double)c.z);
-            dist = __dadd_rn(dist, __dmul_rn(diff, diff));
-            diff = __dsub_rn((double)x[l + 3], (double)c.w);
-            dist = __dadd_rn(dist, __dmul_rn(diff, diff));
-        }
-        return dist;
-    };
     __syncthreads();                                // column information and centroids are there
     const bool any_wide = wide_s[32] != 0;
 
@@ -357,7 +339,7 @@ __global__ void __launch_bounds__(small_threads_of(DP)) lloyd_small_kernel(Sweep
                     double best = INFINITY;
                     int arg = 0x7fffffff;
                     for (int j = hl; j < k; j += 2) {
-                        const double dist = exact_distance(x, j);
+                        const double dist = exact_distance<DP>(x, cs_s + j * CS);
                         if (dist < best) { best = dist; arg = j; }
                     }
                     const double other = __hiloint2double(xchg32(__double2hiint(best)), xchg32(__double2loint(best)));
@@ -433,19 +415,9 @@ __global__ void __launch_bounds__(small_threads_of(DP)) lloyd_small_kernel(Sweep
             for (int p = s0 + n; p < min(s0 + slab, end); p += 32) {
                 float x[DP];
                 whole_row(p, x);
-                sum = __dadd_rn(sum, exact_distance(x, labels_s[p]));
+                sum = __dadd_rn(sum, exact_distance<DP>(x, cs_s + labels_s[p] * CS));
             }
-        // (partners 16, 8, 4, 2, 1 lanes apart, as there)
-        {
-            const unsigned lo = (unsigned)__double2loint(sum), hi = (unsigned)__double2hiint(sum);
-            const auto rl = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-            const auto rh = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-            sum = __dadd_rn(__hiloint2double((int)rh[0], (int)rl[0]), __hiloint2double((int)rh[1], (int)rl[1]));
-        }
-        sum = __dadd_rn(sum, dpp_move<0x128>(sum));        // turned by 8, 4, 2, 1 lanes of 16
-        sum = __dadd_rn(sum, dpp_move<0x124>(sum));
-        sum = __dadd_rn(sum, dpp_move<0x122>(sum));
-        sum = __dadd_rn(sum, dpp_move<0x121>(sum));
+        sum = half_sum_f64(sum);                       // (partners as there)
         if (n == 0) jpart_s[q] = sum;
     }
     __syncthreads();

@@ -259,20 +259,7 @@ __device__ inline int exact_argmin_wave(const float (&x)[DP], const float *crun,
     double best = INFINITY;
     int arg = 0x7fffffff;
     for (int j = lane; j < k; j += 64) {
-        const float *crow = crun + j * cstride;
-        double dist = 0.0;
-#pragma unroll
-        for (int l = 0; l < DP; l += 4) {
-            const float4 cv = *reinterpret_cast<const float4 *>(crow + l);
-            double diff = __dsub_rn((double)x[l], (double)cv.x);
-            dist = __dadd_rn(dist, __dmul_rn(diff, diff));
-            diff = __dsub_rn((double)x[l + 1], (double)cv.y);
-            dist = __dadd_rn(dist, __dmul_rn(diff, diff));
-            diff = __dsub_rn((double)x[l + 2], (double)cv.z);
-            dist = __dadd_rn(dist, __dmul_rn(diff, diff));
-            diff = __dsub_rn((double)x[l + 3], (double)cv.w);
-            dist = __dadd_rn(dist, __dmul_rn(diff, diff));
-        }
+        const double dist = exact_distance<DP>(x, crun + j * cstride);
         if (dist < best) { best = dist; arg = j; }
     }
     // smallest distance of the wave, then the smallest index among the lanes that hold it
