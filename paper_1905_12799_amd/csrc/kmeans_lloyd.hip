@@ -25,7 +25,7 @@
 //            adds them to the 128-bit totals, rounds once to fp64, divides by the count and rounds to fp32
 // The final pass replaces the update by the fp64 loss of every point and the label output.
 //
-// Two other forms share this file's plan and arithmetic, and give the same labels, centroids and sums: sweeps with much distance
+// Two other forms share this file's plan and arithmetic, and give the same labels, centroids and losses: sweeps with much distance
 // work run on a copy of the points in spatial order (kmeans_order.hip), where a unit of neighbouring points meets only the
 // tiles of centroids that can win there (ORD, make_lists); sweeps of a few thousand points are one launch (kmeans_small.hip).
 #include <algorithm>

@@ -112,11 +112,15 @@ def test_ordered_sweep_of_strided_rows_and_given_centres(rls):
     assert equal(got, want) and equal(again, want)
 
 
-def test_ordered_batch_and_smaller_workspace(rls):
+# chunks of their own for every group, and the same chunks for all (19 and 5 spaces: a number of chunks that eight does not divide)
+@pytest.mark.parametrize("batch,N,d,k_min,k_max", [(3, 82421, 10, 1, 40), (19, 20011, 9, 8, 50), (5, 20003, 27, 1, 100)])
+def test_ordered_batch_and_smaller_workspace(rls, batch, N, d, k_min, k_max):
     """Spaces of a batch are ordered one by one; a workspace that only holds the sweep as it comes takes it without an order."""
-    X = torch.stack([torch.as_tensor(make(k, 82421, 10, i)) for i, k in enumerate(("clusters", "noise", "grid"))]).cuda()
-    got = rls.kmeans_sweep_batched(X, 1, 40, 5, seeds=[4, 5, 6])
-    assert equal(got, as_they_come(rls, X, 1, 40, 5, seeds=[4, 5, 6]))
+    kinds = ("clusters", "noise", "grid")
+    X = torch.stack([torch.as_tensor(make(kinds[i % 3], N, d, i)) for i in range(batch)]).cuda()
+    seeds = [4 + i for i in range(batch)]
+    got = rls.kmeans_sweep_batched(X, k_min, k_max, 5, seeds=seeds)
+    assert equal(got, as_they_come(rls, X, k_min, k_max, 5, seeds=seeds))
 
 
 def test_waves_until_the_knee_share_the_order(rls):
