@@ -2702,12 +2702,13 @@ int workgroups_per_cu(int64_t per_cu, int n_groups, int batch)
 
 // An order of the points costs five launches, the copying of the rows, a dearer last pass and some 6 us a round for the lists, and
 // pays by the tiles that the rounds leave out: all but one of a group at most.  The measure: thousands of points times (the tiles
-// of the groups with lists, less one for every group, less two).  Time without against with an order, geometric means over 590
-// sweeps of one to 64 spaces of knob configurations after 10 / 20 / 30 rounds, by that measure:
-//   up to 16 features   1500 .. 3000: 0.90 / 0.96 / 0.98;  3000 .. 4000: 0.92 / 0.98 / 1.00;  4000 .. 5000: 0.96 / 1.01 / 1.04;
-//                       5000 .. 7000: 1.01 / 1.06 / 1.09;  7000 .. 9000: 1.05 / 1.11 / 1.14;  9000 .. 16,000: 1.14 / 1.21 / 1.24
-//   17 to 32            1500 .. 3000: 0.90 / 0.95 / 0.97;  3000 .. 4000: 0.97 / 1.02 / 1.04;  4000 .. 5000: 1.01 / 1.06 / 1.08;
-//                       5000 .. 7000: 1.05 / 1.09 / 1.10;  7000 .. 12,000: 1.12 / 1.17 / 1.20
+// of the groups with lists, less one for every group, up to 16 features less one more, which the cheaper tiles there take to pay for
+// the copying).  Time without against with an order, geometric means over 850 sweeps of one to 64 spaces of knob configurations
+// after 10 / 20 / 30 rounds, by that measure:
+//   up to 16 features   3000 .. 4000: 0.91 / 0.97 / 0.99;  4000 .. 5000: 0.95 / 1.00 / 1.02;  5000 .. 6000: 0.97 / 1.04 / 1.07;
+//                       6000 .. 8000: 1.01 / 1.06 / 1.09;  8000 .. 12,000: 1.07 / 1.13 / 1.16;  12,000 .. 16,000: 1.14 / 1.21 / 1.25
+//   17 to 32            1000 .. 3000: 0.92 / 0.95 / 0.97;  3000 .. 4000: 0.96 / 1.00 / 1.02;  4000 .. 5000: 0.99 / 1.03 / 1.05;
+//                       5000 .. 6000: 1.03 / 1.06 / 1.07;  6000 .. 8000: 1.04 / 1.08 / 1.10;  8000 .. 12,000: 1.10 / 1.15 / 1.17
 // Rows without any structure gain nothing by it, and that cannot be told from the sizes: independent normal deviates take 1.25 times
 // as long with an order at 100,003 x 16, k 1..64, 1.16 at 1M, 1.03 at 2M x 32 (20 rounds).  A caller with such rows hands in the
 // least workspace.
@@ -2718,7 +2719,8 @@ bool sweep_wants_order(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32
     if (make_sweep_plan(N, d, k_min, k_max, 1, true, &plan) != RLS_OK) return false;
     int64_t tiles = 0;
     for (int gi = 0; gi < plan.n_groups; ++gi) tiles += plan.g[gi].list0 >= 0 ? plan.g[gi].n_tiles : 0;
-    return N * batch / 1024 * (tiles - plan.n_groups - 2) >= 4500;
+    const int64_t thousands = N * batch / 1024;
+    return plan.dp == 32 ? thousands * (tiles - plan.n_groups) >= 4000 : thousands * (tiles - plan.n_groups - 1) >= 5000;
 }
 
 // What a slab of a group costs, in fifths of a tile: its tiles - with lists a fifth of them and one more - and the rest.

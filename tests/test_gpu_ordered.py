@@ -61,9 +61,9 @@ def equal(a, b):
 
 # units and chunks that end raggedly, every padded width, groups of 1, 2, 4 and 8 slots per run, groups with fewer and with
 # more tiles than lists are kept for
-CASES = [("clusters", 229376, 16, 1, 40), ("clusters", 81921, 13, 8, 63), ("clusters", 90011, 5, 1, 64), ("clusters", 60017, 32, 1, 100),
+CASES = [("clusters", 245760, 16, 1, 40), ("clusters", 86017, 13, 8, 63), ("clusters", 90011, 5, 1, 64), ("clusters", 60017, 32, 1, 100),
          ("clusters", 67000, 17, 97, 128), ("clusters", 50001, 8, 1, 110), ("clusters", 70001, 24, 10, 90), ("clusters", 66415, 3, 30, 90),
-         ("noise", 86016, 32, 1, 64), ("noise", 93333, 12, 20, 64), ("grid", 97017, 6, 1, 60), ("grid", 96480, 16, 20, 64),
+         ("noise", 86016, 32, 1, 64), ("noise", 96333, 12, 20, 64), ("grid", 99017, 6, 1, 60), ("grid", 96480, 16, 20, 64),
          ("line", 85000, 9, 1, 64), ("line", 86500, 1, 1, 64), ("same", 82400, 8, 1, 65), ("wide", 87000, 7, 1, 64), ("wide", 81000, 20, 10, 64),
          ("islands", 87003, 8, 1, 64), ("islands", 84001, 11, 8, 70), ("islands", 82000, 18, 2, 64)]
 
