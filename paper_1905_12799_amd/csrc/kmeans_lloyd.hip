@@ -172,7 +172,10 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
     const int f0 = hl * H;                          // first feature of this lane's half
     const int nf = min(max(d - f0, 0), H);          // real features of this lane's half
     const uint4 *opA_s = c.opA_s;
-    int mask = (int)0xffffff80;
+    // the index bits of a key: what the tiles that a slab meets take
+    // (eight slots: always 7, the steps become tiles while the halves of a run are still to be compared)
+    int kbits = S == 8 ? 7 : key_bits(4 * S * c.n_tiles);
+    int mask = key_mask(kbits);
     asm volatile("" : "+v"(mask));                  // keep the mask in a VGPR
 
     // this lane's copy of the accumulators
@@ -512,6 +515,11 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 const int len = __builtin_amdgcn_readfirstlane((int)(list >> 24));
                 listed = len != kListAll;
                 if (listed) n_it = len;
+                if constexpr (S < 8) {
+                    kbits = key_bits(4 * S * n_it);
+                    mask = key_mask(kbits);
+                    asm volatile("" : "+v"(mask));
+                }
             }
         }
         auto old_of = [&](int pb, int st) -> int { return (int)((oldl[pb] >> (8 * st)) & 0xffu); };
@@ -707,10 +715,10 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
             }
             fold_tile<S, ST>(acc_prev, kidx_old, mask, m1[NB - 1], m2[NB - 1]);
         }
-        if constexpr (ORD) {
-            // The keys hold steps of the lists: the step becomes the tile that the winner's slot met there.  (The second
-            // key's index is not used.)
-            if (listed) {
+        // The keys hold steps of the lists: the step becomes the tile that the winner's slot met there, and of the key the index is
+        // left.  (The second key's index is not used.)
+        auto steps_to_tiles = [&]() {
+            {
                 // the words of this lane's slots 4 hl .. 4 hl + 3, from lanes that feed them
                 auto slots = [&](unsigned w, unsigned (&out)[4]) {
 #pragma unroll
@@ -719,7 +727,9 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 unsigned own[4];
                 slots(list, own);
                 constexpr int kStepShift = S == 1 ? 2 : (S == 2 ? 3 : (S == 4 ? 4 : 5));
-                constexpr int kStepMask = (127 >> kStepShift) << kStepShift;
+                constexpr int kKeepMask = S == 8 ? ~(3 << kStepShift) : (1 << kStepShift) - 1;      // (S = 8: four tiles at most)
+                const unsigned step_bits = (unsigned)(kbits - kStepShift);
+                auto step_of = [&](int key) -> unsigned { return __builtin_amdgcn_ubfe((unsigned)key, (unsigned)kStepShift, step_bits); };
                 // the word of the slot that a run's key came from (selects by bit masks: an index would put the words in memory)
                 auto either = [](unsigned w0, unsigned w1, int key, int bit) { return w0 ^ ((w0 ^ w1) & (0u - (((unsigned)key >> bit) & 1u))); };
                 auto pick = [&](const unsigned (&w)[4], int st, int key) -> unsigned {
@@ -733,8 +743,8 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
 #pragma unroll
                         for (int st = 0; st < ST; ++st) {
                             const int key = m1[pb][st];
-                            const unsigned step = ((unsigned)key & kStepMask) >> kStepShift;
-                            m1[pb][st] = (key & ~kStepMask) | (int)(((pick(own, st, key) >> (8 * step)) & 255u) << kStepShift);
+                            const unsigned step = step_of(key);
+                            m1[pb][st] = (key & kKeepMask) | (int)(((pick(own, st, key) >> (8 * step)) & 255u) << kStepShift);
                         }
                 } else {
                     unsigned more[4];
@@ -744,13 +754,14 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
 #pragma unroll
                         for (int st = 0; st < ST; ++st) {
                             const int key = m1[pb][st];
-                            const int step = (key & kStepMask) >> kStepShift;
+                            const unsigned step = step_of(key);
                             const unsigned w = step < kListHead ? pick(own, st, key) : pick(more, st, key);
-                            m1[pb][st] = (key & ~kStepMask) | (int)(((w >> (8 * (step < kListHead ? step : step - kListHead))) & 255u) << kStepShift);
+                            m1[pb][st] = (key & kKeepMask) | (int)(((w >> (8 * (step < kListHead ? step : step - kListHead))) & 255u) << kStepShift);
                         }
                 }
             }
-        }
+        };
+        if (ORD && S == 8 && listed) steps_to_tiles();
         if (LATE_FETCH) fetch(min(nxt, n_slabs - 1));
 
         // ---- labels, close calls, sums
@@ -769,6 +780,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         unsigned pend = 0;
         bool closeb[NB][ST];
         bool any_close = false;
+        const float shrink = key_shrink(kbits);
 #pragma unroll
         for (int pb = 0; pb < NB; ++pb) {
             if (S == 8) {
@@ -785,16 +797,24 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
             for (int st = 0; st < ST; ++st) {
                 const int rl = S == 8 ? 0 : hl * ST + st;     // run within the group
                 const bool active = ((S == 8) ? (hl == 0) : true) && rl < c.n_runs && pvalid[pb];
-                // Error bound of the two expansions (rounding of norms, products and the centring) plus the 7
-                // mantissa bits given up to the index.  The keys are compared as they are, index bits included:
-                // read as a float a key g lies within 2^-16 |v| of the value v it was packed from, so
-                // v2 - v1 >= g2 (1 - 2^-15) - g1 whenever g2 >= |g1| - and a negative g1 (a distance of zero
-                // within the bound) is smaller than the bound's own slack.  One multiply-add and one compare.
+                // Error bound of the two expansions (rounding of norms, products and the centring) plus the
+                // mantissa bits given up to the index.  The keys are compared as they are, index bits included (see key_shrink;
+                // a negative g1 - a distance of zero within the bound - is smaller than the bound's own slack).  One multiply-add and
+                // one compare.
                 const float g1 = __int_as_float(m1[pb][st]), g2 = __int_as_float(m2[pb][st]);
                 const float tol0 = fmaf(c.eps_a, xn[pb], tol_run[st]);
-                closeb[pb][st] = active && !(fmaf(g2, 0.999969482421875f, -g1) > tol0);
+                closeb[pb][st] = active && !(fmaf(g2, shrink, -g1) > tol0);
                 any_close = any_close || closeb[pb][st];
             }
+        }
+        // from here on m1 holds indices
+        if (ORD && S < 8 && listed) {
+            steps_to_tiles();
+        } else {
+#pragma unroll
+            for (int pb = 0; pb < NB; ++pb)
+#pragma unroll
+                for (int st = 0; st < ST; ++st) m1[pb][st] &= ~mask;
         }
         if (__builtin_amdgcn_ballot_w64(any_close) != 0ull) {
 #pragma unroll
@@ -938,15 +958,15 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         unsigned mv = 0;                            // bit pb * ST + st: that pair moved
 #pragma unroll
         for (int pb = 0; pb < NB; ++pb) {
-            // the low bytes of the keys side by side (byte permutes), index bits only
+            // the indices side by side (byte permutes)
             unsigned w;
             if constexpr (ST == 4) {
                 w = (__builtin_amdgcn_perm((unsigned)m1[pb][1], (unsigned)m1[pb][0], 0x0c0c0400u) |
-                     __builtin_amdgcn_perm((unsigned)m1[pb][3], (unsigned)m1[pb][2], 0x04000c0cu)) & 0x7f7f7f7fu;
+                     __builtin_amdgcn_perm((unsigned)m1[pb][3], (unsigned)m1[pb][2], 0x04000c0cu));
             } else if constexpr (ST == 2) {
-                w = __builtin_amdgcn_perm((unsigned)m1[pb][1], (unsigned)m1[pb][0], 0x0c0c0400u) & 0x7f7fu;
+                w = __builtin_amdgcn_perm((unsigned)m1[pb][1], (unsigned)m1[pb][0], 0x0c0c0400u);
             } else {
-                w = (unsigned)m1[pb][0] & 127u;
+                w = (unsigned)m1[pb][0];
             }
             neww[pb] = w;
             diffw[pb] = 0u;
@@ -981,7 +1001,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                     for (int st = 0; st < ST; ++st) {
                         const unsigned rb = row0 + (unsigned)st * row_step + (unsigned)(st * (st - 1) / 2);
                         const bool real = ((actmask >> (8 * st)) & 0xffu) != 0u && pvalid[pb];
-                        idx[st] = real ? (int)c.rowidx[rb + (unsigned)(m1[pb][st] & 127)] : 0;
+                        idx[st] = real ? (int)c.rowidx[rb + (unsigned)m1[pb][st]] : 0;
                     }
                     const int below = xchg32(idx[ST - 1]);      // the last run of the lower half-wave
 #pragma unroll
@@ -1017,7 +1037,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                         unsigned step = row_step;
                         asm volatile("" : "+v"(step));
                         const unsigned rowbase = row0 + (unsigned)st * step + (unsigned)(st * (st - 1) / 2);
-                        const unsigned lo = pt | ((rowbase + (unsigned)(m1[pb][st] & 127)) << 17);         // rows: below 2^12
+                        const unsigned lo = pt | ((rowbase + (unsigned)m1[pb][st]) << 17);         // rows: below 2^12
                         const unsigned hi = FIRST ? (unsigned)from[FIRST ? pb : 0][FIRST ? st : 0] : rowbase + (unsigned)old_of(pb, st);
                         c.log[pos & (kLogCap - 1)] = ((unsigned long long)hi << 32) | lo;
                     }
@@ -1068,7 +1088,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                             int nl = 0;
 #pragma unroll
                             for (int st = 0; st < ST; ++st)
-                                if (st == ost) nl = m1[pb][st] & 127;
+                                if (st == ost) nl = m1[pb][st];
                             const int nlo = xchg32(nl);
                             if (hl != oh) nl = nlo;
                             const int rowbase = r * c.k0 + r * (r - 1) / 2;
@@ -1089,7 +1109,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                     int kk = 0;                         // the owner's (old << 8) | new
 #pragma unroll
                     for (int i = 0; i < NBST; ++i)
-                        if (i == idx) kk = (m1[i / ST][i % ST] & 127) | (old_of(i / ST, i % ST) << 8);
+                        if (i == idx) kk = m1[i / ST][i % ST] | (old_of(i / ST, i % ST) << 8);
                     const int kko = xchg32(kk);
                     if (hl != oh) kk = kko;
                     const int nl = kk & 0xff, ol = kk >> 8;
@@ -1136,7 +1156,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 for (int st = 0; st < ST; ++st) {
                     const int rl = S == 8 ? 0 : hl * ST + st;
                     const bool active = ((S == 8) ? (hl == 0) : true) && rl < c.n_runs && pvalid[pb];
-                    const int row = active ? rl * c.k0 + rl * (rl - 1) / 2 + (m1[pb][st] & 127) : 0;
+                    const int row = active ? rl * c.k0 + rl * (rl - 1) / 2 + m1[pb][st] : 0;
                     const double dist = exact_distance<DP>(xf, c.cs + row * CS);
                     if (active) jown[st] = __dadd_rn(jown[st], dist);
                 }
@@ -1154,7 +1174,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                     const int rl = S == 8 ? 0 : hl * ST + st;
                     const bool active = ((S == 8) ? (hl == 0) : true) && rl < c.n_runs && p < c.chunk_end;
                     const unsigned off = run_off[st] + (unsigned)(pb * 32 + n);      // used for active pairs only: inside the chunk
-                    if (active && c.labels_out) (c.labels_out + base)[off] = m1[pb][st] & 127;
+                    if (active && c.labels_out) (c.labels_out + base)[off] = m1[pb][st];
                 }
             } else {
                 // a word with a changed byte is written back whole (bytes of run slots without a run are never looked at)
@@ -1483,16 +1503,7 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
         c.X = reinterpret_cast<const float *>(wsb + a.off_xs);
         c.ldx = DP;
     }
-    // Bound on the summed error of two matrix-pipeline distances, relative to S = |x'|^2 + max |c'|^2 (centred and
-    // scaled).  Per distance: what the two fp16 pieces per operand leave out - the product of the two low pieces and
-    // the two remainders, each below 2^-20 of its element product - is at most 3 2^-20 |x'| |2c'| <= 24 2^-23 S; 4 or 7
-    // chained MFMAs, each charged five fp32 roundings of a partial sum of at most 2 S (20 or 35 times 2^-23 S); fp32
-    // norms d_pad 2^-24 S each; centring 2 2^-23 S: 54.5 2^-23 S at d_pad <= 16 and 77.5 2^-23 S at 32.  Twice that
-    // is 109 and 155; the bound used is 120 and 200.  A piece below 2^-14 (an fp16 subnormal) is counted as lost
-    // altogether: per distance at most 2^-14 sqrt(d) (|x'| + |2c'|) <= 2^-24 S + 0.078 d, hence the absolute term
-    // kTolFloor next to the relative one (the 2^-24 S makes the 24 above 24.5).  (Measured on gfx950: one MFMA of this
-    // shape is within 1.9 2^-24 of the sum of the magnitudes of its terms, against the five roundings charged.)
-    c.eps_a = (float)(5 * ((DP < 16 ? 16 : DP) + 8)) * 1.1920928955078125e-07f;   // 5 (max(DP, 16) + 8) 2^-23
+    c.eps_a = pair_error_of(DP);
 
     if constexpr (ORD) {
         if (g.list0 >= 0) {
@@ -2109,7 +2120,7 @@ template <int DP, bool INIT>
 __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan plan, CentroidArgs a)
 {
     static_assert(kPartRows * DP <= kThreads, "one thread per (centroid, feature) element of a part");
-    __shared__ float cs[kPartRows * DP];     // centred centroids of this part
+    __shared__ float norms[kPartRows];       // squared norms of this part's centred centroids
     __shared__ long long part_hi[INIT ? 1 : kThreads], part_cnt[INIT ? 1 : kThreads];
     __shared__ unsigned long long part_lo[INIT ? 1 : kThreads];
     const int b = blockIdx.y, tid = threadIdx.x;
@@ -2147,11 +2158,8 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
     float col_mean = 0.0f, c_old = 0.0f;
     const int run_row = row0 - rows_before(plan.k_min, g.run0);      // the run's first row in its group
     const unsigned short *rowpos = a.off_rowpos >= 0 ? reinterpret_cast<const unsigned short *>(wsb + a.off_rowpos) + row0 + j0 : nullptr;
-    int place = j0 + tid / DP, place_n = j0 + tid;                   // of the element's centroid; of this thread's when it takes norms
-    if (rowpos) {
-        if (tid < E) place = rowpos[tid / DP] - run_row;
-        if (tid < rows) place_n = rowpos[tid] - run_row;
-    }
+    int place = j0 + tid / DP;                                       // of the element's centroid
+    if (rowpos && tid < E) place = rowpos[tid / DP] - run_row;
     if (tid < E && tid % DP < d) {
         const int l = tid % DP;
         const int64_t at = (int64_t)(row0 + j0 + tid / DP) * d + l;
@@ -2230,7 +2238,16 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
             }
             cp = fmaf(c, scale, col_mean);       // (c - mean) * scale, one rounding, as for the points
         }
-        cs[jj * DP + l] = cp;
+        // squared norm, summed over the DP lanes of the centroid
+        float nrm = cp * cp;
+        nrm += __int_as_float(dpp_move<kDppSwap1>(__float_as_int(nrm)));
+        nrm += __int_as_float(dpp_move<kDppSwap2>(__float_as_int(nrm)));
+        nrm += __int_as_float(dpp_move<kDppHalfMirror>(__float_as_int(nrm)));
+        if (DP >= 16) nrm += __int_as_float(dpp_move<kDppMirror>(__float_as_int(nrm)));
+        if (DP >= 32) {
+            const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(nrm), __float_as_uint(nrm), false, false);
+            nrm = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        }
         // operand position of (centroid j, feature l)
         const int qd = place >> 2, i = place & 3;
         const int t = qd / g.S, slot = rl * g.S + qd % g.S;
@@ -2241,25 +2258,21 @@ __global__ void __launch_bounds__(kThreads) lloyd_centroids_kernel(SweepPlan pla
         const int ks = sf >> 3, el = sf & 7, ln = h * 32 + m;
         opA[((int64_t)(t * NS + 0 * NK + ks) * 64 + ln) * 8 + el] = ph;
         opA[((int64_t)(t * NS + 1 * NK + ks) * 64 + ln) * 8 + el] = pl;
+        if (l == 0) {
+            // bias slot, lower half-wave lane of this row: pieces of the squared norm
+            unsigned nh, nm, nl;
+            split3(nrm, nh, nm, nl);
+            unsigned short *bias = opA + ((int64_t)(t * NS + 2 * NK) * 64 + m) * 8;
+            bias[0] = (unsigned short)nh; bias[1] = (unsigned short)nm; bias[2] = (unsigned short)nl;
+            norms[jj] = nrm;
+        }
     }
     __syncthreads();
-    float mx = 0.0f;
-    if (tid < rows) {
-        float nrm = 0.0f;
-        for (int l = 0; l < DP; ++l) nrm = fmaf(cs[tid * DP + l], cs[tid * DP + l], nrm);
-        const int qd = place_n >> 2, i = place_n & 3;
-        const int t = qd / g.S, slot = rl * g.S + qd % g.S;
-        // bias slot, lower half-wave lane of this row: pieces of the squared norm
-        unsigned ph, pm, pl;
-        split3(nrm, ph, pm, pl);
-        const int m = 8 * (slot & 3) + 4 * (slot >> 2) + i;
-        unsigned short *bias = opA + ((int64_t)(t * NS + 2 * NK) * 64 + m) * 8;
-        bias[0] = (unsigned short)ph; bias[1] = (unsigned short)pm; bias[2] = (unsigned short)pl;
-        mx = nrm;
-    }
-    // rows <= 64: the first wave holds them all; the run's maximum is taken over its parts by the reader
+    // the run's maximum is taken over its parts by the reader
     if (tid < 64) {
-        for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+        static_assert(kPartRows <= 64, "the first wave holds them all");
+        float mx = tid < rows ? norms[tid] : 0.0f;
+        for (int off = kPartRows / 2; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
         if (tid == 0) reinterpret_cast<float *>(wsb + a.off_cnmax)[run * kMaxParts + part] = mx;
     }
 }

@@ -103,7 +103,8 @@ __global__ void __launch_bounds__(small_threads_of(DP)) lloyd_small_kernel(Sweep
     const int row0 = rows_before(a.k_min, run);
     float *const Cb = a.C + (int64_t)b * a.c_bs + (int64_t)row0 * d;
     const float scale = *reinterpret_cast<const float *>(info + kColScaleOff);
-    int mask = (int)0xffffff80;
+    const int kbits = key_bits(32 * n_tiles);
+    int mask = key_mask(kbits);
     asm volatile("" : "+v"(mask));                  // keep the mask in a VGPR
 
     // ---- column information, padding rows, empty sums, the initial centroids
@@ -262,7 +263,7 @@ __global__ void __launch_bounds__(small_threads_of(DP)) lloyd_small_kernel(Sweep
     renew(0);
 
     // (the bound on the error of two distances of the matrix pipeline, as in lloyd_step_kernel)
-    const float eps_a = (float)(5 * ((DP < 16 ? 16 : DP) + 8)) * 1.1920928955078125e-07f;
+    const float eps_a = pair_error_of(DP), shrink = key_shrink(kbits);
     unsigned long long *const sums_l = sums_s + (lane & (copies - 1)) * k * (DP + 1);
     int *const cnts_l = cnts_s + (lane & (copies - 1)) * k;
     const int n_blocks = (int)((a.N + 31) / 32);
@@ -328,8 +329,8 @@ __global__ void __launch_bounds__(small_threads_of(DP)) lloyd_small_kernel(Sweep
                 insert2(o2, k1, k2);
             }
             const float xn = (__uint_as_float(norm.x << 16) + __uint_as_float(norm.x & 0xffff0000u)) + __uint_as_float(norm.y << 16);
-            const bool close = valid && !(fmaf(__int_as_float(k2), 0.999969482421875f, -__int_as_float(k1)) > fmaf(eps_a, xn, tol_run));
-            int label = k1 & 127;
+            const bool close = valid && !(fmaf(__int_as_float(k2), shrink, -__int_as_float(k1)) > fmaf(eps_a, xn, tol_run));
+            int label = k1 & ~mask;
             unsigned todo = (unsigned)__builtin_amdgcn_ballot_w64(close);         // (both halves hold the same points)
             if (4 * __popc(todo) > k) {
                 // many for so few centroids: together, each lane half of the centroids of its own point

@@ -19,6 +19,23 @@ constexpr int kLowBits = 36;                  // further bits kept by the low ac
 // piece below 2^-14 (subnormal) may be lost, which costs a distance at most 0.078 d + S 2^-24 in scaled units (see eps_a)
 constexpr int kScaledMsb = 14;
 constexpr float kTolFloor = 8.0f;             // twice that loss at d = 32, in scaled squared units
+
+// Bound on the summed error of two matrix-pipeline distances, relative to S = |x'|^2 + max |c'|^2 (centred and scaled), in units of
+// 2^-23 S.  Per distance:
+//   6    what the two pieces per operand leave out: the product of the two low pieces and the two remainders, each below 2^-22
+//        |x'| |2c'|, and |x'| |2c'| <= S
+//   5.5  (7.5 at d_pad = 32) the MFMA of the high pieces (two of them).  What it leaves out was probed on gfx950 with one large term
+//        among small ones: the eight products of a half of K are lined up with the largest of them and cut off below 2^-24 of its
+//        power of two - so at most 7 times 2^-24 of it is lost -, and the two half sums are added to the accumulator with a
+//        cut below one unit in the last place each.  The MFMAs of the low pieces, a 2^-10 of the magnitude, lose nothing that counts
+//   5    the MFMA of the norms: products by one, whose pieces lose nothing, and two additions of up to 2 S
+//   2.5  (3) the norm of the centroid: five (six) roundings.  (That of the point is the same in both distances.)
+//   2    centring
+//   0.5  pieces below 2^-14 (fp16 subnormals) counted as lost altogether: at most 2^-14 sqrt(d) (|x'| + |2c'|)
+//        <= 2^-24 S + 0.078 d, hence the absolute term kTolFloor next to the relative one
+// 21.5 (24): twice that is 43 (48), the bound used is 48 (56).  (The pieces were rounded toward zero and every MFMA charged ten units
+// before, 120 and 200: 2.5 and 3.6 times as many close calls.)
+__host__ __device__ constexpr float pair_error_of(int dp) { return (dp == 32 ? 56.0f : 48.0f) * 1.1920928955078125e-07f; }
 constexpr int kColScaleOff = 400;             // byte offset of the scale factor in the column info block
 
 // MFMA operands: a lane holds 8 fp16 values of its half of the features per K-step (v_mfma_f32_32x32x16_f16);
@@ -285,16 +302,17 @@ __device__ inline void split3(float v, unsigned &h, unsigned &m, unsigned &l)
 __device__ inline bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 __device__ inline f16x8 as_f16x8(uint4 v) { return __builtin_bit_cast(f16x8, v); }
 
-// Two fp16 pieces of a value, rounded toward zero: v = h + l + r with |r| < 2^-20 |v| while the pieces are normal
-// fp16 numbers (11 significant bits each; v - h is exact in fp32).  The pair form packs a's pieces into the low
-// halves and b's into the high halves, as two neighbouring operand elements.
-typedef __fp16 fp16x2 __attribute__((ext_vector_type(2)));
+// Two fp16 pieces of a value, rounded to the nearest: v = h + l + r with |l| <= 2^-11 |v| and |r| <= 2^-22 |v| while the
+// pieces are normal fp16 numbers (11 significant bits each; v - h is exact in fp32).  The pair form packs a's pieces into the
+// low halves and b's into the high halves, as two neighbouring operand elements.
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef _Float16 fp16x2 __attribute__((ext_vector_type(2)));
 __device__ inline void split2_pair(float a, float b, unsigned &h, unsigned &l)
 {
-    const fp16x2 hh = __builtin_amdgcn_cvt_pkrtz(a, b);
+    const fp16x2 hh = __builtin_convertvector((floatx2{a, b}), fp16x2);
     h = __builtin_bit_cast(unsigned, hh);
-    const float ra = a - (float)hh[0], rb = b - (float)hh[1];
-    l = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(ra, rb));
+    const floatx2 rest = {a - (float)hh[0], b - (float)hh[1]};
+    l = __builtin_bit_cast(unsigned, __builtin_convertvector(rest, fp16x2));
 }
 __device__ inline void split2(float v, unsigned short &h, unsigned short &l)
 {
@@ -304,7 +322,7 @@ __device__ inline void split2(float v, unsigned short &h, unsigned short &l)
     l = (unsigned short)(pl & 0xffffu);
 }
 
-// The index that phase A packs into the low 7 bits of a key is the centroid index within the run:
+// The index that phase A packs into the low bits of a key (7 at most) is the centroid index within the run:
 // centroid j lives in tile (j/4)/S, slot (j/4)%S of its run, row j%4 (see GroupDesc).
 template <int S>
 __device__ inline int key_index(int t, int a, int i)
@@ -318,6 +336,13 @@ __device__ inline int key_index(int t, int a, int i)
 __host__ __device__ constexpr int index_quads_of(int s) { return s == 1 ? 1 : (s == 2 ? 2 : 4); }
 template <int S>
 __device__ inline int state_of(int a) { return S == 1 ? a : (S == 2 ? (a >> 1) : 0); }
+
+// Keys: the low bits of a distance give way to the index, as many as the indices of a slab take (kidx < 2^bits).
+__device__ inline int key_mask(int bits) { return (int)(0xffffffffu << bits); }
+__device__ inline int key_bits(int indices) { return indices > 1 ? 32 - __builtin_clz((unsigned)(indices - 1)) : 0; }
+// 1 - 2^(bits - 22): read as a float a key g lies within 2^(bits - 23) |v| of the value v it was packed from, so
+// v2 - v1 >= g2 (1 - 2^(bits - 22)) - g1 whenever g2 >= |g1|
+__device__ inline float key_shrink(int bits) { return __uint_as_float(0x3f800000u - (4u << bits)); }
 
 // (bits & mask) | idx.  The mask is kept opaque to the compiler (a VGPR) so that this selects one and-or
 // instruction with the index as its scalar operand.  It must stay a compiler-visible operation (not inline

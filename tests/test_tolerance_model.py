@@ -49,6 +49,57 @@ def test_two_piece_products_stay_inside_the_bound(flush):
     assert worst > 0.01      # the model is exercised: the errors are not orders of magnitude below the bound
 
 
+@pytest.mark.parametrize("flush", [False, True])
+def test_two_nearest_pieces_stay_inside_their_bound(flush):
+    """Pieces rounded to the nearest (`split2_pair` in paper_1905_12799_amd/csrc/lloyd_device.h): what they leave out of a distance
+    is at most 6.5 * 2^-23 * (|x'|^2 + |c'|^2) plus 0.0781 * d (comment at `pair_error_of`: 6 + 0.5)."""
+    rng = np.random.default_rng(15 + int(flush))
+    f64 = np.float64
+    worst = 0.0
+    for trial in range(80):
+        d = int(rng.choice([8, 16, 32]))
+        scale = 2.0 ** rng.integers(-24, 14)
+        x = (rng.standard_normal((2048, d)) * scale).astype(np.float32)
+        c = (rng.standard_normal((2048, d)) * scale * rng.choice([1.0, 0.01, 30.0])).astype(np.float32)
+        if trial % 3 == 0:
+            x[:, 0] *= 2.0 ** 10
+            c[:, 0] *= 2.0 ** 10
+        if trial % 4 == 0:                       # halfway between two pieces: the largest remainders
+            x = (np.clip(x, -2.0 ** 12, 2.0 ** 12).astype(np.float16).astype(f64) * (1 + 2.0 ** -11 - 2.0 ** -22)).astype(np.float32)
+        x = np.clip(x, -2.0 ** 13, 2.0 ** 13)
+        C = (-2.0 * np.clip(c, -2.0 ** 13, 2.0 ** 13)).astype(np.float32)
+        xh, Ch = (v.astype(np.float16).astype(np.float32) for v in (x, C))
+        assert np.all((x - xh).astype(f64) == x.astype(f64) - xh.astype(f64))            # the remainder is exact in fp32
+        xl, Cl = ((v - h).astype(np.float16).astype(np.float32) for v, h in ((x, xh), (C, Ch)))
+        if flush:
+            xh, xl, Ch, Cl = (lost_below_normal(a) for a in (xh, xl, Ch, Cl))
+        approx = (xh.astype(f64) * Ch + xh.astype(f64) * Cl + xl.astype(f64) * Ch).sum(1)
+        exact = (x.astype(f64) * C.astype(f64)).sum(1)
+        S = (x.astype(f64) ** 2).sum(1) + (C.astype(f64) ** 2).sum(1) / 4
+        worst = max(worst, float((np.abs(approx - exact) / (6.5 * 2.0 ** -23 * S + 0.0781 * d + d * 2.0 ** -27)).max()))
+    assert 0.01 < worst <= 1.0
+
+
+@pytest.mark.parametrize("bits", range(8))
+def test_keys_tell_no_more_than_the_distances(bits):
+    """A key is a distance whose lowest `bits` bits gave way to an index.  The difference of two distances is at least
+    g2 (1 - 2^(bits - 22)) - g1 (`key_shrink`), for keys g2 >= |g1| and with one rounding."""
+    rng = np.random.default_rng(bits)
+    v1 = (2.0 ** rng.uniform(-10, 30, 200000)).astype(np.float32)
+    v2 = np.where(rng.random(v1.size) < 0.5, v1 * (1 + 2.0 ** rng.uniform(-24, -8, v1.size)), 2.0 ** rng.uniform(-10, 30, v1.size)).astype(np.float32)
+    v1, v2 = np.minimum(v1, v2), np.maximum(v1, v2)
+
+    def key(v):
+        return ((v.view(np.uint32) >> bits << bits) | rng.integers(0, 1 << bits, v.size).astype(np.uint32)).view(np.float32)
+
+    g = np.sort(np.stack([key(v1), key(v2)]), axis=0).astype(np.float64)
+    shrink = np.array(0x3F800000 - (4 << bits), dtype=np.uint32).view(np.float32).astype(np.float64)
+    assert shrink == 1 - 2.0 ** (bits - 22)
+    told = (g[1] * shrink - g[0]).astype(np.float32).astype(np.float64)
+    diff = v2.astype(np.float64) - v1.astype(np.float64)
+    assert np.all((told <= diff) | (told <= 0))
+
+
 def test_fp32_direct_form_first_stage_keeps_the_fp64_winner():
     """The exact argmin of the Lloyd step settles most calls in fp32: direct-form distances (difference, square, running
     sum with one rounding per multiply-add), then every centroid within 8 (d + 2) 2^-24 of the smallest stays a
