@@ -50,11 +50,14 @@ __host__ __device__ inline int parts_upto(int k)
 __host__ __device__ constexpr int tile_points_of(int dp) { return dp == 32 ? 256 : 512; }
 // Tile lists of an ordered sweep.  A unit is 32 points (64 at d_pad = 32) that follow each other in the order; for every
 // unit, and each of the eight quad slots of a group's tiles, a list names the tiles whose quad in that slot may hold the
-// nearest centroid of one of the unit's points.  16 words per unit and group: eight of first words (one per slot: three tiles,
-// then the length of the longest of the eight lists, or kListAll when one does not fit), eight of second words (four more
-// tiles).  A list that ends before the longest one goes on with the tile of padding rows behind the real ones.
+// nearest centroid of one of the unit's points.  16 words per unit and group, four bits per tile: eight of first words (one per
+// slot: entries 0 to 6, and above them the length of the longest of the eight lists, less one), eight of second words (entries 7
+// to 14, read by the few units that have so many).  Sixteen entries are all tiles in their order: entry 15 is then what the length
+// says.  A list that ends before the longest one goes on with tiles that are not on it: their centroids are farther away, and
+// nothing else is wrong with them.
 __host__ __device__ constexpr int unit_blocks_of(int dp) { return dp == 32 ? 2 : 1; }
-constexpr int kListWords = 16, kListHead = 3, kListMax = 7, kListAll = 255;
+constexpr int kListWords = 16, kListHead = 7;
+__device__ inline unsigned list_entry(unsigned head, unsigned more, int e) { return ((e < kListHead || e == 15 ? head : more) >> (4 * (e < kListHead ? e : (e == 15 ? 7 : e - kListHead)))) & 15u; }
 constexpr int kListMinTiles = 3;              // groups of fewer tiles meet them all: there is little to leave out
 constexpr int kListMaxTiles = 16;             // groups of an ordered sweep have no more
 
@@ -70,8 +73,7 @@ __host__ __device__ inline Carve carve_lds(int dp, int d, int n_tiles, int real_
 {
     Carve c;
     int off = 0;
-    // MFMA operand rows of the group (fp16 pieces + bias slot); with tile lists a tile of padding rows behind them
-    c.opA = off;     off += (n_tiles + (ordered ? 1 : 0)) * tile_bytes_of(dp);
+    c.opA = off;     off += n_tiles * tile_bytes_of(dp);                // MFMA operand rows of the group (fp16 pieces + bias slot)
     c.cs = off;      off += real_rows * (dp + 4) * 4;                   // centroids as given, rows of dp + 4 floats, zero-padded
     // accumulators: `copies` of them side by side (a lane adds to copy lane % copies, which spreads the lanes that
     // hit one cluster of a run with few clusters over several addresses; the copies are summed at the end)
@@ -222,7 +224,15 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
     constexpr int kUnitShift = unit_blocks_of(DP) == 2 ? 6 : 5;
     const unsigned *const lists = ORD && c.lists ? c.lists + (c.chunk_begin >> kUnitShift) * kListWords : nullptr;
     const uint4 *const xp_chunk = PRE ? c.xp + (c.chunk_begin >> 5) * prep_block_u4_of(DP) : nullptr;    // chunks start on a block boundary
-    unsigned listn = 0u, list_moren = 0u;            // the list of the slab being fetched
+    unsigned listn = 0x76543210u;                    // the list of the slab being fetched (groups without lists: all tiles, fewer than eight)
+    static_assert(kListMinTiles <= 8, "groups without lists");
+    // the word of this lane's row slot, of the unit that holds a point of the chunk (a scalar base and a lane offset of 32 bits)
+    auto list_word = [&](unsigned pt, unsigned second) -> unsigned {
+        const char *const at = reinterpret_cast<const char *>(lists + (pt >> kUnitShift) * kListWords + second);
+        unsigned slot = 4u * a_slot;
+        asm volatile("" : "+v"(slot));
+        return *reinterpret_cast<const unsigned *>(at + slot);
+    };
     auto load_labels = [&](unsigned pt) -> unsigned {                    // of a point within the chunk
         return (unsigned)*reinterpret_cast<const LabWord *>(prev_chunk + (pt * (unsigned)R + lab_off));
     };
@@ -241,14 +251,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 if constexpr (!FIRST) oldn[pb] = load_labels(first + li);
             }
             if constexpr (ORD) {
-                if (lists) {
-                    // (a scalar base and a lane offset that is not folded into it: one register instead of two through the loop)
-                    const unsigned *const at = lists + (first >> kUnitShift) * kListWords;
-                    unsigned slot = a_slot;
-                    asm volatile("" : "+v"(slot));
-                    listn = at[slot];
-                    list_moren = at[slot + 8];
-                }
+                if (lists) listn = list_word(first, 0u);
             }
             return;
         }
@@ -282,7 +285,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                     asm volatile("" : "+v"(pnext[pb][sl].x), "+v"(pnext[pb][sl].y), "+v"(pnext[pb][sl].z), "+v"(pnext[pb][sl].w));
                 asm volatile("" : "+v"(nnext[pb].x), "+v"(nnext[pb].y));
             }
-            if constexpr (ORD) asm volatile("" : "+v"(listn), "+v"(list_moren));
+            if constexpr (ORD) asm volatile("" : "+v"(listn));
         } else {
 #pragma unroll
             for (int pb = 0; pb < NB; ++pb)
@@ -308,16 +311,22 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
             return fixed_next;
         }
         int v = 0;
-        if (lane == 0) v = atomicAdd(c.next_slab, 1);
+        // (an address known to be the same in every lane would make it a count of lanes and a scan)
+        typedef __attribute__((address_space(3))) int lds_int;
+        unsigned at = (unsigned)(uintptr_t)(lds_int *)c.next_slab;
+        asm volatile("" : "+v"(at));
+        if (lane == 0) v = __hip_atomic_fetch_add((lds_int *)(uintptr_t)at, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         return __builtin_amdgcn_readfirstlane(v);
     };
     int cur = wave;
     fetch(min(cur, n_slabs - 1));
     const bool any_wide = c.wide_s[32] != 0;
-    // part of the error bound that belongs to a run (the centroids' largest squared norm), per run this lane owns
-    float tol_run[ST];
+    // part of the error bound that belongs to a run (the centroids' largest squared norm), of the runs this lane owns
+    float tol_runs = 0.0f;                           // (the largest over them)
 #pragma unroll
-    for (int st = 0; st < ST; ++st) tol_run[st] = c.eps_a * c.cnmax_s[S == 8 ? 0 : hl * ST + st] + kTolFloor;
+    for (int st = 0; st < ST; ++st) tol_runs = fmaxf(tol_runs, c.eps_a * c.cnmax_s[S == 8 ? 0 : hl * ST + st] + kTolFloor);
+    // |x'|^2 for the error bound: on the prepared copy its upper piece, which is at most 2^-7 of it below
+    const float eps_x = PRE ? c.eps_a * 1.0078125f : c.eps_a;
     // accumulator rows of this lane's runs: run rl of the group begins at row rl k0 + rl (rl - 1) / 2
     const unsigned rl0 = S == 8 ? 0u : (unsigned)(hl * ST);
     const unsigned row0 = rl0 * (unsigned)c.k0 + rl0 * (rl0 - 1u) / 2u, row_step = (unsigned)c.k0 + rl0;
@@ -473,6 +482,11 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         }
         log_head += nrec;
     };
+    // the words of this lane's slots 4 hl .. 4 hl + 3, from lanes that feed them
+    auto slot_words = [&](unsigned w, unsigned (&out)[4]) {
+#pragma unroll
+        for (int a = 0; a < 4; ++a) out[a] = (unsigned)__builtin_amdgcn_ds_bpermute(16 * hl + 32 * a, (int)w);
+    };
     settle();
     if (cur >= n_slabs) return;
     int nxt = grab();
@@ -507,14 +521,15 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         int m1[NB][ST], m2[NB][ST];
         unsigned oldl[NB];                // labels in the previous round, one byte per run of this lane
         // the tiles this slab meets: all of them in order, or those of its unit's list - this lane's slot meets its own ones
-        const unsigned list = listn, list_more = list_moren;
-        bool listed = false;
+        const unsigned list = listn;
+        unsigned list_more = list;
+        unsigned own[4] = {list, list, list, list};    // the first words of this lane's slots 4 hl .. 4 hl + 3, from lanes that feed them
         int n_it = c.n_tiles;
         if constexpr (ORD) {
             if (lists) {
-                const int len = __builtin_amdgcn_readfirstlane((int)(list >> 24));
-                listed = len != kListAll;
-                if (listed) n_it = len;
+                n_it = (int)((unsigned)__builtin_amdgcn_readfirstlane((int)list) >> 28) + 1;
+                if (n_it > kListHead) list_more = list_word((unsigned)cur * SLAB, 8u);
+                slot_words(list, own);
                 if constexpr (S < 8) {
                     kbits = key_bits(4 * S * n_it);
                     mask = key_mask(kbits);
@@ -531,7 +546,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                     bx[pb][0][ks] = as_f16x8(pnext[pb][0 * NK + ks]);
                     bx[pb][1][ks] = as_f16x8(pnext[pb][1 * NK + ks]);
                 }
-                xn[pb] = (__uint_as_float(nnext[pb].x << 16) + __uint_as_float(nnext[pb].x & 0xffff0000u)) + __uint_as_float(nnext[pb].y << 16);
+                xn[pb] = __uint_as_float(nnext[pb].x << 16);            // (the upper piece: see eps_x)
                 bb[pb] = hl ? as_bf16x8(make_uint4(nnext[pb].x, nnext[pb].y, 0u, 0u)) : as_bf16x8(make_uint4(0x3f803f80u, 0x3f80u, 0u, 0u));
 #pragma unroll
                 for (int st = 0; st < ST; ++st) { m1[pb][st] = kBigKey; m2[pb][st] = kBigKey; }
@@ -576,14 +591,10 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         uint4 a_even[NS], a_odd[NS];
         // operands of step t: tile t, or the tile that is next in the list of this lane's slot
         auto load_a = [&](uint4 (&dst)[NS], int t) {
-            unsigned at = (unsigned)t * (NS * 64);
-            if constexpr (ORD) {
-                const unsigned word = t < kListHead ? list : list_more;
-                const unsigned tile = listed ? (word >> (8 * (t < kListHead ? t : t - kListHead))) & 255u : (unsigned)t;
-                at = __umul24(tile, NS * 64);
-            }
+            const uint4 *at = opA_s + t * (NS * 64) + lane;
+            if constexpr (ORD) at = reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(opA_s + lane) + __umul24(list_entry(list, list_more, t), NS * 1024));
 #pragma unroll
-            for (int sl = 0; sl < NS; ++sl) dst[sl] = opA_s[at + (unsigned)(sl * 64 + lane)];
+            for (int sl = 0; sl < NS; ++sl) dst[sl] = at[sl * 64];
         };
         load_a(a_even, 0);
         if constexpr (NB == 1) {
@@ -715,53 +726,40 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
             }
             fold_tile<S, ST>(acc_prev, kidx_old, mask, m1[NB - 1], m2[NB - 1]);
         }
-        // The keys hold steps of the lists: the step becomes the tile that the winner's slot met there, and of the key the index is
-        // left.  (The second key's index is not used.)
+        // The keys hold steps of the lists: the step becomes the tile that the winner's slot met there.  The index is then in the
+        // lowest seven bits (six where runs have one slot), whatever else the key holds.  (The second key's index is not used.)
         auto steps_to_tiles = [&]() {
-            {
-                // the words of this lane's slots 4 hl .. 4 hl + 3, from lanes that feed them
-                auto slots = [&](unsigned w, unsigned (&out)[4]) {
+            constexpr int kStepShift = S == 1 ? 2 : (S == 2 ? 3 : (S == 4 ? 4 : 5));
+            constexpr unsigned kTileMask = (15u << kStepShift) & 127u;       // (16, 16, 8, 4 tiles at most)
+            // four times the step: it is a list's entry, of four bits
+            const unsigned step_mask = (unsigned)~mask >> kStepShift << 2;
+            auto shift_of = [&](int key) -> unsigned { return (S == 1 ? (unsigned)key : (unsigned)key >> (kStepShift - 2)) & step_mask; };
+            // the word of the slot that a run's key came from (selects by bit masks: an index would put the words in memory)
+            auto either = [](unsigned w0, unsigned w1, int key, int bit) { return w0 ^ ((w0 ^ w1) & (0u - (((unsigned)key >> bit) & 1u))); };
+            auto pick = [&](const unsigned (&w)[4], int st, int key) -> unsigned {
+                if (S == 1) return w[st];
+                if (S == 2) return st == 0 ? either(w[0], w[1], key, 2) : either(w[2], w[3], key, 2);
+                return either(either(w[0], w[1], key, 2), either(w[2], w[3], key, 2), key, 3);
+            };
+            auto put = [&](int &key, unsigned tile) { key = (int)(((tile << kStepShift) & kTileMask) | ((unsigned)key & ~kTileMask)); };
+            if (n_it <= kListHead) {
 #pragma unroll
-                    for (int a = 0; a < 4; ++a) out[a] = (unsigned)__builtin_amdgcn_ds_bpermute(16 * hl + 32 * a, (int)w);
-                };
-                unsigned own[4];
-                slots(list, own);
-                constexpr int kStepShift = S == 1 ? 2 : (S == 2 ? 3 : (S == 4 ? 4 : 5));
-                constexpr int kKeepMask = S == 8 ? ~(3 << kStepShift) : (1 << kStepShift) - 1;      // (S = 8: four tiles at most)
-                const unsigned step_bits = (unsigned)(kbits - kStepShift);
-                auto step_of = [&](int key) -> unsigned { return __builtin_amdgcn_ubfe((unsigned)key, (unsigned)kStepShift, step_bits); };
-                // the word of the slot that a run's key came from (selects by bit masks: an index would put the words in memory)
-                auto either = [](unsigned w0, unsigned w1, int key, int bit) { return w0 ^ ((w0 ^ w1) & (0u - (((unsigned)key >> bit) & 1u))); };
-                auto pick = [&](const unsigned (&w)[4], int st, int key) -> unsigned {
-                    if (S == 1) return w[st];
-                    if (S == 2) return st == 0 ? either(w[0], w[1], key, 2) : either(w[2], w[3], key, 2);
-                    return either(either(w[0], w[1], key, 2), either(w[2], w[3], key, 2), key, 3);
-                };
-                if (n_it <= kListHead) {
+                for (int pb = 0; pb < NB; ++pb)
 #pragma unroll
-                    for (int pb = 0; pb < NB; ++pb)
+                    for (int st = 0; st < ST; ++st) put(m1[pb][st], pick(own, st, m1[pb][st]) >> shift_of(m1[pb][st]));
+            } else {
+                unsigned more[4];
+                slot_words(list_more, more);
 #pragma unroll
-                        for (int st = 0; st < ST; ++st) {
-                            const int key = m1[pb][st];
-                            const unsigned step = step_of(key);
-                            m1[pb][st] = (key & kKeepMask) | (int)(((pick(own, st, key) >> (8 * step)) & 255u) << kStepShift);
-                        }
-                } else {
-                    unsigned more[4];
-                    slots(list_more, more);
+                for (int pb = 0; pb < NB; ++pb)
 #pragma unroll
-                    for (int pb = 0; pb < NB; ++pb)
-#pragma unroll
-                        for (int st = 0; st < ST; ++st) {
-                            const int key = m1[pb][st];
-                            const unsigned step = step_of(key);
-                            const unsigned w = step < kListHead ? pick(own, st, key) : pick(more, st, key);
-                            m1[pb][st] = (key & kKeepMask) | (int)(((w >> (8 * (step < kListHead ? step : step - kListHead))) & 255u) << kStepShift);
-                        }
-                }
+                    for (int st = 0; st < ST; ++st) {
+                        const int key = m1[pb][st];
+                        put(m1[pb][st], list_entry(pick(own, st, key), pick(more, st, key), (int)(shift_of(key) >> 2)));
+                    }
             }
         };
-        if (ORD && S == 8 && listed) steps_to_tiles();
+        if (ORD && S == 8 && lists) steps_to_tiles();
         if (LATE_FETCH) fetch(min(nxt, n_slabs - 1));
 
         // ---- labels, close calls, sums
@@ -778,7 +776,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         // Keys: which pairs does the exact arithmetic have to confirm?  Bit pb * ST + st of a lane's mask, put together
         // only when the wave has such a pair at all.
         unsigned pend = 0;
-        bool closeb[NB][ST];
+        float clear[NB][ST];                        // by how much the second key is above the first
         bool any_close = false;
         const float shrink = key_shrink(kbits);
 #pragma unroll
@@ -793,23 +791,24 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 insert2(o2, k1, k2);
                 m1[pb][0] = k1; m2[pb][0] = k2;
             }
+            // Error bound of the two expansions (rounding of norms, products and the centring) plus the mantissa bits given up to
+            // the index.  The keys are compared as they are, index bits included (see key_shrink; a negative first key - a distance
+            // of zero within the bound - is smaller than the bound's own slack).
 #pragma unroll
-            for (int st = 0; st < ST; ++st) {
-                const int rl = S == 8 ? 0 : hl * ST + st;     // run within the group
-                const bool active = ((S == 8) ? (hl == 0) : true) && rl < c.n_runs && pvalid[pb];
-                // Error bound of the two expansions (rounding of norms, products and the centring) plus the
-                // mantissa bits given up to the index.  The keys are compared as they are, index bits included (see key_shrink;
-                // a negative g1 - a distance of zero within the bound - is smaller than the bound's own slack).  One multiply-add and
-                // one compare.
-                const float g1 = __int_as_float(m1[pb][st]), g2 = __int_as_float(m2[pb][st]);
-                const float tol0 = fmaf(c.eps_a, xn[pb], tol_run[st]);
-                closeb[pb][st] = active && !(fmaf(g2, shrink, -g1) > tol0);
-                any_close = any_close || closeb[pb][st];
+            for (int st = 0; st < ST; ++st) clear[pb][st] = fmaf(__int_as_float(m2[pb][st]), shrink, -__int_as_float(m1[pb][st]));
+            if (c.n_runs < R) {
+                asm volatile("");                   // (a branch: few groups have slots without a run, which hold padding rows only)
+#pragma unroll
+                for (int st = 0; st < ST; ++st) clear[pb][st] = ((actmask >> (8 * st)) & 0xffu) != 0u ? clear[pb][st] : INFINITY;
             }
+            float least = clear[pb][0];
+#pragma unroll
+            for (int st = 1; st < ST; ++st) least = fminf(least, clear[pb][st]);
+            any_close = any_close || !(least > fmaf(eps_x, xn[pb], tol_runs));
         }
         // from here on m1 holds indices
-        if (ORD && S < 8 && listed) {
-            steps_to_tiles();
+        if (ORD && lists) {
+            if constexpr (S < 8) steps_to_tiles();
         } else {
 #pragma unroll
             for (int pb = 0; pb < NB; ++pb)
@@ -820,13 +819,16 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
 #pragma unroll
             for (int pb = 0; pb < NB; ++pb)
 #pragma unroll
-                for (int st = 0; st < ST; ++st) pend |= (unsigned)closeb[pb][st] << (pb * ST + st);
+                for (int st = 0; st < ST; ++st) {
+                    const bool close = pvalid[pb] && (S < 8 || hl == 0) && !(clear[pb][st] > fmaf(eps_x, xn[pb], tol_runs));
+                    pend |= (unsigned)close << (pb * ST + st);
+                }
             if constexpr (ORD && S <= 2) {
                 // Where points lie close together their close calls come together as well (on knob data whole blocks of points tie
                 // exactly), and a wave that settles 256 of them one by one holds up its launch.  Many at a time are settled by the
                 // lanes that own them, each its own pair: the exact arithmetic over the centroids that the unit's lists name.
                 constexpr int kMany = 8;                 // (one by one: 100 to 350 instructions each; together: 75 per listed centroid)
-                if (listed && __popcll(__builtin_amdgcn_ballot_w64(pend != 0u)) >= kMany) {
+                if (lists && __popcll(__builtin_amdgcn_ballot_w64(pend != 0u)) >= kMany) {
                 int half = hl;                           // (opaque: nothing of this is worked out ahead of the branch)
                 asm volatile("" : "+v"(half));
 #pragma unroll
@@ -849,8 +851,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                             const unsigned slot = (unsigned)(half * 4 + st * S + a);
                             const unsigned head = lists[(pt0 >> kUnitShift) * kListWords + slot], more = lists[(pt0 >> kUnitShift) * kListWords + 8 + slot];
                             for (int q = 0; q < 4 * n_it; ++q) {
-                                const int step = q >> 2;
-                                const int tile = (int)(((step < kListHead ? head : more) >> (8 * (step < kListHead ? step : step - kListHead))) & 255u);
+                                const int tile = (int)list_entry(head, more, q >> 2);
                                 const int place = 4 * (S * tile + a) + (q & 3);
                                 if (place >= k) continue;                        // padding
                                 const int j = (int)c.rowidx[rowbase + place];
@@ -968,6 +969,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
             } else {
                 w = (unsigned)m1[pb][0];
             }
+            if constexpr (ORD) w &= S == 1 ? 0x3f3f3f3fu : 0x7f7f7f7fu;          // (all else that the keys hold)
             neww[pb] = w;
             diffw[pb] = 0u;
             if constexpr (!FINAL && !FIRST) diffw[pb] = pvalid[pb] ? ((w ^ oldl[pb]) & actmask) : 0u;
@@ -984,6 +986,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
             }
         }
 
+        auto new_of = [&](int pb, int st) -> int { return (int)((neww[pb] >> (8 * st)) & 0xffu); };
         if constexpr (PRE) {
             // Exact sums, later: the moved pairs go into this wave's log; 64 records at a time are worked off below.
             static_assert(64 * NBST + 63 <= kLogCap, "a slab's records and what an earlier flush left over must fit the ring");
@@ -1001,7 +1004,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                     for (int st = 0; st < ST; ++st) {
                         const unsigned rb = row0 + (unsigned)st * row_step + (unsigned)(st * (st - 1) / 2);
                         const bool real = ((actmask >> (8 * st)) & 0xffu) != 0u && pvalid[pb];
-                        idx[st] = real ? (int)c.rowidx[rb + (unsigned)m1[pb][st]] : 0;
+                        idx[st] = real ? (int)c.rowidx[rb + (unsigned)new_of(pb, st)] : 0;
                     }
                     const int below = xchg32(idx[ST - 1]);      // the last run of the lower half-wave
 #pragma unroll
@@ -1037,7 +1040,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                         unsigned step = row_step;
                         asm volatile("" : "+v"(step));
                         const unsigned rowbase = row0 + (unsigned)st * step + (unsigned)(st * (st - 1) / 2);
-                        const unsigned lo = pt | ((rowbase + (unsigned)m1[pb][st]) << 17);         // rows: below 2^12
+                        const unsigned lo = pt | ((rowbase + (unsigned)new_of(pb, st)) << 17);         // rows: below 2^12
                         const unsigned hi = FIRST ? (unsigned)from[FIRST ? pb : 0][FIRST ? st : 0] : rowbase + (unsigned)old_of(pb, st);
                         c.log[pos & (kLogCap - 1)] = ((unsigned long long)hi << 32) | lo;
                     }
@@ -1262,28 +1265,36 @@ __device__ __forceinline__ void make_lists(const WaveCtx &c, const uint4 *centre
 #pragma unroll
             for (int a = 0; a < 4; ++a) in[a] |= quad[t][a] <= lim[state_of<S>(a)] ? 1u << t : 0u;
         }
-        const unsigned pad = (unsigned)c.n_tiles;
         int longest = max(max(__popc(in[0]), __popc(in[1])), max(__popc(in[2]), __popc(in[3])));
         longest = max(max(longest, xchg32(longest)), 1);
-        const unsigned mark = (unsigned)(longest > kListMax ? kListAll : longest) << 24;
+        const unsigned all = (1u << c.n_tiles) - 1u;
         unsigned head[4], more[4];
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-            head[a] = mark;
+            head[a] = (unsigned)(longest - 1) << 28;
             more[a] = 0u;
-#pragma unroll
-            for (int i = 0; i < kListMax; ++i) {
-                const unsigned t = in[a] != 0u ? (unsigned)(__ffs(in[a]) - 1) : pad;
-                in[a] &= in[a] - 1u;
-                if (i < kListHead) head[a] |= t << (8 * i);
-                else more[a] |= t << (8 * (i - kListHead));
-            }
+            if (longest == kListMaxTiles) in[a] = all;
+            in[a] |= (all & ~in[a]) << 16;                   // behind the tiles on the list the others
         }
+        // (as many entries as the longest list of these units has)
+        auto next = [&](int a) -> unsigned {
+            const unsigned e = (unsigned)(__ffs(in[a]) - 1) & 15u;
+            in[a] &= in[a] - 1u;
+            return e;
+        };
+        for (int i = 0; i < kListHead && __builtin_amdgcn_ballot_w64(i < longest) != 0ull; ++i)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) head[a] |= next(a) << (4 * i);
+        const bool any_more = __builtin_amdgcn_ballot_w64(longest > kListHead) != 0ull;
+        if (any_more)
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int a = 0; a < 4; ++a) more[a] |= next(a) << (4 * i);
         const int u = blk * 32 + n;
         if (u >= u0 && u < u1) {
             uint4 *out = reinterpret_cast<uint4 *>(lists + (int64_t)u * kListWords) + hl;
             out[0] = make_uint4(head[0], head[1], head[2], head[3]);
-            out[2] = make_uint4(more[0], more[1], more[2], more[3]);
+            if (any_more) out[2] = make_uint4(more[0], more[1], more[2], more[3]);
         }
     }
 }
@@ -1458,16 +1469,6 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
                 rowpos_s[e] = rowpos[e];
                 rowidx_s[e] = rowidx[e];
             }
-            // the tile of padding rows, as sweep_init_kernel makes them
-            unsigned ph, pm, pl;
-            split3(kPadNorm, ph, pm, pl);
-            constexpr int NSL = tile_slots_of(DP) * 64;
-            if (tid < NSL) {
-                uint4 v = make_uint4(0u, 0u, 0u, 0u);
-                if (tid >= NSL - 64) v = tid < NSL - 32 ? make_uint4(ph | (pm << 16), pl, 0u, 0u) : make_uint4(0x3f803f80u, 0x3f80u, 0u, 0u);
-                opA_s[g.n_tiles * NSL + tid] = v;
-            }
-            static_assert(NSL <= TH, "one thread per operand slot of a tile");
         }
         if (tid == 0) *next_slab = WV;
         if (bad != 0) return;

@@ -202,3 +202,11 @@ def test_ordered_sweep_turns_down_bad_data(rls):
     X = torch.as_tensor(make("clusters", 90011, 16, 4)).cuda()
     X[80000, 3] = float("inf")
     assert int(rls.kmeans_sweep(X, 1, 64, 2, seed=1, check_status=False).status.item()) & rls.RLS_STATUS_NONFINITE
+
+
+@pytest.mark.parametrize("kind,N,d,k_min,k_max", [("noise", 120017, 4, 20, 64), ("noise", 150001, 16, 25, 64), ("clusters", 200001, 2, 33, 64),
+                                                  ("noise", 60001, 30, 40, 90)])
+def test_lists_of_seven_and_more_tiles(rls, kind, N, d, k_min, k_max):
+    """Units that meet up to all sixteen tiles of a group: entries of a list's second word, and the sixteenth."""
+    X = torch.as_tensor(make(kind, N, d, 21)).cuda()
+    assert equal(rls.kmeans_sweep(X, k_min, k_max, 4, seed=6), as_they_come(rls, X, k_min, k_max, 4, seed=6))
