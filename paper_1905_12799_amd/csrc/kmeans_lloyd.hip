@@ -61,10 +61,6 @@ __device__ inline unsigned list_entry(unsigned head, unsigned more, int e) { ret
 constexpr int kListMinTiles = 3;              // groups of fewer tiles meet them all: there is little to leave out
 constexpr int kListMaxTiles = 16;             // groups of an ordered sweep have no more
 
-// Moved pairs of the rounds that run on the prepared copy: every wave keeps a ring of records in global memory
-// (point within the chunk, accumulator row of the new label | row of the old label) and works it off 64 records at a time.
-constexpr int kLogCap = 512;                  // records per wave (a slab adds at most 4 x 64; 63 may be left over)
-
 // ---- LDS carve of lloyd_step_kernel (bytes), shared by the planner and the kernel ------------
 struct Carve {
     int opA, cs, sums, cnts, rowpos, rowidx, misc, total;
@@ -99,7 +95,7 @@ struct StepArgs {
     const int32_t *status;   // [batch]
     char *ws;                // workspace base
     int64_t ws_bs;           // bytes per batch element
-    int64_t off_colinfo, off_opA, off_cnmax, off_psum, off_pcnt, off_pj, off_losum, off_prev, off_xp, off_log;
+    int64_t off_colinfo, off_opA, off_cnmax, off_psum, off_pcnt, off_pj, off_losum, off_prev, off_xp;
     int64_t off_xs, off_centres, off_radius, off_rowpos, off_rowidx, off_lists;      // (ordered copy)
     int32_t first_round;     // 1: no point has a label yet (every pair enters a cluster, nothing leaves one)
     int32_t batch;           // spaces swept by the launch
@@ -126,7 +122,6 @@ struct WaveCtx {
     const unsigned short *rowpos; // LDS: place of each of the group's centroids among its rows (ordered copy; else places are indices)
     const unsigned char *rowidx;  // LDS: the centroid of its run that has a place
     const unsigned *lists;        // global: the tile lists of the group's units, or null
-    unsigned long long *log;      // global: this wave's ring of moved-pair records [kLogCap]
     int64_t ldx, N;
     int d, k0, n_runs, n_tiles, grow0;
     unsigned char *prev;          // global: labels of the last round for the group's run slots, [point][8 / S]
@@ -333,8 +328,12 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
     double jown[ST];                                 // loss sums of the runs this lane owns
 #pragma unroll
     for (int st = 0; st < ST; ++st) jown[st] = 0.0;
-    // ---- the log of moved pairs (PRE): records [log_head, log_tail) of the ring are waiting
-    int log_head = 0, log_tail = 0;                  // wave-uniform
+    // ---- moved pairs (PRE).  A pair's record names the point within the chunk and the two accumulator rows (within the group)
+    // outright: point | row of the new label << 17, and the row of the old one (FIRST: 0xffff for a point that comes from nowhere).
+    // A wave gathers them one per lane, in registers, and works them off 64 at a time.  (A ring in global memory, as before, drained
+    // the wave's stores and waited for them to come back before the rows could be asked for: RING_FIGURES)
+    unsigned rec_lo = 0u, rec_hi = 0u;
+    int rec_n = 0;                                   // lanes 0 .. rec_n - 1 hold one
     auto log_flush = [&](int nrec) {
         // Works off `nrec` <= 64 records: a few lanes per record, eight features each (four at d_pad = 8) - the row is
         // read (16 bytes per load where rows can be read that way), put on the fixed-point grid and moved from the old
@@ -343,13 +342,6 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         // worked out by 4 (2, 2) lanes instead of one per feature, and a flush is 4 (2, 2) steps of 16 (32, 32) records.
         constexpr int FPL = DP >= 16 ? 8 : 4;   // features per lane
         constexpr int LPR = DP / FPL, RPS = 64 / LPR, STEPS = 64 / RPS, BATCH = STEPS < 4 ? STEPS : 4;   // steps whose rows are in flight together
-        // The records were written by other lanes of this wave: their stores must have been issued to the memory
-        // system before the reads.  Both go through this compute unit's own first-level cache, so workgroup scope is
-        // enough (a wider scope would write back the second-level cache, which costs more than the whole flush).
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        unsigned long long rec = 0ull;
-        if (lane < nrec) rec = __hip_atomic_load(&c.log[(unsigned)(log_head + lane) & (kLogCap - 1)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         // (made opaque: what follows from the lane is worked out here, not kept in registers through the tile loop)
         int ln = lane;
         asm volatile("" : "+v"(ln));
@@ -362,7 +354,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         // member counts: the lane that holds a record moves its one member, once per flush
         if (lane < nrec) {
             int *const ccol = c.cnts + (ln & (c.copies - 1)) * c.real_rows;
-            const int nrow = (int)(((unsigned)rec >> 17) & 0xfffu), orow = (int)((unsigned)(rec >> 32) & 0xffffu);
+            const int nrow = (int)((rec_lo >> 17) & 0xfffu), orow = (int)rec_hi;
             atomicAdd(ccol + nrow, 1);
             if (!FIRST || orow != 0xffff) atomicAdd(ccol + orow, -1);
         }
@@ -391,8 +383,8 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
 #pragma unroll
                 for (int u = 0; u < BATCH; ++u) {
                     const int src = (s0 + u) * RPS + g;
-                    lo[u] = (unsigned)__shfl((int)(unsigned)rec, src, 64);
-                    hi[u] = (unsigned)__shfl((int)(unsigned)(rec >> 32), src, 64);
+                    lo[u] = (unsigned)__shfl((int)rec_lo, src, 64);
+                    hi[u] = (unsigned)__shfl((int)rec_hi, src, 64);
                     const bool ok = src < nrec;
                     const float *const row = xcol + (int64_t)(lo[u] & 0x1ffffu) * ldx;
 #pragma unroll
@@ -429,7 +421,6 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                     }
                 }
             }
-            log_head += nrec;
             return;
         }
         // some column has bits below its grid
@@ -439,8 +430,8 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
 #pragma unroll
             for (int u = 0; u < BATCH; ++u) {
                 const int src = (s0 + u) * RPS + g;
-                lo[u] = (unsigned)__shfl((int)(unsigned)rec, src, 64);
-                hi[u] = (unsigned)__shfl((int)(unsigned)(rec >> 32), src, 64);
+                lo[u] = (unsigned)__shfl((int)rec_lo, src, 64);
+                hi[u] = (unsigned)__shfl((int)rec_hi, src, 64);
                 const bool ok = src < nrec;
                 const float *const row = xcol + (int64_t)(lo[u] & 0x1ffffu) * ldx;
                 if (VEC) {
@@ -480,7 +471,23 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 }
             }
         }
-        log_head += nrec;
+    };
+    // puts the records of the lanes in `bal` behind those that wait; 64 of them are worked off
+    auto gather = [&](bool has, unsigned long long bal, unsigned lo, unsigned hi) {
+        const int n_new = (int)__popcll(bal);
+        const int rank = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+        // (the lanes without a record take the places that are left: every lane sends to another one)
+        const int to = (rec_n + (has ? rank : n_new + lane - rank)) & 63;
+        const unsigned new_lo = (unsigned)__builtin_amdgcn_ds_permute(4 * to, (int)lo), new_hi = (unsigned)__builtin_amdgcn_ds_permute(4 * to, (int)hi);
+        rec_lo = lane < rec_n ? rec_lo : new_lo;
+        rec_hi = lane < rec_n ? rec_hi : new_hi;
+        rec_n += n_new;
+        if (rec_n >= 64) {
+            log_flush(64);
+            rec_n -= 64;
+            rec_lo = new_lo;                         // (what came round to the first lanes)
+            rec_hi = new_hi;
+        }
     };
     // the words of this lane's slots 4 hl .. 4 hl + 3, from lanes that feed them
     auto slot_words = [&](unsigned w, unsigned (&out)[4]) {
@@ -988,9 +995,10 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
 
         auto new_of = [&](int pb, int st) -> int { return (int)((neww[pb] >> (8 * st)) & 0xffu); };
         if constexpr (PRE) {
-            // Exact sums, later: the moved pairs go into this wave's log; 64 records at a time are worked off below.
-            static_assert(64 * NBST + 63 <= kLogCap, "a slab's records and what an earlier flush left over must fit the ring");
-            int from[FIRST ? NB : 1][FIRST ? ST : 1];           // FIRST: the row a point comes from, or 0xffff
+            // Exact sums, later: the moved pairs are gathered, and worked off 64 at a time.
+            unsigned fromw[NB];                                 // the labels before: where the point comes from, 0xff: from nowhere
+#pragma unroll
+            for (int pb = 0; pb < NB; ++pb) fromw[pb] = FIRST ? 0u : oldl[pb];
             if constexpr (FIRST) {
                 // No point has a label yet, so every one enters a cluster of every run - but the centroids of a run are those of
                 // the run before and one more, and most points keep the nearest one they had there.  Only the group's first
@@ -1014,8 +1022,10 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                         const bool fills = any_wide || (hl == 0 && st == 0);
                         const int before = st == 0 ? below : idx[st > 0 ? st - 1 : 0];
                         const bool logs = real && (fills || before != idx[st]);
-                        from[pb][st] = logs && !fills ? (int)c.rowpos[rb + (unsigned)before] : 0xffff;
-                        diffw[pb] |= logs ? 0xffu << (8 * st) : 0u;
+                        const unsigned from = fills ? 0xffu : (unsigned)c.rowpos[logs ? rb + (unsigned)before : 0u] - rb;
+                        const unsigned to = (unsigned)new_of(pb, st);
+                        fromw[pb] |= (logs ? from : to) << (8 * st);
+                        diffw[pb] |= logs ? (from ^ to) << (8 * st) : 0u;
                     }
                 }
             }
@@ -1023,31 +1033,27 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
 #pragma unroll
             for (int pb = 0; pb < NB; ++pb) any_diff |= diffw[pb];
             if (__builtin_amdgcn_ballot_w64(any_diff != 0u) != 0ull) {
-#pragma unroll
-            for (int i = 0; i < NBST; ++i) {
-                const bool has = ((diffw[i / ST] >> (8 * (i % ST))) & 0xffu) != 0u;
-                const unsigned long long bal = __builtin_amdgcn_ballot_w64(has);
-                if (bal != 0ull) {
-                    const int pb = i / ST, st = i % ST;
-                    const unsigned pos = (unsigned)log_tail +
-                                         __builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
-                    if (has) {
-                        // the record names the point and the two accumulator rows (within the group) outright, so
-                        // that working it off takes no arithmetic on runs and labels
-                        const unsigned pt = ptl[pb];                                                       // below 2^17
-                        // the run's first row: row0 of this lane's first run, and k0 + rl0 + .. of them per run in between
-                        // (put together here: a row per run would sit in registers through the tile loop)
-                        unsigned step = row_step;
-                        asm volatile("" : "+v"(step));
-                        const unsigned rowbase = row0 + (unsigned)st * step + (unsigned)(st * (st - 1) / 2);
-                        const unsigned lo = pt | ((rowbase + (unsigned)new_of(pb, st)) << 17);         // rows: below 2^12
-                        const unsigned hi = FIRST ? (unsigned)from[FIRST ? pb : 0][FIRST ? st : 0] : rowbase + (unsigned)old_of(pb, st);
-                        c.log[pos & (kLogCap - 1)] = ((unsigned long long)hi << 32) | lo;
+                // (one run slot after the other, not unrolled: working off is a thousand instructions)
+                unsigned moved = diffw[0], now = fromw[0] ^ diffw[0], was = fromw[0], pt = ptl[0];
+                unsigned rowbase = row0, step = row_step;
+#pragma nounroll
+                for (int i = 0; i < NBST; ++i) {
+                    const bool has = (moved & 0xffu) != 0u;
+                    const unsigned long long bal = __builtin_amdgcn_ballot_w64(has);
+                    if (bal != 0ull) {
+                        const unsigned o = was & 0xffu;
+                        gather(has, bal, pt | ((rowbase + (now & 0xffu)) << 17), FIRST && o == 0xffu ? 0xffffu : rowbase + o);   // rows: below 2^12
                     }
-                    log_tail += (int)__popcll(bal);
+                    moved >>= 8;
+                    now >>= 8;
+                    was >>= 8;
+                    rowbase += step;
+                    ++step;
+                    if (NB > 1 && i == ST - 1) {
+                        moved = diffw[NB - 1]; now = fromw[NB - 1] ^ diffw[NB - 1]; was = fromw[NB - 1]; pt = ptl[NB - 1];
+                        rowbase = row0; step = row_step;
+                    }
                 }
-            }
-            while (log_tail - log_head >= 64) log_flush(64);
             }
         }
         if (!FINAL && !PRE) {
@@ -1189,7 +1195,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         nxt = nxt2;
     }
     if constexpr (PRE) {
-        if (log_tail > log_head) log_flush(log_tail - log_head);
+        if (rec_n > 0) log_flush(rec_n);
     }
     if (LOSS) {
         // hand the sums over by run: run r of the group is owned by half-wave r / ST (by the lower one when S = 8)
@@ -1487,7 +1493,6 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
     c.sums = sums; c.cnts = cnts; c.copies = copies; c.real_rows = real_rows; c.mu_s = mu_s; c.shift_s = shift_s; c.pow2hi_s = pow2hi_s; c.wide_s = wide_s; c.cnmax_s = cnmax_s;
     c.scale = *reinterpret_cast<const float *>(wsb + a.off_colinfo + kColScaleOff);
     c.xp = reinterpret_cast<const uint4 *>(wsb + a.off_xp);
-    c.log = reinterpret_cast<unsigned long long *>(wsb + a.off_log) + ((int64_t)(g.wg0 + chunk) * WV + __builtin_amdgcn_readfirstlane(tid >> 6)) * kLogCap;
     c.rowpos = rowpos_s;
     c.rowidx = rowidx_s;
     c.lists = nullptr;
@@ -2584,7 +2589,7 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
     sa.status = a.status; sa.ws = a.ws; sa.ws_bs = L.per_batch;
     sa.off_colinfo = L.colinfo; sa.off_opA = L.opA; sa.off_cnmax = L.cnmax;
     sa.off_psum = L.psum; sa.off_pcnt = L.pcnt; sa.off_pj = L.pj; sa.off_losum = L.losum; sa.off_prev = L.prev;
-    sa.off_xp = L.xp; sa.off_log = L.log;
+    sa.off_xp = L.xp;
     sa.off_xs = L.xs; sa.off_centres = L.centres; sa.off_radius = L.radius; sa.off_rowpos = L.rowpos; sa.off_rowidx = L.rowidx; sa.off_lists = L.lists;
 
     size_t lds = 0;
@@ -2909,14 +2914,6 @@ void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, in
     L->bsum = take((int64_t)L->seed_blocks * 8);
     L->near = take(N);
     L->seedthr = take((int64_t)k_max * 8);
-    // The log, written from the second round on, takes their place, unless the chain is to grow: so what fitted the fixed
-    // workspace of rls_kmeans_sweep_static still fits with the up to 256 workgroups that chunks per group bring to sweeps
-    // of one or few k (12 MiB of log; chunks of at least 4096 points, as before, had 8 at the sizes in question).
-    const int64_t log_bytes = (int64_t)plan.n_wgs * (step_threads_of(plan.dp) / 64) * kLogCap * 8;
-    if (!chain_grows) {
-        L->log = L->colstat_part;
-        off = std::max(off, L->log + align_up(log_bytes, 256));
-    }
     L->colinfo = take(512);
     L->chain = take((int64_t)k_max * 8);
     L->xp = take((N + 31) / 32 * prep_block_u4_of(plan.dp) * 16);     // (with the blocks above: the same place whatever the range of k)
@@ -2943,7 +2940,6 @@ void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, in
     L->tot = take((int64_t)plan.total_rows * d * 16);
     L->totcnt = take((int64_t)plan.total_rows * d * 8);
     L->prev = take((int64_t)plan.lab_slots * align_up(N, 16));
-    if (chain_grows) L->log = take(log_bytes);
     L->per_batch = off;
     L->total = off * batch;
 }

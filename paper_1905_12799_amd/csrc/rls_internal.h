@@ -105,8 +105,6 @@ struct SweepLayout {
     int64_t tot;            // int64 [total_rows][d][2] running 128-bit fixed-point sums (hi, lo)
     int64_t totcnt;         // int64 [total_rows][d] running member counts (one copy per feature)
     int64_t prev;           // uint8 per group [N rounded up to 16][8 / S]: label of every point in the last round (0xff: none yet)
-    int64_t log;            // uint64 [chunks of all groups][waves][512] rings of moved-pair records, one per wave of the step kernel
-                            // (in the place of colstat_part, mind, bsum, near and seedthr, unless the chain is to grow between sweeps)
     int64_t xp;             // prepared copy of the points: per block of 32, the matrix operands and squared norms (kmeans_lloyd.hip)
     // with an order of the points (plan.ordered); xp is in that order, and so are the labels of the last round
     int64_t keyinfo;        // KeyInfo
