@@ -331,7 +331,8 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
     // ---- moved pairs (PRE).  A pair's record names the point within the chunk and the two accumulator rows (within the group)
     // outright: point | row of the new label << 17, and the row of the old one (FIRST: 0xffff for a point that comes from nowhere).
     // A wave gathers them one per lane, in registers, and works them off 64 at a time.  (A ring in global memory, as before, drained
-    // the wave's stores and waited for them to come back before the rows could be asked for: RING_FIGURES)
+    // the wave's stores and waited for them to come back before the rows could be asked for: 8M x 32 8.41 -> 8.29 ms a round,
+    // 64 x (262,144 x 16) 1286 -> 1256 us)
     unsigned rec_lo = 0u, rec_hi = 0u;
     int rec_n = 0;                                   // lanes 0 .. rec_n - 1 hold one
     auto log_flush = [&](int nrec) {

@@ -17,6 +17,8 @@
 // whose computed distance would not have been smaller: D, the block sums and the chain are the same with and without it.
 #include <algorithm>
 #include <atomic>
+#include <mutex>
+#include <type_traits>
 
 #include "rls_internal.h"
 
@@ -379,8 +381,8 @@ __global__ void __launch_bounds__(1024) seed_pick_kernel(SeedList seeds, int b0,
 // exchange two messages through memory - every workgroup the sum of its D, then the workgroup that holds the drawn point
 // that point's row and index.  What bounds a step is the latency of these two exchanges and of the scans between them:
 // two launches per centre (an update of 7 to 12 us, a draw of 9 to 11 us and the ramp of each) took 17 to 23 us.
-// (One launch: 2.5 us per centre at 2000 x 8 - where a single workgroup skips the scan over the others, with it 2.7 -, 5.0 at
-// 65,536 x 16, 8.5 at 1M x 16, against 13.6, 16.6 and 22.4.)
+// (One launch: 1.8 us per centre at 2000 x 8 - a single workgroup skips the scan over the others -, 4.8 at 65,536 x 16, 8.1 at
+// 1M x 16, against 13.6, 16.6 and 22.4.)
 //
 // A message is a word of 8 bytes that carries its own validity - the area is filled with kSlotEmpty before the launch,
 // every word is written once, and a row travels as words of (step, value) - so no flags, fences or counters are needed:
@@ -468,11 +470,16 @@ __device__ inline double lane_value(double v, int lane)
 {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
-__device__ inline double lane_before(double v)      // the value of the lane below; 0 in lane 0
+// one after the other
+template <int P>
+__device__ inline double sum_of(const double (&v)[P])
 {
-    const double o = __shfl_up(v, 1, 64);
-    return (threadIdx.x & 63) ? o : 0.0;
+    double s = v[0];
+#pragma unroll
+    for (int i = 1; i < P; ++i) s = __dadd_rn(s, v[i]);
+    return s;
 }
+__device__ inline double lane_before(double v) { return dpp_or_zero<0x138, 0xf>(v); }     // the value of the lane below; 0 in lane 0
 
 // Of E values per lane, numbered lane * E + e, with exclusive prefixes that start at `before` (`incl`: inclusive prefix
 // sums over the lanes): the first whose inclusive
@@ -520,6 +527,11 @@ template <class Look>
 __device__ inline bool wait_for(long long limit, const unsigned long long *quit, Look look)
 {
     constexpr long long kUndisturbed = 2000;       // 20 us: no exchange lasts that long when all workgroups are running
+    // (most waits are over within a few looks, and reading the clock takes as long as one of them)
+    if (limit > kUndisturbed) {
+        for (int i = 0; i < 8; ++i)
+            if (look()) return true;
+    }
     const long long t0 = wall_clock64();
     for (;;) {
         const long long waited = wall_clock64() - t0;
@@ -539,17 +551,27 @@ __device__ inline int64_t first_not_chosen(const int64_t *chosen, int j)
 }
 
 // DP: padded features (a padded feature is zero on both sides and adds +0), P: points per thread.
+// Where they fit, the rows are in LDS as well, as are the distances, and wave 0 alone draws: it finds the point
+// among the 64 of an entry, reads its row and hands it out, with one barrier before and one behind.  Beyond that the wave that
+// holds the entry does (and a third barrier, of the drawing workgroup only).  (As it was, 64 points of a
+// wave's per scan, rows converted to fp64 in every step and three barriers: 2000 x 8 2.2 -> 1.8 us per centre, 65,536 x 16 5.35 -> 4.8,
+// 65,536 x 32 6.3 -> 5.4, 1M x 16 8.7 -> 8.1.)
+__host__ __device__ constexpr bool chain_rows_in_lds(int dp, int p) { return 1024 * p * (8 + 4 * dp) <= 152 * 1024; }
+__host__ __device__ constexpr int chain_lds_bytes(int dp, int p) { return chain_rows_in_lds(dp, p) ? 1024 * p * (8 + 4 * dp) : 0; }
+
 template <int DP, int P>
 __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainArgs a)
 {
-    constexpr int E = P > 4 ? P / 4 : 1;           // sums of 64 points that a lane of wave 0 looks at
-    __shared__ float cs[DP];
-    __shared__ double wsum[64 * E];
+    constexpr bool ROWS = chain_rows_in_lds(DP, P);
+    extern __shared__ __align__(16) unsigned char smem[];
+    double *const D_s = reinterpret_cast<double *>(smem);                       // ROWS: distances [1024 P], then rows [1024 P][DP]
+    float *const rows_s = reinterpret_cast<float *>(smem + (ROWS ? 1024 * P * 8 : 0));
+    __shared__ __align__(16) double cs[DP];
+    __shared__ double wsum[64];                     // sums of the 16 waves, then zeros
     __shared__ int64_t chosen[RLS_MAX_K];
-    __shared__ int64_t s_pick;
     __shared__ double s_before, s_r;
-    __shared__ int s_owner, s_entry;
-    __shared__ int s_no_sums, s_no_row;             // a wait of this step ran out (a word each: set only before the barrier it is read behind)
+    __shared__ int s_entry;                         // not ROWS: the wave to draw from, or -1 where another workgroup draws
+    __shared__ int s_quit;                          // a wait of this workgroup ran out
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int w = blockIdx.x, G = a.groups, b = blockIdx.y, d = a.d;
     const float *Xb = a.X + (int64_t)b * a.x_bs;
@@ -560,54 +582,55 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
     const int j0 = a.j_begin > 1 ? a.j_begin : 1;
     const bool own_limit = w >= a.wait_from && a.wait_ticks >= 0;
 
-    // this workgroup's points are base .. base + 1024 P - 1, point 1024 i + tid of them belongs to thread tid
+    // this workgroup's points are base .. base + 1024 P - 1, P in a row belong to a thread: one scan per wave
     const int64_t base = (int64_t)w * (1024 * P);
-    float x[P][DP];
+    using Coord = std::conditional_t<ROWS, double, float>;      // (in fp64 where the registers hold it)
+    Coord x[P][DP];
     double D[P];                                    // 0 for a point past the end: it is never drawn
 #pragma unroll
     for (int i = 0; i < P; ++i) {
-        const int64_t p = base + 1024 * i + tid;
+        const int64_t p = base + P * tid + i;
         const float *row = Xb + min(p, a.N - 1) * a.ldx;
 #pragma unroll
-        for (int l = 0; l < DP; ++l) x[i][l] = l < d ? row[min(l, d - 1)] : 0.0f;
+        for (int l = 0; l < DP; ++l) {
+            const float v = l < d ? row[min(l, d - 1)] : 0.0f;
+            x[i][l] = v;
+            if constexpr (ROWS) rows_s[(P * tid + i) * DP + l] = v;
+        }
         D[i] = a.j_begin > 1 && p < a.N ? mind[p] : 0.0;
     }
     if (tid < j0) chosen[tid] = chain[tid];
-    if (tid < 64 * E) wsum[tid] = 0.0;
-    if (tid == 0) {
-        s_no_sums = peek(ex + kExQuit) != 0ull;     // started when another had already given up
-        s_no_row = 0;
-    }
+    if (tid < 64) wsum[tid] = 0.0;
+    if (tid == 0) s_quit = peek(ex + kExQuit) != 0ull;          // started when another had already given up
     __syncthreads();
-    if (s_no_sums) return;
-    if (tid < DP) cs[tid] = tid < d ? Xb[chosen[j0 - 1] * a.ldx + tid] : 0.0f;
+    if (s_quit) return;
+    if (tid < DP) cs[tid] = tid < d ? (double)Xb[chosen[j0 - 1] * a.ldx + tid] : 0.0;
     __syncthreads();
 
     for (int j = j0; j < a.k_max; ++j) {
-        const double u01 = uniform01(seed, (uint64_t)j);
         // ---- the newest centre
 #pragma unroll
         for (int i = 0; i < P; ++i) {
             double acc = 0.0;
 #pragma unroll
             for (int l = 0; l < DP; ++l) {
-                const double diff = __dsub_rn((double)x[i][l], (double)cs[l]);
+                const double diff = __dsub_rn((double)x[i][l], cs[l]);
                 acc = __dadd_rn(acc, __dmul_rn(diff, diff));
             }
-            if (base + 1024 * i + tid < a.N && (j == 1 || acc < D[i])) D[i] = acc;
-            const double incl = wave_scan_dpp(D[i]);
-            if (lane == 63) wsum[i * 16 + wave] = incl;
+            if (base + P * tid + i < a.N && (j == 1 || acc < D[i])) D[i] = acc;
+            if constexpr (ROWS) D_s[P * tid + i] = D[i];
+        }
+        {
+            const double incl = wave_scan_dpp(sum_of(D));
+            if (lane == 63) wsum[wave] = incl;
         }
         __syncthreads();
         // ---- total, draw, and whose point it is: wave 0 of every workgroup finds the same answer
         if (wave == 0) {
-            double own[E];
-            double loc = 0.0;
-#pragma unroll
-            for (int e = 0; e < E; ++e) { own[e] = wsum[lane * E + e]; loc = __dadd_rn(loc, own[e]); }
-            const double own_incl = wave_scan_dpp(loc), total = lane_value(own_incl, 63);
+            const double u01 = uniform01(seed, (uint64_t)j);
+            const double own[1] = {wsum[lane]}, own_incl = wave_scan_dpp(own[0]), total = lane_value(own_incl, 63);
             double v[4] = {0.0, 0.0, 0.0, 0.0};
-            bool lost = false;
+            bool there = true;
             if (G > 1) {
                 unsigned long long *slot = ex + j * kChainWgs;
                 if (lane == 0) {
@@ -615,7 +638,7 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
                     if (bits == kSlotEmpty) bits = 0x7ff8000000000000ull;
                     post(slot + w, bits);
                 }
-                lost = !wait_for(own_limit ? a.wait_ticks : (j == j0 ? kArriveTicks : kWaitTicks), ex + kExQuit, [&] {
+                there = wait_for(own_limit ? a.wait_ticks : (j == j0 ? kArriveTicks : kWaitTicks), ex + kExQuit, [&] {
                     bool miss = false;
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
@@ -628,99 +651,106 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
                     return __ballot(miss) == 0ull;
                 });
             }
+            int owner = -1, entry = 0;              // (owner -1: every point coincides with a chosen centre)
+            double before = 0.0, r = 0.0;
             if (G == 1) {
                 // nothing to exchange: the same draw without the scan over the workgroups
-                int owner = -1, entry = 0;
-                double before = 0.0, r = 0.0;
-                if (total > 0.0) {                  // else: every point coincides with a chosen centre
+                if (total > 0.0) {
                     r = __dmul_rn(u01, total);
                     owner = w;
-                    entry = max(wave_locate<E>(own, own_incl, total > r ? 0.0 : r, r, before), 0);
+                    entry = max(wave_locate<1>(own, own_incl, total > r ? 0.0 : r, r, before), 0);
                 }
-                if (lane == 0) { s_owner = owner; s_entry = entry; s_before = before; s_r = r; }
-            } else if (lost) {
-                if (lane == 0) {
-                    s_no_sums = 1;
-                    post(ex + kExQuit, 1ull);
-                }
-            } else {
+            } else if (there) {
                 const double incl = wave_scan_dpp(__dadd_rn(__dadd_rn(__dadd_rn(v[0], v[1]), v[2]), v[3])), S = lane_value(incl, 63);
-                int owner = -1, entry = 0;
-                double before = 0.0, r = 0.0;
-                if (S > 0.0) {                      // else: every point coincides with a chosen centre
+                if (S > 0.0) {
                     r = __dmul_rn(u01, S);
                     owner = wave_locate<4>(v, incl, 0.0, r, before);
                     if (owner == w) {
                         double at;
-                        entry = max(wave_locate<E>(own, own_incl, before, r, at), 0);
+                        entry = max(wave_locate<1>(own, own_incl, before, r, at), 0);
                         before = at;
                     }
                 }
-                if (lane == 0) { s_owner = owner; s_entry = entry; s_before = before; s_r = r; }
             }
-        }
-        __syncthreads();
-        if (s_no_sums) return;                      // same for the whole workgroup
-        const int owner = s_owner;
-        // ---- the drawn point: its workgroup hands out row and index
-        if (owner < 0) {
-            if (tid == 0) s_pick = first_not_chosen(chosen, j);
-            __syncthreads();
-            if (tid < DP) cs[tid] = tid < d ? Xb[s_pick * a.ldx + tid] : 0.0f;
-        } else if (owner == w) {
-            if (wave == (s_entry & 15)) {
-                const int ii = s_entry >> 4;
-                double v[1] = {D[0]};
-#pragma unroll
-                for (int i = 1; i < P; ++i)
-                    if (ii == i) v[0] = D[i];
-                double at;
-                const int ln = __builtin_amdgcn_readfirstlane(max(wave_locate<1>(v, wave_scan_dpp(v[0]), s_before, s_r, at), 0));
-                float mine = 0.0f;
-#pragma unroll
-                for (int l = 0; l < DP; ++l) {
-                    float val = x[0][l];
-#pragma unroll
-                    for (int i = 1; i < P; ++i)
-                        if (ii == i) val = x[i][l];
-                    const int got = __builtin_amdgcn_readlane(__float_as_int(val), ln);
-                    if (lane == l) mine = __int_as_float(got);
-                }
-                const int64_t pick = min(base + 1024 * ii + 64 * wave + ln, a.N - 1);
-                if (G > 1 && (lane < DP || lane == RLS_MAX_D)) {
-                    const unsigned val = lane < DP ? __float_as_uint(mine) : (unsigned)pick;
-                    post(ex + kExRows + j * kRowWords + lane, ((unsigned long long)j << 32) | val);
-                }
-                if (lane < DP) cs[lane] = mine;
-                if (lane == 0) s_pick = pick;
-            }
-        } else if (wave == 0) {
-            const bool mine = lane < DP || lane == RLS_MAX_D;
-            unsigned long long bits = 0ull;
-            const bool there = wait_for(own_limit ? a.wait_ticks : kWaitTicks, ex + kExQuit, [&] {
-                if (mine) bits = peek(ex + kExRows + j * kRowWords + lane);
-                return __ballot(mine && bits == kSlotEmpty) == 0ull;
-            });
+            // ---- the drawn point: its workgroup hands out row and index
+            float mine = 0.0f;
+            int64_t pick = 0;
+            bool have_row = true;
             if (!there) {
-                if (lane == 0) {
-                    s_no_row = 1;
-                    post(ex + kExQuit, 1ull);
+                have_row = false;
+            } else if (owner < 0) {
+                pick = first_not_chosen(chosen, j);
+                if (lane < DP) mine = lane < d ? Xb[pick * a.ldx + lane] : 0.0f;
+            } else if (owner == w) {
+                if constexpr (ROWS) {
+                    double dv[P], at;
+#pragma unroll
+                    for (int i = 0; i < P; ++i) dv[i] = D_s[P * (64 * entry + lane) + i];
+                    const int pt = 64 * P * entry + max(wave_locate<P>(dv, wave_scan_dpp(sum_of(dv)), before, r, at), 0);
+                    if (lane < DP) mine = rows_s[pt * DP + lane];
+                    pick = min(base + pt, a.N - 1);
+                    if (G > 1 && (lane < DP || lane == RLS_MAX_D))
+                        post(ex + kExRows + j * kRowWords + lane, ((unsigned long long)j << 32) | (lane < DP ? __float_as_uint(mine) : (unsigned)pick));
+                } else {
+                    have_row = false;               // (below)
+                    if (lane == 0) { s_before = before; s_r = r; }
                 }
             } else {
-                if (lane < DP) cs[lane] = __uint_as_float((unsigned)bits);
-                if (lane == RLS_MAX_D) s_pick = (int64_t)(unsigned)bits;
+                const bool reads = lane < DP || lane == RLS_MAX_D;
+                unsigned long long bits = 0ull;
+                there = wait_for(own_limit ? a.wait_ticks : kWaitTicks, ex + kExQuit, [&] {
+                    if (reads) bits = peek(ex + kExRows + j * kRowWords + lane);
+                    return __ballot(reads && bits == kSlotEmpty) == 0ull;
+                });
+                mine = __uint_as_float((unsigned)bits);
+                pick = (int64_t)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)bits, RLS_MAX_D);
+            }
+            if (have_row && lane < DP) cs[lane] = (double)mine;
+            if (lane == 0) {
+                chosen[j] = pick;
+                if (w == 0 && have_row) chain[j] = pick;
+                if constexpr (!ROWS) s_entry = there && owner == w ? entry : -1;
+                if (!there) {
+                    s_quit = 1;
+                    post(ex + kExQuit, 1ull);
+                }
             }
         }
         __syncthreads();
-        if (s_no_row) return;
-        if (tid == 0) {
-            chosen[j] = s_pick;
-            if (w == 0) chain[j] = s_pick;
+        if (s_quit) return;                         // same for the whole workgroup
+        if constexpr (!ROWS) {
+            const int entry = s_entry;
+            if (entry >= 0) {
+                if (wave == entry) {
+                    double at;
+                    const int pt = __builtin_amdgcn_readfirstlane(max(wave_locate<P>(D, wave_scan_dpp(sum_of(D)), s_before, s_r, at), 0));
+                    const int ln = pt / P, ii = pt % P;
+                    float mine = 0.0f;
+#pragma unroll
+                    for (int l = 0; l < DP; ++l) {
+                        float val = x[0][l];
+#pragma unroll
+                        for (int i = 1; i < P; ++i)
+                            if (ii == i) val = x[i][l];
+                        const int got = __builtin_amdgcn_readlane(__float_as_int(val), ln);
+                        if (lane == l) mine = __int_as_float(got);
+                    }
+                    const int64_t pick = min(base + 64 * P * wave + pt, a.N - 1);
+                    if (G > 1 && (lane < DP || lane == RLS_MAX_D))
+                        post(ex + kExRows + j * kRowWords + lane, ((unsigned long long)j << 32) | (lane < DP ? __float_as_uint(mine) : (unsigned)pick));
+                    if (lane < DP) cs[lane] = (double)mine;
+                    if (lane == 0) {
+                        chosen[j] = pick;
+                        if (w == 0) chain[j] = pick;
+                    }
+                }
+                __syncthreads();
+            }
         }
     }
 #pragma unroll
     for (int i = 0; i < P; ++i) {
-        const int64_t p = base + 1024 * i + tid;
+        const int64_t p = base + P * tid + i;
         if (p < a.N) mind[p] = D[i];
     }
     if (tid == 0) ex[kExDone + w] = 1ull;
@@ -741,9 +771,8 @@ constexpr long long kRestTicks = 1000000000;       // 10 s.  Only another call t
 template <int DP>
 __global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, ChainArgs a, int P)
 {
-    constexpr int E = 2;                           // sums of 64 points per lane of wave 0: P <= 8
     __shared__ float cs[DP];
-    __shared__ double wsum[64 * E];
+    __shared__ double wsum[64];                    // sums of the 16 waves, then zeros
     __shared__ int64_t chosen[RLS_MAX_K];
     __shared__ int64_t s_pick;
     __shared__ double s_before, s_r;
@@ -757,7 +786,7 @@ __global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, C
     int64_t *chain = a.chain + (int64_t)b * a.chain_bs;
     const int j0 = a.j_begin > 1 ? a.j_begin : 1;
     if (tid < j0) chosen[tid] = chain[tid];
-    if (tid < 64 * E) wsum[tid] = 0.0;
+    if (tid < 64) wsum[tid] = 0.0;
     for (;;) {
         if (tid == 0) s_ticket = (int)__hip_atomic_fetch_add(ex + kExTicket, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
@@ -779,8 +808,9 @@ __global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, C
             __syncthreads();
             if (tid < DP) cs[tid] = tid < d ? Xb[chosen[m] * a.ldx + tid] : 0.0f;
             __syncthreads();
+            double loc = 0.0;
             for (int i = 0; i < P; ++i) {
-                const int64_t p = base + 1024 * i + tid;
+                const int64_t p = base + P * tid + i;
                 double cur = 0.0;
                 if (p < a.N) {
                     const float *row = Xb + p * a.ldx;
@@ -800,14 +830,15 @@ __global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, C
                     }
                     D[p] = cur;
                 }
-                const double incl = wave_scan_dpp(cur);
-                if (lane == 63) wsum[i * 16 + wave] = incl;
+                loc = i == 0 ? cur : __dadd_rn(loc, cur);
             }
+            const double incl = wave_scan_dpp(loc);
+            if (lane == 63) wsum[wave] = incl;
         }
         __builtin_amdgcn_s_waitcnt(0x0f70);        // vmcnt(0): this wave's distances have left the compute unit ...
         __syncthreads();
         if (wave == 0) {
-            const double total = lane_value(wave_scan_dpp(__dadd_rn(wsum[lane * E], wsum[lane * E + 1])), 63);
+            const double total = lane_value(wave_scan_dpp(wsum[lane]), 63);
             if (lane == 0) {
                 post(ex + kExSums + blk, (unsigned long long)__double_as_longlong(total));
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");     // ... and are there for all, with the sum, before the block counts as done
@@ -837,27 +868,29 @@ __global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, C
             if (tid == 0) s_pick = first_not_chosen(chosen, j);
         } else {
             const int64_t from = (int64_t)s_owner * 1024 * P;
+            double loc = 0.0;
             for (int i = 0; i < P; ++i) {
-                const int64_t p = from + 1024 * i + tid;
-                const double incl = wave_scan_dpp(p < a.N ? D[p] : 0.0);
-                if (lane == 63) wsum[i * 16 + wave] = incl;
+                const int64_t p = from + P * tid + i;
+                const double cur = p < a.N ? D[p] : 0.0;
+                loc = i == 0 ? cur : __dadd_rn(loc, cur);
             }
+            const double incl = wave_scan_dpp(loc);
+            if (lane == 63) wsum[wave] = incl;
             __syncthreads();
             if (wave == 0) {
-                double own[E];
-#pragma unroll
-                for (int e = 0; e < E; ++e) own[e] = wsum[lane * E + e];
+                const double own[1] = {wsum[lane]};
                 double at;
-                const int entry = max(wave_locate<E>(own, wave_scan_dpp(__dadd_rn(own[0], own[1])), s_before, s_r, at), 0);
+                const int entry = max(wave_locate<1>(own, wave_scan_dpp(own[0]), s_before, s_r, at), 0);
                 if (lane == 0) { s_entry = entry; s_before = at; }
             }
             __syncthreads();
-            if (wave == (s_entry & 15)) {
-                const int64_t first = from + 1024 * (s_entry >> 4) + 64 * wave;
-                const double v[1] = {first + lane < a.N ? D[first + lane] : 0.0};
-                double at;
-                const int ln = max(wave_locate<1>(v, wave_scan_dpp(v[0]), s_before, s_r, at), 0);
-                if (lane == 0) s_pick = min(first + ln, a.N - 1);
+            if (wave == s_entry) {
+                const int64_t first = from + (int64_t)64 * P * wave;
+                double v[8], at;                   // (P <= 8; what is not there is zero and never drawn)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = i < P && first + P * lane + i < a.N ? D[first + P * lane + i] : 0.0;
+                const int e = max(wave_locate<8>(v, wave_scan_dpp(sum_of(v)), s_before, s_r, at), 0);
+                if (lane == 0) s_pick = min(first + P * (e / 8) + e % 8, a.N - 1);
             }
         }
         __syncthreads();
@@ -914,7 +947,16 @@ static hipError_t launch_chain_in_one(int dp, int p, int spaces, const SeedList 
     hipLaunchKernelGGL(seed_begin_kernel, dim3(16, spaces), dim3(256), 0, s, sl, a);
     const dim3 grid(a.groups, spaces), block(1024);
 #define RLS_SEED_CHAIN(DPV, PV)                                                                                          \
-    case DPV * 16 + PV: hipLaunchKernelGGL((seed_chain_kernel<DPV, PV>), grid, block, 0, s, sl, a); break
+    case DPV * 16 + PV: {                                                                                                \
+        static std::once_flag once;                                                                                      \
+        static hipError_t attr = hipSuccess;                                                                             \
+        std::call_once(once, [] {                                                                                        \
+            attr = hipFuncSetAttribute(reinterpret_cast<const void *>(seed_chain_kernel<DPV, PV>),                       \
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, chain_lds_bytes(DPV, PV));            \
+        });                                                                                                              \
+        if (attr != hipSuccess) return attr;                                                                             \
+        hipLaunchKernelGGL((seed_chain_kernel<DPV, PV>), grid, block, chain_lds_bytes(DPV, PV), s, sl, a);               \
+    } break
     switch (dp * 16 + p) {
     RLS_SEED_CHAIN(8, 1);
     RLS_SEED_CHAIN(8, 2);
