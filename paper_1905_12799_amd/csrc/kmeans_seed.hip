@@ -52,13 +52,17 @@ struct SeedList {
     uint64_t seed[64];
 };
 
+// the first centre: uniform over the points
+__device__ inline int64_t first_centre(uint64_t seed, int64_t N)
+{
+    const int64_t first = (int64_t)(uniform01(seed, 0) * (double)N);
+    return min(first, N - 1);
+}
+
 __global__ void seed_first_kernel(SeedList seeds, int b0, int64_t N, int64_t *chain, int64_t chain_batch_stride)
 {
     const int b = b0 + blockIdx.x;
-    if (threadIdx.x != 0) return;
-    int64_t first = (int64_t)(uniform01(seeds.seed[blockIdx.x], 0) * (double)N);
-    if (first >= N) first = N - 1;
-    chain[(int64_t)b * chain_batch_stride] = first;
+    if (threadIdx.x == 0) chain[(int64_t)b * chain_batch_stride] = first_centre(seeds.seed[blockIdx.x], N);
 }
 
 // inclusive scan / sum over a 1024-thread block in fixed order; `tmp` holds 17 doubles
@@ -439,11 +443,7 @@ __global__ void __launch_bounds__(256) seed_begin_kernel(SeedList seeds, ChainAr
     }
     if (t0 == 0) {
         ex[kExQuit] = ex[kExTicket] = 0ull;
-        if (a.j_begin == 0) {
-            int64_t first = (int64_t)(uniform01(seeds.seed[b], 0) * (double)a.N);
-            if (first >= a.N) first = a.N - 1;
-            chain[0] = first;
-        }
+        if (a.j_begin == 0) chain[0] = first_centre(seeds.seed[b], a.N);
     }
 }
 
@@ -599,9 +599,15 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
         }
         D[i] = a.j_begin > 1 && p < a.N ? mind[p] : 0.0;
     }
-    if (tid < j0) chosen[tid] = chain[tid];
+    // (a single workgroup has no seed_begin_kernel before it: the first centre is its own to draw, and nobody gives up; sweeps of
+    // 100 x 8 45.6 -> 44.0 us, 2000 x 8 153.2 -> 151.3.  Asked by the size of the grid: with a.groups d_pad 32 spilled more scalars, 1.6%)
+    if (gridDim.x == 1 && a.j_begin == 0) {
+        if (tid == 0) chosen[0] = chain[0] = first_centre(seed, a.N);
+    } else if (tid < j0) {
+        chosen[tid] = chain[tid];
+    }
     if (tid < 64) wsum[tid] = 0.0;
-    if (tid == 0) s_quit = peek(ex + kExQuit) != 0ull;          // started when another had already given up
+    if (tid == 0) s_quit = gridDim.x > 1 && peek(ex + kExQuit) != 0ull;     // started when another had already given up
     __syncthreads();
     if (s_quit) return;
     if (tid < DP) cs[tid] = tid < d ? (double)Xb[chosen[j0 - 1] * a.ldx + tid] : 0.0;
@@ -944,7 +950,7 @@ static int chain_points_per_thread(int64_t N, int dp, int spaces, int *groups)
 
 static hipError_t launch_chain_in_one(int dp, int p, int spaces, const SeedList &sl, const ChainArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(seed_begin_kernel, dim3(16, spaces), dim3(256), 0, s, sl, a);
+    if (a.groups > 1) hipLaunchKernelGGL(seed_begin_kernel, dim3(16, spaces), dim3(256), 0, s, sl, a);
     const dim3 grid(a.groups, spaces), block(1024);
 #define RLS_SEED_CHAIN(DPV, PV)                                                                                          \
     case DPV * 16 + PV: {                                                                                                \

@@ -376,6 +376,23 @@ def test_seeding_chain_one_launch(rls, orc, N, d, k_max):
         rls.lib().rls_seed_wait_limit(ctypes.c_int64(-1))
 
 
+@pytest.mark.parametrize("N,d", [(1, 8), (1500, 5), (4096, 8), (4096, 16), (2048, 32)])
+def test_seeding_chain_of_one_workgroup(rls, orc, N, d):
+    """Nothing is prepared for a chain that one workgroup draws: whatever the workspace holds, at once and wave by wave."""
+    rng = np.random.default_rng(N + d)
+    X = rng.integers(0, 7, (N, d)).astype(np.float32)
+    Xd, k_max = dev(X), min(N, 11)
+    ref = orc.kmeanspp_chain(X, k_max, 17)
+    ws = torch.empty(1 << 24, dtype=torch.uint8, device="cuda")
+    for content in (0, 1, 255):
+        ws.fill_(content)
+        np.testing.assert_array_equal(rls.kmeanspp_chain(Xd, k_max, 17, workspace=ws).cpu().numpy(), ref)
+        ws.fill_(content)
+        _, n_done, part = rls.kmeans_sweep_until_knee(Xd, 1, k_max, 3, 0, 1e-9, seed=17, workspace=ws, want_labels=False)
+        assert n_done == k_max
+        np.testing.assert_array_equal(part.centroids_of(k_max).cpu().numpy(), X[ref])
+
+
 def exchange_words(ws, k_max):
     """The words that the workgroups of a chain exchange, at the head of the workspace: the sums of step j are words
     256 j + workgroup, and a word nobody has written is -1."""
