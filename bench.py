@@ -48,14 +48,14 @@ VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4.0   # wave64 vector instructions per secon
 # source they were taken with (step_source_digest); with any other the fields made from them are null.
 COUNTERS = {
     # mean over the 30 rounds of a sweep (first round included, like the launches the events time)
-    "mid": {"source": "90b37b1b7222", "fetch_kib": 8642.2, "write_kib": 11653.6, "fetch_scale": 2.0, "write_scale": 1.0,
-           "valu_insts": 1.056e+07, "mfma_insts": 5.898e+05},
-    "whole_layer": {"source": "90b37b1b7222", "fetch_kib": 316780.3, "write_kib": 50229.5, "fetch_scale": 2.0, "write_scale": 1.0,
-                   "valu_insts": 8.092e+07, "mfma_insts": 2.86e+06},
-    "large": {"source": "90b37b1b7222", "fetch_kib": 7867538.6, "write_kib": 1250376.8, "fetch_scale": 2.0, "write_scale": 1.0,
-             "valu_insts": 2.879e+09, "mfma_insts": 1.869e+08},
-    "batched": {"source": "90b37b1b7222", "fetch_kib": 2564929.1, "write_kib": 341051.8, "fetch_scale": 2.0, "write_scale": 1.0,
-               "valu_insts": 5.367e+08, "mfma_insts": 1.971e+07},
+    "mid": {"source": "0592a683fb35", "fetch_kib": 8232.4, "write_kib": 11007.3, "fetch_scale": 2.0, "write_scale": 1.0,
+           "valu_insts": 1.044e+07, "mfma_insts": 5.898e+05},
+    "whole_layer": {"source": "0592a683fb35", "fetch_kib": 306727.5, "write_kib": 27534.2, "fetch_scale": 2.0, "write_scale": 1.0,
+                   "valu_insts": 6.989e+07, "mfma_insts": 2.858e+06},
+    "large": {"source": "0592a683fb35", "fetch_kib": 7748961.4, "write_kib": 687623.5, "fetch_scale": 2.0, "write_scale": 1.0,
+             "valu_insts": 2.461e+09, "mfma_insts": 1.868e+08},
+    "batched": {"source": "0592a683fb35", "fetch_kib": 2534941.9, "write_kib": 169489.1, "fetch_scale": 2.0, "write_scale": 1.0,
+               "valu_insts": 4.862e+08, "mfma_insts": 1.97e+07},
 }
 
 
