@@ -835,7 +835,11 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 // Where points lie close together their close calls come together as well (on knob data whole blocks of points tie
                 // exactly), and a wave that settles 256 of them one by one holds up its launch.  Many at a time are settled by the
                 // lanes that own them, each its own pair: the exact arithmetic over the centroids that the unit's lists name.
-                constexpr int kMany = 8;                 // (one by one: 100 to 350 instructions each; together: 75 per listed centroid)
+                // One by one they take 100 to 350 instructions each, together 75 per listed centroid, of which there are 4 S n_it: with a
+                // short list eight pairs are enough, with more than kListHead tiles on it 1.5 pairs per slot and tile.  (Eight whatever the
+                // length: 200,003 x 16 integers 0..3, k 1..64, 10 rounds 2.97 ms, 2.46 now; the same of 0..1 3.26 and 3.15.  Long lists
+                // one by one always: 2.46 and 4.02.)
+                const int kMany = n_it <= kListHead ? 8 : 3 * S * n_it / 2;
                 if (lists && __popcll(__builtin_amdgcn_ballot_w64(pend != 0u)) >= kMany) {
                 int half = hl;                           // (opaque: nothing of this is worked out ahead of the branch)
                 asm volatile("" : "+v"(half));
