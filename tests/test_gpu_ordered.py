@@ -79,7 +79,7 @@ def test_ordered_sweep_equals_plain_sweep(rls, kind, N, d, k_min, k_max):
 
 
 @pytest.mark.parametrize("kind,N,d,k_min,k_max", [("clusters", 87999, 11, 9, 64), ("islands", 90001, 8, 1, 64), ("grid", 50003, 19, 10, 90),
-                                                  ("grid", 83017, 16, 8, 64)])
+                                                  ("grid", 95003, 16, 8, 64)])
 def test_ordered_sweep_against_the_oracle(rls, orc, kind, N, d, k_min, k_max):
     X = make(kind, N, d, 5)
     got = rls.kmeans_sweep(torch.as_tensor(X).cuda(), k_min, k_max, 3, seed=9)
