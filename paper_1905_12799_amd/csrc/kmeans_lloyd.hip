@@ -52,11 +52,14 @@ __host__ __device__ constexpr int tile_points_of(int dp) { return dp == 32 ? 256
 // unit, and each of the eight quad slots of a group's tiles, a list names the tiles whose quad in that slot may hold the
 // nearest centroid of one of the unit's points.  16 words per unit and group, four bits per tile: eight of first words (one per
 // slot: entries 0 to 6, and above them the length of the longest of the eight lists, less one), eight of second words (entries 7
-// to 14, read by the few units that have so many).  Sixteen entries are all tiles in their order: entry 15 is then what the length
-// says.  A list that ends before the longest one goes on with tiles that are not on it: their centroids are farther away, and
-// nothing else is wrong with them.
+// to 14, read by the few units that have so many).  A list that ends before the longest one goes on with tiles that are not on it:
+// their centroids are farther away, and nothing else is wrong with them.  A list as long as the group has tiles is all of them in
+// their order (of sixteen, entry 15 is what the length says).  Long ones of that kind need no second words and no way back from
+// steps to tiles, and a long list that would leave out a single tile is made one of them.  (All long lists worked off alike:
+// 1,000,003 x 12 integers 0..8, k 1..64, 10 rounds 6.67 ms, 6.51 now, 6.51 before long lists were followed.)
 __host__ __device__ constexpr int unit_blocks_of(int dp) { return dp == 32 ? 2 : 1; }
 constexpr int kListWords = 16, kListHead = 7;
+constexpr unsigned kAllMore = 0xedcba987u;    // the second word of all tiles in their order
 __device__ inline unsigned list_entry(unsigned head, unsigned more, int e) { return ((e < kListHead || e == 15 ? head : more) >> (4 * (e < kListHead ? e : (e == 15 ? 7 : e - kListHead)))) & 15u; }
 constexpr int kListMinTiles = 3;              // groups of fewer tiles meet them all: there is little to leave out
 constexpr int kListMaxTiles = 16;             // groups of an ordered sweep have no more
@@ -530,13 +533,13 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         unsigned oldl[NB];                // labels in the previous round, one byte per run of this lane
         // the tiles this slab meets: all of them in order, or those of its unit's list - this lane's slot meets its own ones
         const unsigned list = listn;
-        unsigned list_more = list;
+        unsigned list_more = kAllMore;
         unsigned own[4] = {list, list, list, list};    // the first words of this lane's slots 4 hl .. 4 hl + 3, from lanes that feed them
         int n_it = c.n_tiles;
         if constexpr (ORD) {
             if (lists) {
                 n_it = (int)((unsigned)__builtin_amdgcn_readfirstlane((int)list) >> 28) + 1;
-                if (n_it > kListHead) list_more = list_word((unsigned)cur * SLAB, 8u);
+                if (n_it > kListHead && n_it < c.n_tiles) list_more = list_word((unsigned)cur * SLAB, 8u);
                 slot_words(list, own);
                 if constexpr (S < 8) {
                     kbits = key_bits(4 * S * n_it);
@@ -755,6 +758,12 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 for (int pb = 0; pb < NB; ++pb)
 #pragma unroll
                     for (int st = 0; st < ST; ++st) put(m1[pb][st], pick(own, st, m1[pb][st]) >> shift_of(m1[pb][st]));
+            } else if (S < 8 && n_it == c.n_tiles) {
+                // (all tiles in their order: a step is its tile.  Eight slots have four tiles at most, and their keys are still wanted)
+#pragma unroll
+                for (int pb = 0; pb < NB; ++pb)
+#pragma unroll
+                    for (int st = 0; st < ST; ++st) m1[pb][st] &= ~mask;
             } else {
                 unsigned more[4];
                 slot_words(list_more, more);
@@ -1279,12 +1288,13 @@ __device__ __forceinline__ void make_lists(const WaveCtx &c, const uint4 *centre
         int longest = max(max(__popc(in[0]), __popc(in[1])), max(__popc(in[2]), __popc(in[3])));
         longest = max(max(longest, xchg32(longest)), 1);
         const unsigned all = (1u << c.n_tiles) - 1u;
+        if (longest > kListHead && longest == c.n_tiles - 1) longest = c.n_tiles;
         unsigned head[4], more[4];
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
             head[a] = (unsigned)(longest - 1) << 28;
             more[a] = 0u;
-            if (longest == kListMaxTiles) in[a] = all;
+            if (longest == c.n_tiles) in[a] = all;
             in[a] |= (all & ~in[a]) << 16;                   // behind the tiles on the list the others
         }
         // (as many entries as the longest list of these units has)
