@@ -557,7 +557,12 @@ __device__ inline int64_t first_not_chosen(const int64_t *chosen, int j)
 // wave's per scan, rows converted to fp64 in every step and three barriers: 2000 x 8 2.2 -> 1.8 us per centre, 65,536 x 16 5.35 -> 4.8,
 // 65,536 x 32 6.3 -> 5.4, 1M x 16 8.7 -> 8.1.)
 __host__ __device__ constexpr bool chain_rows_in_lds(int dp, int p) { return 1024 * p * (8 + 4 * dp) <= 152 * 1024; }
-__host__ __device__ constexpr int chain_lds_bytes(int dp, int p) { return chain_rows_in_lds(dp, p) ? 1024 * p * (8 + 4 * dp) : 0; }
+// The rows come by way of LDS in either case, a wave's 64 P all at once or, where they do not stay there and take more than 8 KB,
+// one half of the features after the other.  (A lane that reads its own rows asks for a line per row with every instruction, and with
+// a branch around every feature that may not be there each load waited for the one before.  A chain of two centres at
+// 500,009 x 16 44 -> 17 us, at 1,000,003 x 13 52 -> 29, at 262,144 x 32 42 -> 15; of 128 713 -> 683, 942 -> 919, 700 -> 690.)
+__host__ __device__ constexpr int chain_pieces(int dp, int p) { return !chain_rows_in_lds(dp, p) && 64 * p * dp * 4 > 8192 ? 2 : 1; }
+__host__ __device__ constexpr int chain_lds_bytes(int dp, int p) { return chain_rows_in_lds(dp, p) ? 1024 * p * (8 + 4 * dp) : 1024 * p * 4 * dp / chain_pieces(dp, p); }
 
 template <int DP, int P>
 __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainArgs a)
@@ -584,19 +589,53 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
 
     // this workgroup's points are base .. base + 1024 P - 1, P in a row belong to a thread: one scan per wave
     const int64_t base = (int64_t)w * (1024 * P);
+    const bool has_points = base + 64 * P * __builtin_amdgcn_readfirstlane(wave) < a.N;     // (of this wave; the sums of the others stay zero)
     using Coord = std::conditional_t<ROWS, double, float>;      // (in fp64 where the registers hold it)
     Coord x[P][DP];
     double D[P];                                    // 0 for a point past the end: it is never drawn
+    constexpr int W = DP / chain_pieces(DP, P);     // features that are staged at a time
+    // where a quad of a staged row lies: turned from row to row, so that lanes whose rows begin at the same banks read different ones
+    auto row_quad = [](int row, int q) { return row * W + 4 * (q ^ ((row * W / 64) & (W / 4 - 1))); };
+    {
+        float *const area = rows_s + wave * (64 * P) * W;
+        const int64_t first = base + 64 * P * wave;
+        const bool vec = (d & 3) == 0 && (a.ldx & 3) == 0 && (reinterpret_cast<uintptr_t>(Xb) & 15) == 0;
+#pragma unroll
+        for (int f0 = 0; f0 < DP; f0 += W) {
+            if (vec) {
+                constexpr int U = P * W / 4, RU = 256 / W;         // quads per lane, rows per step
+                const int q = lane % (W / 4), r0 = lane / (W / 4), f = f0 + 4 * q;
+                float4 v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const float4 *>(Xb + min(first + r0 + RU * u, a.N - 1) * a.ldx + min(f, d - 4));
+#pragma unroll
+                for (int u = 0; u < U; ++u) *reinterpret_cast<float4 *>(area + row_quad(r0 + RU * u, q)) = f < d ? v[u] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            } else {
+                constexpr int U = P * W, RU = 64 / W;
+                const int l = lane % W, r0 = lane / W, f = f0 + l;
+                float v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[u] = Xb[min(first + r0 + RU * u, a.N - 1) * a.ldx + min(f, d - 1)];
+#pragma unroll
+                for (int u = 0; u < U; ++u) area[row_quad(r0 + RU * u, l >> 2) + (l & 3)] = f < d ? v[u] : 0.0f;
+            }
+            // (what the wave's lanes have put down is read by its lanes alone, and the LDS keeps their order)
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int i = 0; i < P; ++i)
+#pragma unroll
+                for (int q = 0; q < W / 4; ++q) {
+                    const float4 v = *reinterpret_cast<const float4 *>(area + row_quad(P * lane + i, q));
+                    x[i][f0 + 4 * q + 0] = v.x; x[i][f0 + 4 * q + 1] = v.y; x[i][f0 + 4 * q + 2] = v.z; x[i][f0 + 4 * q + 3] = v.w;
+                }
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
 #pragma unroll
     for (int i = 0; i < P; ++i) {
         const int64_t p = base + P * tid + i;
-        const float *row = Xb + min(p, a.N - 1) * a.ldx;
-#pragma unroll
-        for (int l = 0; l < DP; ++l) {
-            const float v = l < d ? row[min(l, d - 1)] : 0.0f;
-            x[i][l] = v;
-            if constexpr (ROWS) rows_s[(P * tid + i) * DP + l] = v;
-        }
         D[i] = a.j_begin > 1 && p < a.N ? mind[p] : 0.0;
     }
     // (a single workgroup has no seed_begin_kernel before it: the first centre is its own to draw, and nobody gives up; sweeps of
@@ -615,18 +654,24 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
 
     for (int j = j0; j < a.k_max; ++j) {
         // ---- the newest centre
+        if (has_points) {
+            double acc[P] = {};
+            constexpr int AT_ONCE = !ROWS && DP == 32 ? 8 : DP;      // features (with all 32 of both points mixed, 27 registers were spilled)
 #pragma unroll
-        for (int i = 0; i < P; ++i) {
-            double acc = 0.0;
+            for (int l0 = 0; l0 < DP; l0 += AT_ONCE) {
+                if constexpr (AT_ONCE < DP) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int l = 0; l < DP; ++l) {
-                const double diff = __dsub_rn((double)x[i][l], cs[l]);
-                acc = __dadd_rn(acc, __dmul_rn(diff, diff));
+                for (int i = 0; i < P; ++i) {
+#pragma unroll
+                    for (int l = l0; l < l0 + AT_ONCE; ++l) {
+                        const double diff = __dsub_rn((double)x[i][l], cs[l]);
+                        acc[i] = __dadd_rn(acc[i], __dmul_rn(diff, diff));
+                    }
+                    if (l0 + AT_ONCE < DP) continue;
+                    if (base + P * tid + i < a.N && (j == 1 || acc[i] < D[i])) D[i] = acc[i];
+                    if constexpr (ROWS) D_s[P * tid + i] = D[i];
+                }
             }
-            if (base + P * tid + i < a.N && (j == 1 || acc < D[i])) D[i] = acc;
-            if constexpr (ROWS) D_s[P * tid + i] = D[i];
-        }
-        {
             const double incl = wave_scan_dpp(sum_of(D));
             if (lane == 63) wsum[wave] = incl;
         }
@@ -693,7 +738,7 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
 #pragma unroll
                     for (int i = 0; i < P; ++i) dv[i] = D_s[P * (64 * entry + lane) + i];
                     const int pt = 64 * P * entry + max(wave_locate<P>(dv, wave_scan_dpp(sum_of(dv)), before, r, at), 0);
-                    if (lane < DP) mine = rows_s[pt * DP + lane];
+                    if (lane < DP) mine = rows_s[row_quad(pt, lane >> 2) + (lane & 3)];
                     pick = min(base + pt, a.N - 1);
                     if (G > 1 && (lane < DP || lane == RLS_MAX_D))
                         post(ex + kExRows + j * kRowWords + lane, ((unsigned long long)j << 32) | (lane < DP ? __float_as_uint(mine) : (unsigned)pick));

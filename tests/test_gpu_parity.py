@@ -393,6 +393,21 @@ def test_seeding_chain_of_one_workgroup(rls, orc, N, d):
         np.testing.assert_array_equal(part.centroids_of(k_max).cpu().numpy(), X[ref])
 
 
+@pytest.mark.parametrize("d,points", [(d, n) for d in (1, 6, 8) for n in (1, 2, 4, 8)] + [(d, n) for d in (12, 13) for n in (1, 2, 4)] +
+                         [(d, n) for d in (19, 28) for n in (1, 2)])
+def test_seeding_chain_stages_every_kind_of_rows(rls, orc, d, points):
+    """Every number of points per thread of the chain in one launch, a last workgroup with a few points: rows that follow each other, rows
+    further apart, rows that can and cannot be read 16 bytes at a time."""
+    N = 5001 if points == 1 else 1024 * (256 * points // 2 + 3) + 5
+    rng = np.random.default_rng(N + d)
+    X = (rng.integers(0, 9, (N, d)) + rng.integers(0, 2, (N, 1)) * 0.25).astype(np.float32)
+    ref = orc.kmeanspp_chain(X, 5, 8)
+    for lead, width in ((0, d), (1, d + 3), (4, (d + 11) // 4 * 4)):
+        full = torch.full((N, width), float("nan"), device="cuda")        # (what lies between the rows is not read as a feature)
+        full[:, lead:lead + d] = dev(X)
+        np.testing.assert_array_equal(rls.kmeanspp_chain(full[:, lead:lead + d], 5, 8).cpu().numpy(), ref)
+
+
 def exchange_words(ws, k_max):
     """The words that the workgroups of a chain exchange, at the head of the workspace: the sums of step j are words
     256 j + workgroup, and a word nobody has written is -1."""
