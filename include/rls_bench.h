@@ -30,6 +30,12 @@ int32_t rls_profile_read(int32_t *n_launches, double *total_ms);
 int32_t rls_seed_wait_limit(int64_t ticks);
 /* The same for the workgroups of a space from `first_workgroup` on; the ones before it wait the default time. */
 int32_t rls_seed_wait_limit_from(int32_t first_workgroup, int64_t ticks);
+/* `n` single matrix instructions (32 x 32 x 16, fp16 or bf16 operands, fp32 accumulators) on operands as the kernels hold them, for
+ * tests of what the instruction leaves out of a sum:
+ *   a_dev, b_dev  [n][64 lanes][8] 16-bit elements: lane l holds those of row (column) l % 32, k = 8 (l / 32) .. + 7; 16-byte aligned
+ *   acc_dev       [n][64][16] fp32 (acc_out_dev: the same, may be acc_dev): entry 4 q + e of lane l is row 8 q + 4 (l / 32) + e, column l % 32 */
+int32_t rls_matrix_step(int32_t bf16, const void *a_dev, const void *b_dev, const float *acc_dev, float *acc_out_dev, int32_t n,
+                        void *stream);
 
 #ifdef __cplusplus
 }

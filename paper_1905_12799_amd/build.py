@@ -12,7 +12,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librls.so")
 SOURCES = ["rls_api.hip", "gbt_score.hip", "kmeans_seed.hip", "kmeans_order.hip", "kmeans_lloyd.hip", "kmeans_small.hip", "snap.hip", "modes_visited.hip",
-           "sweep_static.hip"]
+           "sweep_static.hip", "matrix_step.hip"]
 
 
 def sources():
