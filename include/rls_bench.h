@@ -30,6 +30,10 @@ int32_t rls_profile_read(int32_t *n_launches, double *total_ms);
 int32_t rls_seed_wait_limit(int64_t ticks);
 /* The same for the workgroups of a space from `first_workgroup` on; the ones before it wait the default time. */
 int32_t rls_seed_wait_limit_from(int32_t first_workgroup, int64_t ticks);
+/* Where in its workspace a sweep of one space over rows in spatial order keeps the tile lists of its last round, for tests of what
+ * lists occur: byte offset and number of 32-bit words (0: the sweep takes the points as they come).  Per group with lists and
+ * unit of points 16 words; the four highest bits of each of the first eight are the number of tiles the unit meets, less one. */
+int32_t rls_sweep_tile_lists(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int64_t *offset_out, int64_t *words_out);
 /* `n` single matrix instructions (32 x 32 x 16, fp16 or bf16 operands, fp32 accumulators) on operands as the kernels hold them, for
  * tests of what the instruction leaves out of a sum:
  *   a_dev, b_dev  [n][64 lanes][8] 16-bit elements: lane l holds those of row (column) l % 32, k = 8 (l / 32) .. + 7; 16-byte aligned

@@ -2915,6 +2915,11 @@ int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int3
     return RLS_OK;
 }
 
+int64_t tile_list_words(const SweepPlan &plan, int64_t N)
+{
+    return (int64_t)plan.n_lists * ((N + 32 * unit_blocks_of(plan.dp) - 1) / (32 * unit_blocks_of(plan.dp))) * kListWords;
+}
+
 void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, int32_t batch, bool chain_grows, SweepLayout *L)
 {
     int64_t off = 0;
@@ -2944,7 +2949,7 @@ void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, in
         // (from here on: a place that depends on the range of k)
         L->rowpos = take((int64_t)plan.total_rows * 2);
         L->rowidx = take((int64_t)plan.total_rows);
-        L->lists = take((int64_t)plan.n_lists * n_units * kListWords * 4);
+        L->lists = take(tile_list_words(plan, N) * 4);
     }
     L->opA = take((int64_t)plan.total_tiles * tile_bytes_of(plan.dp));
     L->cnmax = take((int64_t)plan.n_runs * kMaxParts * 4);

@@ -190,6 +190,23 @@ int64_t rls_kmeans_sweep_least_workspace_bytes(int64_t N, int32_t d, int32_t k_m
     return rc != RLS_OK ? rc : form_workspace(N, d, k_min, k_max, batch, false);
 }
 
+int32_t rls_sweep_tile_lists(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int64_t *offset_out, int64_t *words_out)
+{
+    if (!offset_out || !words_out) return RLS_ERR_NULL;
+    const int32_t rc = check_sweep(N, d, k_min, k_max, 1);
+    if (rc != RLS_OK) return rc;
+    *offset_out = *words_out = 0;
+    if (!sweep_wants_order(N, d, k_min, k_max, 1)) return RLS_OK;
+    SweepPlan plan;
+    const int32_t prc = make_sweep_plan(N, d, k_min, k_max, 1, true, &plan);
+    if (prc != RLS_OK) return prc;
+    SweepLayout L;
+    sweep_layout(plan, N, d, k_max, 1, false, &L);
+    *offset_out = L.lists;
+    *words_out = tile_list_words(plan, N);
+    return RLS_OK;
+}
+
 int32_t rls_kmeanspp_chain(const float *X_dev, int64_t N, int32_t d, int64_t ldx, int32_t k_max, uint64_t seed,
                            int64_t *init_idx_dev, void *workspace_dev, int64_t workspace_bytes, void *stream)
 {

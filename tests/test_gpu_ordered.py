@@ -1,6 +1,8 @@
 """Sweeps on the spatially ordered copy of the points, whose blocks meet listed tiles of centroids only, against the same
 sweep on the points as they come (taken with a workspace that holds nothing else, and by a sweep that also returns the loss of
 every round), bit for bit, losses included, and against the oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -26,7 +28,7 @@ def make(kind, N, d, seed):
     rng = np.random.default_rng(seed)
     if kind == "clusters":
         X = clustered(rng, N, d, 4.0)
-    elif kind == "noise":                       # no structure: most units meet more tiles than a list holds
+    elif kind == "noise":                       # no structure: most units meet most tiles
         X = rng.standard_normal((N, d)).astype(np.float32)
     elif kind == "grid":                        # few distinct rows: exact ties between centroids, long buckets
         X = rng.integers(0, 3, (N, d)).astype(np.float32)
@@ -59,8 +61,7 @@ def equal(a, b):
     return torch.equal(a.labels, b.labels) and torch.equal(a.centroids, b.centroids) and torch.equal(a.inertia, b.inertia)
 
 
-# units and chunks that end raggedly, every padded width, groups of 1, 2, 4 and 8 slots per run, groups with fewer and with
-# more tiles than lists are kept for
+# units and chunks that end raggedly, every padded width, groups of 1, 2, 4 and 8 slots per run, groups with and without lists
 CASES = [("clusters", 245760, 16, 1, 40), ("clusters", 86017, 13, 8, 63), ("clusters", 90011, 5, 1, 64), ("clusters", 60017, 32, 1, 100),
          ("clusters", 67000, 17, 97, 128), ("clusters", 50001, 8, 1, 110), ("clusters", 70001, 24, 10, 90), ("clusters", 66415, 3, 30, 90),
          ("noise", 86016, 32, 1, 64), ("noise", 96333, 12, 20, 64), ("grid", 99017, 6, 1, 60), ("grid", 96480, 16, 20, 64),
@@ -205,9 +206,32 @@ def test_ordered_sweep_turns_down_bad_data(rls):
     assert int(rls.kmeans_sweep(X, 1, 64, 2, seed=1, check_status=False).status.item()) & rls.RLS_STATUS_NONFINITE
 
 
-@pytest.mark.parametrize("kind,N,d,k_min,k_max", [("noise", 120017, 4, 20, 64), ("noise", 150001, 16, 25, 64), ("clusters", 200001, 2, 33, 64),
-                                                  ("noise", 60001, 30, 40, 90)])
-def test_lists_of_seven_and_more_tiles(rls, kind, N, d, k_min, k_max):
+def list_lengths(rls, workspace, N, d, k_min, k_max):
+    """How many tiles the units of the sweep that last used the workspace met in its last round, per group with lists."""
+    at, words = ctypes.c_int64(0), ctypes.c_int64(0)
+    assert rls.lib().rls_sweep_tile_lists(ctypes.c_int64(N), d, k_min, k_max, ctypes.byref(at), ctypes.byref(words)) == 0
+    assert words.value > 0, "this sweep is not an ordered one"
+    base = -workspace.data_ptr() % 256 + at.value
+    lists = workspace[base:base + 4 * words.value].view(torch.int32).view(-1, 16).cpu().numpy().view(np.uint32)
+    lengths = (lists[:, :8] >> 28) + 1
+    assert np.all(lengths == lengths[:, :1])
+    units = -(-N // (64 if d > 16 else 32))
+    return lengths[:, 0].reshape(-1, units)
+
+
+# `found`: lengths that have to occur.  (A unit that would leave out one tile of many meets them all: 15 of 16 are never listed.)
+@pytest.mark.parametrize("kind,N,d,k_min,k_max,found", [("noise", 120017, 4, 20, 64, range(1, 14)), ("noise", 150001, 16, 25, 64, (12, 14, 16)),
+                                                        ("clusters", 200001, 2, 33, 64, (1, 2)), ("noise", 60001, 30, 40, 90, (7, 8, 9))])
+def test_lists_of_seven_and_more_tiles(rls, orc, kind, N, d, k_min, k_max, found):
     """Units that meet up to all sixteen tiles of a group: entries of a list's second word, and the sixteenth."""
-    X = torch.as_tensor(make(kind, N, d, 21)).cuda()
-    assert equal(rls.kmeans_sweep(X, k_min, k_max, 4, seed=6), as_they_come(rls, X, k_min, k_max, 4, seed=6))
+    rows = make(kind, N, d, 21)
+    X = torch.as_tensor(rows).cuda()
+    workspace = torch.zeros(rls.kmeans_sweep_workspace_bytes(N, d, k_min, k_max) + 256, dtype=torch.uint8, device="cuda")
+    got = rls.kmeans_sweep(X, k_min, k_max, 4, seed=6, workspace=workspace)
+    lengths = list_lengths(rls, workspace, N, d, k_min, k_max)
+    print([(int(n), int((lengths == n).sum())) for n in np.unique(lengths)])
+    assert set(found) <= set(np.unique(lengths).tolist()) and lengths.max() <= 16
+    assert equal(got, as_they_come(rls, X, k_min, k_max, 4, seed=6))
+    ref = orc.kmeans_sweep(rows, k_min, k_max, 4, seed=6)
+    np.testing.assert_array_equal(got.labels.cpu().numpy(), ref["labels"])
+    np.testing.assert_array_equal(got.centroids.cpu().numpy(), ref["centroids"])
