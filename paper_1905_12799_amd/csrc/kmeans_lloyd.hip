@@ -926,7 +926,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
         if constexpr (PRE) {
             // Raw rows on demand: the exact arithmetic of a close call needs the point's row; both lanes of such a
             // point (each holds half of the features) load their half.  (The exact sums need the rows of the points
-            // whose label changed: those are read when the wave works off its log of moved pairs.)  Loads, wait and
+            // whose label changed: those are read when the wave works off the moved pairs it has gathered.)  Loads, wait and
             // scans sit in one branch, so that a slab without close calls never waits on the memory counter here: what
             // is in flight then are the operands of the next slab, wanted a whole slab later.
             if (__builtin_amdgcn_ballot_w64(pend != 0u) != 0ull) {
@@ -1017,7 +1017,7 @@ __device__ inline void wave_loop(const WaveCtx &c, double (&jloc)[8])
                 // No point has a label yet, so every one enters a cluster of every run - but the centroids of a run are those of
                 // the run before and one more, and most points keep the nearest one they had there.  Only the group's first
                 // run is filled point by point; a later run logs the points whose centroid is another one than in the run
-                // before it, as moves, and its sums are those of the run before plus what its own log moved (put together
+                // before it, as moves, and its sums are those of the run before plus what its own moves change (put together
                 // when the workgroup is done).  (Wide columns: their low-order sums are global, every run is filled.)
 #pragma unroll
                 for (int pb = 0; pb < NB; ++pb) {
@@ -2707,7 +2707,7 @@ int64_t lloyd_group_lds_bytes(int dp, int d, int n_tiles, int real_rows, int cop
 }
 
 constexpr int kFillWorkgroups = 256;   // one per compute unit
-// What a slab of 32 points costs beside the tiles of its group (operand loads, close calls, labels, log), in tiles.  Sweeps
+// What a slab of 32 points costs beside the tiles of its group (operand loads, close calls, labels, moved pairs), in tiles.  Sweeps
 // at 65 shapes from 20,003 x 8 to 3.2M x 32 with 2, 4, 8 and 12 in its place: 2 up to 27% and 4 up to 12% slower, 8 and 12
 // within 5% either way.
 constexpr int kSlabCost = 6;
@@ -2767,7 +2767,7 @@ int32_t make_sweep_plan(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int3
 {
     const int dp = padded_d(d);
     LloydGeometry geo = lloyd_geometry(dp);
-    if (ordered) geo.lds_budget = 160 * 1024;      // the tile of padding rows and the places have to fit as well
+    if (ordered) geo.lds_budget = 160 * 1024;      // the places of the centroids have to fit as well
     plan->ordered = ordered ? 1 : 0;
     int n_lists = 0;
     plan->n_runs = k_max - k_min + 1;
@@ -2920,7 +2920,7 @@ int64_t tile_list_words(const SweepPlan &plan, int64_t N)
     return (int64_t)plan.n_lists * ((N + 32 * unit_blocks_of(plan.dp) - 1) / (32 * unit_blocks_of(plan.dp))) * kListWords;
 }
 
-void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, int32_t batch, bool chain_grows, SweepLayout *L)
+void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, int32_t batch, SweepLayout *L)
 {
     int64_t off = 0;
     auto take = [&](int64_t bytes) { const int64_t o = off; off += align_up(bytes, 256); return o; };

@@ -552,7 +552,7 @@ __device__ inline int64_t first_not_chosen(const int64_t *chosen, int j)
 
 // DP: padded features (a padded feature is zero on both sides and adds +0), P: points per thread.
 // Where they fit, the rows are in LDS as well, as are the distances, and wave 0 alone draws: it finds the point
-// among the 64 of an entry, reads its row and hands it out, with one barrier before and one behind.  Beyond that the wave that
+// among the 64 P of an entry, a wave's, reads its row and hands it out, with one barrier before and one behind.  Beyond that the wave that
 // holds the entry does (and a third barrier, of the drawing workgroup only).  (As it was, 64 points of a
 // wave's per scan, rows converted to fp64 in every step and three barriers: 2000 x 8 2.2 -> 1.8 us per centre, 65,536 x 16 5.35 -> 4.8,
 // 65,536 x 32 6.3 -> 5.4, 1M x 16 8.7 -> 8.1.)

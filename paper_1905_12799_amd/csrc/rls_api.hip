@@ -71,7 +71,7 @@ static int32_t plan_sweep(int64_t N, int32_t d, int32_t k_min, int32_t k_max, in
         const int32_t rc = make_sweep_plan(N, d, k_min, k_max, batch, ordered != 0, plan);
         if (rc != RLS_OK) return rc;
         if (ordered != 0 && !sweep_uses_prepared(*plan, iters, trace)) continue;
-        sweep_layout(*plan, N, d, k_max, batch, false, L);
+        sweep_layout(*plan, N, d, k_max, batch, L);
         if (L->total <= bytes) break;
     }
     return RLS_OK;
@@ -83,7 +83,7 @@ static int64_t form_workspace(int64_t N, int32_t d, int32_t k_min, int32_t k_max
     const int32_t rc = make_sweep_plan(N, d, k_min, k_max, batch, ordered, &plan);
     if (rc != RLS_OK) return rc;
     SweepLayout L;
-    sweep_layout(plan, N, d, k_max, batch, false, &L);
+    sweep_layout(plan, N, d, k_max, batch, &L);
     return L.total;
 }
 
@@ -201,7 +201,7 @@ int32_t rls_sweep_tile_lists(int64_t N, int32_t d, int32_t k_min, int32_t k_max,
     const int32_t prc = make_sweep_plan(N, d, k_min, k_max, 1, true, &plan);
     if (prc != RLS_OK) return prc;
     SweepLayout L;
-    sweep_layout(plan, N, d, k_max, 1, false, &L);
+    sweep_layout(plan, N, d, k_max, 1, &L);
     *offset_out = L.lists;
     *words_out = tile_list_words(plan, N);
     return RLS_OK;
@@ -219,7 +219,7 @@ int32_t rls_kmeanspp_chain(const float *X_dev, int64_t N, int32_t d, int64_t ldx
     rc = make_sweep_plan(N, d, k_max, k_max, 1, false, &plan);
     if (rc != RLS_OK) return rc;
     SweepLayout L;
-    sweep_layout(plan, N, d, k_max, 1, false, &L);
+    sweep_layout(plan, N, d, k_max, 1, &L);
     if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < L.total) return RLS_ERR_WORKSPACE;
     char *ws = static_cast<char *>(workspace_dev);
     RLS_HIP_TRY(launch_seed_chain(X_dev, N, d, ldx, 0, 1, k_max, &seed, init_idx_dev, k_max, ws, L, (hipStream_t)stream));
@@ -295,7 +295,7 @@ static int32_t until_knee_workspace(int64_t N, int32_t d, int32_t k_min, int32_t
             const int32_t rc = make_sweep_plan(N, d, k_lo, k_hi, 1, form != 0, &plan);
             if (rc != RLS_OK) return rc;
             SweepLayout L;
-            sweep_layout(plan, N, d, k_max, 1, true, &L);     // chain sized for k_max: the leading blocks sit at the same offsets in every wave
+            sweep_layout(plan, N, d, k_max, 1, &L);     // chain sized for k_max: the leading blocks sit at the same offsets in every wave
             if (L.total > need) need = L.total;
         }
     }
@@ -354,7 +354,7 @@ int32_t rls_kmeans_sweep_until_knee(const float *X_dev, int64_t N, int32_t d, in
         rc = plan_wave(N, d, k_lo, k_hi, iters, ordered, &plan);
         if (rc != RLS_OK) return rc;
         SweepLayout L;
-        sweep_layout(plan, N, d, k_max, 1, true, &L);
+        sweep_layout(plan, N, d, k_max, 1, &L);
         const int64_t *init = init_idx_dev;
         if (!init) {
             // the chain grows with the waves: centres chain_done .. k_hi-1 are drawn now, from the distance state of the earlier ones

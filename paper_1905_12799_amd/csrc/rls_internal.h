@@ -120,8 +120,7 @@ struct SweepLayout {
     int32_t seed_blocks;
     int32_t stat_blocks;
 };
-// `chain_grows`: a later call with the same workspace adds centres to the chain (the waves of a sweep until the knee)
-void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, int32_t batch, bool chain_grows, SweepLayout *L);
+void sweep_layout(const SweepPlan &plan, int64_t N, int32_t d, int32_t k_max, int32_t batch, SweepLayout *L);
 // words of the tile lists of all groups, as they lie in the workspace of an ordered sweep
 int64_t tile_list_words(const SweepPlan &plan, int64_t N);
 
