@@ -385,8 +385,8 @@ __global__ void __launch_bounds__(1024) seed_pick_kernel(SeedList seeds, int b0,
 // exchange two messages through memory - every workgroup the sum of its D, then the workgroup that holds the drawn point
 // that point's row and index.  What bounds a step is the latency of these two exchanges and of the scans between them:
 // two launches per centre (an update of 7 to 12 us, a draw of 9 to 11 us and the ramp of each) took 17 to 23 us.
-// (One launch: 1.8 us per centre at 2000 x 8 - a single workgroup skips the scan over the others -, 4.8 at 65,536 x 16, 8.1 at
-// 1M x 16, against 13.6, 16.6 and 22.4.)
+// (One launch, chains of 128: 1.4 us per centre at 2000 x 8 - a single workgroup skips the scan over the others -, 4.5 at 65,536 x 16,
+// 7.2 at 1M x 16, against 13.6, 16.6 and 22.4.)
 //
 // A message is a word of 8 bytes that carries its own validity - the area is filled with kSlotEmpty before the launch,
 // every word is written once, and a row travels as words of (step, value) - so no flags, fences or counters are needed:
@@ -553,16 +553,52 @@ __device__ inline int64_t first_not_chosen(const int64_t *chosen, int j)
 // DP: padded features (a padded feature is zero on both sides and adds +0), P: points per thread.
 // Where they fit, the rows are in LDS as well, as are the distances, and wave 0 alone draws: it finds the point
 // among the 64 P of an entry, a wave's, reads its row and hands it out, with one barrier before and one behind.  Beyond that the wave that
-// holds the entry does (and a third barrier, of the drawing workgroup only).  (As it was, 64 points of a
-// wave's per scan, rows converted to fp64 in every step and three barriers: 2000 x 8 2.2 -> 1.8 us per centre, 65,536 x 16 5.35 -> 4.8,
-// 65,536 x 32 6.3 -> 5.4, 1M x 16 8.7 -> 8.1.)
+// holds the entry does (and a third barrier, of the drawing workgroup only).  (64 points of a wave's per scan, rows converted to fp64
+// in every step and three barriers, chains of 128: 2000 x 8 1.9 us per centre, 1.5 so, 65,536 x 16 5.0 and 4.5, 65,536 x 32 5.9 and 5.0,
+// 1M x 16 8.0 and 7.4.)
 __host__ __device__ constexpr bool chain_rows_in_lds(int dp, int p) { return 1024 * p * (8 + 4 * dp) <= 152 * 1024; }
-// The rows come by way of LDS in either case, a wave's 64 P all at once or, where they do not stay there and take more than 8 KB,
-// one half of the features after the other.  (A lane that reads its own rows asks for a line per row with every instruction, and with
-// a branch around every feature that may not be there each load waited for the one before.  A chain of two centres at
-// 500,009 x 16 44 -> 17 us, at 1,000,003 x 13 52 -> 29, at 262,144 x 32 42 -> 15; of 128 713 -> 683, 942 -> 919, 700 -> 690.)
-__host__ __device__ constexpr int chain_pieces(int dp, int p) { return !chain_rows_in_lds(dp, p) && 64 * p * dp * 4 > 8192 ? 2 : 1; }
-__host__ __device__ constexpr int chain_lds_bytes(int dp, int p) { return chain_rows_in_lds(dp, p) ? 1024 * p * (8 + 4 * dp) : 1024 * p * 4 * dp / chain_pieces(dp, p); }
+// The rows come by way of LDS in either case, a wave's 64 P all at once or, where that is more than 8 KB, one half of the features
+// after the other.  (A lane that reads its own rows asks for a line per row with every instruction, and with a branch around every
+// feature that may not be there each load waited for the one before.  A chain of two centres at 500,009 x 16 44 -> 17 us, at
+// 1,000,003 x 13 52 -> 29, at 262,144 x 32 42 -> 15; of 128 713 -> 683, 942 -> 919, 700 -> 690.)
+__host__ __device__ constexpr int stage_width(int dp, int p) { return 64 * p * dp * 4 > 8192 ? dp / 2 : dp; }      // features at a time
+__host__ __device__ constexpr int stage_bytes(int dp, int p) { return 1024 * p * stage_width(dp, p) * 4; }          // all waves
+__host__ __device__ constexpr int chain_lds_bytes(int dp, int p) { return stage_bytes(dp, p) + (chain_rows_in_lds(dp, p) ? 1024 * p * 8 : 0); }
+// where a quad of features of a staged row lies: turned from row to row, so that lanes whose rows begin at the same banks read different ones
+template <int W>
+__device__ inline int row_quad(int row, int q) { return row * W + 4 * (q ^ ((row * W / 64) & (W / 4 - 1))); }
+
+// whether rows can be read 16 bytes at a time
+__device__ inline bool rows_in_quads(const float *X, int d, int64_t ldx) { return (d & 3) == 0 && (ldx & 3) == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0; }
+// Features f0 .. f0 + W - 1 of 64 P rows from `first` on, zero past the last feature (past the last row its values: nobody uses them),
+// read side by side by the lanes of a wave and put down in its `area`.
+template <int P, int W>
+__device__ inline void stage_rows(const float *X, int64_t N, int d, int64_t ldx, bool quads, int64_t first, int f0, float *area)
+{
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));       // (addresses are worked out by every call: kept between two they take the registers that rows need)
+    if (quads) {
+        constexpr int U = P * W / 4, RU = 256 / W;             // quads per lane, rows per step
+        const int q = lane % (W / 4), r0 = lane / (W / 4), f = f0 + 4 * q;
+        float4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const float4 *>(X + min(first + r0 + RU * u, N - 1) * ldx + min(f, d - 4));
+#pragma unroll
+        for (int u = 0; u < U; ++u) *reinterpret_cast<float4 *>(area + row_quad<W>(r0 + RU * u, q)) = f < d ? v[u] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    } else {
+        constexpr int U = P * W, RU = 64 / W;
+        const int l = lane % W, r0 = lane / W, f = f0 + l;
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = X[min(first + r0 + RU * u, N - 1) * ldx + min(f, d - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) area[row_quad<W>(r0 + RU * u, l >> 2) + (l & 3)] = f < d ? v[u] : 0.0f;
+    }
+    // (what the wave's lanes have put down is read by its lanes alone, and the LDS keeps their order)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 template <int DP, int P>
 __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainArgs a)
@@ -593,45 +629,20 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
     using Coord = std::conditional_t<ROWS, double, float>;      // (in fp64 where the registers hold it)
     Coord x[P][DP];
     double D[P];                                    // 0 for a point past the end: it is never drawn
-    constexpr int W = DP / chain_pieces(DP, P);     // features that are staged at a time
-    // where a quad of a staged row lies: turned from row to row, so that lanes whose rows begin at the same banks read different ones
-    auto row_quad = [](int row, int q) { return row * W + 4 * (q ^ ((row * W / 64) & (W / 4 - 1))); };
-    {
-        float *const area = rows_s + wave * (64 * P) * W;
-        const int64_t first = base + 64 * P * wave;
-        const bool vec = (d & 3) == 0 && (a.ldx & 3) == 0 && (reinterpret_cast<uintptr_t>(Xb) & 15) == 0;
+    constexpr int W = stage_width(DP, P);
+    float *const area = rows_s + wave * (64 * P) * W;
+    const bool quads = rows_in_quads(Xb, d, a.ldx);
 #pragma unroll
-        for (int f0 = 0; f0 < DP; f0 += W) {
-            if (vec) {
-                constexpr int U = P * W / 4, RU = 256 / W;         // quads per lane, rows per step
-                const int q = lane % (W / 4), r0 = lane / (W / 4), f = f0 + 4 * q;
-                float4 v[U];
+    for (int f0 = 0; f0 < DP; f0 += W) {
+        stage_rows<P, W>(Xb, a.N, d, a.ldx, quads, base + 64 * P * wave, f0, area);
 #pragma unroll
-                for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const float4 *>(Xb + min(first + r0 + RU * u, a.N - 1) * a.ldx + min(f, d - 4));
+        for (int i = 0; i < P; ++i)
 #pragma unroll
-                for (int u = 0; u < U; ++u) *reinterpret_cast<float4 *>(area + row_quad(r0 + RU * u, q)) = f < d ? v[u] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            } else {
-                constexpr int U = P * W, RU = 64 / W;
-                const int l = lane % W, r0 = lane / W, f = f0 + l;
-                float v[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) v[u] = Xb[min(first + r0 + RU * u, a.N - 1) * a.ldx + min(f, d - 1)];
-#pragma unroll
-                for (int u = 0; u < U; ++u) area[row_quad(r0 + RU * u, l >> 2) + (l & 3)] = f < d ? v[u] : 0.0f;
+            for (int q = 0; q < W / 4; ++q) {
+                const float4 v = *reinterpret_cast<const float4 *>(area + row_quad<W>(P * lane + i, q));
+                x[i][f0 + 4 * q + 0] = v.x; x[i][f0 + 4 * q + 1] = v.y; x[i][f0 + 4 * q + 2] = v.z; x[i][f0 + 4 * q + 3] = v.w;
             }
-            // (what the wave's lanes have put down is read by its lanes alone, and the LDS keeps their order)
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-            for (int i = 0; i < P; ++i)
-#pragma unroll
-                for (int q = 0; q < W / 4; ++q) {
-                    const float4 v = *reinterpret_cast<const float4 *>(area + row_quad(P * lane + i, q));
-                    x[i][f0 + 4 * q + 0] = v.x; x[i][f0 + 4 * q + 1] = v.y; x[i][f0 + 4 * q + 2] = v.z; x[i][f0 + 4 * q + 3] = v.w;
-                }
-            __builtin_amdgcn_wave_barrier();
-        }
+        __builtin_amdgcn_wave_barrier();
     }
 #pragma unroll
     for (int i = 0; i < P; ++i) {
@@ -738,7 +749,7 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
 #pragma unroll
                     for (int i = 0; i < P; ++i) dv[i] = D_s[P * (64 * entry + lane) + i];
                     const int pt = 64 * P * entry + max(wave_locate<P>(dv, wave_scan_dpp(sum_of(dv)), before, r, at), 0);
-                    if (lane < DP) mine = rows_s[row_quad(pt, lane >> 2) + (lane & 3)];
+                    if (lane < DP) mine = rows_s[row_quad<W>(pt, lane >> 2) + (lane & 3)];
                     pick = min(base + pt, a.N - 1);
                     if (G > 1 && (lane < DP || lane == RLS_MAX_D))
                         post(ex + kExRows + j * kRowWords + lane, ((unsigned long long)j << 32) | (lane < DP ? __float_as_uint(mine) : (unsigned)pick));
@@ -812,16 +823,19 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
 // A block waits for the draw of the step before, that is for blocks with smaller tickets, which workgroups hold that are
 // running and wait for smaller tickets still - so whatever number of workgroups is running, every wait ends.  Who finishes
 // the last block of a step draws.  The distances to the centres drawn by earlier calls are worked out again (some of them may be
-// half updated).  Distances, block sums and the draw are those of seed_chain_kernel.  Rows and distances come from memory in every step, and
-// between two steps lie a ticket, a count and a message: 14 us per centre at 65,536 x 16, 55 at 1M x 16, 167 at 524,288 x 32, against
-// 5.1, 10.5 and 11 undisturbed.  (One workgroup that walked all points: 631, 9970 and 8790.  All waves fencing in all three places
-// instead of one wave, acquire or release: 45, 175 and 313.)
+// half updated).  Distances, block sums and the draw are those of seed_chain_kernel, and so is the way in which rows are read.  Rows and
+// distances come from memory in every step, and between two steps lie a ticket, a count and a message: chains of 128 take 7.6 us per
+// centre at 65,536 x 16, 34 at 1M x 16, 30 at 524,288 x 32, against 4.5, 7.2 and 7.5 undisturbed.  (Every lane reading its own rows, feature
+// by feature: 14, 178 and 163.  One workgroup that walked all points: 631, 9970 and 8790.  All waves fencing in all three places
+// instead of one wave, acquire or release: 45, 175 and 313, where 14, 55 and 167 were reached.)
 constexpr int kRestWgs = 256;                      // workgroups per space at most: launched for nothing almost always
 constexpr long long kRestTicks = 1000000000;       // 10 s.  Only another call that uses the same workspace at the same time can make a
                                                    // wait last that long; its results are undefined then, but it ends
-template <int DP>
-__global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, ChainArgs a, int P)
+template <int DP, int P>
+__global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, ChainArgs a)
 {
+    extern __shared__ __align__(16) unsigned char smem[];       // staged rows
+    constexpr int W = stage_width(DP, P);
     __shared__ float cs[DP];
     __shared__ double wsum[64];                    // sums of the 16 waves, then zeros
     __shared__ int64_t chosen[RLS_MAX_K];
@@ -859,25 +873,35 @@ __global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, C
             __syncthreads();
             if (tid < DP) cs[tid] = tid < d ? Xb[chosen[m] * a.ldx + tid] : 0.0f;
             __syncthreads();
+            double acc[P] = {};
+            float *const area = reinterpret_cast<float *>(smem) + wave * (64 * P) * W;
+#pragma unroll
+            for (int f0 = 0; f0 < DP; f0 += W) {
+                stage_rows<P, W>(Xb, a.N, d, a.ldx, rows_in_quads(Xb, d, a.ldx), base + 64 * P * wave, f0, area);
+#pragma nounroll
+                for (int q = 0; q < W / 4; ++q)
+#pragma unroll
+                    for (int i = 0; i < P; ++i) {
+                        const float4 v = *reinterpret_cast<const float4 *>(area + row_quad<W>(P * lane + i, q));
+                        const float x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const double diff = __dsub_rn((double)x[e], (double)cs[f0 + 4 * q + e]);
+                            acc[i] = __dadd_rn(acc[i], __dmul_rn(diff, diff));
+                        }
+                    }
+                __builtin_amdgcn_wave_barrier();
+            }
             double loc = 0.0;
+#pragma unroll
             for (int i = 0; i < P; ++i) {
                 const int64_t p = base + P * tid + i;
                 double cur = 0.0;
                 if (p < a.N) {
-                    const float *row = Xb + p * a.ldx;
-                    float x[DP];
-#pragma unroll
-                    for (int l = 0; l < DP; ++l) x[l] = l < d ? row[min(l, d - 1)] : 0.0f;
-                    double acc = 0.0;
-#pragma unroll
-                    for (int l = 0; l < DP; ++l) {
-                        const double diff = __dsub_rn((double)x[l], (double)cs[l]);
-                        acc = __dadd_rn(acc, __dmul_rn(diff, diff));
-                    }
-                    cur = acc;
+                    cur = acc[i];
                     if (m > 0) {
                         const double old = D[p];
-                        if (!(acc < old)) cur = old;
+                        if (!(cur < old)) cur = old;
                     }
                     D[p] = cur;
                 }
@@ -937,11 +961,11 @@ __global__ void __launch_bounds__(1024) seed_chain_rest_kernel(SeedList seeds, C
             __syncthreads();
             if (wave == s_entry) {
                 const int64_t first = from + (int64_t)64 * P * wave;
-                double v[8], at;                   // (P <= 8; what is not there is zero and never drawn)
+                double v[P], at;                   // (what is not there is zero and never drawn)
 #pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = i < P && first + P * lane + i < a.N ? D[first + P * lane + i] : 0.0;
-                const int e = max(wave_locate<8>(v, wave_scan_dpp(sum_of(v)), s_before, s_r, at), 0);
-                if (lane == 0) s_pick = min(first + P * (e / 8) + e % 8, a.N - 1);
+                for (int i = 0; i < P; ++i) v[i] = first + P * lane + i < a.N ? D[first + P * lane + i] : 0.0;
+                const int e = max(wave_locate<P>(v, wave_scan_dpp(sum_of(v)), s_before, s_r, at), 0);
+                if (lane == 0) s_pick = min(first + e, a.N - 1);
             }
         }
         __syncthreads();
@@ -997,6 +1021,7 @@ static hipError_t launch_chain_in_one(int dp, int p, int spaces, const SeedList 
 {
     if (a.groups > 1) hipLaunchKernelGGL(seed_begin_kernel, dim3(16, spaces), dim3(256), 0, s, sl, a);
     const dim3 grid(a.groups, spaces), block(1024);
+    const dim3 rest(std::min(a.groups, kRestWgs), spaces);
 #define RLS_SEED_CHAIN(DPV, PV)                                                                                          \
     case DPV * 16 + PV: {                                                                                                \
         static std::once_flag once;                                                                                      \
@@ -1004,9 +1029,13 @@ static hipError_t launch_chain_in_one(int dp, int p, int spaces, const SeedList 
         std::call_once(once, [] {                                                                                        \
             attr = hipFuncSetAttribute(reinterpret_cast<const void *>(seed_chain_kernel<DPV, PV>),                       \
                                        hipFuncAttributeMaxDynamicSharedMemorySize, chain_lds_bytes(DPV, PV));            \
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(seed_chain_rest_kernel<DPV, PV>),    \
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, stage_bytes(DPV, PV));  \
+            if (attr == hipSuccess) attr = e;                                                                            \
         });                                                                                                              \
         if (attr != hipSuccess) return attr;                                                                             \
         hipLaunchKernelGGL((seed_chain_kernel<DPV, PV>), grid, block, chain_lds_bytes(DPV, PV), s, sl, a);               \
+        if (a.groups > 1) hipLaunchKernelGGL((seed_chain_rest_kernel<DPV, PV>), rest, block, stage_bytes(DPV, PV), s, sl, a); \
     } break
     switch (dp * 16 + p) {
     RLS_SEED_CHAIN(8, 1);
@@ -1021,12 +1050,6 @@ static hipError_t launch_chain_in_one(int dp, int p, int spaces, const SeedList 
     default: return hipErrorInvalidValue;
     }
 #undef RLS_SEED_CHAIN
-    if (a.groups > 1) {
-        const dim3 rest(std::min(a.groups, kRestWgs), spaces);
-        if (dp == 8) hipLaunchKernelGGL(seed_chain_rest_kernel<8>, rest, block, 0, s, sl, a, p);
-        else if (dp == 16) hipLaunchKernelGGL(seed_chain_rest_kernel<16>, rest, block, 0, s, sl, a, p);
-        else hipLaunchKernelGGL(seed_chain_rest_kernel<32>, rest, block, 0, s, sl, a, p);
-    }
     return hipGetLastError();
 }
 

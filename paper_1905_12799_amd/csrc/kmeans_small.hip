@@ -6,11 +6,11 @@
 // prepared copy, which the second-level cache holds.  The arithmetic is that of kmeans_lloyd.hip: distances on the matrix
 // pipeline, close calls settled with the exact form, integer sums, means rounded once, losses added in the same order.
 //
-// 2000 x 8, k 1..16, 20 rounds: 102 us instead of 390, 4.9 a round.  Of a round's 11,700 cycles the waves spend 5100 on the
-// distances of their four blocks (half of it waiting for the operands: two blocks ahead did not help, the second copy of the
-// loop's code cost as much), 3000 waiting for the wave with the most close calls, 2100 on the new centroids, 1000 on labels
-// and moves.  One block per wave at a time: with two the 128 registers that 16 waves leave spilled (116 us); eight waves of
-// 256 registers each hide less (126).
+// 2000 x 8, k 1..16, 20 rounds: 96 us instead of 390, 4.6 a round.  Of a round's 11,000 cycles (with the clock read between the phases,
+// which takes some 1500 of them) the waves spend 2600 on the distances of their four blocks (two blocks ahead did not help, the
+// second copy of the loop's code cost as much), 1300 on close calls, 1200 on labels and moves, 1700 waiting for the wave that takes
+// longest and 2000 on the new centroids.  One block per wave at a time: with two the 128 registers that 16 waves leave spilled (116 us
+// against 102, as the rest was then); eight waves of 256 registers each hide less (126).
 #include <algorithm>
 #include <mutex>
 

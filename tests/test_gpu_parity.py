@@ -405,7 +405,13 @@ def test_seeding_chain_stages_every_kind_of_rows(rls, orc, d, points):
     for lead, width in ((0, d), (1, d + 3), (4, (d + 11) // 4 * 4)):
         full = torch.full((N, width), float("nan"), device="cuda")        # (what lies between the rows is not read as a feature)
         full[:, lead:lead + d] = dev(X)
-        np.testing.assert_array_equal(rls.kmeanspp_chain(full[:, lead:lead + d], 5, 8).cpu().numpy(), ref)
+        rows = full[:, lead:lead + d]
+        np.testing.assert_array_equal(rls.kmeanspp_chain(rows, 5, 8).cpu().numpy(), ref)
+        try:                                     # (the kernel that takes over stages them as well)
+            rls.lib().rls_seed_wait_limit(ctypes.c_int64(0))
+            np.testing.assert_array_equal(rls.kmeanspp_chain(rows, 5, 8).cpu().numpy(), ref)
+        finally:
+            rls.lib().rls_seed_wait_limit(ctypes.c_int64(-1))
 
 
 def exchange_words(ws, k_max):
