@@ -2743,8 +2743,8 @@ int workgroups_per_cu(int64_t per_cu, int n_groups, int batch)
 //                       6000 .. 8000: 1.01 / 1.06 / 1.09;  8000 .. 12,000: 1.07 / 1.13 / 1.16;  12,000 .. 16,000: 1.14 / 1.21 / 1.25
 //   17 to 32            1000 .. 3000: 0.92 / 0.95 / 0.97;  3000 .. 4000: 0.96 / 1.00 / 1.02;  4000 .. 5000: 0.99 / 1.03 / 1.05;
 //                       5000 .. 6000: 1.03 / 1.06 / 1.07;  6000 .. 8000: 1.04 / 1.08 / 1.10;  8000 .. 12,000: 1.10 / 1.15 / 1.17
-// Rows without any structure gain nothing by it, and that cannot be told from the sizes: independent normal deviates take 1.25 times
-// as long with an order at 100,003 x 16, k 1..64, 1.16 at 1M, 1.03 at 2M x 32 (20 rounds).  A caller with such rows hands in the
+// Rows without any structure gain nothing by it, and that cannot be told from the sizes: independent normal deviates take 1.17 times
+// as long with an order at 100,003 x 16, k 1..64, 1.18 at 1M, 1.03 at 2M x 32 (20 rounds).  A caller with such rows hands in the
 // least workspace.
 bool sweep_wants_order(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int32_t batch)
 {
