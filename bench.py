@@ -48,14 +48,14 @@ VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4.0   # wave64 vector instructions per secon
 # source they were taken with (step_source_digest); with any other the fields made from them are null.
 COUNTERS = {
     # mean over the 30 rounds of a sweep (first round included, like the launches the events time)
-    "mid": {"source": "0592a683fb35", "fetch_kib": 8232.4, "write_kib": 11007.3, "fetch_scale": 2.0, "write_scale": 1.0,
+    "mid": {"source": "b641b696cbc9", "fetch_kib": 8232.7, "write_kib": 11007.3, "fetch_scale": 2.0, "write_scale": 1.0,
            "valu_insts": 1.044e+07, "mfma_insts": 5.898e+05},
-    "whole_layer": {"source": "0592a683fb35", "fetch_kib": 306727.5, "write_kib": 27534.2, "fetch_scale": 2.0, "write_scale": 1.0,
-                   "valu_insts": 6.989e+07, "mfma_insts": 2.858e+06},
-    "large": {"source": "0592a683fb35", "fetch_kib": 7748961.4, "write_kib": 687623.5, "fetch_scale": 2.0, "write_scale": 1.0,
-             "valu_insts": 2.461e+09, "mfma_insts": 1.868e+08},
-    "batched": {"source": "0592a683fb35", "fetch_kib": 2534941.9, "write_kib": 169489.1, "fetch_scale": 2.0, "write_scale": 1.0,
-               "valu_insts": 4.862e+08, "mfma_insts": 1.97e+07},
+    "whole_layer": {"source": "b641b696cbc9", "fetch_kib": 307025.5, "write_kib": 27534.3, "fetch_scale": 2.0, "write_scale": 1.0,
+                   "valu_insts": 6.879e+07, "mfma_insts": 2.858e+06},
+    "large": {"source": "b641b696cbc9", "fetch_kib": 7749051.5, "write_kib": 687622.3, "fetch_scale": 2.0, "write_scale": 1.0,
+             "valu_insts": 2.43e+09, "mfma_insts": 1.868e+08},
+    "batched": {"source": "b641b696cbc9", "fetch_kib": 2546011.1, "write_kib": 169489.3, "fetch_scale": 2.0, "write_scale": 1.0,
+               "valu_insts": 4.786e+08, "mfma_insts": 1.97e+07},
 }
 
 
