@@ -1017,6 +1017,23 @@ static int chain_points_per_thread(int64_t N, int dp, int spaces, int *groups)
     return 0;
 }
 
+// Whether a chain whose spaces do not fit the chip together is faster in parts, one launch for as many spaces as do, than walked
+// in memory, all spaces side by side.  A part costs 17.5 us of launches and first reads of its rows and 6.8 us a centre (the two exchanges,
+// not the points); the walk 15 us a centre for its two launches and what it moves: state of nine bytes a point and the rows
+// that the bounds leave, 5, 8.5 and 12.5 us a million points at 8, 16 and 32 features (a third more where rows cannot be read 16 bytes at a
+// time).  The walk's figures are those of rows with structure, where most rows are left out; of others it takes up to twice as long.  Chain
+// and one round of a batched sweep, walked and in parts: 64 x (262,144 x 16) knob rows, k = 32 6481 and 4721 us, k = 4 1671 and 1632, k = 2
+// 1216 and 1430; 64 x (20,000 x 16), k = 32 902 and 536, k = 2 184 and 203; 16 x (1,048,576 x 16) 6269 and 4895; 64 x (131,072 x 32) 5023 and
+// 4715; 6 x (300,000 x 32) 1474 and 1682; 8 x (524,288 x 32) 2725 and 2481; 2 x (2M x 8) 1309 and 754; rows without structure 64 x (262,144 x 16)
+// 9137 and 4698, 64 x (262,144 x 8) 5885 and 2590, 64 x (131,072 x 32) 8348 and 4728.
+static bool chain_in_parts_pays(int64_t points, int dp, bool quads, int parts, int centres)
+{
+    if (centres < 1) return false;
+    const double million = (double)points * 1e-6 * (quads ? 1.0 : 4.0 / 3.0);
+    const double walked = 15.0 + million * (dp == 8 ? 5.0 : (dp == 16 ? 8.5 : 12.5));
+    return parts * (17.5 / centres + 6.8) < walked;
+}
+
 static hipError_t launch_chain_in_one(int dp, int p, int spaces, const SeedList &sl, const ChainArgs &a, hipStream_t s)
 {
     if (a.groups > 1) hipLaunchKernelGGL(seed_begin_kernel, dim3(16, spaces), dim3(256), 0, s, sl, a);
@@ -1070,17 +1087,29 @@ hipError_t launch_seed_chain(const float *X, int64_t N, int32_t d, int64_t ldx, 
             continue;
         }
         const int dp = padded_d(d);
-        int groups = 0;
-        if (const int p = chain_points_per_thread(N, dp, nb, &groups)) {
-            ChainArgs ca;
-            ca.X = X + (int64_t)b0 * x_batch_stride; ca.N = N; ca.d = d; ca.ldx = ldx; ca.x_bs = x_batch_stride;
-            ca.j_begin = j_begin; ca.k_max = k_max; ca.groups = groups;
-            ca.mind = reinterpret_cast<double *>(wsb + L.mind); ca.mind_bs = L.per_batch / 8;
-            ca.chain = chain + (int64_t)b0 * chain_batch_stride; ca.chain_bs = chain_batch_stride;
-            ca.ex = reinterpret_cast<unsigned long long *>(wsb + L.colstat_part); ca.ex_bs = L.per_batch / 8;
-            ca.wait_ticks = t_wait_ticks; ca.wait_from = t_wait_from;
-            const hipError_t e = launch_chain_in_one(dp, p, nb, sl, ca, s);
-            if (e != hipSuccess) return e;
+        // all spaces side by side, or as many at a time as the chip holds
+        int at_once = nb, groups = 0, p = 0;
+        while (at_once > 0 && (p = chain_points_per_thread(N, dp, at_once, &groups)) == 0) --at_once;
+        if (p != 0 && at_once < nb) {
+            const bool quads = d % 4 == 0 && ldx % 4 == 0 && x_batch_stride % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+            if (!chain_in_parts_pays(N * nb, dp, quads, (nb + at_once - 1) / at_once, k_max - std::max(j_begin, 1))) p = 0;
+        }
+        if (p != 0) {
+            for (int i0 = 0; i0 < nb; i0 += at_once) {
+                const int64_t first = b0 + i0;
+                const int spaces = std::min(at_once, nb - i0);
+                SeedList part = sl;
+                for (int i = 0; i < spaces; ++i) part.seed[i] = sl.seed[i0 + i];
+                ChainArgs ca;
+                ca.X = X + first * x_batch_stride; ca.N = N; ca.d = d; ca.ldx = ldx; ca.x_bs = x_batch_stride;
+                ca.j_begin = j_begin; ca.k_max = k_max; ca.groups = groups;
+                ca.mind = reinterpret_cast<double *>(ws + first * L.per_batch + L.mind); ca.mind_bs = L.per_batch / 8;
+                ca.chain = chain + first * chain_batch_stride; ca.chain_bs = chain_batch_stride;
+                ca.ex = reinterpret_cast<unsigned long long *>(ws + first * L.per_batch + L.colstat_part); ca.ex_bs = L.per_batch / 8;
+                ca.wait_ticks = t_wait_ticks; ca.wait_from = t_wait_from;
+                const hipError_t e = launch_chain_in_one(dp, p, spaces, part, ca, s);
+                if (e != hipSuccess) return e;
+            }
             continue;
         }
         SeedState st;

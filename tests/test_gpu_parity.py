@@ -343,7 +343,7 @@ def test_seeding_chain_walked_in_memory(rls, orc, N, d, span, stride):
 
 @pytest.mark.parametrize("N,d,gap", [(17001, 16, 0), (33000, 7, 0), (8200, 20, 8), (8200, 20, 6)])
 def test_seeding_chain_of_many_spaces(rls, orc, N, d, gap):
-    """64 spaces that do not fit the chip together are walked in memory, the six after them are one launch; rows that can
+    """64 spaces that do not fit the chip together are drawn in parts, the six after them in one launch; rows that can
     and (spaces 2 floats off) cannot be read 16 bytes at a time in every space."""
     batch, k_max = 70, 6
     rng = np.random.default_rng(N + gap)
@@ -412,6 +412,24 @@ def test_seeding_chain_stages_every_kind_of_rows(rls, orc, d, points):
             np.testing.assert_array_equal(rls.kmeanspp_chain(rows, 5, 8).cpu().numpy(), ref)
         finally:
             rls.lib().rls_seed_wait_limit(ctypes.c_int64(-1))
+
+
+# spaces that fit the chip 25, 51 and one at a time, a last part that is shorter, and two centres, which are walked in memory
+@pytest.mark.parametrize("batch,N,d,k,limit", [(64, 40009, 13, 16, -1), (64, 20011, 16, 24, -1), (64, 20011, 16, 24, 0), (5, 262145, 16, 12, -1), (9, 70001, 32, 20, -1),
+                                               (3, 600007, 13, 30, -1), (66, 20011, 16, 9, -1), (64, 20011, 16, 2, -1), (64, 17003, 7, 2, -1)])
+def test_seeding_of_more_spaces_than_fit_together(rls, batch, N, d, k, limit):
+    """Chains of a batch, one part of its spaces after the other: every space draws what it draws on its own."""
+    gen = torch.Generator(device="cuda").manual_seed(N + k)
+    X = torch.randint(0, 50, (batch, N, d), generator=gen, device="cuda").float()
+    X[:, :, 0] += torch.arange(batch, device="cuda")[:, None]
+    seeds = [1000 + 7 * b for b in range(batch)]
+    try:
+        rls.lib().rls_seed_wait_limit(ctypes.c_int64(limit))
+        got = rls.kmeans_sweep_batched(X, k, k, 0, seeds=seeds, want_labels=False).centroids.view(batch, k, d)
+    finally:
+        rls.lib().rls_seed_wait_limit(ctypes.c_int64(-1))
+    for b in range(batch):
+        assert torch.equal(got[b], X[b][rls.kmeanspp_chain(X[b], k, seeds[b])]), b
 
 
 def exchange_words(ws, k_max):
