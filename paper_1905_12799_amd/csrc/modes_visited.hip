@@ -4,19 +4,24 @@
 // knob_hist_kernel   every workgroup keeps the domain values and a histogram over all domain entries in LDS;
 //                    a thread takes whole rows of the trajectory, finds for every knob the nearest domain entry
 //                    (|x - v| in fp64, first minimum wins, as in the snap kernel; a bisection when the knob's
-//                    entries are sorted) and counts it with an integer LDS atomic, or per entry with a wave
+//                    entries are sorted, of eight knobs side by side) and counts it with an integer LDS atomic, or per entry with a wave
 //                    ballot when the knob has only a few; the workgroup then adds its counts to the global
 //                    histogram (integer atomics: the result does not depend on the order).
-// knob_mode_kernel   one thread per knob: first maximum of its slice of the histogram.
-// visited_scan_kernel / visited_apply_kernel  workgroups compare one sample with a slice of the visited rows and
-//                    flag it; flagged samples are then overwritten with the mode.
+// knob_mode_kernel   one wave per knob: first maximum of its slice of the histogram.
+// visited_scan_kernel / visited_apply_kernel  workgroups compare a slice of the visited rows with up to 64 samples and
+//                    flag those that are among them; flagged samples are then overwritten with the mode.
+//
+// A trajectory of ordinary size is a chain of dependent reads: with one bisection after the other and four rows per thread 100,003 x 16
+// (domains of up to 165 values) took 30 us, and the maximum, found by a thread per knob, 17; now 15 and 4. (8M x 32: 290 us, as before.)
+#include <algorithm>
+
 #include "rls_internal.h"
 
 namespace rls {
 
 namespace {
 
-constexpr int kHistThreads = 256;
+constexpr int kHistThreads = 1024;
 constexpr int kMaxKnobs = RLS_MAX_D;
 
 __global__ void fill_zero_kernel(int32_t *p, int n)
@@ -25,33 +30,21 @@ __global__ void fill_zero_kernel(int32_t *p, int n)
     if (i < n) p[i] = 0;
 }
 
-// nearest entry of vals[lo, hi) to x: |x - v| in fp64, the first minimum wins.  `sorted`: the slice is
-// non-decreasing, so two probes around the lower bound decide; otherwise the slice is scanned.
-__device__ inline int nearest_entry(const float *vals, int lo, int hi, float xf, bool sorted)
+// nearest entry of vals[lo, hi) to x: |x - v| in fp64, the first minimum wins.  Any slice, by a scan.
+__device__ inline int nearest_entry(const float *vals, int lo, int hi, float xf)
 {
     const double x = (double)xf;
-    if (!sorted) {
-        double best = INFINITY;
-        int arg = lo;
-        for (int v = lo; v < hi; ++v) {
-            const double gap = fabs(x - (double)vals[v]);
-            if (gap < best) { best = gap; arg = v; }
-        }
-        return arg;
+    double best = INFINITY;
+    int arg = lo;
+    for (int v = lo; v < hi; ++v) {
+        const double gap = fabs(x - (double)vals[v]);
+        if (gap < best) { best = gap; arg = v; }
     }
-    int a = lo, b = hi;                       // first entry >= x
-    while (a < b) {
-        const int m = (a + b) >> 1;
-        if (vals[m] < xf) a = m + 1; else b = m;
-    }
-    int arg = a < hi ? a : hi - 1;
-    if (a > lo && a < hi) {
-        // entry below against entry at or above: the lower index wins a tie
-        if (fabs(x - (double)vals[a - 1]) <= fabs(x - (double)vals[a])) arg = a - 1;
-    }
-    while (arg > lo && vals[arg - 1] == vals[arg]) --arg;     // equal entries: the first of them
     return arg;
 }
+
+// what is known of a knob's entries
+constexpr int kUnsorted = 1, kRepeats = 2;
 
 __global__ void __launch_bounds__(kHistThreads) knob_hist_kernel(const float *__restrict__ X, int64_t N, int64_t ldx,
                                                                   DomainArgs dm, int n_total, int32_t *__restrict__ hist)
@@ -60,17 +53,17 @@ __global__ void __launch_bounds__(kHistThreads) knob_hist_kernel(const float *__
     float *vals = reinterpret_cast<float *>(smem);                 // [n_total]
     int *cnt = reinterpret_cast<int *>(vals + n_total);            // [n_total]
     __shared__ int offs[kMaxKnobs + 1];
-    __shared__ int unsorted[kMaxKnobs];
+    __shared__ int traits[kMaxKnobs];
     const int tid = threadIdx.x, lane = tid & 63;
     for (int e = tid; e < n_total; e += kHistThreads) { vals[e] = dm.values[e]; cnt[e] = 0; }
     if (tid <= dm.n_knobs) offs[tid] = dm.offsets[tid];
-    if (tid < kMaxKnobs) unsorted[tid] = 0;
+    if (tid < kMaxKnobs) traits[tid] = 0;
     __syncthreads();
     for (int e = tid; e + 1 < n_total; e += kHistThreads) {
-        if (vals[e + 1] < vals[e]) {
-            // a descent inside one knob's slice (not across a boundary) marks that knob as unsorted
+        if (!(vals[e] < vals[e + 1])) {
+            // a descent or a repetition inside one knob's slice (not across a boundary) marks that knob
             for (int j = 0; j < dm.n_knobs; ++j)
-                if (e >= offs[j] && e + 1 < offs[j + 1]) unsorted[j] = 1;
+                if (e >= offs[j] && e + 1 < offs[j + 1]) atomicOr(&traits[j], vals[e + 1] < vals[e] ? kUnsorted : kRepeats);
         }
     }
     __syncthreads();
@@ -87,12 +80,46 @@ __global__ void __launch_bounds__(kHistThreads) knob_hist_kernel(const float *__
             float xv[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) xv[u] = row[min(j0 + u, dm.n_knobs - 1)];
+            // the first entry that is not below the value, of all eight knobs (an unsorted one's is not used)
+            int at[8], left[8], most = 0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int j = min(j0 + u, dm.n_knobs - 1);
+                at[u] = offs[j];
+                left[u] = offs[j + 1] - offs[j];
+                most = max(most, left[u]);
+            }
+            for (; most > 0; most >>= 1) {
+                float mid[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) mid[u] = vals[min(at[u] + (left[u] >> 1), n_total - 1)];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int half = left[u] >> 1;
+                    const bool above = left[u] > 0 && mid[u] < xv[u];
+                    at[u] = above ? at[u] + half + 1 : at[u];
+                    left[u] = above ? left[u] - half - 1 : half;
+                }
+            }
+            // that entry against the one below it: the lower index wins a tie
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int j = min(j0 + u, dm.n_knobs - 1), lo = offs[j], hi = offs[j + 1];
+                const float below = vals[max(at[u] - 1, 0)], here = vals[min(at[u], n_total - 1)];
+                const bool inside = at[u] > lo && at[u] < hi;
+                const bool lower = inside && fabs((double)xv[u] - (double)below) <= fabs((double)xv[u] - (double)here);
+                at[u] = at[u] < hi ? (lower ? at[u] - 1 : at[u]) : hi - 1;
+            }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int j = j0 + u;
                 if (j >= dm.n_knobs) break;              // same for every lane
-                const int lo = offs[j], hi = offs[j + 1];
-                const int arg = valid ? nearest_entry(vals, lo, hi, xv[u], unsorted[j] == 0) : -1;
+                const int lo = offs[j], hi = offs[j + 1], trait = traits[j];
+                int arg = at[u];
+                if (trait & kUnsorted) arg = nearest_entry(vals, lo, hi, xv[u]);
+                else if (trait & kRepeats)
+                    while (arg > lo && vals[arg - 1] == vals[arg]) --arg;     // equal entries: the first of them
+                if (!valid) arg = -1;
                 if (hi - lo <= 8) {
                     // few entries: most lanes would hit the same counters; count per entry with a ballot instead
                     for (int v = lo; v < hi; ++v) {
@@ -112,33 +139,52 @@ __global__ void __launch_bounds__(kHistThreads) knob_hist_kernel(const float *__
 
 __global__ void knob_mode_kernel(DomainArgs dm, const int32_t *__restrict__ hist, int32_t *__restrict__ mode_cfg)
 {
-    const int j = threadIdx.x;
-    if (j >= dm.n_knobs) return;
+    const int j = blockIdx.x, lane = threadIdx.x;
     const int lo = dm.offsets[j], hi = dm.offsets[j + 1];
-    int arg = lo;
-    for (int v = lo + 1; v < hi; ++v)
-        if (hist[v] > hist[arg]) arg = v;
-    mode_cfg[j] = arg - lo;
+    int most = -1, arg = 0;
+    constexpr int U = 4;
+    for (int v0 = lo; v0 < hi; v0 += 64 * U) {
+        int count[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) count[u] = hist[min(v0 + 64 * u + lane, hi - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int v = v0 + 64 * u + lane;
+            if (v < hi && count[u] > most) { most = count[u]; arg = v - lo; }      // (the lane's entries ascend)
+        }
+    }
+    for (int off = 32; off >= 1; off >>= 1) {
+        const int other = __shfl_xor(most, off, 64), oarg = __shfl_xor(arg, off, 64);
+        if (other > most || (other == most && oarg < arg)) { most = other; arg = oarg; }
+    }
+    if (lane == 0) mode_cfg[j] = arg;
 }
 
-// grid (slices of the visited rows, samples): a workgroup compares one sample with its slice of v_Theta
-__global__ void __launch_bounds__(kHistThreads) visited_scan_kernel(const int32_t *__restrict__ cfg, int n_knobs,
-                                                                     const int32_t *__restrict__ visited, int64_t n_visited,
-                                                                     int64_t slice, int32_t *__restrict__ replaced)
+// grid (visited rows, samples): a workgroup compares its rows with up to kScanSamples samples, each row read once; most rows differ in
+// the first knobs already.  (A workgroup per sample and slice of the rows read them once for every sample, 16 after each other per
+// thread: 65,536 rows of 8, 32 samples 8.4 us, 4.0 now.)
+constexpr int kScanThreads = 256, kScanSamples = 64;
+
+__global__ void __launch_bounds__(kScanThreads) visited_scan_kernel(const int32_t *__restrict__ cfg, int k, int n_knobs,
+                                                                    const int32_t *__restrict__ visited, int64_t n_visited,
+                                                                    int32_t *__restrict__ replaced)
 {
-    __shared__ int mine[kMaxKnobs];
-    const int i = blockIdx.y, tid = threadIdx.x;
-    if (tid < n_knobs) mine[tid] = cfg[(int64_t)i * n_knobs + tid];
+    __shared__ int mine[kScanSamples * kMaxKnobs];
+    const int i0 = blockIdx.y * kScanSamples, n = min(kScanSamples, k - i0), tid = threadIdx.x;
+    for (int e = tid; e < n * n_knobs; e += kScanThreads) mine[e] = cfg[(int64_t)i0 * n_knobs + e];
     __syncthreads();
-    const int64_t v0 = (int64_t)blockIdx.x * slice, v1 = min(n_visited, v0 + slice);
-    int hit = 0;
-    for (int64_t v = v0 + tid; v < v1; v += kHistThreads) {
+    for (int64_t v = (int64_t)blockIdx.x * kScanThreads + tid; v < n_visited; v += (int64_t)gridDim.x * kScanThreads) {
         const int32_t *row = visited + v * n_knobs;
-        int same = 1;
-        for (int j = 0; j < n_knobs; ++j) same &= (row[j] == mine[j]) ? 1 : 0;
-        hit |= same;
+        const int last = n_knobs - 1;
+        const int r0 = row[0], r1 = row[min(1, last)], r2 = row[min(2, last)], r3 = row[min(3, last)];
+        for (int i = 0; i < n; ++i) {
+            const int *const m = mine + i * n_knobs;
+            bool same = r0 == m[0] && r1 == m[min(1, last)] && r2 == m[min(2, last)] && r3 == m[min(3, last)];
+            if (!same) continue;
+            for (int j = 4; j < n_knobs; ++j) same &= row[j] == m[j];
+            if (same) atomicOr(&replaced[i0 + i], 1);
+        }
     }
-    if (__ballot(hit != 0) != 0ull && (tid & 63) == 0) atomicOr(&replaced[i], 1);
 }
 
 // one thread per (sample, knob): visited samples take the mode
@@ -179,15 +225,15 @@ hipError_t launch_knob_modes(const float *X, int64_t N, int64_t ldx, const Domai
     hipLaunchKernelGGL(fill_zero_kernel, dim3((n_total + 255) / 256), dim3(256), 0, s, hist, (int)n_total);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // enough workgroups to fill the chip a few times; each row costs n_knobs short scans
-    int64_t blocks = (N + kHistThreads * 4 - 1) / (kHistThreads * 4);
-    if (blocks > 2048) blocks = 2048;
-    if (blocks < 1) blocks = 1;
+    // a row per thread as long as the chip has room for that, then four, then enough to fill it twice.  (Large workgroups: all add
+    // their counts to the same few entries, one after the other.)
+    const int64_t one = (N + kHistThreads - 1) / kHistThreads;
+    const int64_t blocks = std::min<int64_t>(std::max<int64_t>(std::min<int64_t>(one, 256), (one + 3) / 4), 512);
     const size_t lds = (size_t)n_total * 8;
     hipLaunchKernelGGL(knob_hist_kernel, dim3((unsigned)blocks), dim3(kHistThreads), lds, s, X, N, ldx, dm, (int)n_total, hist);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(knob_mode_kernel, dim3(1), dim3(64), 0, s, dm, hist, mode_cfg);
+    hipLaunchKernelGGL(knob_mode_kernel, dim3((unsigned)dm.n_knobs), dim3(64), 0, s, dm, hist, mode_cfg);
     return hipGetLastError();
 }
 
@@ -197,14 +243,11 @@ hipError_t launch_replace_visited(int32_t *cfg, int32_t k, int32_t n_knobs, cons
     hipLaunchKernelGGL(fill_zero_kernel, dim3((k + 255) / 256), dim3(256), 0, s, replaced, (int)k);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || n_visited == 0) return e;
-    // slices of at least 4096 rows, at most ~1024 workgroups in all
-    int64_t slices = (n_visited + 4095) / 4096;
-    const int64_t cap = (1024 + k - 1) / k;
-    if (slices > cap) slices = cap;
-    if (slices < 1) slices = 1;
-    const int64_t slice = (n_visited + slices - 1) / slices;
-    hipLaunchKernelGGL(visited_scan_kernel, dim3((unsigned)slices, (unsigned)k), dim3(kHistThreads), 0, s, cfg, (int)n_knobs,
-                       visited, n_visited, slice, replaced);
+    // a row per thread up to some 1024 workgroups in all (k is at most 65535)
+    const unsigned batches = (unsigned)((k + kScanSamples - 1) / kScanSamples);
+    const unsigned rows = (unsigned)std::min<int64_t>((n_visited + kScanThreads - 1) / kScanThreads, std::max(1024u / batches, 4u));
+    hipLaunchKernelGGL(visited_scan_kernel, dim3(rows, batches), dim3(kScanThreads), 0, s, cfg, (int)k, (int)n_knobs, visited, n_visited,
+                       replaced);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(visited_apply_kernel, dim3((k * n_knobs + 255) / 256), dim3(256), 0, s, cfg, (int)k, (int)n_knobs,

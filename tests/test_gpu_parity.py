@@ -173,6 +173,46 @@ def test_snap_irregular_domains_and_batched(rls, orc):
         np.testing.assert_array_equal(got[b], orc.snap_to_valid(Cs[b], *doms[b]))
 
 
+# sizes around the lanes of a wave and the values it reads at a time; more knobs than are searched side by side; rows around a workgroup's
+@pytest.mark.parametrize("sizes,n,order", [([1, 2, 3, 8, 9, 63, 64, 65, 127], 257, "sorted"), ([255, 256, 257, 300, 1000], 1023, "sorted"),
+                                           ([511, 513, 5, 1, 70, 64, 33, 17, 9, 2, 40], 255, "shuffled"), ([64, 300, 9, 8], 131073, "repeats"), ([220], 1, "sorted")])
+def test_nearest_entries_over_domain_sizes(rls, orc, sizes, n, order):
+    """Snap, histogram and mode: nearest entry and first of equal ones, whichever lane or step has them."""
+    rng = np.random.default_rng(sum(sizes) + n)
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    parts = [np.sort(rng.permutation(4 * s)[:s]).astype(np.float32) for s in sizes]
+    if order == "repeats":
+        parts = [np.sort(rng.integers(0, max(2, s // 3), s)).astype(np.float32) for s in sizes]
+    if order == "shuffled":
+        parts = [rng.permutation(q) for q in parts]
+    values = np.concatenate(parts)
+    X = (rng.integers(-4, 8 * np.array(sizes) + 4, size=(n, len(sizes))) * 0.5).astype(np.float32)      # half-way cases among them
+    dom = rls.DeviceDomains(offsets, values)
+    mode, hist = rls.knob_modes(dev(X), dom)
+    mode_o, hist_o = orc.knob_modes(X, offsets, values)
+    np.testing.assert_array_equal(hist.cpu().numpy().astype(np.int64), hist_o)
+    np.testing.assert_array_equal(mode.cpu().numpy(), mode_o)
+    C = X[:300].copy()
+    C[:1, 0], C[1:2, 0], C[2:3, 0] = np.nan, np.inf, -np.inf
+    np.testing.assert_array_equal(rls.snap_to_valid(dev(C), dom).cpu().numpy(), orc.snap_to_valid(C, offsets, values))
+
+
+@pytest.mark.parametrize("k,knobs,n", [(1, 1, 1), (64, 3, 255), (65, 4, 257), (130, 5, 70001), (3, 9, 300000)])
+def test_visited_over_samples_and_knobs(rls, orc, k, knobs, n):
+    """Samples around those of a workgroup, rows of fewer and more knobs than are compared first, several rows per thread."""
+    rng = np.random.default_rng(k + n)
+    top = max(2, int(round(n ** (1.0 / knobs))) + 1)
+    visited = rng.integers(0, top, (n, knobs)).astype(np.int32)
+    cfg = rng.integers(0, top, (k, knobs)).astype(np.int32)
+    cfg[-1] = visited[-1]
+    mode = np.full(knobs, top, dtype=np.int32)
+    got = dev(cfg)
+    flags = rls.replace_visited(got, dev(visited), dev(mode)).cpu().numpy()
+    want, want_flags = orc.replace_visited(cfg, visited, mode)
+    np.testing.assert_array_equal(flags, want_flags)
+    np.testing.assert_array_equal(got.cpu().numpy(), want)
+
+
 # ----------------------------------------------------------------------------------------------
 @pytest.mark.parametrize("name,N", [("tiny", None), ("mid", 50001), ("large", 20000)])
 def test_knob_modes_match_oracle(rls, orc, name, N):
