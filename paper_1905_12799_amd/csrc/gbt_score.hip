@@ -27,8 +27,16 @@ namespace {
 
 constexpr int kScoreThreads = 1024;
 constexpr int kScoreLds = 160 * 1024;
-constexpr int kStageQuads = 3;                                         // groups of four nodes a thread carries in registers for the next chunk
-constexpr int kChunkNodes = 4 * kStageQuads * kScoreThreads;           // nodes of a chunk at most (96 KB)
+constexpr int kChunkNodes = 12 * kScoreThreads;                        // nodes of a chunk at most (96 KB)
+// Where four slices share the trees, the first one adds the leaf values of a chunk while the others move the next chunk's nodes, if a chunk
+// has many trees.  (When all moved nodes and the first then added, the others waited for it: 65,536 x 8, 256 trees of depth 8, 48 a chunk 41.2 ->
+// 39.9 us, 60,000 x 16 41.9 -> 40.9; chunks of few trees are more to move than to add: 50,000 x 32, depth 10, 8 a chunk 67.6 -> 71.6.  With two
+// slices one of them moves too slowly, 100,003 x 32 of depth 10 114 -> 130; with eight or more the others gain nothing, 30,000 x 32 34.9 -> 37.1.)
+constexpr int kApartTile = 256, kApartTrees = 32;
+// (a kernel of its own: with the choice at run time the chunks of few trees were 3% slower)
+// groups of four nodes a thread carries in registers for the next chunk
+constexpr int stage_quads_of(bool apart) { return apart ? 4 : 3; }
+static_assert(4 * 3 * kScoreThreads >= kChunkNodes && 4 * 4 * (kScoreThreads - kApartTile) >= kChunkNodes, "a chunk fits the registers of those that move it");
 constexpr int kScoreBatch = 64;                                        // forests per launch (they travel as kernel arguments)
 
 struct ForestBatch {
@@ -49,7 +57,7 @@ __device__ inline void lds_write_u4(unsigned a, uint4v v) { *(__attribute__((add
 // P configurations per tile, 1024 / P slices of the trees, W trees walked side by side by a thread.
 // `quads`: the forests' node arrays start at multiples of 16 bytes and the chunks at multiples of four trees, so that a
 // chunk of a multiple of four trees is moved four nodes at a time.
-template <int P, int W>
+template <int P, int W, bool APART = false>
 __global__ void __launch_bounds__(kScoreThreads) gbt_score_kernel(ForestBatch fb, const float *__restrict__ Xall, int64_t N, int d, int64_t ldx,
                                                                   int64_t x_bs, float *__restrict__ score, int trees_per_chunk, int quads)
 {
@@ -90,19 +98,21 @@ __global__ void __launch_bounds__(kScoreThreads) gbt_score_kernel(ForestBatch fb
     // The next chunk of the forest travels in registers while the current one is walked: its loads are issued
     // before the walk (offsets clamped to the chunk) and written to LDS after it.  Every offset is a 32-bit byte
     // offset from the chunk's start in its array; staging costs a few instructions per node.
-    constexpr int E = 4 * kStageQuads;
+    constexpr int Q = stage_quads_of(APART), E = 4 * Q, M = APART ? kScoreThreads - P : kScoreThreads;
+    const int mover = APART ? tid - P : tid;                                    // (negative: a thread of the slice that adds)
     int st_feat[E];
     float st_thr[E];
     auto fetch_chunk = [&](int t0, int tc) {
+        if (APART && mover < 0) return;
         const unsigned n_nodes = (unsigned)(tc * n_int);
         const char *const fc = reinterpret_cast<const char *>(f.feat + (size_t)t0 * n_int);
         const char *const hc = reinterpret_cast<const char *>(f.thr + (size_t)t0 * n_int);
         if (quads && (tc & 3) == 0) {
             const unsigned last_n = n_nodes * 4u - 16u;
 #pragma unroll
-            for (int i = 0; i < kStageQuads; ++i) {
-                if ((unsigned)(4 * i * kScoreThreads) >= n_nodes) break;        // same for the whole workgroup
-                const unsigned on = min((unsigned)(tid + i * kScoreThreads) * 16u, last_n);
+            for (int i = 0; i < Q; ++i) {
+                if ((unsigned)(4 * i * M) >= n_nodes) break;        // same for the whole workgroup
+                const unsigned on = min((unsigned)(mover + i * M) * 16u, last_n);
                 const int4 a = *reinterpret_cast<const int4 *>(fc + on);
                 const float4 h = *reinterpret_cast<const float4 *>(hc + on);
                 st_feat[4 * i + 0] = a.x; st_feat[4 * i + 1] = a.y; st_feat[4 * i + 2] = a.z; st_feat[4 * i + 3] = a.w;
@@ -112,8 +122,8 @@ __global__ void __launch_bounds__(kScoreThreads) gbt_score_kernel(ForestBatch fb
             const unsigned last_n = n_nodes * 4u - 4u;
 #pragma unroll
             for (int i = 0; i < E; ++i) {
-                if ((unsigned)(i * kScoreThreads) >= n_nodes) break;
-                const unsigned on = min((unsigned)(tid + i * kScoreThreads) * 4u, last_n);
+                if ((unsigned)(i * M) >= n_nodes) break;
+                const unsigned on = min((unsigned)(mover + i * M) * 4u, last_n);
                 st_feat[i] = *reinterpret_cast<const int *>(fc + on);
                 st_thr[i] = *reinterpret_cast<const float *>(hc + on);
             }
@@ -122,11 +132,12 @@ __global__ void __launch_bounds__(kScoreThreads) gbt_score_kernel(ForestBatch fb
     // a node in LDS: (LDS address of its feature's row of the tile, threshold bits)
     auto row_of = [&](int ft) { return lds0 + (unsigned)min(max(ft, 0), d - 1) * (unsigned)(P * 4); };
     auto store_chunk = [&](int tc) {
+        if (APART && mover < 0) return;
         const unsigned nodes_end = (unsigned)(tc * n_int) * 8u;
         if (quads && (tc & 3) == 0) {
 #pragma unroll
-            for (int i = 0; i < kStageQuads; ++i) {
-                const unsigned g = (unsigned)(tid + i * kScoreThreads);
+            for (int i = 0; i < Q; ++i) {
+                const unsigned g = (unsigned)(mover + i * M);
                 if (g * 32u < nodes_end) {
                     uint4v lo, hi;
                     lo.x = row_of(st_feat[4 * i + 0]); lo.y = __float_as_uint(st_thr[4 * i + 0]);
@@ -140,7 +151,7 @@ __global__ void __launch_bounds__(kScoreThreads) gbt_score_kernel(ForestBatch fb
         } else {
 #pragma unroll
             for (int i = 0; i < E; ++i) {
-                const unsigned e = (unsigned)(tid + i * kScoreThreads);
+                const unsigned e = (unsigned)(mover + i * M);
                 if (e * 8u < nodes_end) {
                     uint2v n;
                     n.x = row_of(st_feat[i]); n.y = __float_as_uint(st_thr[i]);
@@ -266,6 +277,9 @@ hipError_t launch_gbt_score(const ForestArgs *forests_host, int32_t batch, const
             for (const Kernel k : t.kernel)
                 if (attr_status == hipSuccess)
                     attr_status = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kScoreLds);
+        if (attr_status == hipSuccess)
+            attr_status = hipFuncSetAttribute(reinterpret_cast<const void *>(gbt_score_kernel<kApartTile, 4, true>),
+                                              hipFuncAttributeMaxDynamicSharedMemorySize, kScoreLds);
     });
     if (attr_status != hipSuccess) return attr_status;
     for (int32_t b0 = 0; b0 < batch;) {
@@ -312,7 +326,9 @@ hipError_t launch_gbt_score(const ForestArgs *forests_host, int32_t batch, const
         }
         if (best.tile == nullptr) return hipErrorInvalidValue;     // depth <= 12: cannot happen
         const int quads = (best.tpc % 4 == 0 || best.tpc == n_trees) && (bits & 15) == 0;
-        const Kernel kernel = best.tile->kernel[best.side == 8 ? 0 : (best.side == 4 ? 1 : (best.side == 2 ? 2 : 3))];
+        const bool apart = best.tile->tile == kApartTile && best.side == 4 && best.tpc >= kApartTrees && best.tpc < n_trees;
+        const Kernel kernel = apart ? gbt_score_kernel<kApartTile, 4, true>
+                                    : best.tile->kernel[best.side == 8 ? 0 : (best.side == 4 ? 1 : (best.side == 2 ? 2 : 3))];
         const unsigned grid = (unsigned)((N + best.tile->tile - 1) / best.tile->tile);
         hipLaunchKernelGGL(kernel, dim3(grid, (unsigned)nb), dim3(kScoreThreads), best.lds, s, fb, X + (int64_t)b0 * x_batch_stride, N, (int)d,
                            ldx, x_batch_stride, score + (int64_t)b0 * N, best.tpc, quads);

@@ -77,6 +77,15 @@ def test_gbt_score_tiles_and_slices(rls, orc, N, d, T, D):
     check_scores(rls, orc, f, X)
 
 
+# tiles of 256: a slice that adds while the others move (32 and more trees a chunk), last chunks of 6 and 3 trees, and the fewest nodes
+@pytest.mark.parametrize("N,d,T,D", [(60001, 8, 150, 8), (50003, 16, 99, 8), (65000, 8, 200, 6), (64999, 24, 130, 7)])
+def test_gbt_score_slice_that_adds(rls, orc, N, d, T, D):
+    rng = np.random.default_rng(N + T)
+    X = rng.standard_normal((N, d)).astype(np.float32)
+    f = synth.random_forest(X, T, D, 0, rng)
+    check_scores(rls, orc, f, X)
+
+
 def test_gbt_score_batched_forests_of_different_shapes(rls, orc):
     """Spaces whose forests share a shape go into one launch (at most 64 of them), the others into launches of their own."""
     rng = np.random.default_rng(5)
