@@ -1663,14 +1663,28 @@ struct ColPart {
 
 static_assert(kStatBlocks * 32 * sizeof(ColPart) >= kSeedExchangeBytes, "the seeding chain's exchange area lies in this block");
 
-__global__ void __launch_bounds__(kThreads) colstats_kernel(const float *__restrict__ X, int64_t N, int d, int dp, int64_t ldx,
-                                                           int64_t x_bs, char *ws, int64_t ws_bs, int64_t off_part)
+__device__ inline void add_part(ColPart &t, const ColPart &o)
 {
-    __shared__ ColPart sh[kThreads];
+    t.sum = __dadd_rn(t.sum, o.sum);
+    t.sumsq += o.sumsq;
+    t.min_lsb = min(t.min_lsb, o.min_lsb);
+    t.max_msb = max(t.max_msb, o.max_msb);
+    t.bad |= o.bad;
+    t.vmin = fminf(t.vmin, o.vmin);
+    t.vmax = fmaxf(t.vmax, o.vmax);
+}
+
+// A thread takes one column of every 1024 / dp-th row.  What bounds it is the work per value and the waves that hide its loads: without a
+// branch per value, the highest bit taken once from the extremes, and 16 waves per workgroup instead of 8.  (1M x 16 32 -> 22 us, 300,007 x 13 12.1 -> 10.0.)
+constexpr int kStatThreads = 1024;
+__global__ void __launch_bounds__(kStatThreads) colstats_kernel(const float *__restrict__ X, int64_t N, int d, int dp, int64_t ldx,
+                                                               int64_t x_bs, char *ws, int64_t ws_bs, int64_t off_part)
+{
+    __shared__ ColPart sh[kStatThreads];
     const int b = blockIdx.y;
     const float *Xb = X + (int64_t)b * x_bs;
     const int tid = threadIdx.x;
-    const int l = tid % dp, pg = tid / dp, ppp = kThreads / dp;
+    const int l = tid % dp, pg = tid / dp, ppp = kStatThreads / dp;
     const int64_t per = (N + gridDim.x - 1) / gridDim.x;
     const int64_t r0 = (int64_t)blockIdx.x * per, r1 = min(N, r0 + per);
     ColPart c = {0.0, 1 << 20, -(1 << 20), 0, 0, INFINITY, -INFINITY, 0.0};
@@ -1687,36 +1701,34 @@ __global__ void __launch_bounds__(kThreads) colstats_kernel(const float *__restr
                 if (rb + (int64_t)u * ppp >= r1) continue;
                 const float x = xs[u];
                 const unsigned bits = __float_as_uint(x);
-                int e = (int)((bits >> 23) & 0xffu);
-                unsigned m = bits & 0x7fffffu;
-                if (e == 255) { c.bad = 1; continue; }
+                const int e = (int)((bits >> 23) & 0xffu);
+                c.bad |= e == 255 ? 1 : 0;                   // (nothing else of such a column is used)
                 c.sum = __dadd_rn(c.sum, (double)x);
                 c.sumsq = fma((double)x, (double)x, c.sumsq);
                 c.vmin = fminf(c.vmin, x);
                 c.vmax = fmaxf(c.vmax, x);
-                if (e == 0) { if (m == 0) continue; e = 1; } else m |= 0x800000u;
-                const int lsb = e - 150 + (__ffs((int)m) - 1);
-                const int msb = e - 150 + (31 - __clz((int)m));
-                c.min_lsb = min(c.min_lsb, lsb);
-                c.max_msb = max(c.max_msb, msb);
+                const unsigned m = (bits & 0x7fffffu) | (e != 0 ? 0x800000u : 0u);
+                const int lsb = max(e, 1) - 151 + __ffs((int)m);
+                c.min_lsb = min(c.min_lsb, m != 0u ? lsb : 1 << 20);
             }
+        }
+        const unsigned far = max(__float_as_uint(fabsf(c.vmin)), __float_as_uint(fabsf(c.vmax)));      // (of no values: infinity, and a column of them is bad)
+        if (r0 + pg < r1 && (far & 0x7fffffffu) != 0u) {
+            const int e = (int)(far >> 23);
+            c.max_msb = e != 0 ? e - 127 : (31 - __clz((int)far)) - 149;
         }
     }
     sh[tid] = c;
     __syncthreads();
+    // eight threads per column add up an eighth each, then one of them the eight (in a fixed order)
+    if (tid < 8 * dp) {
+        for (int g = tid + 8 * dp; g < kStatThreads; g += 8 * dp) add_part(c, sh[g]);
+        sh[tid] = c;
+    }
+    __syncthreads();
     if (tid < dp) {
-        ColPart t = sh[tid];
-        for (int g = 1; g < ppp; ++g) {
-            const ColPart o = sh[g * dp + tid];
-            t.sum = __dadd_rn(t.sum, o.sum);
-            t.sumsq += o.sumsq;
-            t.min_lsb = min(t.min_lsb, o.min_lsb);
-            t.max_msb = max(t.max_msb, o.max_msb);
-            t.bad |= o.bad;
-            t.vmin = fminf(t.vmin, o.vmin);
-            t.vmax = fmaxf(t.vmax, o.vmax);
-        }
-        reinterpret_cast<ColPart *>(ws + (int64_t)b * ws_bs + off_part)[blockIdx.x * 32 + tid] = t;
+        for (int g = 1; g < 8; ++g) add_part(c, sh[g * dp + tid]);
+        reinterpret_cast<ColPart *>(ws + (int64_t)b * ws_bs + off_part)[blockIdx.x * 32 + tid] = c;
     }
 }
 
@@ -2554,13 +2566,13 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
     const int64_t n_units = (a.N + 32 * unit_blocks_of(DP) - 1) / (32 * unit_blocks_of(DP));
     // column statistics
     if (!a.reuse_colstats) {
-        hipLaunchKernelGGL(colstats_kernel, dim3(L.stat_blocks, batch), dim3(kThreads), 0, s, a.X, a.N, (int)a.d, DP, a.ldx,
+        hipLaunchKernelGGL(colstats_kernel, dim3(L.stat_blocks, batch), dim3(kStatThreads), 0, s, a.X, a.N, (int)a.d, DP, a.ldx,
                            a.x_batch_stride, a.ws, L.per_batch, L.colstat_part);
         hipLaunchKernelGGL(colstats_final_kernel, dim3(batch), dim3(256), 0, s, a.N, (int)a.d, (int)L.stat_blocks, a.ws,
                            L.per_batch, L.colstat_part, L.colinfo, plan.ordered ? L.keyinfo : (int64_t)-1, a.status);
     }
     if (ordered && !a.reuse_prepared) {
-        const hipError_t e = launch_order(a.X, a.N, a.ldx, a.x_batch_stride, batch, a.status, a.ws, L.per_batch, L.keyinfo, L.perm, L.inv, L.xs,
+        const hipError_t e = launch_order(a.X, a.N, a.d, a.ldx, a.x_batch_stride, batch, a.status, a.ws, L.per_batch, L.keyinfo, L.perm, L.inv, L.xs,
                                           unit_blocks_of(DP) == 2 ? 6 : 5, s);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((lloyd_prepare_ordered_kernel<DP>), dim3((unsigned)ordered_prepare_grid(n_units), batch), dim3(256), 0, s, a.X, a.N,

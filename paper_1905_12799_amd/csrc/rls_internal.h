@@ -212,7 +212,7 @@ struct OrderSpread {
 };
 OrderSpread order_spread(int64_t N, int unit_shift);
 int64_t order_scratch_bytes(int64_t N);
-hipError_t launch_order(const float *X, int64_t N, int64_t ldx, int64_t x_batch_stride, int32_t batch, const int32_t *status, char *ws,
+hipError_t launch_order(const float *X, int64_t N, int32_t d, int64_t ldx, int64_t x_batch_stride, int32_t batch, const int32_t *status, char *ws,
                         int64_t ws_bs, int64_t off_keyinfo, int64_t off_perm, int64_t off_inv, int64_t off_scratch, int unit_shift, hipStream_t s);
 // whether the rounds after the first of such a sweep read the prepared copy of the points
 bool sweep_uses_prepared(const SweepPlan &plan, int32_t iters, bool trace);
