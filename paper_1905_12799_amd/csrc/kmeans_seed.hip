@@ -8,8 +8,8 @@
 // blocks) in a fixed order, so a chain is reproducible run to run.
 //
 // Two forms.  Up to about a million points the whole chain is one launch with the points in registers
-// (seed_chain_kernel).  More points, or more spaces than compute units, are walked in memory, one update and one draw
-// launch per centre:
+// (seed_chain_kernel); a batch that does not fit together goes in parts of as many spaces as fit, where that pays
+// (chain_in_parts_pays).  More points, and the other batches, are walked in memory, one update and one draw launch per centre:
 // Most rows are never read after the first steps: with each point the position a_i of its nearest centre is kept, and
 // when centre c is added a point with D_i <= |c_{a_i} - c|^2 / 4 cannot come closer to c than it is to c_{a_i}
 // (triangle inequality: |x_i - c| >= |c_{a_i} - c| - |x_i - c_{a_i}| >= sqrt(D_i)), so D_i stays and the row is not
