@@ -34,6 +34,8 @@ int32_t rls_seed_wait_limit_from(int32_t first_workgroup, int64_t ticks);
  * lists occur: byte offset and number of 32-bit words (0: the sweep takes the points as they come).  Per group with lists and
  * unit of points 16 words; the four highest bits of each of the first eight are the number of tiles the unit meets, less one. */
 int32_t rls_sweep_tile_lists(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int64_t *offset_out, int64_t *words_out);
+/* Lanes that rls_snap_to_valid_batched puts on a (centroid, knob): 64, or 1 where there are many of them. */
+int32_t rls_snap_lanes(int32_t batch, int32_t k, int32_t n_knobs);
 /* `n` single matrix instructions (32 x 32 x 16, fp16 or bf16 operands, fp32 accumulators) on operands as the kernels hold them, for
  * tests of what the instruction leaves out of a sum:
  *   a_dev, b_dev  [n][64 lanes][8] 16-bit elements: lane l holds those of row (column) l % 32, k = 8 (l / 32) .. + 7; 16-byte aligned

@@ -207,6 +207,12 @@ int32_t rls_sweep_tile_lists(int64_t N, int32_t d, int32_t k_min, int32_t k_max,
     return RLS_OK;
 }
 
+int32_t rls_snap_lanes(int32_t batch, int32_t k, int32_t n_knobs)
+{
+    if (batch < 1 || batch > RLS_MAX_BATCH || k < 1 || n_knobs < 1 || n_knobs > RLS_MAX_D) return RLS_ERR_INVALID_ARG;
+    return snap_lanes(batch, k, n_knobs);
+}
+
 int32_t rls_kmeanspp_chain(const float *X_dev, int64_t N, int32_t d, int64_t ldx, int32_t k_max, uint64_t seed,
                            int64_t *init_idx_dev, void *workspace_dev, int64_t workspace_bytes, void *stream)
 {

@@ -148,6 +148,7 @@ struct DomainArgs {
 };
 hipError_t launch_snap(const DomainArgs *domains_host, int32_t batch, const float *C, int32_t k, int32_t d, int64_t ldc,
                        int64_t c_batch_stride, int32_t *cfg, hipStream_t s);
+int32_t snap_lanes(int32_t batch, int32_t k, int32_t n_knobs);     // lanes per (centroid, knob): 64 or 1
 
 hipError_t launch_knob_modes(const float *X, int64_t N, int64_t ldx, const DomainArgs &dm, int32_t n_total,
                              int32_t *mode_cfg, int32_t *hist, hipStream_t s);

@@ -182,6 +182,28 @@ def test_snap_irregular_domains_and_batched(rls, orc):
         np.testing.assert_array_equal(got[b], orc.snap_to_valid(Cs[b], *doms[b]))
 
 
+# either side of the number of pairs that a wave each takes, one space and more than a launch holds; knobs that do not divide a workgroup;
+# so many rows that a workgroup takes several turns, and a wave each would be a launch of 2^32 threads
+SNAP_ROWS = [(1, 4096, 8, 64), (1, 4097, 8, 1), (1, 1025, 32, 1), (1, 32769, 1, 1), (64, 64, 8, 64), (66, 65, 8, 1), (3, 2999, 5, 1), (1, 1 << 23, 8, 1)]
+
+
+@pytest.mark.parametrize("batch,k,knobs,lanes", SNAP_ROWS)
+def test_snap_of_few_and_of_many_rows(rls, orc, batch, k, knobs, lanes):
+    assert rls.lib().rls_snap_lanes(batch, k, knobs) == lanes
+    rng = np.random.default_rng(k + knobs)
+    doms = []
+    for _ in range(batch):
+        sizes = [2, 3, 9, 17] if k < 1 << 20 else [2, 3]
+        sizes = (sizes * 8)[:knobs]
+        parts = [rng.permutation(rng.integers(0, 2 * s, s)).astype(np.float32) for s in sizes]
+        doms.append((np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32), np.concatenate(parts)))
+    C = (rng.integers(-4, 36, size=(batch, k, min(knobs + 1, 32)), dtype=np.int8) * np.float32(0.5)).astype(np.float32)
+    C[:, 0, 0], C[:, 1, 0], C[:, -1, 0] = np.nan, np.inf, -np.inf
+    got = rls.snap_to_valid_batched(dev(C), [rls.DeviceDomains(*dom) for dom in doms]).cpu().numpy()
+    for b in range(batch):
+        np.testing.assert_array_equal(got[b], orc.snap_to_valid(C[b], *doms[b]))
+
+
 # sizes around the lanes of a wave and the values it reads at a time; more knobs than are searched side by side; rows around a workgroup's
 @pytest.mark.parametrize("sizes,n,order", [([1, 2, 3, 8, 9, 63, 64, 65, 127], 257, "sorted"), ([255, 256, 257, 300, 1000], 1023, "sorted"),
                                            ([511, 513, 5, 1, 70, 64, 33, 17, 9, 2, 40], 255, "shuffled"), ([64, 300, 9, 8], 131073, "repeats"), ([220], 1, "sorted")])
