@@ -244,6 +244,49 @@ def test_visited_over_samples_and_knobs(rls, orc, k, knobs, n):
     np.testing.assert_array_equal(got.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("k,knobs,n", [(64, 8, 100001), (130, 3, 5000), (7, 4, 300)])
+def test_visited_rows_that_repeat(rls, orc, k, knobs, n):
+    """Every other row is one configuration, which every third sample has: found by many waves, again and again."""
+    rng = np.random.default_rng(k + n)
+    visited = rng.integers(0, 40, (n, knobs)).astype(np.int32)
+    cfg = rng.integers(40, 80, (k, knobs)).astype(np.int32)
+    visited[::2] = 7
+    cfg[::3] = 7
+    cfg[1, :min(4, knobs)] = 7                   # (agrees in what is compared first)
+    if knobs <= 4:
+        cfg[1, -1] = 85
+    mode = np.full(knobs, 90, dtype=np.int32)
+    got = dev(cfg)
+    flags = rls.replace_visited(got, dev(visited), dev(mode)).cpu().numpy()
+    want, want_flags = orc.replace_visited(cfg, visited, mode)
+    np.testing.assert_array_equal(flags, want_flags)
+    np.testing.assert_array_equal(got.cpu().numpy(), want)
+    assert want_flags.sum() == (k + 2) // 3
+
+
+def test_visited_rows_that_repeat_form_no_queue(rls):
+    """A history of one configuration that all samples have: some five times as long as one that none has (waves that all wrote to the
+    samples' flags took 170 times as long)."""
+    visited = torch.full((1000000, 8), 7, dtype=torch.int32, device="cuda")
+    mode = torch.full((8,), 7, dtype=torch.int32, device="cuda")
+
+    def shortest(value):
+        cfg = torch.full((64, 8), value, dtype=torch.int32, device="cuda")
+        times = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(8):
+                flags = rls.replace_visited(cfg, visited, mode if value == 7 else cfg[0])
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+            assert bool((flags == (1 if value == 7 else 0)).all())
+        return min(times)
+
+    assert shortest(7) < 25 * shortest(9)
+
+
 # ----------------------------------------------------------------------------------------------
 @pytest.mark.parametrize("name,N", [("tiny", None), ("mid", 50001), ("large", 20000)])
 def test_knob_modes_match_oracle(rls, orc, name, N):
