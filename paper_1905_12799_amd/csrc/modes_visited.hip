@@ -4,7 +4,7 @@
 // knob_hist_kernel   every workgroup keeps the domain values and a histogram over all domain entries in LDS;
 //                    a thread takes whole rows of the trajectory, finds for every knob the nearest domain entry
 //                    (|x - v| in fp64, first minimum wins, as in the snap kernel; a bisection when the knob's
-//                    entries are sorted, of eight knobs side by side) and counts it with an integer LDS atomic, or per entry with a wave
+//                    entries are sorted, of eight knobs side by side where there are few rows) and counts it with an integer LDS atomic, or per entry with a wave
 //                    ballot when the knob has only a few; the workgroup then adds its counts to the global
 //                    histogram (integer atomics: the result does not depend on the order).
 // knob_mode_kernel   one wave per knob: first maximum of its slice of the histogram.
@@ -12,7 +12,7 @@
 //                    flag those that are among them; flagged samples are then overwritten with the mode.
 //
 // A trajectory of ordinary size is a chain of dependent reads: with one bisection after the other and four rows per thread 100,003 x 16
-// (domains of up to 165 values) took 30 us, and the maximum, found by a thread per knob, 17; now 15 and 4. (8M x 32: 290 us, as before.)
+// (domains of up to 165 values) took 30 us, and the maximum, found by a thread per knob, 17; now 15 and 4.  A large one is work instead: see kHistSideRows.
 #include <algorithm>
 
 #include "rls_internal.h"
@@ -21,7 +21,6 @@ namespace rls {
 
 namespace {
 
-constexpr int kHistThreads = 1024;
 constexpr int kMaxKnobs = RLS_MAX_D;
 
 __global__ void fill_zero_kernel(int32_t *p, int n)
@@ -31,7 +30,7 @@ __global__ void fill_zero_kernel(int32_t *p, int n)
 }
 
 // nearest entry of vals[lo, hi) to x: |x - v| in fp64, the first minimum wins.  Any slice, by a scan.
-__device__ inline int nearest_entry(const float *vals, int lo, int hi, float xf)
+__device__ inline int scanned_entry(const float *vals, int lo, int hi, float xf)
 {
     const double x = (double)xf;
     double best = INFINITY;
@@ -43,27 +42,53 @@ __device__ inline int nearest_entry(const float *vals, int lo, int hi, float xf)
     return arg;
 }
 
+// The same of a slice that does not descend, by a bisection; where entries repeat, any of those that equal it.
+__device__ inline int bisected_entry(const float *vals, int lo, int hi, float xf)
+{
+    int a = lo, b = hi;                       // first entry >= x
+    while (a < b) {
+        const int m = (a + b) >> 1;
+        if (vals[m] < xf) a = m + 1; else b = m;
+    }
+    if (a == hi) return hi - 1;
+    // entry below against entry at or above: the lower index wins a tie
+    return a > lo && fabs((double)xf - (double)vals[a - 1]) <= fabs((double)xf - (double)vals[a]) ? a - 1 : a;
+}
+
 // what is known of a knob's entries
 constexpr int kUnsorted = 1, kRepeats = 2;
 
-__global__ void __launch_bounds__(kHistThreads) knob_hist_kernel(const float *__restrict__ X, int64_t N, int64_t ldx,
-                                                                  DomainArgs dm, int n_total, int32_t *__restrict__ hist)
+// SIDE: the bisections of eight knobs side by side, a few large workgroups; else one after the other
+template <bool SIDE>
+__global__ void __launch_bounds__(SIDE ? 1024 : 256) knob_hist_kernel(const float *__restrict__ X, int64_t N, int64_t ldx,
+                                                                      DomainArgs dm, int n_total, int32_t *__restrict__ hist)
 {
+    constexpr int kHistThreads = SIDE ? 1024 : 256;
     extern __shared__ __align__(16) unsigned char smem[];
     float *vals = reinterpret_cast<float *>(smem);                 // [n_total]
     int *cnt = reinterpret_cast<int *>(vals + n_total);            // [n_total]
     __shared__ int offs[kMaxKnobs + 1];
     __shared__ int traits[kMaxKnobs];
+    __shared__ int begin[kMaxKnobs], span[kMaxKnobs];      // what a bisection begins with: the knob's slice; empty past the last knob and where entries descend
     const int tid = threadIdx.x, lane = tid & 63;
     for (int e = tid; e < n_total; e += kHistThreads) { vals[e] = dm.values[e]; cnt[e] = 0; }
     if (tid <= dm.n_knobs) offs[tid] = dm.offsets[tid];
-    if (tid < kMaxKnobs) traits[tid] = 0;
+    if (tid < kMaxKnobs) {
+        const int j = min(tid, dm.n_knobs - 1), lo = dm.offsets[j], hi = dm.offsets[j + 1];
+        traits[tid] = 0;
+        begin[tid] = lo;
+        span[tid] = tid < dm.n_knobs ? hi - lo : 0;
+    }
     __syncthreads();
     for (int e = tid; e + 1 < n_total; e += kHistThreads) {
         if (!(vals[e] < vals[e + 1])) {
             // a descent or a repetition inside one knob's slice (not across a boundary) marks that knob
-            for (int j = 0; j < dm.n_knobs; ++j)
-                if (e >= offs[j] && e + 1 < offs[j + 1]) atomicOr(&traits[j], vals[e + 1] < vals[e] ? kUnsorted : kRepeats);
+            const bool descends = vals[e + 1] < vals[e];
+            for (int j = 0; j < dm.n_knobs; ++j) {
+                if (e < offs[j] || e + 1 >= offs[j + 1]) continue;
+                atomicOr(&traits[j], descends ? kUnsorted : kRepeats);
+                if (descends) span[j] = 0;
+            }
         }
     }
     __syncthreads();
@@ -80,46 +105,51 @@ __global__ void __launch_bounds__(kHistThreads) knob_hist_kernel(const float *__
             float xv[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) xv[u] = row[min(j0 + u, dm.n_knobs - 1)];
-            // the first entry that is not below the value, of all eight knobs (an unsorted one's is not used)
-            int at[8], left[8], most = 0;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int j = min(j0 + u, dm.n_knobs - 1);
-                at[u] = offs[j];
-                left[u] = offs[j + 1] - offs[j];
-                most = max(most, left[u]);
-            }
-            for (; most > 0; most >>= 1) {
-                float mid[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) mid[u] = vals[min(at[u] + (left[u] >> 1), n_total - 1)];
+            int at[8];
+            if constexpr (SIDE) {
+                // the first entry that is not below the value, of all eight knobs
+                int left[8], most = 0;
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
-                    const int half = left[u] >> 1;
-                    const bool above = left[u] > 0 && mid[u] < xv[u];
-                    at[u] = above ? at[u] + half + 1 : at[u];
-                    left[u] = above ? left[u] - half - 1 : half;
+                    at[u] = begin[j0 + u];
+                    left[u] = span[j0 + u];
+                    most = max(most, left[u]);
                 }
-            }
-            // that entry against the one below it: the lower index wins a tie
+                for (; most > 0; most >>= 1) {
+                    float mid[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int j = min(j0 + u, dm.n_knobs - 1), lo = offs[j], hi = offs[j + 1];
-                const float below = vals[max(at[u] - 1, 0)], here = vals[min(at[u], n_total - 1)];
-                const bool inside = at[u] > lo && at[u] < hi;
-                const bool lower = inside && fabs((double)xv[u] - (double)below) <= fabs((double)xv[u] - (double)here);
-                at[u] = at[u] < hi ? (lower ? at[u] - 1 : at[u]) : hi - 1;
+                    for (int u = 0; u < 8; ++u) mid[u] = vals[min(at[u] + (left[u] >> 1), n_total - 1)];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const int half = left[u] >> 1;
+                        const bool above = left[u] > 0 && mid[u] < xv[u];
+                        at[u] = above ? at[u] + half + 1 : at[u];
+                        left[u] = above ? left[u] - half - 1 : half;
+                    }
+                }
+                // that entry against the one below it: the lower index wins a tie
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int lo = begin[j0 + u], hi = lo + span[j0 + u];
+                    const float below = vals[max(at[u] - 1, 0)], here = vals[min(at[u], n_total - 1)];
+                    const bool inside = at[u] > lo && at[u] < hi;
+                    const bool lower = inside && fabs((double)xv[u] - (double)below) <= fabs((double)xv[u] - (double)here);
+                    at[u] = at[u] < hi ? (lower ? at[u] - 1 : at[u]) : hi - 1;
+                }
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int j = j0 + u;
                 if (j >= dm.n_knobs) break;              // same for every lane
                 const int lo = offs[j], hi = offs[j + 1], trait = traits[j];
-                int arg = at[u];
-                if (trait & kUnsorted) arg = nearest_entry(vals, lo, hi, xv[u]);
-                else if (trait & kRepeats)
-                    while (arg > lo && vals[arg - 1] == vals[arg]) --arg;     // equal entries: the first of them
-                if (!valid) arg = -1;
+                int arg = -1;
+                if (valid) {
+                    if (trait & kUnsorted) arg = scanned_entry(vals, lo, hi, xv[u]);
+                    else if constexpr (SIDE) arg = at[u];
+                    else arg = bisected_entry(vals, lo, hi, xv[u]);
+                    if (trait == kRepeats)
+                        while (arg > lo && vals[arg - 1] == vals[arg]) --arg;     // equal entries: the first of them
+                }
                 if (hi - lo <= 8) {
                     // few entries: most lanes would hit the same counters; count per entry with a ballot instead
                     for (int v = lo; v < hi; ++v) {
@@ -136,6 +166,12 @@ __global__ void __launch_bounds__(kHistThreads) knob_hist_kernel(const float *__
     for (int e = tid; e < n_total; e += kHistThreads)
         if (cnt[e] != 0) atomicAdd(&hist[e], cnt[e]);
 }
+
+// Up to this many rows the bisections of a row are a chain of dependent reads and go side by side; beyond it they are work, and side by side
+// every knob takes as many steps as the largest domain asks for.  Calls, one after the other | side by side, domains of 220, 40, 40, 10, 2, 2, 3, 2 values:
+// 100,003 rows 32 | 18 us, 1M 52 | 47, 8M 169 | 267; with a ninth knob of 40 values 1M 55 | 63, 8M 191 | 419; eight of 1000 values 1M 107 | 56; descending
+// ones, which are scanned, 100,003 91 | 38, 1M 123 | 122, 8M 696 | 948.
+constexpr int64_t kHistSideRows = 1 << 20;
 
 __global__ void knob_mode_kernel(DomainArgs dm, const int32_t *__restrict__ hist, int32_t *__restrict__ mode_cfg)
 {
@@ -233,12 +269,17 @@ hipError_t launch_knob_modes(const float *X, int64_t N, int64_t ldx, const Domai
     hipLaunchKernelGGL(fill_zero_kernel, dim3((n_total + 255) / 256), dim3(256), 0, s, hist, (int)n_total);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // a row per thread as long as the chip has room for that, then four, then enough to fill it twice.  (Large workgroups: all add
-    // their counts to the same few entries, one after the other.)
-    const int64_t one = (N + kHistThreads - 1) / kHistThreads;
-    const int64_t blocks = std::min<int64_t>(std::max<int64_t>(std::min<int64_t>(one, 256), (one + 3) / 4), 512);
     const size_t lds = (size_t)n_total * 8;
-    hipLaunchKernelGGL(knob_hist_kernel, dim3((unsigned)blocks), dim3(kHistThreads), lds, s, X, N, ldx, dm, (int)n_total, hist);
+    if (N <= kHistSideRows) {
+        // a row per thread as long as the chip has room for that, then four, then enough to fill it twice.  (Large workgroups: all add
+        // their counts to the same few entries, one after the other.)
+        const int64_t one = (N + 1023) / 1024;
+        const int64_t blocks = std::min<int64_t>(std::max<int64_t>(std::min<int64_t>(one, 256), (one + 3) / 4), 512);
+        hipLaunchKernelGGL(knob_hist_kernel<true>, dim3((unsigned)blocks), dim3(1024), lds, s, X, N, ldx, dm, (int)n_total, hist);
+    } else {
+        const int64_t blocks = std::min<int64_t>((N + 1023) / 1024, 2048);       // (to fill the chip a few times)
+        hipLaunchKernelGGL(knob_hist_kernel<false>, dim3((unsigned)blocks), dim3(256), lds, s, X, N, ldx, dm, (int)n_total, hist);
+    }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(knob_mode_kernel, dim3((unsigned)dm.n_knobs), dim3(64), 0, s, dm, hist, mode_cfg);

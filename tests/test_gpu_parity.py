@@ -206,7 +206,10 @@ def test_snap_of_few_and_of_many_rows(rls, orc, batch, k, knobs, lanes):
 
 # sizes around the lanes of a wave and the values it reads at a time; more knobs than are searched side by side; rows around a workgroup's
 @pytest.mark.parametrize("sizes,n,order", [([1, 2, 3, 8, 9, 63, 64, 65, 127], 257, "sorted"), ([255, 256, 257, 300, 1000], 1023, "sorted"),
-                                           ([511, 513, 5, 1, 70, 64, 33, 17, 9, 2, 40], 255, "shuffled"), ([64, 300, 9, 8], 131073, "repeats"), ([220], 1, "sorted")])
+                                           ([511, 513, 5, 1, 70, 64, 33, 17, 9, 2, 40], 255, "shuffled"), ([64, 300, 9, 8], 131073, "repeats"), ([220], 1, "sorted"),
+                                           # some knobs sorted and some not, in groups of eight and beyond; rows that are searched one knob after the other
+                                           ([300, 9, 40, 2, 70, 5, 17, 64, 33, 220], 1025, "mixed"), ([300, 9, 40, 2, 70, 5, 17, 64, 33], (1 << 20) + 77, "mixed"),
+                                           ([64, 300, 9, 8], (1 << 20) + 1, "repeats"), ([220, 40, 2], 1 << 20, "sorted")])
 def test_nearest_entries_over_domain_sizes(rls, orc, sizes, n, order):
     """Snap, histogram and mode: nearest entry and first of equal ones, whichever lane or step has them."""
     rng = np.random.default_rng(sum(sizes) + n)
@@ -214,8 +217,8 @@ def test_nearest_entries_over_domain_sizes(rls, orc, sizes, n, order):
     parts = [np.sort(rng.permutation(4 * s)[:s]).astype(np.float32) for s in sizes]
     if order == "repeats":
         parts = [np.sort(rng.integers(0, max(2, s // 3), s)).astype(np.float32) for s in sizes]
-    if order == "shuffled":
-        parts = [rng.permutation(q) for q in parts]
+    if order in ("shuffled", "mixed"):
+        parts = [rng.permutation(q) if order == "shuffled" or j % 3 == 1 else q for j, q in enumerate(parts)]
     values = np.concatenate(parts)
     X = (rng.integers(-4, 8 * np.array(sizes) + 4, size=(n, len(sizes))) * 0.5).astype(np.float32)      # half-way cases among them
     dom = rls.DeviceDomains(offsets, values)
