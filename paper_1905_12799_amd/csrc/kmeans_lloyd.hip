@@ -1657,7 +1657,7 @@ __global__ void __launch_bounds__(step_threads_of(DP)) lloyd_step_kernel(SweepPl
 struct ColPart {
     double sum;
     int min_lsb, max_msb, bad, pad;
-    float vmin, vmax;     // smallest and largest finite value
+    float vmin, vmax;     // smallest and largest value (of a column that is not bad)
     double sumsq;         // (for the order of the points only)
 };
 
@@ -1674,17 +1674,26 @@ __device__ inline void add_part(ColPart &t, const ColPart &o)
     t.vmax = fmaxf(t.vmax, o.vmax);
 }
 
-// A thread takes one column of every 1024 / dp-th row.  What bounds it is the work per value and the waves that hide its loads: without a
-// branch per value, the highest bit taken once from the extremes, and 16 waves per workgroup instead of 8.  (1M x 16 32 -> 22 us, 300,007 x 13 12.1 -> 10.0.)
-constexpr int kStatThreads = 1024;
-__global__ void __launch_bounds__(kStatThreads) colstats_kernel(const float *__restrict__ X, int64_t N, int d, int dp, int64_t ldx,
-                                                               int64_t x_bs, char *ws, int64_t ws_bs, int64_t off_part)
+// A thread takes one column of every T / dp-th row.  What bounds it is the work per value and the waves that hide its loads: without a
+// branch per value, the highest bit taken once from the extremes, and where one space has to fill the chip, or has long columns, 16 waves per workgroup
+// instead of 8 (us, 512 | 1024 threads: 1M x 16 28 | 22, 300,007 x 13 10.4 | 9.6, 4 x (1M x 16) 71 | 67).  With many spaces the chip is full as it is, and with
+// few values per thread putting them together is what is left (64 x (262,144 x 16) 265 | 293, 64 x (262,144 x 8) 142 | 180, 64 x (20,000 x 16)
+// 27 | 43, 64 x (2000 x 8) 5.4 | 7.2, 16 x (1M x 16) 251 | 256, 2000 x 8 4.8 | 5.4).  (512 threads with a branch per value: 32, 11.7, 72, 260, 148, 28, 6.5, 248, 5.4.)
+constexpr int kStatFew = 512;
+inline int stat_threads(int64_t N, int dp, int stat_blocks, int batch)
 {
-    __shared__ ColPart sh[kStatThreads];
+    const int64_t rows = (N + stat_blocks - 1) / stat_blocks, workgroups = (int64_t)stat_blocks * batch;
+    return (workgroups <= 256 && rows * dp > 4096) || (workgroups <= 1024 && rows >= 4096) ? 1024 : kStatFew;
+}
+template <int T>
+__global__ void __launch_bounds__(T) colstats_kernel(const float *__restrict__ X, int64_t N, int d, int dp, int64_t ldx,
+                                                    int64_t x_bs, char *ws, int64_t ws_bs, int64_t off_part)
+{
+    __shared__ ColPart sh[T];
     const int b = blockIdx.y;
     const float *Xb = X + (int64_t)b * x_bs;
     const int tid = threadIdx.x;
-    const int l = tid % dp, pg = tid / dp, ppp = kStatThreads / dp;
+    const int l = tid % dp, pg = tid / dp, ppp = T / dp;
     const int64_t per = (N + gridDim.x - 1) / gridDim.x;
     const int64_t r0 = (int64_t)blockIdx.x * per, r1 = min(N, r0 + per);
     ColPart c = {0.0, 1 << 20, -(1 << 20), 0, 0, INFINITY, -INFINITY, 0.0};
@@ -1722,7 +1731,7 @@ __global__ void __launch_bounds__(kStatThreads) colstats_kernel(const float *__r
     __syncthreads();
     // eight threads per column add up an eighth each, then one of them the eight (in a fixed order)
     if (tid < 8 * dp) {
-        for (int g = tid + 8 * dp; g < kStatThreads; g += 8 * dp) add_part(c, sh[g]);
+        for (int g = tid + 8 * dp; g < T; g += 8 * dp) add_part(c, sh[g]);
         sh[tid] = c;
     }
     __syncthreads();
@@ -2566,8 +2575,9 @@ hipError_t launch_sweep_dp(const SweepPlan &plan, const SweepLayout &L, const Sw
     const int64_t n_units = (a.N + 32 * unit_blocks_of(DP) - 1) / (32 * unit_blocks_of(DP));
     // column statistics
     if (!a.reuse_colstats) {
-        hipLaunchKernelGGL(colstats_kernel, dim3(L.stat_blocks, batch), dim3(kStatThreads), 0, s, a.X, a.N, (int)a.d, DP, a.ldx,
-                           a.x_batch_stride, a.ws, L.per_batch, L.colstat_part);
+        const int threads = stat_threads(a.N, DP, L.stat_blocks, batch);
+        hipLaunchKernelGGL(threads == 1024 ? colstats_kernel<1024> : colstats_kernel<kStatFew>, dim3(L.stat_blocks, batch), dim3(threads), 0, s, a.X, a.N,
+                           (int)a.d, DP, a.ldx, a.x_batch_stride, a.ws, L.per_batch, L.colstat_part);
         hipLaunchKernelGGL(colstats_final_kernel, dim3(batch), dim3(256), 0, s, a.N, (int)a.d, (int)L.stat_blocks, a.ws,
                            L.per_batch, L.colstat_part, L.colinfo, plan.ordered ? L.keyinfo : (int64_t)-1, a.status);
     }

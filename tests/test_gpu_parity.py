@@ -1150,6 +1150,24 @@ def test_sweep_status_flags(rls):
     assert int(res.status.item()) & rls.RLS_STATUS_RANGE
 
 
+# workgroups of either size over the columns: one space and few, long columns and short ones, rows that do not divide among the workgroups
+@pytest.mark.parametrize("batch,N,d", [(1, 2000, 8), (1, 65537, 29), (1, 300007, 13), (64, 2000, 8), (8, 70001, 13), (3, 300007, 16), (4, 1048577, 5), (5, 262144, 32)])
+def test_column_statistics_of_spaces_together(rls, batch, N, d):
+    """Every space of a batch as on its own, and what a column must not hold is seen in the last row of the last space."""
+    gen = torch.Generator(device="cuda").manual_seed(N + d)
+    X = torch.randn(batch, N, d, generator=gen, device="cuda").mul_(20).round_().mul_(0.25).add_(3000.0)
+    seeds = [5 + b for b in range(batch)]
+    got = rls.kmeans_sweep_batched(X, 2, 4, 3, seeds=seeds)
+    for b in {0, batch // 2, batch - 1}:
+        own = rls.kmeans_sweep(X[b], 2, 4, 3, seed=seeds[b])
+        for name in ("labels", "centroids", "inertia"):
+            assert torch.equal(getattr(got, name)[b], getattr(own, name)), (b, name)
+    for value, status in ((float("nan"), 1), (float("-inf"), 1), (1e-30, 2), (3e38, 2), (-1e-44, 2), (0.0, 0)):
+        X[-1, -1, -1] = value
+        res = rls.kmeans_sweep_batched(X, 2, 2, 1, seeds=seeds, want_labels=False, check_status=False)
+        assert res.status.tolist() == [0] * (batch - 1) + [status], value
+
+
 def test_end_to_end_chain_tiny(rls, orc):
     """score -> sweep -> knee -> snap on the tiny space, every stage against the oracle."""
     w = synth.WORKLOADS["tiny"]
