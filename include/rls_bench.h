@@ -30,6 +30,10 @@ int32_t rls_profile_read(int32_t *n_launches, double *total_ms);
 int32_t rls_seed_wait_limit(int64_t ticks);
 /* The same for the workgroups of a space from `first_workgroup` on; the ones before it wait the default time. */
 int32_t rls_seed_wait_limit_from(int32_t first_workgroup, int64_t ticks);
+/* How the seeding chains of up to 64 spaces of a batch are drawn on a chip with so many compute units: the number of spaces per launch
+ * (`batch`: all together; fewer: in parts), or 0 where they are walked in memory, with launches for every centre.  `quads` != 0: the rows of
+ * every space can be read 16 bytes at a time. */
+int32_t rls_seed_spaces_at_once(int64_t N, int32_t d, int32_t batch, int32_t k_max, int32_t quads, int32_t compute_units);
 /* Where in its workspace a sweep of one space over rows in spatial order keeps the tile lists of its last round, for tests of what
  * lists occur: byte offset and number of 32-bit words (0: the sweep takes the points as they come).  Per group with lists and
  * unit of points 16 words; the four highest bits of each of the first eight are the number of tiles the unit meets, less one. */

@@ -774,7 +774,7 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
                 if constexpr (!ROWS) s_entry = there && owner == w ? entry : -1;
                 if (!there) {
                     s_quit = 1;
-                    post(ex + kExQuit, 1ull);
+                    post(ex + kExQuit, s_held ? kGaveUp | kHeld : kGaveUp);
                 }
             }
         }
@@ -1003,10 +1003,9 @@ static int compute_units()
 // Points per thread of seed_chain_kernel: the fewest with which the workgroups of all spaces fit the compute units one
 // each (a workgroup of 1024 threads with up to 64 row registers fills one); 0: they do not fit, the points are walked in
 // memory, one update and one draw per centre.  Up to 4096 points of a space stay in one workgroup, which has nothing to exchange.
-static int chain_points_per_thread(int64_t N, int dp, int spaces, int *groups)
+static int chain_points_per_thread(int64_t N, int dp, int spaces, int cus, int *groups)
 {
     const int most = 64 / dp;
-    const int cus = compute_units();
     for (int p = 1; p <= most; p *= 2) {
         const int64_t g = (N + 1024 * p - 1) / (1024 * p);
         if (g > 1 && N <= 4096 && 2 * p <= most && p < 4) continue;
@@ -1032,6 +1031,24 @@ static bool chain_in_parts_pays(int64_t points, int dp, bool quads, int parts, i
     const double million = (double)points * 1e-6 * (quads ? 1.0 : 4.0 / 3.0);
     const double walked = 15.0 + million * (dp == 8 ? 5.0 : (dp == 16 ? 8.5 : 12.5));
     return parts * (17.5 / centres + 6.8) < walked;
+}
+
+// How a chain is drawn: all spaces side by side, or as many at a time as the chip holds, or (0) walked in memory.
+static int chain_spaces_at_once(int64_t N, int32_t d, int spaces, bool quads, int j_begin, int k_max, int cus, int *points, int *groups)
+{
+    const int dp = padded_d(d);
+    int at_once = spaces, p = 0;
+    while (at_once > 0 && (p = chain_points_per_thread(N, dp, at_once, cus, groups)) == 0) --at_once;
+    if (at_once > 0 && at_once < spaces && !chain_in_parts_pays(N * spaces, dp, quads, (spaces + at_once - 1) / at_once, k_max - std::max(j_begin, 1)))
+        at_once = 0;
+    *points = p;
+    return at_once;
+}
+
+int seed_spaces_at_once(int64_t N, int32_t d, int spaces, bool quads, int k_max, int cus)
+{
+    int points = 0, groups = 0;
+    return chain_spaces_at_once(N, d, spaces, quads, 0, k_max, cus, &points, &groups);
 }
 
 static hipError_t launch_chain_in_one(int dp, int p, int spaces, const SeedList &sl, const ChainArgs &a, hipStream_t s)

@@ -207,6 +207,14 @@ int32_t rls_sweep_tile_lists(int64_t N, int32_t d, int32_t k_min, int32_t k_max,
     return RLS_OK;
 }
 
+int32_t rls_seed_spaces_at_once(int64_t N, int32_t d, int32_t batch, int32_t k_max, int32_t quads, int32_t compute_units)
+{
+    const int32_t rc = check_sweep(N, d, k_max, k_max, batch);
+    if (rc != RLS_OK) return rc;
+    if (k_max < 2 || batch > 64 || compute_units < 1) return RLS_ERR_INVALID_ARG;
+    return seed_spaces_at_once(N, d, batch, quads != 0, k_max, compute_units);
+}
+
 int32_t rls_snap_lanes(int32_t batch, int32_t k, int32_t n_knobs)
 {
     if (batch < 1 || batch > RLS_MAX_BATCH || k < 1 || n_knobs < 1 || n_knobs > RLS_MAX_D) return RLS_ERR_INVALID_ARG;

@@ -162,6 +162,8 @@ hipError_t launch_seed_chain(const float *X, int64_t N, int32_t d, int64_t ldx, 
                              int32_t k_max, const uint64_t *seeds_host, int64_t *chain, int64_t chain_batch_stride,
                              char *ws, const SweepLayout &L, hipStream_t s, int32_t j_begin = 0);
 
+// spaces per launch of a chain of `spaces` (at most 64) on a chip with `cus` compute units; 0: walked in memory.  `quads`: rows can be read 16 bytes at a time
+int seed_spaces_at_once(int64_t N, int32_t d, int spaces, bool quads, int k_max, int cus);
 // how long the workgroups (from `first_workgroup` of each space on) of the chains launched by this host thread wait for
 // each other, in ticks of the 100 MHz clock; negative: the default (see rls_bench.h)
 void set_seed_wait_ticks(int32_t first_workgroup, long long ticks);

@@ -458,19 +458,59 @@ def test_seeding_chain_walked_in_memory(rls, orc, N, d, span, stride):
         np.testing.assert_array_equal(part.centroids_of(7).cpu().numpy(), X[ref[:7]])
 
 
-@pytest.mark.parametrize("N,d,gap", [(17001, 16, 0), (33000, 7, 0), (8200, 20, 8), (8200, 20, 6)])
-def test_seeding_chain_of_many_spaces(rls, orc, N, d, gap):
-    """64 spaces that do not fit the chip together are drawn in parts, the six after them in one launch; rows that can
-    and (spaces 2 floats off) cannot be read 16 bytes at a time in every space."""
-    batch, k_max = 70, 6
-    rng = np.random.default_rng(N + gap)
-    X = rng.integers(0, 3, size=(batch, N, d)).astype(np.float32)
+def spaces_at_once(rls, batch, N, d, k, gap=0, compute_units=256):
+    """The route of the chains of the first 64 spaces: so many per launch, 0 where they are walked in memory."""
+    quads = d % 4 == 0 and (batch == 1 or (N * d + gap) % 4 == 0)
+    return rls.lib().rls_seed_spaces_at_once(ctypes.c_int64(N), d, min(batch, 64), k, int(quads), compute_units)
+
+
+def compute_units():
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def spaces_with_gaps(X, gap):
+    batch, N, d = X.shape
     buf = torch.zeros((batch, N * d + gap), dtype=torch.float32, device="cuda")
     buf[:, :N * d] = dev(X).view(batch, -1)
     Xd = buf[:, :N * d].view(batch, N, d)
     assert Xd.stride(0) == N * d + gap
+    return Xd
+
+
+MANY_SPACES = [(17001, 16, 0), (33000, 7, 0), (8200, 20, 8), (8200, 20, 6)]
+
+
+@pytest.mark.parametrize("N,d,gap", MANY_SPACES)
+def test_seeding_chain_of_many_spaces(rls, orc, N, d, gap):
+    """64 spaces that do not fit the chip together are drawn in parts, the six after them in one launch; rows that can
+    and (spaces 2 floats off) cannot be read 16 bytes at a time in every space."""
+    batch, k_max = 70, 6
+    assert spaces_at_once(rls, batch, N, d, k_max, gap, compute_units()) == 51
+    rng = np.random.default_rng(N + gap)
+    X = rng.integers(0, 3, size=(batch, N, d)).astype(np.float32)
+    Xd = spaces_with_gaps(X, gap)
     seeds = [100 + b for b in range(batch)]
     res = rls.kmeans_sweep_batched(Xd, k_max, k_max, 0, seeds=seeds)
+    got = res.centroids.cpu().numpy().reshape(batch, k_max, d)
+    for b in range(batch):
+        np.testing.assert_array_equal(got[b], X[b][orc.kmeanspp_chain(X[b], k_max, seeds[b])], err_msg=f"space {b}")
+
+
+# spaces too large for the chip one at a time, or too few centres for parts to pay; rows of 2, 4, 5 and 8 units of 16 bytes, rows that are no multiple
+# of 16 bytes, spaces that begin 8 bytes off; 64 spaces, and six more that are one launch
+WALKED_SPACES = [(6, 300000, 32, 0, 8), (2, 530001, 32, 0, 8), (2, 524300, 17, 0, 8), (3, 300000, 32, 2, 5), (2, 2097153, 8, 0, 5), (64, 17001, 16, 0, 4), (64, 8200, 20, 8, 4),
+                 (70, 8200, 20, 6, 3), (64, 33000, 7, 0, 3), (64, 20011, 16, 0, 2)]
+
+
+@pytest.mark.parametrize("batch,N,d,gap,k_max", WALKED_SPACES)
+def test_seeding_chain_of_spaces_walked_in_memory(rls, orc, batch, N, d, gap, k_max):
+    """The chains of a batch with an update and a draw launch per centre, from the third centre on with rows left out by the bound: integer
+    lattices, where it is met with equality."""
+    assert spaces_at_once(rls, batch, N, d, k_max, gap, compute_units()) == 0
+    rng = np.random.default_rng(N + gap + k_max)
+    X = rng.integers(0, 3, size=(batch, N, d), dtype=np.int8).astype(np.float32)
+    seeds = [100 + b for b in range(batch)]
+    res = rls.kmeans_sweep_batched(spaces_with_gaps(X, gap), k_max, k_max, 0, seeds=seeds, want_labels=False)
     got = res.centroids.cpu().numpy().reshape(batch, k_max, d)
     for b in range(batch):
         np.testing.assert_array_equal(got[b], X[b][orc.kmeanspp_chain(X[b], k_max, seeds[b])], err_msg=f"space {b}")
@@ -531,11 +571,15 @@ def test_seeding_chain_stages_every_kind_of_rows(rls, orc, d, points):
             rls.lib().rls_seed_wait_limit(ctypes.c_int64(-1))
 
 
-# spaces that fit the chip 25, 51 and one at a time, a last part that is shorter, and two centres, which are walked in memory
-@pytest.mark.parametrize("batch,N,d,k,limit", [(64, 40009, 13, 16, -1), (64, 20011, 16, 24, -1), (64, 20011, 16, 24, 0), (5, 262145, 16, 12, -1), (9, 70001, 32, 20, -1),
-                                               (3, 600007, 13, 30, -1), (66, 20011, 16, 9, -1), (64, 20011, 16, 2, -1), (64, 17003, 7, 2, -1)])
-def test_seeding_of_more_spaces_than_fit_together(rls, batch, N, d, k, limit):
+# spaces that fit the chip 25, 51, 3, 7 and one at a time, a last part that is shorter, two spaces after the first 64
+SPACES_IN_PARTS = [(64, 40009, 13, 16, -1, 25), (64, 20011, 16, 24, -1, 51), (64, 20011, 16, 24, 0, 51), (5, 262145, 16, 12, -1, 3), (9, 70001, 32, 20, -1, 7),
+                   (3, 600007, 13, 30, -1, 1), (66, 20011, 16, 9, -1, 51)]
+
+
+@pytest.mark.parametrize("batch,N,d,k,limit,at_once", SPACES_IN_PARTS)
+def test_seeding_of_more_spaces_than_fit_together(rls, batch, N, d, k, limit, at_once):
     """Chains of a batch, one part of its spaces after the other: every space draws what it draws on its own."""
+    assert spaces_at_once(rls, batch, N, d, k, 0, compute_units()) == at_once
     gen = torch.Generator(device="cuda").manual_seed(N + k)
     X = torch.randint(0, 50, (batch, N, d), generator=gen, device="cuda").float()
     X[:, :, 0] += torch.arange(batch, device="cuda")[:, None]

@@ -13,3 +13,29 @@ def test_snap_lanes(batch, k, knobs, lanes):
 def test_snap_cases_lie_on_both_sides():
     assert {c[3] for c in gpu.SNAP_ROWS} == {1, 64}
     assert rls.lib().rls_snap_lanes(1, 0, 8) == rls.lib().rls_snap_lanes(1, 4, 33) == -1
+
+
+@pytest.mark.parametrize("batch,N,d,k,limit,at_once", gpu.SPACES_IN_PARTS)
+def test_seeding_in_parts(batch, N, d, k, limit, at_once):
+    assert gpu.spaces_at_once(rls, batch, N, d, k) == at_once
+    assert 0 < at_once < min(batch, 64)
+
+
+@pytest.mark.parametrize("N,d,gap", gpu.MANY_SPACES)
+def test_seeding_of_many_spaces_in_parts(N, d, gap):
+    assert gpu.spaces_at_once(rls, 70, N, d, 6, gap) == 51
+    assert gpu.spaces_at_once(rls, 6, N, d, 6, gap) == 6          # (what comes after the first 64)
+
+
+@pytest.mark.parametrize("batch,N,d,gap,k", gpu.WALKED_SPACES)
+def test_seeding_walked(batch, N, d, gap, k):
+    assert gpu.spaces_at_once(rls, batch, N, d, k, gap) == 0
+
+
+def test_seeding_on_smaller_chips():
+    """The rule goes by the compute units at hand: what is one launch on 256 goes in parts on 64, and a space that fits no chip is walked."""
+    assert gpu.spaces_at_once(rls, 8, 65536, 16, 32) == 8
+    assert gpu.spaces_at_once(rls, 8, 65536, 16, 32, compute_units=64) == 4
+    assert gpu.spaces_at_once(rls, 1, 1 << 20, 16, 32) == 1
+    assert gpu.spaces_at_once(rls, 1, (1 << 20) + 1, 16, 32) == 0
+    assert gpu.spaces_at_once(rls, 1, 1 << 20, 16, 32, compute_units=64) == 0
