@@ -23,8 +23,8 @@ int32_t rls_profile_enable(int32_t on);
  * milliseconds, and forgets them.  RLS_ERR_NULL / RLS_ERR_HIP as in rls.h. */
 int32_t rls_profile_read(int32_t *n_launches, double *total_ms);
 /* The seeding chain of up to about a million points runs in one launch whose workgroups wait for each other; one that has
- * waited too long (2 ms for all of them to be there, 50 ms later on) gives up, and a second kernel, whose workgroups need not
- * run at the same time, does the chain again.  This sets both limits, in ticks of the 100 MHz clock, for the calls of the
+ * waited too long (2 ms for all of them to be there, 0.1 ms in the parts of a batch after one that gave up, 50 ms later on) gives up, and a
+ * second kernel, whose workgroups need not run at the same time, does the chain again.  This sets these limits, in ticks of the 100 MHz clock, for the calls of the
  * host thread that sets it.  0 makes every launch with more than one workgroup take that second path, for tests; a negative
  * value restores the default. */
 int32_t rls_seed_wait_limit(int64_t ticks);

@@ -42,10 +42,13 @@ __device__ inline double uniform01(uint64_t seed, uint64_t j)
 // How long a workgroup of seed_chain_kernel waits for the others before it gives up, in ticks of the 100 MHz clock: 2 ms in
 // its first exchange, which some workgroups may never reach while other streams hold compute units (beside a tree scoring of 1M x 16
 // that fills the chip the last one arrives after 0.7 to 0.9 ms; giving up costs the chain again, 0.9 ms at 65,536 x 16 and 3.4 at
-// 1M x 16 with 64 centres), then 50 ms, since from there on all are running.  A test may change both for the launches of its own host thread.
+// 1M x 16 with 64 centres), then 50 ms, since from there on all are running.  Of a batch in parts each could wait that long, one after the
+// other, and 64 x (262,144 x 16) has 16: once one has given up, the chip is known to be held, and those behind it wait 0.1 ms for the first exchange
+// (workgroups that find the chip free are all there within 20 us).  A test may change these limits for the launches of its own host thread.
 constexpr long long kArriveTicks = 200000;
+constexpr long long kArriveTicksHeld = 10000;
 constexpr long long kWaitTicks = 5000000;
-thread_local long long t_wait_ticks = -1;          // negative: the two limits above
+thread_local long long t_wait_ticks = -1;          // negative: the limits above
 thread_local int t_wait_from = 0;                  // first workgroup of a space that the thread's limit holds for
 
 struct SeedList {
@@ -402,12 +405,13 @@ constexpr int kChainWgs = 256;                                 // workgroups per
 constexpr int kRowWords = RLS_MAX_D + 1;                       // row, then the index
 constexpr int kExRows = RLS_MAX_K * kChainWgs;                 // word offsets within the exchange area of a space
 constexpr int kExDone = kExRows + RLS_MAX_K * kRowWords;        // one per workgroup: 1 when it has finished
-constexpr int kExQuit = kExDone + kChainWgs;                   // 1 when a workgroup has given up
+constexpr int kExQuit = kExDone + kChainWgs;                   // kGaveUp when a workgroup has given up, kHeld when one of the part before had
 constexpr int kExTicket = kExQuit + 1;                         // seed_chain_rest_kernel: the next block of points to be worked on
 constexpr int kExSums = kExTicket + 1;                         //   sums of a step, one per block
 constexpr int kExCount = kExSums + kChainWgs;                  //   blocks of a step that are done, one per step
 constexpr int kExPick = kExCount + RLS_MAX_K;                  //   drawn index, one per step
 constexpr int kExWords = kExPick + RLS_MAX_K;
+constexpr unsigned long long kGaveUp = 1, kHeld = 2;
 static_assert(kExWords * 8 <= kSeedExchangeBytes, "the exchange area must fit its place in the workspace");
 
 struct ChainArgs {
@@ -422,6 +426,8 @@ struct ChainArgs {
     int64_t chain_bs;
     unsigned long long *ex;               // exchange area
     int64_t ex_bs;
+    const unsigned long long *ex_before;  // a batch in parts: that of the part before (null: none), ...
+    int32_t spaces_before;                // ... which has so many spaces
     long long wait_ticks;                 // limit of every wait in workgroups from wait_from on; negative: the default limits
     int32_t wait_from;
 };
@@ -441,9 +447,14 @@ __global__ void __launch_bounds__(256) seed_begin_kernel(SeedList seeds, ChainAr
         ex[kExPick + t0] = kSlotEmpty;
         if (t0 >= max(a.j_begin, 1)) chain[t0] = 0;
     }
-    if (t0 == 0) {
-        ex[kExQuit] = ex[kExTicket] = 0ull;
-        if (a.j_begin == 0) chain[0] = first_centre(seeds.seed[b], a.N);
+    if (t0 < 64) {
+        const bool held = a.ex_before != nullptr && t0 < a.spaces_before && a.ex_before[(int64_t)t0 * a.ex_bs + kExQuit] != 0ull;
+        const unsigned long long any = __ballot(held);
+        if (t0 == 0) {
+            ex[kExQuit] = any != 0ull ? kHeld : 0ull;
+            ex[kExTicket] = 0ull;
+            if (a.j_begin == 0) chain[0] = first_centre(seeds.seed[b], a.N);
+        }
     }
 }
 
@@ -536,7 +547,7 @@ __device__ inline bool wait_for(long long limit, const unsigned long long *quit,
     for (;;) {
         const long long waited = wall_clock64() - t0;
         if (look()) return true;
-        if (waited > limit || (quit && waited > kUndisturbed && peek(quit) != 0ull)) return false;
+        if (waited > limit || (quit && waited > kUndisturbed && (peek(quit) & kGaveUp) != 0ull)) return false;
     }
 }
 
@@ -613,6 +624,7 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
     __shared__ double s_before, s_r;
     __shared__ int s_entry;                         // not ROWS: the wave to draw from, or -1 where another workgroup draws
     __shared__ int s_quit;                          // a wait of this workgroup ran out
+    __shared__ int s_held;                          // a workgroup of the part before gave up
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int w = blockIdx.x, G = a.groups, b = blockIdx.y, d = a.d;
     const float *Xb = a.X + (int64_t)b * a.x_bs;
@@ -657,7 +669,11 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
         chosen[tid] = chain[tid];
     }
     if (tid < 64) wsum[tid] = 0.0;
-    if (tid == 0) s_quit = gridDim.x > 1 && peek(ex + kExQuit) != 0ull;     // started when another had already given up
+    if (tid == 0) {
+        const unsigned long long quit = gridDim.x > 1 ? peek(ex + kExQuit) : 0ull;
+        s_quit = (quit & kGaveUp) != 0ull;          // started when another had already given up
+        s_held = (quit & kHeld) != 0ull;
+    }
     __syncthreads();
     if (s_quit) return;
     if (tid < DP) cs[tid] = tid < d ? (double)Xb[chosen[j0 - 1] * a.ldx + tid] : 0.0;
@@ -700,7 +716,7 @@ __global__ void __launch_bounds__(1024) seed_chain_kernel(SeedList seeds, ChainA
                     if (bits == kSlotEmpty) bits = 0x7ff8000000000000ull;
                     post(slot + w, bits);
                 }
-                there = wait_for(own_limit ? a.wait_ticks : (j == j0 ? kArriveTicks : kWaitTicks), ex + kExQuit, [&] {
+                there = wait_for(own_limit ? a.wait_ticks : (j != j0 ? kWaitTicks : (s_held ? kArriveTicksHeld : kArriveTicks)), ex + kExQuit, [&] {
                     bool miss = false;
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
@@ -1025,6 +1041,9 @@ static int chain_points_per_thread(int64_t N, int dp, int spaces, int cus, int *
 // 1216 and 1430; 64 x (20,000 x 16), k = 32 902 and 536, k = 2 184 and 203; 16 x (1,048,576 x 16) 6269 and 4895; 64 x (131,072 x 32) 5023 and
 // 4715; 6 x (300,000 x 32) 1474 and 1682; 8 x (524,288 x 32) 2725 and 2481; 2 x (2M x 8) 1309 and 754; rows without structure 64 x (262,144 x 16)
 // 9137 and 4698, 64 x (262,144 x 8) 5885 and 2590, 64 x (131,072 x 32) 8348 and 4728.
+// A part needs its workgroups resident together, the walk does not.  Beside another stream of tree scorings that fill the chip (256 trees x 1M, 512 x 8M,
+// 2048 x 8M rows a launch) 64 x (262,144 x 16), k = 32 takes 14.5, 18.6 and 31.2 ms walked and 10.4, 15.4 and 30.1 in parts.  At the worst, with other
+// streams holding the chip throughout, the first part gives up after 2 ms, each later one after 0.1, and each is drawn by tickets instead (10 to 30 us a centre).
 static bool chain_in_parts_pays(int64_t points, int dp, bool quads, int parts, int centres)
 {
     if (centres < 1) return false;
@@ -1094,6 +1113,8 @@ hipError_t launch_seed_chain(const float *X, int64_t N, int32_t d, int64_t ldx, 
     // positions j_begin .. k_max-1 of the chain are produced; the distance state of an earlier call for the same
     // chain (positions 0 .. j_begin-1) must still be in the workspace
     const int32_t seed_blocks = L.seed_blocks;
+    const unsigned long long *ex_before = nullptr;
+    int32_t spaces_before = 0;
     for (int b0 = 0; b0 < batch; b0 += 64) {
         const int nb = batch - b0 < 64 ? batch - b0 : 64;
         SeedList sl;
@@ -1104,14 +1125,10 @@ hipError_t launch_seed_chain(const float *X, int64_t N, int32_t d, int64_t ldx, 
             continue;
         }
         const int dp = padded_d(d);
-        // all spaces side by side, or as many at a time as the chip holds
-        int at_once = nb, groups = 0, p = 0;
-        while (at_once > 0 && (p = chain_points_per_thread(N, dp, at_once, &groups)) == 0) --at_once;
-        if (p != 0 && at_once < nb) {
-            const bool quads = d % 4 == 0 && ldx % 4 == 0 && x_batch_stride % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
-            if (!chain_in_parts_pays(N * nb, dp, quads, (nb + at_once - 1) / at_once, k_max - std::max(j_begin, 1))) p = 0;
-        }
-        if (p != 0) {
+        const bool quads = d % 4 == 0 && ldx % 4 == 0 && (nb == 1 || x_batch_stride % 4 == 0) && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+        int groups = 0, p = 0;
+        const int at_once = chain_spaces_at_once(N, d, nb, quads, j_begin, k_max, compute_units(), &p, &groups);
+        if (at_once > 0) {
             for (int i0 = 0; i0 < nb; i0 += at_once) {
                 const int64_t first = b0 + i0;
                 const int spaces = std::min(at_once, nb - i0);
@@ -1123,9 +1140,12 @@ hipError_t launch_seed_chain(const float *X, int64_t N, int32_t d, int64_t ldx, 
                 ca.mind = reinterpret_cast<double *>(ws + first * L.per_batch + L.mind); ca.mind_bs = L.per_batch / 8;
                 ca.chain = chain + first * chain_batch_stride; ca.chain_bs = chain_batch_stride;
                 ca.ex = reinterpret_cast<unsigned long long *>(ws + first * L.per_batch + L.colstat_part); ca.ex_bs = L.per_batch / 8;
+                ca.ex_before = ex_before; ca.spaces_before = spaces_before;
                 ca.wait_ticks = t_wait_ticks; ca.wait_from = t_wait_from;
                 const hipError_t e = launch_chain_in_one(dp, p, spaces, part, ca, s);
                 if (e != hipSuccess) return e;
+                ex_before = groups > 1 ? ca.ex : nullptr;
+                spaces_before = spaces;
             }
             continue;
         }

@@ -593,6 +593,27 @@ def test_seeding_of_more_spaces_than_fit_together(rls, batch, N, d, k, limit, at
         assert torch.equal(got[b], X[b][rls.kmeanspp_chain(X[b], k, seeds[b])]), b
 
 
+@pytest.mark.parametrize("limit,words", [(-1, (0, 0)), (0, (1, 3))])
+def test_seeding_in_parts_does_not_wait_for_a_held_chip_again(rls, limit, words):
+    """Once the workgroups of a part have given up, those of the next one are told (and wait a twentieth of the time to begin with)."""
+    batch, N, d, k = 64, 20011, 16, 5
+    assert spaces_at_once(rls, batch, N, d, k, 0, compute_units()) == 51
+    X = torch.randint(0, 50, (batch, N, d), generator=torch.Generator(device="cuda").manual_seed(4), device="cuda").float()
+    ws = torch.zeros(rls.kmeans_sweep_least_workspace_bytes(N, d, k, k, batch) + 256, dtype=torch.uint8, device="cuda")
+    per_space = (ws.numel() - 256) // batch
+    try:
+        rls.lib().rls_seed_wait_limit(ctypes.c_int64(limit))
+        got = rls.kmeans_sweep_batched(X, k, k, 0, seeds=range(batch), want_labels=False, workspace=ws).centroids.view(batch, k, d)
+    finally:
+        rls.lib().rls_seed_wait_limit(ctypes.c_int64(-1))
+    # word 37248 of a space's exchange area, which the column statistics of so few rows leave alone: 1 its workgroups gave up, 2 those of the part before did
+    at = (-ws.data_ptr()) % 256
+    quit = ws[at:at + batch * per_space].view(batch, per_space)[:, 37248 * 8:37248 * 8 + 8].contiguous().view(torch.int64).flatten().cpu().numpy()
+    np.testing.assert_array_equal(quit, [words[0]] * 51 + [words[1]] * 13)
+    for b in range(0, batch, 7):
+        assert torch.equal(got[b], X[b][rls.kmeanspp_chain(X[b], k, b)]), b
+
+
 def exchange_words(ws, k_max):
     """The words that the workgroups of a chain exchange, at the head of the workspace: the sums of step j are words
     256 j + workgroup, and a word nobody has written is -1."""
