@@ -38,6 +38,10 @@ int32_t rls_seed_spaces_at_once(int64_t N, int32_t d, int32_t batch, int32_t k_m
  * lists occur: byte offset and number of 32-bit words (0: the sweep takes the points as they come).  Per group with lists and
  * unit of points 16 words; the four highest bits of each of the first eight are the number of tiles the unit meets, less one. */
 int32_t rls_sweep_tile_lists(int64_t N, int32_t d, int32_t k_min, int32_t k_max, int64_t *offset_out, int64_t *words_out);
+/* How rls_gbt_score_batched scores with forests of one shape: configurations of a tile, trees walked side by side, trees of a chunk, and whether
+ * one part of a workgroup's threads adds leaf values while the others move the next chunk. */
+int32_t rls_score_plan(int64_t N, int32_t d, int32_t batch, int32_t n_trees, int32_t depth, int32_t *tile_out, int32_t *side_out,
+                       int32_t *trees_per_chunk_out, int32_t *apart_out);
 /* Lanes that rls_snap_to_valid_batched puts on a (centroid, knob): 64, or 1 where there are many of them. */
 int32_t rls_snap_lanes(int32_t batch, int32_t k, int32_t n_knobs);
 /* `n` single matrix instructions (32 x 32 x 16, fp16 or bf16 operands, fp32 accumulators) on operands as the kernels hold them, for

@@ -257,19 +257,66 @@ constexpr TileKernels tile_kernels()
 static_assert(RLS_MAX_D * kScoreThreads * 4 + ((1 << RLS_MAX_DEPTH) - 1) * 8 <= kScoreLds,
               "the deepest tree fits beside the largest tile at the largest number of features");
 
+const TileKernels tiles[] = {tile_kernels<1024>(), tile_kernels<512>(), tile_kernels<256>(), tile_kernels<128>(), tile_kernels<64>()};
+
 struct ScorePlan {
     const TileKernels *tile;
     int side, tpc;           // trees side by side, trees per chunk
+    bool apart;              // a slice that adds while the others move the next chunk
     size_t lds;
 };
 
+// The tile: a workgroup pays for moving the whole forest through LDS and for the walks of its tile, and there are
+// as many turns as the workgroups fill the 256 compute units.  Times in ns per tree, fitted to depths 4 to 10 with
+// tiles of 64 to 1024: 0.15 per node moved, 70 for a tree whatever the tile, 0.032 per configuration and level
+// walked, and a walk of one group of trees takes at least 100 per level.  (141,494 x 8, 145 trees of depth 7: one
+// turn of 1024 takes 50 us, three of 256 take 64.)
+ScorePlan plan_score(int64_t N, int32_t d, int nb, int n_trees, int depth)
+{
+    const int64_t n_int = ((int64_t)1 << depth) - 1;
+    ScorePlan best{nullptr, 0, 0, false, 0};
+    double best_ns = 0.0;
+    for (const TileKernels &t : tiles) {
+        const int P = t.tile, SL = kScoreThreads / P;
+        const int64_t space = kScoreLds - (int64_t)d * P * 4;
+        int64_t fit = std::min<int64_t>(space / (n_int * 8 + (SL > 1 ? P * 4 : 0)), kChunkNodes / n_int);
+        if (fit < 1) continue;
+        if (fit > n_trees) fit = n_trees;
+        // (eight side by side hide more of the chains' latency where a thread walks whole chunks: 1M x 16, 512 trees of depth 5
+        // 508 -> 482 us, of depth 8 794 -> 782; split over slices they leave more of a chunk's last round idle,
+        // and chunks of 8 trees where 12 fit cost more than that: 6.8M x 16, 67 trees of depth 10 1141 -> 1255 us)
+        const int side = SL == 1 && fit >= 8 && fit % 8 < 4 ? 8 : (fit >= 4 * SL ? 4 : (fit >= 2 * SL ? 2 : 1));
+        int tpc = (int)fit;
+        if (tpc > side * SL) tpc -= tpc % (side * SL);      // whole rounds of the slices ...
+        if (tpc > 4) tpc -= tpc % 4;                        // ... and chunks that start at a multiple of four trees
+        if (tpc < n_trees && tpc > 4 && tpc % 4 != 0) continue;
+        const double turns = (double)(((N + P - 1) / P * nb + 255) / 256);
+        const int busy = std::min(SL, (tpc + side - 1) / side);
+        const double walk = 70.0 + std::max(0.032 * P * depth, 100.0 * depth / (busy * side));
+        const double ns = turns * n_trees * (0.15 * (double)(n_int + 1) + walk);
+        if (best.tile == nullptr || ns < best_ns) {
+            const bool apart = P == kApartTile && side == 4 && tpc >= kApartTrees && tpc < n_trees;
+            best = ScorePlan{&t, side, tpc, apart, (size_t)d * P * 4 + (size_t)tpc * (n_int * 8 + (SL > 1 ? P * 4 : 0))};
+            best_ns = ns;
+        }
+    }
+    return best;
+}
+
 }  // namespace
+
+bool score_plan(int64_t N, int32_t d, int32_t batch, int32_t n_trees, int32_t depth, int32_t *tile, int32_t *side, int32_t *trees_per_chunk)
+{
+    const ScorePlan p = plan_score(N, d, std::min(batch, (int32_t)kScoreBatch), n_trees, depth);
+    *tile = p.tile ? p.tile->tile : 0;
+    *side = p.side;
+    *trees_per_chunk = p.tpc;
+    return p.apart;
+}
 
 hipError_t launch_gbt_score(const ForestArgs *forests_host, int32_t batch, const float *X, int64_t N, int32_t d,
                             int64_t ldx, int64_t x_batch_stride, float *score, hipStream_t s)
 {
-    static const TileKernels tiles[] = {tile_kernels<1024>(), tile_kernels<512>(), tile_kernels<256>(), tile_kernels<128>(),
-                                        tile_kernels<64>()};
     static std::once_flag attr_once;
     static hipError_t attr_status = hipSuccess;
     std::call_once(attr_once, [] {
@@ -293,42 +340,11 @@ hipError_t launch_gbt_score(const ForestArgs *forests_host, int32_t batch, const
             fb.f[i] = forests_host[b0 + (i < nb ? i : 0)];
             bits |= reinterpret_cast<uintptr_t>(fb.f[i].feat) | reinterpret_cast<uintptr_t>(fb.f[i].thr);
         }
-        const int64_t n_int = ((int64_t)1 << depth) - 1;
-        // The tile: a workgroup pays for moving the whole forest through LDS and for the walks of its tile, and there are
-        // as many turns as the workgroups fill the 256 compute units.  Times in ns per tree, fitted to depths 4 to 10 with
-        // tiles of 64 to 1024: 0.15 per node moved, 70 for a tree whatever the tile, 0.032 per configuration and level
-        // walked, and a walk of one group of trees takes at least 100 per level.  (141,494 x 8, 145 trees of depth 7: one
-        // turn of 1024 takes 50 us, three of 256 take 64.)
-        ScorePlan best{nullptr, 0, 0, 0};
-        double best_ns = 0.0;
-        for (const TileKernels &t : tiles) {
-            const int P = t.tile, SL = kScoreThreads / P;
-            const int64_t space = kScoreLds - (int64_t)d * P * 4;
-            int64_t fit = std::min<int64_t>(space / (n_int * 8 + (SL > 1 ? P * 4 : 0)), kChunkNodes / n_int);
-            if (fit < 1) continue;
-            if (fit > n_trees) fit = n_trees;
-            // (eight side by side hide more of the chains' latency where a thread walks whole chunks: 1M x 16, 512 trees of depth 5
-            // 508 -> 482 us, of depth 8 794 -> 782; split over slices they leave more of a chunk's last round idle,
-            // and chunks of 8 trees where 12 fit cost more than that: 6.8M x 16, 67 trees of depth 10 1141 -> 1255 us)
-            const int side = SL == 1 && fit >= 8 && fit % 8 < 4 ? 8 : (fit >= 4 * SL ? 4 : (fit >= 2 * SL ? 2 : 1));
-            int tpc = (int)fit;
-            if (tpc > side * SL) tpc -= tpc % (side * SL);      // whole rounds of the slices ...
-            if (tpc > 4) tpc -= tpc % 4;                        // ... and chunks that start at a multiple of four trees
-            if (tpc < n_trees && tpc > 4 && tpc % 4 != 0) continue;
-            const double turns = (double)(((N + P - 1) / P * nb + 255) / 256);
-            const int busy = std::min(SL, (tpc + side - 1) / side);
-            const double walk = 70.0 + std::max(0.032 * P * depth, 100.0 * depth / (busy * side));
-            const double ns = turns * n_trees * (0.15 * (double)(n_int + 1) + walk);
-            if (best.tile == nullptr || ns < best_ns) {
-                best = ScorePlan{&t, side, tpc, (size_t)d * P * 4 + (size_t)tpc * (n_int * 8 + (SL > 1 ? P * 4 : 0))};
-                best_ns = ns;
-            }
-        }
+        const ScorePlan best = plan_score(N, d, nb, n_trees, depth);
         if (best.tile == nullptr) return hipErrorInvalidValue;     // depth <= 12: cannot happen
         const int quads = (best.tpc % 4 == 0 || best.tpc == n_trees) && (bits & 15) == 0;
-        const bool apart = best.tile->tile == kApartTile && best.side == 4 && best.tpc >= kApartTrees && best.tpc < n_trees;
-        const Kernel kernel = apart ? gbt_score_kernel<kApartTile, 4, true>
-                                    : best.tile->kernel[best.side == 8 ? 0 : (best.side == 4 ? 1 : (best.side == 2 ? 2 : 3))];
+        const Kernel kernel = best.apart ? gbt_score_kernel<kApartTile, 4, true>
+                                         : best.tile->kernel[best.side == 8 ? 0 : (best.side == 4 ? 1 : (best.side == 2 ? 2 : 3))];
         const unsigned grid = (unsigned)((N + best.tile->tile - 1) / best.tile->tile);
         hipLaunchKernelGGL(kernel, dim3(grid, (unsigned)nb), dim3(kScoreThreads), best.lds, s, fb, X + (int64_t)b0 * x_batch_stride, N, (int)d,
                            ldx, x_batch_stride, score + (int64_t)b0 * N, best.tpc, quads);

@@ -215,6 +215,16 @@ int32_t rls_seed_spaces_at_once(int64_t N, int32_t d, int32_t batch, int32_t k_m
     return seed_spaces_at_once(N, d, batch, quads != 0, k_max, compute_units);
 }
 
+int32_t rls_score_plan(int64_t N, int32_t d, int32_t batch, int32_t n_trees, int32_t depth, int32_t *tile_out, int32_t *side_out,
+                       int32_t *trees_per_chunk_out, int32_t *apart_out)
+{
+    if (!tile_out || !side_out || !trees_per_chunk_out || !apart_out) return RLS_ERR_NULL;
+    if (N < 1 || N > RLS_MAX_N || d < 1 || d > RLS_MAX_D || batch < 1 || batch > RLS_MAX_BATCH || n_trees < 1 || depth < 1 || depth > RLS_MAX_DEPTH)
+        return RLS_ERR_INVALID_ARG;
+    *apart_out = score_plan(N, d, batch, n_trees, depth, tile_out, side_out, trees_per_chunk_out) ? 1 : 0;
+    return RLS_OK;
+}
+
 int32_t rls_snap_lanes(int32_t batch, int32_t k, int32_t n_knobs)
 {
     if (batch < 1 || batch > RLS_MAX_BATCH || k < 1 || n_knobs < 1 || n_knobs > RLS_MAX_D) return RLS_ERR_INVALID_ARG;

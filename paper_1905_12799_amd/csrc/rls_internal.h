@@ -140,6 +140,9 @@ struct ForestArgs {
 };
 hipError_t launch_gbt_score(const ForestArgs *forests_host, int32_t batch, const float *X, int64_t N, int32_t d,
                             int64_t ldx, int64_t x_batch_stride, float *score, hipStream_t s);
+// what such a call of forests of one shape would take: configurations per tile, trees side by side, trees per chunk; returns whether one slice of the threads
+// adds while the others move the next chunk
+bool score_plan(int64_t N, int32_t d, int32_t batch, int32_t n_trees, int32_t depth, int32_t *tile, int32_t *side, int32_t *trees_per_chunk);
 
 struct DomainArgs {
     int32_t n_knobs;

@@ -78,8 +78,18 @@ def test_gbt_score_tiles_and_slices(rls, orc, N, d, T, D):
 
 
 # tiles of 256: a slice that adds while the others move (32 and more trees a chunk), last chunks of 6 and 3 trees, and the fewest nodes
-@pytest.mark.parametrize("N,d,T,D", [(60001, 8, 150, 8), (50003, 16, 99, 8), (65000, 8, 200, 6), (64999, 24, 130, 7)])
+SLICE_THAT_ADDS = [(60001, 8, 150, 8), (50003, 16, 99, 8), (65000, 8, 200, 6), (64999, 24, 130, 7)]
+
+
+def score_plan(rls, N, d, T, D, batch=1):
+    out = [ctypes.c_int32() for _ in range(4)]
+    assert rls.lib().rls_score_plan(ctypes.c_int64(N), d, batch, T, D, *[ctypes.byref(o) for o in out]) == 0
+    return [o.value for o in out]
+
+
+@pytest.mark.parametrize("N,d,T,D", SLICE_THAT_ADDS)
 def test_gbt_score_slice_that_adds(rls, orc, N, d, T, D):
+    assert score_plan(rls, N, d, T, D)[3] == 1
     rng = np.random.default_rng(N + T)
     X = rng.standard_normal((N, d)).astype(np.float32)
     f = synth.random_forest(X, T, D, 0, rng)

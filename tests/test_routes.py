@@ -39,3 +39,16 @@ def test_seeding_on_smaller_chips():
     assert gpu.spaces_at_once(rls, 1, 1 << 20, 16, 32) == 1
     assert gpu.spaces_at_once(rls, 1, (1 << 20) + 1, 16, 32) == 0
     assert gpu.spaces_at_once(rls, 1, 1 << 20, 16, 32, compute_units=64) == 0
+
+
+@pytest.mark.parametrize("N,d,T,D", gpu.SLICE_THAT_ADDS)
+def test_score_with_a_slice_that_adds(N, d, T, D):
+    tile, side, trees, apart = gpu.score_plan(rls, N, d, T, D)
+    assert (tile, side, apart) == (256, 4, 1)
+    assert 32 <= trees < T
+
+
+def test_score_without_one():
+    """One chunk, few trees a chunk, other tiles."""
+    for N, d, T, D in ((60001, 8, 32, 8), (50000, 32, 256, 10), (1 << 20, 16, 256, 8), (2000, 8, 64, 6), (30000, 32, 256, 8)):
+        assert gpu.score_plan(rls, N, d, T, D)[3] == 0
