@@ -45,18 +45,17 @@ VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4.0   # wave64 vector instructions per secon
 # rocprofv3 counters of one lloyd_step_kernel launch (mean over the rounds of a sweep), from the summaries under
 # profiles/ (lloyd_step_<workload>_hbm_counters.md: FETCH_SIZE / WRITE_SIZE in KiB per dispatch with the factors a
 # plain 1 GiB copy gives for each counter; lloyd_step_<workload>_sq_counters.md: SQ_INSTS_VALU, SQ_INSTS_MFMA).  Valid only for the
-# source they were taken with (step_source_digest); with any other the fields made from them are null.  (Taken with b641b696cbc9, whose
-# step kernels compile to the same instructions as those of the source named here.)
+# source they were taken with (step_source_digest); with any other the fields made from them are null.
 COUNTERS = {
     # mean over the 30 rounds of a sweep (first round included, like the launches the events time)
-    "mid": {"source": "fa54c3102bf1", "fetch_kib": 8232.7, "write_kib": 11007.3, "fetch_scale": 2.0, "write_scale": 1.0,
+    "mid": {"source": "e77f8ea89363", "fetch_kib": 8238.6, "write_kib": 11007.3, "fetch_scale": 2.0, "write_scale": 1.0,
            "valu_insts": 1.044e+07, "mfma_insts": 5.898e+05},
-    "whole_layer": {"source": "fa54c3102bf1", "fetch_kib": 307025.5, "write_kib": 27534.3, "fetch_scale": 2.0, "write_scale": 1.0,
+    "whole_layer": {"source": "e77f8ea89363", "fetch_kib": 306929.8, "write_kib": 27534.1, "fetch_scale": 2.0, "write_scale": 1.0,
                    "valu_insts": 6.879e+07, "mfma_insts": 2.858e+06},
-    "large": {"source": "fa54c3102bf1", "fetch_kib": 7749051.5, "write_kib": 687622.3, "fetch_scale": 2.0, "write_scale": 1.0,
-             "valu_insts": 2.43e+09, "mfma_insts": 1.868e+08},
-    "batched": {"source": "fa54c3102bf1", "fetch_kib": 2546011.1, "write_kib": 169489.3, "fetch_scale": 2.0, "write_scale": 1.0,
-               "valu_insts": 4.786e+08, "mfma_insts": 1.97e+07},
+    "large": {"source": "e77f8ea89363", "fetch_kib": 7759444.9, "write_kib": 687623.7, "fetch_scale": 2.0, "write_scale": 1.0,
+             "valu_insts": 2.430e+09, "mfma_insts": 1.868e+08},
+    "batched": {"source": "e77f8ea89363", "fetch_kib": 2550818.2, "write_kib": 169489.0, "fetch_scale": 2.0, "write_scale": 1.0,
+               "valu_insts": 4.786e+08, "mfma_insts": 1.970e+07},
 }
 
 
