@@ -199,7 +199,7 @@ __global__ void knob_mode_kernel(DomainArgs dm, const int32_t *__restrict__ hist
 // grid (visited rows, samples): a workgroup compares its rows with up to kScanSamples samples, each row read once; most rows differ in
 // the first knobs already.  What it has found it notes in LDS and hands on at the end, one word per sample: rows that repeat are
 // compared no further, and no queue forms at the samples' flags.  (Rows of 8 knobs, the call with its three launches.  Flags in memory set by every
-// wave that found a sample: 1M rows that all equal the 64 samples 6.0 ms, 0.17 now; where none does 36 us, 37 now.  A workgroup per sample and slice of the
+// wave that found a sample: 1M rows that all equal the 64 samples 6.0 ms, 0.17 now; where none does 36 us, 35 now.  A workgroup per sample and slice of the
 // rows, which read them once for every sample: 0.09 ms and 73 us; 65,536 rows, 32 samples 8.7 us, 7.3 now.)
 constexpr int kScanThreads = 256, kScanSamples = 64;
 
@@ -218,6 +218,7 @@ __global__ void __launch_bounds__(kScanThreads) visited_scan_kernel(const int32_
         const int32_t *row = visited + v * n_knobs;
         const int last = n_knobs - 1;
         const int r0 = row[0], r1 = row[min(1, last)], r2 = row[min(2, last)], r3 = row[min(3, last)];
+#pragma unroll 4       // (with two, as the compiler takes, 1M rows, 64 samples 36.2 us, 35.1 so)
         for (int i = 0; i < n; ++i) {
             const int *const m = mine + i * n_knobs;
             bool same = r0 == m[0] && r1 == m[min(1, last)] && r2 == m[min(2, last)] && r3 == m[min(3, last)];
